@@ -971,7 +971,7 @@ def main():
         k2 = "refine_mask_kernel<%d,true>" % index_words(K) if bits else "refine_dist_kernel<%d>" % index_words(K)
         tr2 = pmc_traffic(k2.split("<")[0], wl)
         result["roofline_stage2"] = {
-            "bound": "hbm", "kernel": k2 + " (+ its unfiltered first part and two selections)" if bits else k2 + " + select_keys_kernel",
+            "bound": "hbm", "kernel": k2 + " (+ its unfiltered first part and two selections)" if bits else k2 + " + select_kernel",
             "achieved": round(ach2, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach2 / HBM_PEAK_GBS, 4),
             "algorithmic_bytes": alg2, "traffic": tr2["bytes"] if tr2 else None, "traffic_source": tr2["source"] if tr2 else None,
             "ms": round(stage[2], 4), "survivors_per_call": n_surv_batch,

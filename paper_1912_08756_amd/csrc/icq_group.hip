@@ -883,7 +883,7 @@ static int group_parts(const icq_index *ix, int Q) {
 int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
                           uint32_t *cand_ids, bool as_positions, uint32_t *cand_count, int64_t cap,
                           hipStream_t s) {
-    // cand_count has been zeroed by the caller (icq_launch_scan)
+    // cand_count is zero
     const int parts = group_parts(ix, Q);
     const int rows = (256 + parts - 1) / parts;
     for (int q0 = 0; q0 < Q; q0 += 65535) {
@@ -922,7 +922,7 @@ int icq_group_fused_parts(const icq_index *ix, int Q) {
 int icq_launch_group_keys(const icq_index *ix, const float *lut, int Q, const float *thr,
                           unsigned long long *cand_keys, uint32_t *cand_count, int64_t cap, int topk,
                           uint32_t *out_ids, float *out_dist, hipStream_t s) {
-    // cand_count has been zeroed by the caller (icq_launch_scan); item_stride <= 16 here
+    // cand_count is zero; item_stride <= 16 here
     const bool fused = out_ids != nullptr && icq_group_fused(ix, Q, topk);
     const int parts = fused ? icq_group_fused_parts(ix, Q) : group_parts(ix, Q);
     // cand_keys: [Q][cap] keys of the survivors, or (fused, several parts) [Q][parts][topk] part lists
@@ -956,7 +956,8 @@ int icq_launch_group_keys(const icq_index *ix, const float *lut, int Q, const fl
 #undef ICQ_GK
     }
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    if (fused && parts > 1) return icq_launch_merge(cand_keys, Q, parts, topk, true, out_ids, out_dist, s);
+    if (fused && parts > 1)
+        return icq_launch_select(cand_keys, nullptr, (int64_t)parts * topk, Q, topk, 1, false, nullptr, nullptr, out_ids, out_dist, s);
     return ICQ_OK;
 }
 

@@ -98,11 +98,10 @@ __device__ __forceinline__ uint32_t icq_order_bits(float x) {
 
 // Sub-buffers carved out of the caller's workspace for one query batch.
 struct icq_ws_layout {
-    size_t lut_off, ids_off, count_off, keys_off, total;
-    int splits;                // stage-2 blocks per query
+    size_t lut_off, ids_off, count_off, keycount_off, ticket_off, keys_off, total;
+    int splits;                // parts a query's work in stage 2 is cut into
     // icq_search with the item-by-item stage 1: hit bits instead of candidate lists (ids_off holds them)
     bool masked;
-    size_t keycount_off;       // [Q] keys written per query
     size_t mask_stride;        // 16-bit words of hit bits per query
     int64_t scan_end;          // scan positions the hit bits cover (whole chunks)
 };
@@ -114,19 +113,21 @@ static inline size_t icq_align_up(size_t x, size_t a) { return (x + a - 1) / a *
 // from the caller).
 icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool with_lut,
                          bool with_cands);
-int icq_refine_splits(const icq_index *ix, int Q, int64_t cap, int topk);
+int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk);
+int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk);
 // icq_search with the item-by-item stage 1 hands the survivors to stage 2 as one hit bit per scan
 // position and query instead of lists.
 bool icq_masks_usable(const icq_index *ix, int Q, int topk);
 int64_t icq_mask_scan_end(const icq_index *ix);              // positions the hit bits cover: whole stage-2 chunks
-// Stage 1 into hit bits (zeroes cand_count and key_count first; after_fill as in icq_launch_scan).
-// icq_search's body; lut_ext (device, [Q][K][256]) replaces the table build when not null.
+// icq_search's body; lut_ext (device, [Q][K][256]) replaces the table build when not null.  The table build
+// zeroes the call's counters; with lut_ext the caller has done so: out_survivors (not null then) and the first
+// 2 * Q words of the workspace.
 int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_ext, int Q, const float *thresholds,
                     int64_t cap, int topk, uint32_t *out_ids, float *out_dist, uint32_t *out_survivors,
                     void *workspace, size_t workspace_bytes, void *stream);
+// Stage 1 into hit bits.
 int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
-                          size_t mask_stride, int64_t scan_end, uint32_t *cand_count, uint32_t *key_count,
-                          hipEvent_t after_fill, bool *superset, hipStream_t s);
+                          size_t mask_stride, int64_t scan_end, bool *superset, hipStream_t s);
 // The 16-bit pre-filter over the pair ordering (icq_scan16.hip): hit bits of a superset of the survivors.
 bool icq_scan_q16_usable(const icq_index *ix, int Q);
 int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
@@ -136,12 +137,16 @@ int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, cons
 // (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, unsigned long long *keys,
-                            uint32_t *key_count, uint32_t *cand_count, const float *thr, uint32_t *out_ids,
-                            float *out_dist, hipStream_t s);
+                            uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr,
+                                 uint32_t *out_ids, float *out_dist, hipStream_t s);
+
+// p[0..n) = 0, by a kernel (the call can sit inside a captured graph).
+void icq_zero_words(uint32_t *p, int n, hipStream_t s);
 
 // Kernel launchers (each checks nothing; the extern "C" entry points validate).
-int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float *lut,
-                         hipStream_t s);
+// zero0 / zero1 (may be nullptr): [Q] and [2 * Q] words the launch also sets to zero.
+int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float *lut, uint32_t *zero0,
+                         uint32_t *zero1, hipStream_t s);
 // cand_part == nullptr: the crude distances are not materialised (the fused path
 // recomputes the full sum in stage 2 from the item records).
 // list_kind == nullptr: the list must hold item ids (public contract).  Otherwise the
@@ -149,11 +154,11 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
 // cand_keys ([Q][cap], may be nullptr), grouped positions, or plain ids.
 // topk / out_ids / out_dist (may be nullptr): where the scan may write the final lists
 // itself (ICQ_LIST_DONE) when its grouped form covers stage 2 as well.
-// after_fill (may be nullptr): event recorded once the survivor counters are zeroed.
+// cand_count is zero on entry.
 int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
                     uint32_t *cand_ids, float *cand_part, unsigned long long *cand_keys, int *list_kind,
                     uint32_t *cand_count, int64_t cap, int topk, uint32_t *out_ids, float *out_dist,
-                    hipEvent_t after_fill, hipStream_t s);
+                    hipStream_t s);
 // Grouped stage 1 fused with stage 2: the final lists when icq_group_fused() holds and
 // out_ids is given, else one 64-bit key per survivor in cand_keys.
 bool icq_group_fused(const icq_index *ix, int Q, int topk);
@@ -167,8 +172,13 @@ static inline unsigned long long *icq_cand_keys(unsigned long long *keys, int Q,
 // Grouped stage 1 (icq_group.hip); as_positions: list grouped positions instead of ids.
 bool icq_group_usable(const icq_index *ix, int Q);
 int icq_group_fused_parts(const icq_index *ix, int Q);
-int icq_launch_merge(const unsigned long long *keys, int Q, int splits, int topk, bool ascending,
-                     uint32_t *out_ids, float *out_dist, hipStream_t s);
+// The topk smallest keys of every query (icq_select.hip; topk <= 512).  count != nullptr: count[q] <= cap keys at
+// keys + q * cap, selected in up to `splits` parts (part_lists [Q][splits][topk], ticket [Q] zero, left zero);
+// count == nullptr: cap keys at keys + q * cap, KEY_PAD where there is none, splits = 1.
+int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk);
+// compact: the result's keys also replace the query's keys (and count[q] their number).
+int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
+                      unsigned long long *part_lists, uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
 int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
                           uint32_t *cand_ids, bool as_positions, uint32_t *cand_count, int64_t cap,
                           hipStream_t s);
@@ -178,7 +188,7 @@ int icq_group_build(icq_index *ix, hipStream_t s);
 int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32_t *cand_ids,
                       const float *cand_part, int list_kind,
                       const uint32_t *cand_count, int64_t cap, int topk, int splits,
-                      unsigned long long *keys, uint32_t *out_ids, float *out_dist, hipStream_t s);
+                      unsigned long long *keys, uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
 
 #define ICQ_HIP_TRY(expr)                      \
     do {                                       \

@@ -148,47 +148,6 @@ __global__ __launch_bounds__(RF_THREADS) void merge_kernel(const u64 *__restrict
     }
 }
 
-// grid (Q): join the lists of one query when every list is already ascending (pads last) and all
-// keys differ: a key's row is the number of keys below it, one binary search per list, no sort.
-// LDS: keys[parts * topk].
-__global__ __launch_bounds__(RF_THREADS) void merge_sorted_kernel(const u64 *__restrict__ keys_in, int parts,
-                                                                  int topk, uint32_t *__restrict__ out_ids,
-                                                                  float *__restrict__ out_dist) {
-    extern __shared__ u64 smem64[];
-    u64 *keys = smem64;
-    __shared__ int s_real;
-    const int q = blockIdx.x;
-    const int n = parts * topk;
-    if (threadIdx.x == 0) s_real = 0;
-    for (int i = threadIdx.x; i < n; i += RF_THREADS) keys[i] = keys_in[(int64_t)q * n + i];
-    __syncthreads();
-    auto below = [&](const u64 *list, u64 k) -> int {      // keys of an ascending list that are < k
-        int lo = 0, hi = topk;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (list[mid] < k) lo = mid + 1;
-            else hi = mid;
-        }
-        return lo;
-    };
-    if ((int)threadIdx.x < parts) atomicAdd(&s_real, below(keys + threadIdx.x * topk, KEY_PAD));
-    for (int i = threadIdx.x; i < n; i += RF_THREADS) {
-        const u64 k = keys[i];
-        if (k == KEY_PAD) continue;
-        int rank = 0;
-        for (int p = 0; p < parts && rank < topk; ++p) rank += below(keys + p * topk, k);
-        if (rank < topk) {
-            out_ids[(int64_t)q * topk + rank] = (uint32_t)k;
-            out_dist[(int64_t)q * topk + rank] = unorder_bits((uint32_t)(k >> 32));
-        }
-    }
-    __syncthreads();
-    for (int r = s_real + (int)threadIdx.x; r < topk; r += RF_THREADS) {
-        out_ids[(int64_t)q * topk + r] = ICQ_PAD_ID;
-        out_dist[(int64_t)q * topk + r] = INFINITY;
-    }
-}
-
 int bufn_for(int topk) { return topk <= 256 ? 2048 : 4096; }
 
 // ------------------------------------------------------------------ distances, then bounded select
@@ -198,12 +157,7 @@ int bufn_for(int topk) { return topk <= 256 ? 2048 : 4096; }
 //     keeps that query's tables in LDS (one table per record byte; tables that do not
 //     take part are zero, so the sum has no conditions) and writes one 64-bit key
 //     (order-preserving bits of D, item id) per candidate.
-//   select_keys_kernel: one wavefront per (query, slice) streams the keys.  An exact
-//     radix select (8-bit digits over the occupied range, LDS histogram) over the first
-//     512 keys gives their topk-th distance, the bound; afterwards only keys at or
-//     below the bound enter a key list (ballot compaction).  Whenever the list could
-//     overflow it is bitonic-sorted, cut to topk and the bound tightened; the final
-//     sort orders the result.
+//   select_kernel (icq_select.hip): the topk smallest of a query's keys.
 constexpr int RD_PER = 8;                            // candidates per thread and step
 constexpr int RD_STEP = RF_THREADS * RD_PER;         // 2048
 constexpr int RD_BLOCK = 2 * RD_STEP;                // candidates per block
@@ -212,7 +166,8 @@ template <int WORDS>
 __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
     const uint8_t *__restrict__ items, int K, int Kf, const float *__restrict__ lut,
     const uint32_t *__restrict__ cand_ids, const float *__restrict__ cand_part,
-    const uint32_t *__restrict__ cand_count, int64_t cap, int blocks_per_query, u64 *__restrict__ keys) {
+    const uint32_t *__restrict__ cand_count, int64_t cap, int blocks_per_query, u64 *__restrict__ keys,
+    uint32_t *__restrict__ ticket) {
     __shared__ float T[4 * WORDS * ICQ_LUT_W];
     constexpr int RW = WORDS;                         // words per item record
     // Blocks are numbered piece-major: blocks that run together take the same stretch of every
@@ -225,6 +180,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
     const int tid = threadIdx.x;
     u64 n = cand_count[q];
     if (n > (u64)cap) n = (u64)cap;
+    if (c0 == 0 && tid == 0) ticket[q] = 0;           // for the selection that follows
     if (c0 >= n) return;                              // block-uniform
     const int k0 = cand_part ? Kf : 0;
     const uint32_t *ids = cand_ids + (int64_t)q * cap;
@@ -299,221 +255,6 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
             }
             const u64 i = c0 + (u64)st * RD_STEP + j * RF_THREADS + tid;
             if (i < n) out[i] = ((u64)order_bits(d) << 32) | id[st][j];
-        }
-    }
-}
-
-// One WAVEFRONT per (query, slice): nothing in the select needs more than 64 lanes,
-// and a one-wavefront block pays no barrier waits, so a CU keeps ~15 independent
-// selects in flight instead of 3 barrier-bound blocks.
-constexpr int SK_THREADS = 64;
-constexpr int SK_CHUNK = 8;                           // keys per lane and chunk
-constexpr int SK_FIRST = SK_THREADS * SK_CHUNK;       // 512
-
-struct SelectShared {
-    uint32_t hist[256];
-    uint32_t bin, below, cnt;
-};
-
-// Locate the bin that holds the kr-th smallest element (1-based) of a complete
-// 256-bin histogram with one wavefront (4 bins per lane).
-__device__ __forceinline__ void find_bin(SelectShared *sh, uint32_t kr) {
-    const int lane = threadIdx.x;
-    uint32_t h[4], mine = 0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        h[r] = sh->hist[lane * 4 + r];
-        mine += h[r];
-    }
-    const uint32_t incl = wave_scan_add(mine);
-    uint32_t run = incl - mine;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        if (run < kr && run + h[r] >= kr) {
-            sh->bin = (uint32_t)(lane * 4 + r);
-            sh->below = run;
-        }
-        run += h[r];
-    }
-    __syncthreads();
-}
-
-// The kr-th smallest (1-based) of U[0..n), n >= kr >= 1; vmin/vmax bound the values.
-__device__ uint32_t wave_radix_select(SelectShared *sh, const uint32_t *U, uint32_t n, uint32_t kr,
-                                      uint32_t vmin, uint32_t vmax) {
-    const int tid = threadIdx.x;
-    const uint32_t range = vmax - vmin;
-    const int bits = range == 0 ? 0 : 32 - __builtin_clz(range);
-    int shift = bits > 8 ? bits - 8 : 0;
-    int width = bits < 8 ? bits : 8;
-    uint32_t prefix = 0;       // chosen high digits of (value - vmin)
-    int fixed_from = bits;     // bits [fixed_from, 32) of (value - vmin) are decided
-    for (;;) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sh->hist[tid * 4 + r] = 0;
-        __syncthreads();
-        const uint32_t dmask = (1u << width) - 1u;
-        for (uint32_t i = tid; i < n; i += SK_THREADS) {
-            const uint32_t y = U[i] - vmin;
-            const bool match = fixed_from >= 32 ? true : (y >> fixed_from) == prefix;
-            if (match) atomicAdd(&sh->hist[(y >> shift) & dmask], 1u);
-        }
-        __syncthreads();
-        find_bin(sh, kr);
-        kr -= sh->below;
-        prefix = (prefix << width) | sh->bin;
-        fixed_from = shift;
-        if (shift == 0) break;
-        const int ns = shift > 8 ? shift - 8 : 0;
-        width = shift - ns;
-        shift = ns;
-        __syncthreads();
-    }
-    return vmin + prefix;
-}
-
-// Cut the list back to its topk smallest distances (ties at the cut kept): exact radix
-// select of the topk-th distance, then an in-place ballot compaction.  One wavefront,
-// cnt <= 1024 (wave-uniform), cnt > topk.  Returns the new count; *ubound = the cut.
-__device__ uint32_t wave_cut_list(SelectShared *sh, u64 *list, uint32_t *U, uint32_t cnt, int topk,
-                                  uint32_t *ubound) {
-    const int lane = threadIdx.x;
-    u64 x[16];
-    uint32_t umin = 0xFFFFFFFFu, umax = 0u;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const uint32_t i = r * 64 + lane;
-        x[r] = i < cnt ? list[i] : KEY_PAD;
-        if (i < cnt) {
-            const uint32_t u = (uint32_t)(x[r] >> 32);
-            U[i] = u;
-            umin = u < umin ? u : umin;
-            umax = u > umax ? u : umax;
-        }
-    }
-    umin = wave_min_u32(umin);
-    umax = wave_max_u32(umax);
-    __syncthreads();
-    const uint32_t cut = wave_radix_select(sh, U, cnt, (uint32_t)topk, umin, umax);
-    __syncthreads();
-    uint32_t kept = 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        if ((uint32_t)(r * 64) < cnt) {   // wave-uniform
-            const bool keep = (uint32_t)(r * 64 + lane) < cnt && (uint32_t)(x[r] >> 32) <= cut;
-            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
-            if (keep) list[kept + __builtin_popcountll(mask & ((1ull << lane) - 1))] = x[r];
-            kept += (uint32_t)__builtin_popcountll(mask);
-        }
-    }
-    __syncthreads();
-    *ubound = cut;
-    return kept;
-}
-
-// grid (Q * splits), block = one wavefront.  LDS: list[listcap] (u64) | U[listcap] (u32);
-// listcap is a power of two, topk + SK_FIRST <= listcap <= 1024... 2048 (see launcher).
-__global__ __launch_bounds__(SK_THREADS) __attribute__((amdgpu_waves_per_eu(3, 8))) void select_keys_kernel(
-    const u64 *__restrict__ keys_in, const uint32_t *__restrict__ cand_count, int64_t cap, int topk,
-    int listcap, int splits, u64 *__restrict__ keys_out, uint32_t *__restrict__ out_ids,
-    float *__restrict__ out_dist) {
-    extern __shared__ u64 smem64[];
-    __shared__ SelectShared sh;
-    u64 *list = smem64;
-    uint32_t *U = reinterpret_cast<uint32_t *>(list + listcap);
-    const int q = blockIdx.x / splits, sp = blockIdx.x % splits;
-    const int tid = threadIdx.x;
-    u64 ntot = cand_count[q];
-    if (ntot > (u64)cap) ntot = (u64)cap;
-    const u64 lo = ntot * (u64)sp / (u64)splits, hi = ntot * (u64)(sp + 1) / (u64)splits;
-    const u64 n = hi - lo;
-    const u64 *in = keys_in + (int64_t)q * cap + lo;
-
-    uint32_t ubound = 0xFFFFFFFFu;   // keep keys whose distance bits are <= ubound
-    uint32_t cnt = 0;                // keys in the list (wave-uniform)
-    // Keys are loaded one chunk ahead, unconditionally with the index clamped.
-    auto load_chunk = [&](u64 c, u64(&k)[SK_CHUNK]) {
-#pragma unroll
-        for (int j = 0; j < SK_CHUNK; ++j) {
-            const u64 i = c + (u64)j * SK_THREADS + tid;
-            k[j] = in[i < n ? i : n - 1];
-        }
-    };
-    auto step = [&](u64 c, u64(&kA)[SK_CHUNK], u64(&kNext)[SK_CHUNK]) {   // wave-uniform c < n
-        load_chunk(c + (u64)SK_FIRST, kNext);   // one chunk ahead
-        if (c == 0 && n > (u64)topk && (uint32_t)topk < (uint32_t)SK_FIRST) {
-            // first chunk: its topk-th smallest distance bounds everything that follows
-            const uint32_t n1 = n < (u64)SK_FIRST ? (uint32_t)n : (uint32_t)SK_FIRST;
-            uint32_t umin = 0xFFFFFFFFu, umax = 0u;
-#pragma unroll
-            for (int j = 0; j < SK_CHUNK; ++j) {
-                const uint32_t i = j * SK_THREADS + tid;
-                const uint32_t u = (uint32_t)(kA[j] >> 32);
-                if (i < n1) {
-                    U[i] = u;
-                    umin = u < umin ? u : umin;
-                    umax = u > umax ? u : umax;
-                }
-            }
-            umin = wave_min_u32(umin);
-            umax = wave_max_u32(umax);
-            __syncthreads();
-            if (n1 > (uint32_t)topk) ubound = wave_radix_select(&sh, U, n1, (uint32_t)topk, umin, umax);
-        }
-        // keep what is at or below the bound (ties at the bound included; the final sort
-        // decides); ballot compaction, the list cursor is wave-uniform
-#pragma unroll
-        for (int j = 0; j < SK_CHUNK; ++j) {
-            const u64 i = c + (u64)j * SK_THREADS + tid;
-            const bool keep = i < n && (uint32_t)(kA[j] >> 32) <= ubound;
-            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
-            if (keep) list[cnt + __builtin_popcountll(mask & ((1ull << tid) - 1))] = kA[j];
-            cnt += (uint32_t)__builtin_popcountll(mask);
-        }
-        if (cnt > (uint32_t)(listcap - SK_FIRST) && c + SK_FIRST < n) {
-            // the next chunk might not fit: cut the list back to topk, tighten the bound
-            __syncthreads();
-            cnt = wave_cut_list(&sh, list, U, cnt, topk, &ubound);
-            if (cnt > (uint32_t)(listcap - SK_FIRST)) {
-                // so many ties at the cut that the list is still too full: order by the
-                // whole key and keep exactly topk (the ids decide among equal distances)
-                for (int i = (int)cnt + tid; i < listcap; i += SK_THREADS) list[i] = KEY_PAD;
-                __syncthreads();
-                wave_sort(list, listcap, threadIdx.x);
-                __syncthreads();
-                cnt = (uint32_t)topk;
-                ubound = (uint32_t)(list[topk - 1] >> 32);
-            }
-        }
-    };
-    if (n > 0) {
-        u64 k0[SK_CHUNK], k1[SK_CHUNK];
-        load_chunk(0, k0);
-        for (u64 c = 0; c < n; c += 2 * (u64)SK_FIRST) {
-            step(c, k0, k1);
-            if (c + SK_FIRST < n) step(c + SK_FIRST, k1, k0);
-        }
-    }
-
-    // ---- final order: cut to the topk smallest distances, then sort what is left
-    __syncthreads();
-    if (cnt > (uint32_t)topk) cnt = wave_cut_list(&sh, list, U, cnt, topk, &ubound);
-    int len = 64;
-    while (len < (int)cnt) len <<= 1;
-    for (int i = (int)cnt + tid; i < len; i += SK_THREADS) list[i] = KEY_PAD;
-    __syncthreads();
-    wave_sort(list, len, threadIdx.x);
-    __syncthreads();
-    const int kept = (int)cnt < topk ? (int)cnt : topk;
-    uint32_t *oi = out_ids + (int64_t)q * topk;
-    float *od = out_dist + (int64_t)q * topk;
-    u64 *dst = keys_out + ((int64_t)q * splits + sp) * topk;
-    for (int r = tid; r < topk; r += SK_THREADS) {
-        if (splits == 1) {
-            oi[r] = r < kept ? (uint32_t)list[r] : ICQ_PAD_ID;
-            od[r] = r < kept ? unorder_bits((uint32_t)(list[r] >> 32)) : INFINITY;
-        } else {
-            dst[r] = r < kept ? list[r] : KEY_PAD;
         }
     }
 }
@@ -782,22 +523,11 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
 // (K > 16) the generic streaming kernel.
 static bool use_select(const icq_index *ix, int topk) { return ix->item_stride <= 16 && topk <= 512; }
 
-// keys: [Q][splits][topk] keys (bits of D, id), KEY_PAD where a list is short; splits * topk <= 4096.
-// ascending: every list is sorted (pads last) and no key occurs twice.
-int icq_launch_merge(const unsigned long long *keys, int Q, int splits, int topk, bool ascending,
-                     uint32_t *out_ids, float *out_dist, hipStream_t s) {
-    if (ascending) {
-        merge_sorted_kernel<<<Q, RF_THREADS, sizeof(u64) * splits * topk, s>>>(keys, splits, topk, out_ids, out_dist);
-        return icq_check_launch();
-    }
-    int len = 2;
-    while (len < splits * topk) len <<= 1;
-    merge_kernel<<<Q, RF_THREADS, sizeof(u64) * len, s>>>(keys, splits, topk, len, out_ids, out_dist);
-    return icq_check_launch();
-}
-
-int icq_refine_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
+// Parts a query's work is cut into: the selection of the keys, or (wider records, longer results) the slices of
+// the generic kernel's candidate list.
+int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
     if (Q <= 0) return 1;
+    if (use_select(ix, topk)) return icq_select_splits(ix, Q, cap, topk);
     int64_t s = (4LL * ix->num_cu + Q - 1) / Q;
     int64_t by_len = cap / 2048 + 1;            // do not slice short lists
     int64_t by_merge = 4096 / topk;             // merge buffer holds splits*topk keys
@@ -811,7 +541,7 @@ int icq_refine_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
 int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32_t *cand_ids,
                       const float *cand_part, int list_kind,
                       const uint32_t *cand_count, int64_t cap, int topk, int splits, u64 *keys,
-                      uint32_t *out_ids, float *out_dist, hipStream_t s) {
+                      uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0 || list_kind == ICQ_LIST_DONE) return ICQ_OK;
     const uint8_t *items = list_kind == ICQ_LIST_POSITIONS ? ix->items_grouped : ix->items;
     const uint32_t *perm = list_kind == ICQ_LIST_POSITIONS ? ix->perm : nullptr;
@@ -826,7 +556,7 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
         if (list_kind != ICQ_LIST_KEYS) {
 #define ICQ_RD_LAUNCH(W)                                                                          \
     refine_dist_kernel<W><<<dgrid, RF_THREADS, 0, s>>>(items, ix->K, ix->Kf, lut, cand_ids,       \
-                                                       cand_part, cand_count, cap, bpq, cand_keys)
+                                                       cand_part, cand_count, cap, bpq, cand_keys, ticket)
         switch (ix->item_stride) {
             case 4: ICQ_RD_LAUNCH(1); break;
             case 8: ICQ_RD_LAUNCH(2); break;
@@ -835,20 +565,22 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
 #undef ICQ_RD_LAUNCH
         if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
         }
-        const int listcap = 1024;   // register sort and cut handle up to 1024 keys: topk <= 512 here
-        select_keys_kernel<<<grid, SK_THREADS, (sizeof(u64) + sizeof(uint32_t)) * listcap, s>>>(
-            cand_keys, cand_count, cap, topk, listcap, splits, keys, out_ids, out_dist);
-    } else {
-        const int bufn = bufn_for(topk);
-        const size_t lds = sizeof(u64) * bufn + tab;
-        ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(&refine_kernel), 98304));
-        refine_kernel<<<grid, RF_THREADS, lds, s>>>(items, ix->item_stride, ix->K, ix->Kf, lut,
-                                                    cand_ids, cand_part, perm, cand_count, cap, topk,
-                                                    bufn, splits, keys, out_ids, out_dist);
+        return icq_launch_select(cand_keys, const_cast<uint32_t *>(cand_count), cap, Q, topk, splits, false, keys, ticket, out_ids, out_dist, s);
     }
+    const int bufn = bufn_for(topk);
+    const size_t lds = sizeof(u64) * bufn + tab;
+    ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(&refine_kernel), 98304));
+    refine_kernel<<<grid, RF_THREADS, lds, s>>>(items, ix->item_stride, ix->K, ix->Kf, lut, cand_ids, cand_part, perm,
+                                                cand_count, cap, topk, bufn, splits, keys, out_ids, out_dist);
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    if (splits > 1) return icq_launch_merge(keys, Q, splits, topk, false, out_ids, out_dist, s);
-    return ICQ_OK;
+    if (splits == 1) return ICQ_OK;
+    // join the slices' lists, KEY_PAD where one is short (splits * topk <= 4096)
+    if (topk <= 512)
+        return icq_launch_select(keys, nullptr, (int64_t)splits * topk, Q, topk, 1, false, nullptr, nullptr, out_ids, out_dist, s);
+    int len = 2;
+    while (len < splits * topk) len <<= 1;
+    merge_kernel<<<Q, RF_THREADS, sizeof(u64) * len, s>>>(keys, splits, topk, len, out_ids, out_dist);
+    return icq_check_launch();
 }
 
 ICQ_EXPORT int icq_refine(const icq_index *ix, const float *lut, int Q, const uint32_t *cand_ids,
@@ -866,7 +598,8 @@ ICQ_EXPORT int icq_refine(const icq_index *ix, const float *lut, int Q, const ui
         return ICQ_ERR_WORKSPACE;
     u64 *keys = reinterpret_cast<u64 *>(static_cast<char *>(workspace) + L.keys_off);
     return icq_launch_refine(ix, lut, Q, cand_ids, cand_part, ICQ_LIST_IDS, cand_count, cap, topk,
-                             L.splits, keys, out_ids, out_dist, (hipStream_t)stream);
+                             L.splits, keys, reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + L.ticket_off),
+                             out_ids, out_dist, (hipStream_t)stream);
 }
 
 // From about four million items on: below that the item records stay in the caches whatever the
@@ -887,7 +620,8 @@ int64_t icq_mask_scan_end(const icq_index *ix) {
 
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, u64 *keys, uint32_t *key_count,
-                            uint32_t *cand_count, const float *thr, uint32_t *out_ids, float *out_dist, hipStream_t s) {
+                            uint32_t *ticket, uint32_t *cand_count, const float *thr, uint32_t *out_ids, float *out_dist,
+                            hipStream_t s) {
     if (Q == 0) return ICQ_OK;
     const bool g2 = icq_g2_usable(ix);
     const uint8_t *items = g2 ? ix->items_grouped : ix->items;
@@ -897,15 +631,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // few chunks: one unfiltered launch over all of them (a bound would save less than its second launch costs)
     const uint32_t seed_every = chunks < 2 * RM_SEED_EVERY ? 1u : (uint32_t)RM_SEED_EVERY;
     const uint32_t nseed = (chunks + seed_every - 1) / seed_every, nmain = chunks - nseed;
-    const unsigned grid_sel = (unsigned)Q * (unsigned)splits;
-    const int listcap = 1024;
-    auto select = [&]() -> int {
-        select_keys_kernel<<<grid_sel, SK_THREADS, (sizeof(u64) + sizeof(uint32_t)) * listcap, s>>>(
-            cand_keys, key_count, cap, topk, listcap, splits, keys, out_ids, out_dist);
-        if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-        // every slice comes out of the selection ascending, and a position -- hence an id -- has one key
-        if (splits > 1) return icq_launch_merge(keys, Q, splits, topk, true, out_ids, out_dist, s);
-        return ICQ_OK;
+    auto select = [&](bool more) -> int {
+        return icq_launch_select(cand_keys, key_count, cap, Q, topk, splits, more, keys, ticket, out_ids, out_dist, s);
     };
     // Chunks per block: few, so that the blocks in flight (two windows' worth when the queries fill the
     // chip) keep to a few chunks per XCD; more when there are so few queries that the table load would weigh.
@@ -949,8 +676,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         default: ICQ_RM_LAUNCH(4, false, nseed); break;
     }
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    if (nmain == 0) return select();
-    int rc = select();
+    if (nmain == 0) return select(false);
+    int rc = select(true);
     if (rc != ICQ_OK) return rc;
     switch (ix->item_stride) {
         case 4: ICQ_RM_LAUNCH(1, true, nmain); break;
@@ -959,5 +686,5 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     }
 #undef ICQ_RM_LAUNCH
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    return select();
+    return select(false);
 }

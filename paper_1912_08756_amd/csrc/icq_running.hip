@@ -15,7 +15,8 @@ namespace {
 constexpr int RM_T = 256;
 
 __global__ void running_init_kernel(uint32_t *__restrict__ ids, float *__restrict__ dist, int64_t n, float *__restrict__ thr,
-                                    uint32_t *__restrict__ refined, int Q) {
+                                    uint32_t *__restrict__ refined, uint32_t *__restrict__ tile_surv,
+                                    uint32_t *__restrict__ counters, int Q) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) {
         ids[i] = ICQ_PAD_ID;
@@ -24,6 +25,7 @@ __global__ void running_init_kernel(uint32_t *__restrict__ ids, float *__restric
     if (i < Q) {
         thr[i] = __builtin_inff();
         refined[i] = 0u;
+        tile_surv[i] = counters[i] = counters[Q + i] = 0u;         // of the first tile's search
     }
 }
 
@@ -39,7 +41,7 @@ __device__ __forceinline__ unsigned long long list_key(float d, uint32_t id) {
 // tiles differ, so only paddings tie; the running list's paddings go first among them.
 __global__ __launch_bounds__(RM_T) void running_merge_kernel(
     uint32_t *__restrict__ ids, float *__restrict__ dist, float *__restrict__ crude, const uint32_t *__restrict__ tile_ids,
-    const float *__restrict__ tile_dist, const uint32_t *__restrict__ tile_surv, uint32_t id_base,
+    const float *__restrict__ tile_dist, uint32_t *__restrict__ tile_surv, uint32_t *__restrict__ counters, uint32_t id_base,
     const uint8_t *__restrict__ items, int stride, int K, int Kf, const float *__restrict__ lut,
     const float *__restrict__ sigma, int topk, float *__restrict__ thr, uint32_t *__restrict__ refined) {
     extern __shared__ __attribute__((aligned(16))) unsigned char rm_smem[];
@@ -86,7 +88,10 @@ __global__ __launch_bounds__(RM_T) void running_merge_kernel(
                 thr[q] = id != ICQ_PAD_ID ? pc[e] + (sigma ? sigma[q] : 0.0f) : __builtin_inff();
         }
     }
-    if (threadIdx.x == 0) refined[q] += tile_surv[q];
+    if (threadIdx.x == 0) {
+        refined[q] += tile_surv[q];
+        tile_surv[q] = counters[q] = counters[gridDim.x + q] = 0u;     // for the next tile's search
+    }
 }
 
 struct running_layout {
@@ -157,18 +162,20 @@ ICQ_EXPORT int icq_search_running(const icq_index *const *tiles, const uint32_t 
     uint32_t *tids = reinterpret_cast<uint32_t *>(ws + L.tids_off);
     float *tdist = reinterpret_cast<float *>(ws + L.tdist_off);
     uint32_t *tsurv = reinterpret_cast<uint32_t *>(ws + L.tsurv_off);
+    uint32_t *counters = reinterpret_cast<uint32_t *>(ws + L.inner_off);      // the tile searches' own, see icq_layout
     float *crude = reinterpret_cast<float *>(ws + L.crude_off);
-    rc = icq_launch_build_lut(tiles[0], queries, Q, lut, s);
+    rc = icq_launch_build_lut(tiles[0], queries, Q, lut, nullptr, nullptr, s);
     if (rc != ICQ_OK) return rc;
     const int64_t n = (int64_t)Q * topk;
-    running_init_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out_ids, out_dist, n, thr, out_refined, Q);
+    running_init_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out_ids, out_dist, n, thr, out_refined, tsurv,
+                                                                     counters, Q);
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     for (int r = 0; r < R; ++r) {
         const icq_index *t = tiles[r];
         const int64_t c = cap < t->N ? cap : t->N;
         rc = icq_search_impl(t, nullptr, lut, Q, thr, c, topk, tids, tdist, tsurv, ws + L.inner_off, L.inner_bytes, stream);
         if (rc != ICQ_OK) return rc;
-        running_merge_kernel<<<Q, RM_T, lds, s>>>(out_ids, out_dist, crude, tids, tdist, tsurv, id_base[r], t->items,
+        running_merge_kernel<<<Q, RM_T, lds, s>>>(out_ids, out_dist, crude, tids, tdist, tsurv, counters, id_base[r], t->items,
                                                   t->item_stride, t->K, t->Kf, lut, sigma, topk, thr, out_refined);
         if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     }

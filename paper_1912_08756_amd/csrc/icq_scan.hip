@@ -491,7 +491,7 @@ int launch_stream_as(const icq_index *ix, const float *lut, int Q, const float *
         scan_stream_kernel<KF, B, NT, G2, MASK><<<grid, threads, lds, s>>>(
             G2 ? ix->g2_rows : ix->fast, G2 ? ix->g2_npad : ix->Npad, (uint32_t)nitems,
             lut + (int64_t)q0 * ix->K * ICQ_LUT_W, ix->K, thr + q0, nq, MASK ? nullptr : cand_ids + (int64_t)q0 * cap,
-            cand_count + q0, cap, per, wave_cap, G2 ? ix->g2_info : nullptr, G2 ? ix->perm : nullptr,
+            MASK ? nullptr : cand_count + q0, cap, per, wave_cap, G2 ? ix->g2_info : nullptr, G2 ? ix->perm : nullptr,
             MASK ? masks + (size_t)q0 * mask_stride : nullptr, mask_stride, (uint32_t)scan_end);
     }
     return icq_check_launch();
@@ -617,14 +617,15 @@ __global__ __launch_bounds__(SI_THREADS) void scan_items_kernel(
 
 }  // namespace
 
-int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
-                    uint32_t *cand_ids, float *cand_part, unsigned long long *cand_keys, int *list_kind, uint32_t *cand_count, int64_t cap,
-                    int topk, uint32_t *out_ids, float *out_dist, hipEvent_t after_fill, hipStream_t s) {
+void icq_zero_words(uint32_t *p, int n, hipStream_t s) {
+    if (n > 0) zero_counts_kernel<<<(n + 255) / 256, 256, 0, s>>>(p, n);
+}
+
+int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr, uint32_t *cand_ids, float *cand_part, unsigned long long *cand_keys, int *list_kind, uint32_t *cand_count, int64_t cap,
+                    int topk, uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (list_kind) *list_kind = ICQ_LIST_IDS;
     if (Q == 0) return ICQ_OK;
-    zero_counts_kernel<<<(Q + 255) / 256, 256, 0, s>>>(cand_count, Q);
-    if (after_fill) ICQ_HIP_TRY(hipEventRecord(after_fill, s));
-    if (ix->N == 0) return icq_check_launch();
+    if (ix->N == 0) return ICQ_OK;
 
     const int bpq_fill = (int)((cap + 255) / 256 < 32 ? (cap + 255) / 256 : 32);
     if (icq_group_usable(ix, Q) && list_kind && !cand_part && ix->item_stride <= 16 &&
@@ -690,18 +691,14 @@ int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *t
 // *superset: the bits written mark a superset of the survivors (the 16-bit pre-filter); stage 2 then
 // applies the exact comparison itself.
 int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
-                          size_t mask_stride, int64_t scan_end, uint32_t *cand_count, uint32_t *key_count,
-                          hipEvent_t after_fill, bool *superset, hipStream_t s) {
+                          size_t mask_stride, int64_t scan_end, bool *superset, hipStream_t s) {
     *superset = false;
     if (Q == 0) return ICQ_OK;
-    zero_counts_kernel<<<(Q + 255) / 256, 256, 0, s>>>(cand_count, Q);
-    zero_counts_kernel<<<(Q + 255) / 256, 256, 0, s>>>(key_count, Q);
-    if (after_fill) ICQ_HIP_TRY(hipEventRecord(after_fill, s));
     if (icq_scan_q16_usable(ix, Q)) {
         *superset = true;
         return icq_launch_scan_masks_q16(ix, lut, Q, thr, masks, mask_stride, scan_end, s);
     }
-    return launch_stream_any(ix, lut, Q, thr, nullptr, cand_count, 0, masks, mask_stride, scan_end, s);
+    return launch_stream_any(ix, lut, Q, thr, nullptr, nullptr, 0, masks, mask_stride, scan_end, s);
 }
 
 ICQ_EXPORT int icq_scan_fast(const icq_index *ix, const float *lut, int Q, const float *thresholds,
@@ -723,8 +720,10 @@ ICQ_EXPORT int icq_scan_fast(const icq_index *ix, const float *lut, int Q, const
         ev = tm->ev[tm->calls % ICQ_TIMED_CALLS];
         ICQ_HIP_TRY(hipEventRecord(ev[0], s));
     }
+    icq_zero_words(cand_count, Q, s);
+    if (ev) ICQ_HIP_TRY(hipEventRecord(ev[1], s));
     const int rc = icq_launch_scan(ix, lut, Q, thresholds, cand_ids, cand_part, nullptr, nullptr, cand_count, cap,
-                                   0, nullptr, nullptr, ev ? ev[1] : nullptr, s);
+                                   0, nullptr, nullptr, s);
     if (rc != ICQ_OK) return rc;
     if (ev) {
         ICQ_HIP_TRY(hipEventRecord(ev[2], s));

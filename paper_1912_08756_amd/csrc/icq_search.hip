@@ -9,22 +9,23 @@
 icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool with_lut,
                          bool with_cands) {
     icq_ws_layout L = {};
-    size_t off = 0;
+    // the counters first: a caller that zeroes them need not know the form the search takes
+    L.keycount_off = 0;                                    // [Q] keys written per query (hit-bit form)
+    L.ticket_off = sizeof(uint32_t) * (size_t)Q;           // [Q] parts of the selection that are done
+    size_t off = icq_align_up(2 * sizeof(uint32_t) * (size_t)Q, ICQ_ALIGN);
     L.lut_off = off;
     if (with_lut) off = icq_align_up(off + sizeof(float) * (size_t)Q * ix->K * ICQ_LUT_W, ICQ_ALIGN);
     // icq_search with the grouped stage 1 keeping the lists on chip: no candidate lists in the
     // workspace, only (few queries, several blocks per query) the parts' lists for the merge
     const bool on_chip = with_cands && icq_group_fused(ix, Q, topk);
     L.masked = with_cands && !on_chip && icq_masks_usable(ix, Q, topk);
-    L.splits = icq_refine_splits(ix, Q, cap, topk);
+    L.splits = icq_stage2_splits(ix, Q, cap, topk);
     L.ids_off = off;
     if (L.masked) {
         L.scan_end = icq_mask_scan_end(ix);
         L.mask_stride = (size_t)(L.scan_end / 16);
         // rows for whole groups of eight queries: the pre-filter kernel stores all eight slots of its last group
         off = icq_align_up(off + sizeof(uint16_t) * (size_t)((Q + 7) / 8 * 8) * L.mask_stride, ICQ_ALIGN);
-        L.keycount_off = off;
-        off = icq_align_up(off + sizeof(uint32_t) * (size_t)Q, ICQ_ALIGN);
     } else if (with_cands && !on_chip) {
         off = icq_align_up(off + sizeof(uint32_t) * (size_t)Q * (size_t)cap, ICQ_ALIGN);
     }
@@ -109,19 +110,24 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
         unsigned long long *keys = reinterpret_cast<unsigned long long *>(ws + L.keys_off);
         if (timed) ICQ_HIP_TRY(hipEventRecord(ev[0], s));
         int rc = ICQ_OK;
-        if (own_lut) rc = icq_launch_build_lut(ix, queries + (int64_t)q0 * ix->d, nq, reinterpret_cast<float *>(ws + L.lut_off), s);
+        uint32_t *key_count = reinterpret_cast<uint32_t *>(ws + L.keycount_off);
+        uint32_t *ticket = reinterpret_cast<uint32_t *>(ws + L.ticket_off);
+        if (own_lut)
+            rc = icq_launch_build_lut(ix, queries + (int64_t)q0 * ix->d, nq, reinterpret_cast<float *>(ws + L.lut_off), cnt,
+                                      key_count, s);
+        else if (q0 > 0)
+            icq_zero_words(key_count, 2 * nq, s);
         if (rc != ICQ_OK) return rc;
+        if (timed) ICQ_HIP_TRY(hipEventRecord(ev[1], s));
         if (L.masked) {
             // item-by-item stage 1 into hit bits, stage 2 chunk by chunk from them
             uint16_t *masks = reinterpret_cast<uint16_t *>(ws + L.ids_off);
-            uint32_t *key_count = reinterpret_cast<uint32_t *>(ws + L.keycount_off);
             bool superset = false;
-            rc = icq_launch_scan_masks(ix, lut, nq, thresholds + q0, masks, L.mask_stride, L.scan_end, cnt, key_count,
-                                       timed ? ev[1] : nullptr, &superset, s);
+            rc = icq_launch_scan_masks(ix, lut, nq, thresholds + q0, masks, L.mask_stride, L.scan_end, &superset, s);
             if (rc != ICQ_OK) return rc;
             if (timed) ICQ_HIP_TRY(hipEventRecord(ev[2], s));
             rc = icq_launch_refine_masks(ix, lut, nq, masks, L.mask_stride, L.scan_end, cap, topk, L.splits, keys,
-                                         key_count, cnt, superset ? thresholds + q0 : nullptr,
+                                         key_count, ticket, cnt, superset ? thresholds + q0 : nullptr,
                                          out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, s);
             if (rc != ICQ_OK) return rc;
             if (timed) ICQ_HIP_TRY(hipEventRecord(ev[3], s));
@@ -133,11 +139,10 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
                                         : (ix->item_stride <= 16 && topk <= 512) ? icq_cand_keys(keys, nq, L.splits, topk)
                                                                                  : nullptr;
         rc = icq_launch_scan(ix, lut, nq, thresholds + q0, ids, nullptr, cand_keys, &list_kind, cnt,
-                             cap, topk, out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk,
-                             timed ? ev[1] : nullptr, s);
+                             cap, topk, out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, s);
         if (rc != ICQ_OK) return rc;
         if (timed) ICQ_HIP_TRY(hipEventRecord(ev[2], s));
-        rc = icq_launch_refine(ix, lut, nq, ids, nullptr, list_kind, cnt, cap, topk, L.splits, keys,
+        rc = icq_launch_refine(ix, lut, nq, ids, nullptr, list_kind, cnt, cap, topk, L.splits, keys, ticket,
                                out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, s);
         if (rc != ICQ_OK) return rc;
         if (timed) ICQ_HIP_TRY(hipEventRecord(ev[3], s));

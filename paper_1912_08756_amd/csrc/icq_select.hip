@@ -1,0 +1,303 @@
+// The nearest-neighbour list of arxiv 1912.08756, Sec. 3.4, out of keys: the topk smallest of a
+// query's 64-bit keys (order-preserving bits of D, item id), ascending.  The keys are either the
+// survivors' (count[q] of them) or the ascending lists that several blocks left for one query.
+//
+// One block per query.  Every thread takes the smallest distance of its share of the keys; the
+// topk-th smallest of those minima (one histogram pass) bounds the topk-th smallest key from above,
+// because at least topk keys are at or below it -- and hardly more are: with 10^4 keys, 1024 threads
+// and topk = 100 some 110.  Those are collected into LDS and ranked by counting.  The keys stay in
+// registers between the two looks while there are at most PER per thread (8192 with 1024 threads),
+// else they are read again from the caches.
+//
+// What bounds it is latency: three dependent trips to memory (count, keys, results) and a dozen
+// barriers; 128 queries of 15000 keys also take the time their keys need to come from another
+// chiplet's cache.  One query of 10^4 keys: 11 us, where a wavefront per slice (17 us) and a kernel
+// that joined 25 sorted slices (103 us) did the same before; 40 slices joined by binary searches took
+// 20 + 198 us, now 16.
+//
+// A query with very many keys is cut into up to `splits` parts, as many as its count asks for; each
+// part leaves its ascending list and the last block to finish selects again from those.
+#include "icq_internal.h"
+#include "icq_sort.h"
+
+#include <math.h>
+
+namespace {
+
+constexpr int SEL_LIST = 1024;     // keys the LDS list holds; topk <= 512
+constexpr int SEL_PART = 131072;   // keys a block takes alone: joining parts costs two device-wide fences, several
+                                   // passes' worth (Q = 128, 15000 keys each in one / two parts: 20 / 218 us)
+constexpr int SEL_RANK = 256;      // up to so many keys are ranked by counting, more are sorted
+
+template <int T>
+struct SelShared {
+    IcqKthSharedT<T> kth;
+    uint32_t cnt, total, minima, last;
+    uint32_t rank[SEL_RANK];
+};
+
+// The topk smallest keys of in[0..n) (KEY_PAD entries are skipped) -> list[0..kept) ascending;
+// returns kept = min(topk, number of keys).  PER: keys per thread held in registers.  Every thread of the block calls.
+template <int T, int PER>
+__device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, int topk) {
+    const int tid = threadIdx.x;
+    const uint32_t lane = (uint32_t)tid & 63u;
+    const int wave = tid >> 6;
+    if (n == 0) return 0;
+    u64 r[PER];
+    auto load = [&](u64 base) {        // unconditional, clamped: all of a thread's loads are in flight together
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const u64 i = base + (u64)j * T + tid;
+            r[j] = in[i < n ? i : n - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (base + (u64)j * T + tid >= n) r[j] = KEY_PAD;
+    };
+    const bool once = n <= (u64)PER * T;
+    uint32_t m = 0xFFFFFFFFu, real = 0;
+    bool any = false;
+    if (tid == 0) sh.cnt = sh.total = sh.minima = 0;
+    for (u64 base = 0; base < n; base += (u64)PER * T) {
+        load(base);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint32_t d = (uint32_t)(r[j] >> 32);
+            const bool ok = r[j] != KEY_PAD;
+            m = ok && d < m ? d : m;
+            any |= ok;
+            real += ok ? 1u : 0u;
+        }
+    }
+    __syncthreads();
+    {
+        const uint32_t wr = wave_scan_add(real);
+        const uint64_t wm = __builtin_amdgcn_ballot_w64(any);
+        if (lane == 63) {
+            atomicAdd(&sh.total, wr);
+            atomicAdd(&sh.minima, (uint32_t)__builtin_popcountll(wm));
+        }
+    }
+    __syncthreads();
+    const uint32_t total = sh.total, minima = sh.minima;
+    uint32_t bound = 0xFFFFFFFFu;
+    if (total > (uint32_t)topk && minima >= (uint32_t)topk) {
+        const uint32_t v[1] = {m};
+        bound = block_kth<1>(sh.kth, v, any ? 1u : 0u, (uint32_t)topk, false, tid, lane, wave);
+    }
+    // collect: keys at or below the bound
+    auto collect = [&]() {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const bool keep = r[j] != KEY_PAD && (uint32_t)(r[j] >> 32) <= bound;
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+            if (mask == 0) continue;                       // wavefront-uniform
+            uint32_t slot = 0;
+            if (lane == 0) slot = atomicAdd(&sh.cnt, (uint32_t)__builtin_popcountll(mask));
+            slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+            slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, slot));
+            if (keep && slot < (uint32_t)SEL_LIST) list[slot] = r[j];
+        }
+    };
+    if (once) {
+        collect();
+    } else {
+        for (u64 base = 0; base < n; base += (u64)PER * T) {
+            load(base);
+            collect();
+        }
+    }
+    __syncthreads();
+    uint32_t cnt = sh.cnt;
+    if (cnt > (uint32_t)SEL_RANK && cnt <= (uint32_t)SEL_LIST && cnt > (uint32_t)topk) {
+        // a fat histogram bin: cut the list exactly at the topk-th smallest distance (ties stay)
+        constexpr int LPT = SEL_LIST / T;
+        u64 e[LPT];
+        uint32_t v[LPT], ok = 0;
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const uint32_t i = (uint32_t)u * T + tid;
+            e[u] = list[i];
+            v[u] = (uint32_t)(e[u] >> 32);
+            if (i < cnt) ok |= 1u << u;
+        }
+        const uint32_t cut = block_kth<LPT>(sh.kth, v, ok, (uint32_t)topk, true, tid, lane, wave);
+        if (tid == 0) sh.cnt = 0;
+        __syncthreads();                                   // the list has been read, the counter is zero
+#pragma unroll
+        for (int u = 0; u < LPT; ++u)
+            if (((ok >> u) & 1u) && v[u] <= cut) list[atomicAdd(&sh.cnt, 1u)] = e[u];
+        __syncthreads();
+        cnt = sh.cnt;
+    }
+    if (cnt > (uint32_t)SEL_LIST) {
+        // Masses of equal distances, or too few threads with a key: exact radix select over whole keys (the
+        // id decides among equal distances), 8 bits at a time, re-reading the keys for every digit.
+        const uint32_t want = total < (uint32_t)topk ? total : (uint32_t)topk;
+        u64 prefix = 0;
+        uint32_t kr = want;
+        for (int shift = 56; shift >= 0; shift -= 8) {
+            __syncthreads();
+            if (tid < 256) sh.kth.hist[tid] = 0;
+            __syncthreads();
+            for (u64 i = tid; i < n; i += T) {
+                const u64 k = in[i];
+                if (k != KEY_PAD && (shift == 56 || (k >> (shift + 8)) == prefix))
+                    atomicAdd(&sh.kth.hist[(uint32_t)(k >> shift) & 255u], 1u);
+            }
+            __syncthreads();
+            // every wavefront locates the bin by itself (4 bins per lane)
+            uint32_t h[4], mine = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                h[b] = sh.kth.hist[lane * 4 + b];
+                mine += h[b];
+            }
+            const uint32_t incl = wave_scan_add(mine);
+            const int L = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl >= kr));
+            uint32_t run = incl - mine, my_bin = 0, my_below = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                if (run < kr && run + h[b] >= kr) {
+                    my_bin = lane * 4 + b;
+                    my_below = run;
+                }
+                run += h[b];
+            }
+            prefix = (prefix << 8) | (uint32_t)__builtin_amdgcn_readlane((int)my_bin, L);
+            kr -= (uint32_t)__builtin_amdgcn_readlane((int)my_below, L);
+        }
+        // the keys below the cut, then copies of it (a caller's list may name an item twice) up to `want`
+        __syncthreads();
+        if (tid == 0) sh.cnt = 0;
+        __syncthreads();
+        for (u64 i = tid; i < n; i += T) {
+            const u64 k = in[i];
+            if (k < prefix) list[atomicAdd(&sh.cnt, 1u)] = k;
+        }
+        __syncthreads();
+        for (uint32_t i = sh.cnt + (uint32_t)tid; i < want; i += T) list[i] = prefix;
+        __syncthreads();
+        cnt = want;
+    }
+    const int kept = (int)cnt < topk ? (int)cnt : topk;
+    if (cnt <= (uint32_t)SEL_RANK) {
+        // rank = number of keys before one's own (equal keys: by place); W threads side by side, T / W
+        // groups of them share the counting
+        const uint32_t W = cnt <= 64 ? 64u : cnt <= 128 ? 128u : 256u;
+        const uint32_t i = (uint32_t)tid & (W - 1u), part = (uint32_t)tid / W, parts = (uint32_t)T / W;
+        const uint32_t per = (cnt + parts - 1) / parts, j0 = part * per, j1 = j0 + per < cnt ? j0 + per : cnt;
+        const u64 mine = i < cnt ? list[i] : KEY_PAD;
+        if (tid < SEL_RANK) sh.rank[tid] = 0;
+        __syncthreads();
+        uint32_t rank = 0;
+        for (uint32_t j = j0; j < j1; ++j) {
+            const u64 k = list[j];                         // one address for all lanes
+            rank += (k < mine || (k == mine && j < i)) ? 1u : 0u;
+        }
+        if (i < cnt && rank != 0) atomicAdd(&sh.rank[i], rank);
+        __syncthreads();                                   // the list has been read
+        if (tid < (int)cnt) list[sh.rank[tid]] = mine;     // tid < cnt <= W: i == tid
+    } else {
+        // bitonic sort of up to SEL_LIST keys in LDS by the whole block
+        int len = 512;
+        while (len < (int)cnt) len <<= 1;
+        for (int i = (int)cnt + tid; i < len; i += T) list[i] = KEY_PAD;
+        for (int k = 2; k <= len; k <<= 1) {
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                __syncthreads();
+                for (int i = tid; i < len / 2; i += T) {
+                    const int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1)), hi = lo | j;
+                    const u64 x = list[lo], y = list[hi];
+                    if ((x > y) == ((lo & k) == 0)) {
+                        list[lo] = y;
+                        list[hi] = x;
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    return kept;
+}
+
+// Grid: Q * splits blocks.  count != nullptr: count[q] keys (at most cap) at keys_in + q * cap, worked off
+// by one of the query's blocks per SEL_PART keys; count == nullptr: cap keys,
+// splits == 1.  compact: the result's keys also replace the query's keys, and their number count[q] (more keys
+// are going to be appended; what is left out here cannot reach the result).
+template <int T, int PER>
+__global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count, int64_t cap, int topk, int splits,
+                                                   int compact, u64 *part_lists, uint32_t *ticket,
+                                                   uint32_t *__restrict__ out_ids, float *__restrict__ out_dist) {
+    __shared__ SelShared<T> sh;
+    __shared__ __attribute__((aligned(16))) u64 list[SEL_LIST];
+    const int q = blockIdx.x / splits, sp = blockIdx.x % splits;
+    const int tid = threadIdx.x;
+    u64 n = (u64)cap;
+    int used = 1;
+    if (count) {
+        n = count[q];
+        if (n > (u64)cap) n = (u64)cap;
+        const u64 want = (n + (u64)SEL_PART - 1) / (u64)SEL_PART;
+        used = want > (u64)splits ? splits : want > 1 ? (int)want : 1;
+    }
+    if (sp >= used) return;                                // block-uniform
+    const u64 lo = n * (u64)sp / (u64)used, hi = n * (u64)(sp + 1) / (u64)used;
+    int kept = block_select<T, PER>(sh, list, keys_in + (int64_t)q * cap + lo, hi - lo, topk);
+    if (used > 1) {
+        u64 *mine = part_lists + ((int64_t)q * splits + sp) * topk;
+        for (int i = tid; i < topk; i += T) mine[i] = i < kept ? list[i] : KEY_PAD;
+        __threadfence();                                   // the list is visible before the ticket is
+        __syncthreads();
+        if (tid == 0) sh.last = atomicAdd(&ticket[q], 1u) == (uint32_t)(used - 1) ? 1u : 0u;
+        __syncthreads();
+        if (sh.last == 0) return;                          // block-uniform
+        __threadfence();
+        if (tid == 0) ticket[q] = 0;                       // for the call's next selection
+        __syncthreads();
+        kept = block_select<T, PER>(sh, list, part_lists + (int64_t)q * splits * topk, (u64)used * topk, topk);
+    }
+    for (int i = tid; i < topk; i += T) {
+        const bool have = i < kept;
+        const u64 k = list[have ? i : 0];
+        out_ids[(int64_t)q * topk + i] = have ? (uint32_t)k : ICQ_PAD_ID;
+        out_dist[(int64_t)q * topk + i] = have ? icq_unorder_bits((uint32_t)(k >> 32)) : INFINITY;
+        if (compact && have) keys_in[(int64_t)q * cap + i] = k;        // kept <= count[q]: inside the query's keys
+    }
+    if (compact && tid == 0) count[q] = (uint32_t)kept;
+}
+
+template <int T, int PER>
+int launch_select(u64 *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact, u64 *part_lists,
+                  uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
+    select_kernel<T, PER><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, compact ? 1 : 0, part_lists, ticket,
+                                                                       out_ids, out_dist);
+    return icq_check_launch();
+}
+
+}  // namespace
+
+// Parts a query's keys may be cut into: more than one only where the queries leave the chip mostly idle.
+int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
+    if (Q <= 0) return 1;
+    int64_t s = ix->num_cu / Q;
+    const int64_t by_len = cap / SEL_PART + 1;
+    const int64_t by_merge = 4096 / topk;       // the parts' lists fit one block's registers again
+    if (s > by_len) s = by_len;
+    if (s > by_merge) s = by_merge;
+    if (s > 32) s = 32;
+    return s < 1 ? 1 : (int)s;
+}
+
+int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
+                      unsigned long long *part_lists, uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
+    if (Q == 0) return ICQ_OK;
+    // 1024 threads while every query's block finds a CU to itself or to share with one other, or where the list is
+    // longer than the minima of 512 threads bound well; else 512 threads, of which a CU runs four blocks (1000
+    // queries of 10^4 keys: 34 us against 45).  Eight keys per thread in registers: sixteen gain nothing on lists
+    // that fit and hold twice the registers on those that do not.
+    const bool wide = topk > 256 || (count && (int64_t)Q * splits <= 512);
+    if (wide) return launch_select<1024, 8>(keys, count, cap, Q, topk, splits, compact, part_lists, ticket, out_ids, out_dist, s);
+    return launch_select<512, 8>(keys, count, cap, Q, topk, splits, compact, part_lists, ticket, out_ids, out_dist, s);
+}

@@ -172,20 +172,22 @@ __device__ inline void wave_sort(u64 *keys, int len, int lane) {
         if (r < E) keys[r * 64 + lane] = x[r];
 }
 
-// LDS scratch of block_kth.
-struct IcqKthShared {
+// LDS scratch of block_kth for blocks of THREADS threads.
+template <int THREADS>
+struct IcqKthSharedT {
     uint32_t hist[256];
-    uint32_t wred[ICQ_SORT_THREADS / 64][2];
+    uint32_t wred[THREADS / 64][2];
 };
+using IcqKthShared = IcqKthSharedT<ICQ_SORT_THREADS>;
 
 // The kr-th smallest (1-based) of the values v[u] whose bit u is set in `ok`, taken over
-// the whole block of ICQ_SORT_THREADS threads (LPT <= 32 values per thread); at least kr values are flagged.  EXACT: that value (radix select, 8-bit
+// the whole block of THREADS >= 256 threads (LPT <= 32 values per thread); at least kr values are flagged.  EXACT: that value (radix select, 8-bit
 // digits over the occupied range).  Otherwise a single counting pass over the top 8 bits
 // of the occupied range; the result is the largest value of the bin that holds the kr-th
 // smallest, i.e. an upper bound that keeps the bin whole.  Every thread calls (barriers).
 // WEIGHTED: value v[u] counts wgt[u] times (kr at most the flagged weights' sum, which fits 32 bits).
-template <int LPT, bool WEIGHTED>
-__device__ __forceinline__ uint32_t block_kth_impl(IcqKthShared &sh, const uint32_t (&v)[LPT], const uint32_t (&wgt)[LPT],
+template <int LPT, bool WEIGHTED, int THREADS>
+__device__ __forceinline__ uint32_t block_kth_impl(IcqKthSharedT<THREADS> &sh, const uint32_t (&v)[LPT], const uint32_t (&wgt)[LPT],
                                                    uint32_t ok, uint32_t kr, bool EXACT, int tid, uint32_t lane, int wave) {
     uint32_t vmin = 0xFFFFFFFFu, vmax = 0u;
 #pragma unroll
@@ -201,7 +203,7 @@ __device__ __forceinline__ uint32_t block_kth_impl(IcqKthShared &sh, const uint3
     if (lane == 0) { sh.wred[wave][0] = vmin; sh.wred[wave][1] = vmax; }
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < ICQ_SORT_THREADS / 64; ++w) {
+    for (int w = 0; w < THREADS / 64; ++w) {
         const uint32_t a = sh.wred[w][0], b = sh.wred[w][1];
         vmin = a < vmin ? a : vmin;
         vmax = b > vmax ? b : vmax;
@@ -214,7 +216,7 @@ __device__ __forceinline__ uint32_t block_kth_impl(IcqKthShared &sh, const uint3
     uint32_t prefix = 0;       // chosen high digits of (value - vmin)
     int fixed_from = 32;       // bits [fixed_from, 32) of (value - vmin) are decided
     for (;;) {
-        sh.hist[tid] = 0;
+        if (THREADS == 256 || tid < 256) sh.hist[tid] = 0;
         __syncthreads();
         const uint32_t dmask = (1u << width) - 1u;
 #pragma unroll
@@ -259,16 +261,16 @@ __device__ __forceinline__ uint32_t block_kth_impl(IcqKthShared &sh, const uint3
     const unsigned long long top = (unsigned long long)vmin + ((((unsigned long long)prefix + 1ull) << shift) - 1ull);
     return top < (unsigned long long)vmax ? (uint32_t)top : vmax;
 }
-template <int LPT>
-__device__ __forceinline__ uint32_t block_kth(IcqKthShared &sh, const uint32_t (&v)[LPT], uint32_t ok, uint32_t kr,
+template <int LPT, int THREADS>
+__device__ __forceinline__ uint32_t block_kth(IcqKthSharedT<THREADS> &sh, const uint32_t (&v)[LPT], uint32_t ok, uint32_t kr,
                                               bool EXACT, int tid, uint32_t lane, int wave) {
-    return block_kth_impl<LPT, false>(sh, v, v, ok, kr, EXACT, tid, lane, wave);
+    return block_kth_impl<LPT, false, THREADS>(sh, v, v, ok, kr, EXACT, tid, lane, wave);
 }
 // One counting pass with weights: the top of the first bin at which the weights of the flagged
 // values at or below it add up to kr or more.
 template <int LPT>
 __device__ __forceinline__ uint32_t block_kth_weighted(IcqKthShared &sh, const uint32_t (&v)[LPT], const uint32_t (&wgt)[LPT],
                                                        uint32_t ok, uint32_t kr, int tid, uint32_t lane, int wave) {
-    return block_kth_impl<LPT, true>(sh, v, wgt, ok, kr, false, tid, lane, wave);
+    return block_kth_impl<LPT, true, ICQ_SORT_THREADS>(sh, v, wgt, ok, kr, false, tid, lane, wave);
 }
 

@@ -236,6 +236,38 @@ def test_refine_matches_oracle(gpu, name, N, Q, over, rule, topk):
     assert np.array_equal(out_ids2, out_ids) and np.array_equal(out_dist2, out_dist)
 
 
+@pytest.mark.parametrize("Q,n,topk,values", [
+    (1, 8192, 100, "real"), (1, 8193, 100, "real"),        # one load of a block's registers, and one key more
+    (2, 131_073, 20, "real"), (1, 300_001, 512, "real"),   # several parts per query, joined
+    (3, 20_000, 512, "few"), (2, 140_000, 64, "few"),      # masses of equal distances: the ids decide
+    (600, 700, 256, "real"), (5, 1000, 257, "few"),        # the two block sizes at their longest result
+    (4, 300, 1, "real"), (40, 257, 300, "real"),           # shortest result; fewer keys than the result holds
+])
+def test_refine_lists_are_the_exact_smallest_keys(gpu, Q, n, topk, values):
+    """The list of every query = the first topk of its candidates ordered by (D, id), D the fp32 sum in codebook
+    order: exact, since the sums are formed from the given tables in that order on both sides."""
+    torch, _ = gpu
+    rng = np.random.default_rng(Q * 1000 + topk)
+    K, m, d, N = 4, 256, 8, n + 50
+    cfg = dict(K=K, Kf=2, codebooks=rng.standard_normal((K, m, d)).astype(np.float32),
+               codes=rng.integers(0, m, (K, N), dtype=np.uint8), queries=np.zeros((Q, d), np.float32))
+    g = Gpu(gpu, cfg)
+    lut = rng.random((Q, K, 256), dtype=np.float32) if values == "real" else \
+        rng.integers(0, 2, (Q, K, 256)).astype(np.float32)
+    ids = np.stack([rng.permutation(N)[:n] for _ in range(Q)]).astype(np.int32)
+    cnt = np.array([n if q % 4 == 0 else n // (q % 4 + 1) * (q % 7 != 3) for q in range(Q)], np.int32)
+    out_ids, out_dist = g.refine(_dev(torch, lut), _dev(torch, ids), None, _dev(torch, cnt), topk)
+    for q in range(Q):
+        mine = ids[q, :cnt[q]]
+        D = lut[q, 0, cfg["codes"][0, mine]]
+        for k in range(1, K):
+            D = D + lut[q, k, cfg["codes"][k, mine]]
+        order = np.lexsort((mine, D))[:topk]
+        kept = order.size
+        assert np.array_equal(out_ids[q, :kept], mine[order].astype(np.uint32)) and np.array_equal(out_dist[q, :kept], D[order])
+        assert (out_ids[q, kept:] == 0xFFFFFFFF).all() and np.isinf(out_dist[q, kept:]).all()
+
+
 # ------------------------------------------------------------------ whole path
 def _check_search(g, cfg, T, P, D, thr, topk, cap, min_equal=0.9):
     out_ids, out_dist, surv = g.search(thr, cap, topk)
