@@ -86,101 +86,132 @@ __global__ void group_zero_kernel(uint32_t *__restrict__ p, int n) {
 
 // ---- query time
 constexpr int GS_THREADS = 256;
-constexpr int GS_HITS = 8192;     // LDS buffer of tuples below the threshold
-constexpr int GS_ROWS = 16;       // rows (of 256 tuples) between two looks at the buffer
+constexpr int GS_WAVES = GS_THREADS / 64;
+constexpr int GS_WHITS = 1024;    // tuples below the threshold a wavefront buffers between two expansions
+constexpr int GS_AHEAD = 4;       // windows of 64 survivors whose ids are loaded together
 
-// grid (parts, Q): a block evaluates the tuples (c0, c1) with c0 in its part's row
-// range for one query; thread t owns column c1 = t (Kf == 2) or tuple c0 = t (Kf == 1).
-// Tuples below the threshold are buffered in LDS (typically all of a query's fit, so
-// there is one expansion at the end); each wavefront then takes 64 of them at a
-// time, reserves list space for all their items with one atomic and writes the
-// items' positions (or ids) with coalesced stores.
+// grid (parts, Q): a block takes the tuples (c0, c1) of one query whose c0 is congruent to its part's number;
+// at its i-th row wavefront w evaluates the 64 columns of group (w + i) mod 4, so that the rows and columns
+// of a query's nearest codewords -- where its survivors sit -- are dealt out evenly (Kf == 1: one row, tuple
+// c0 = column).  A wavefront is on its own once the tables are in LDS: the tuples below the threshold go to
+// its own buffer (ballot, no atomics); expanding it takes one atomic on the query's counter for all their
+// items and then writes them 64 at a time, whatever the tuple sizes: a tuple that starts inside a window
+// marks its first survivor's lane, a running maximum over the lanes carries it to the others.  One tuple at
+// a time instead, its few items as one short row of lanes, was a chain of one memory round trip per tuple
+// (199 queries, 250 001 items, 6 % survivors: 104 us, 118 with the partial sums in a kernel of their own;
+// now 21 us for both).  What bounds it: latency -- the loads of `start`, then of `perm`, then the stores.
 template <int KF>
 __global__ __launch_bounds__(GS_THREADS) void group_scan_kernel(
     const float *__restrict__ lut, int K, const float *__restrict__ thr,
     const uint32_t *__restrict__ start, const uint32_t *__restrict__ perm,
-    uint32_t *__restrict__ out, uint32_t *__restrict__ count, int64_t cap, int rows_per_block) {
-    __shared__ float t0[ICQ_LUT_W];
-    __shared__ uint32_t hits[GS_HITS];
-    __shared__ uint32_t s_nh;
+    uint32_t *__restrict__ out, float *__restrict__ out_part, uint32_t *__restrict__ count, int64_t cap) {
+    __shared__ float t0[ICQ_LUT_W], t1[ICQ_LUT_W];
+    __shared__ uint16_t hits_all[GS_WAVES][GS_WHITS];
+    __shared__ uint32_t mark_all[GS_WAVES][GS_AHEAD * 64];
+    __shared__ uint2 tuple_all[GS_WAVES][64];              // first position minus prefix, bits of P
     const int tid = threadIdx.x;
     const uint32_t lane = lane_id();
-    const int wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int q = blockIdx.y;
     const float *T = lut + (int64_t)q * K * ICQ_LUT_W;
     const float t = thr[q];
     uint32_t *my_out = out + (int64_t)q * cap;
+    float *my_part = out_part ? out_part + (int64_t)q * cap : nullptr;
+    uint16_t *hits = hits_all[wave];
+    uint32_t *mark = mark_all[wave];
+    uint2 *tuple = tuple_all[wave];
 
     t0[tid] = T[tid];
-    const float t1 = KF == 2 ? T[ICQ_LUT_W + tid] : 0.0f;
-    if (tid == 0) s_nh = 0;
-    __syncthreads();
+    if (KF == 2) t1[tid] = T[ICQ_LUT_W + tid];
+#pragma unroll
+    for (int u = 0; u < GS_AHEAD; ++u) mark[u * 64 + lane] = 0;
+    __syncthreads();                                       // the only barrier
 
-    auto expand = [&](uint32_t nh) {   // every thread calls; nh is block-uniform
-        for (uint32_t h0 = wave * 64; h0 < nh; h0 += (GS_THREADS / 64) * 64) {
+    auto expand = [&](uint32_t nh) {                       // nh <= GS_WHITS, wavefront-uniform
+        __builtin_amdgcn_wave_barrier();                   // LDS runs a wavefront's accesses in order
+        uint32_t tot = 0;
+        for (uint32_t h0 = 0; h0 < nh; h0 += 64) {
             const uint32_t h = h0 + lane;
-            uint32_t s = 0, n = 0;
-            if (h < nh) {
-                const uint32_t g = hits[h];
-                s = start[g];
-                n = start[g + 1] - s;
-            }
-            const uint32_t incl = wave_scan_add(n);
-            const uint32_t tot = __builtin_amdgcn_readlane(incl, 63);
-            if (tot == 0) continue;
-            uint32_t base = 0;
-            if (lane == 0) base = atomicAdd(&count[q], tot);
-            base = __builtin_amdgcn_readfirstlane(base);
-            const uint32_t excl = incl - n;
-            uint64_t live = __builtin_amdgcn_ballot_w64(n != 0);
-            while (live != 0) {
-                const int l = __builtin_ctzll(live);
-                live &= live - 1;
-                const uint32_t sl = __builtin_amdgcn_readlane(s, l);
-                const uint32_t nl = __builtin_amdgcn_readlane(n, l);
-                const uint64_t ol = (uint64_t)base + __builtin_amdgcn_readlane(excl, l);
-                for (uint32_t j = lane; j < nl; j += 64) {
-                    const uint64_t slot = ol + j;
-                    if (slot < (uint64_t)cap) my_out[slot] = perm ? perm[sl + j] : sl + j;
+            const uint32_t g = hits[h < nh ? h : 0];
+            const uint32_t n = start[g + 1] - start[g];
+            tot += h < nh ? n : 0u;
+        }
+        tot = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(tot), 63);
+        if (tot == 0) return;
+        uint32_t slot0 = 0;
+        if (lane == 0) slot0 = atomicAdd(&count[q], tot);
+        slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot0);
+        for (uint32_t h0 = 0; h0 < nh; h0 += 64) {
+            const uint32_t h = h0 + lane;
+            const uint32_t g = hits[h < nh ? h : 0];
+            const uint32_t s = start[g];
+            const uint32_t n = h < nh ? start[g + 1] - s : 0u;
+            const uint32_t incl = wave_scan_add(n), excl = incl - n;
+            const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            // same additions as the item-by-item scan: lut[0][c0] (+ lut[1][c1])
+            const float P = KF == 2 ? t0[g >> 8] + t1[g & 255u] : t0[g];
+            __builtin_amdgcn_wave_barrier();
+            tuple[lane] = make_uint2(s - excl, __float_as_uint(P));
+            uint32_t carry = 0;                            // tuple (lane + 1) that holds the survivor before the window
+            for (uint32_t w0 = 0; w0 < m; w0 += GS_AHEAD * 64) {
+                // marks of the tuples that start inside these windows
+                const bool starts = n != 0 && excl >= w0 && excl < w0 + GS_AHEAD * 64;
+                if (starts) mark[excl - w0] = lane + 1;
+                __builtin_amdgcn_wave_barrier();
+                uint32_t id[GS_AHEAD], pb[GS_AHEAD];
+#pragma unroll
+                for (int u = 0; u < GS_AHEAD; ++u) {
+                    uint32_t x = mark[u * 64 + lane];
+                    uint32_t y;                            // inclusive maximum over the lanes: tuples are numbered in order
+                    y = icq_dpp<0x111, 0xf, 0u>(x); x = y > x ? y : x;
+                    y = icq_dpp<0x112, 0xf, 0u>(x); x = y > x ? y : x;
+                    y = icq_dpp<0x114, 0xf, 0u>(x); x = y > x ? y : x;
+                    y = icq_dpp<0x118, 0xf, 0u>(x); x = y > x ? y : x;
+                    y = icq_dpp<0x142, 0xa, 0u>(x); x = y > x ? y : x;
+                    y = icq_dpp<0x143, 0xc, 0u>(x); x = y > x ? y : x;
+                    x = x > carry ? x : carry;
+                    carry = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+                    const uint2 tu = tuple[x - 1];         // x >= 1: the first survivor's tuple is marked
+                    const uint32_t p = w0 + (uint32_t)u * 64u + lane;
+                    const uint32_t pos = tu.x + (p < m ? p : m - 1);   // past the end: the last tuple's last item again
+                    id[u] = perm ? perm[pos] : pos;
+                    pb[u] = tu.y;
+                }
+                __builtin_amdgcn_wave_barrier();
+                if (starts) mark[excl - w0] = 0;
+#pragma unroll
+                for (int u = 0; u < GS_AHEAD; ++u) {
+                    const uint32_t p = w0 + (uint32_t)u * 64u + lane;
+                    const uint64_t slot = (uint64_t)slot0 + p;
+                    if (p < m && slot < (uint64_t)cap) {
+                        my_out[slot] = id[u];
+                        if (my_part) my_part[slot] = __uint_as_float(pb[u]);
+                    }
                 }
             }
+            slot0 += m;                                    // at most N in all: no wrap
         }
     };
 
-    const int row_begin = KF == 2 ? blockIdx.x * rows_per_block : 0;
-    const int row_end = KF == 2 ? (row_begin + rows_per_block < 256 ? row_begin + rows_per_block : 256) : 1;
-    for (int r0 = row_begin; r0 < row_end; r0 += GS_ROWS) {
-        const int r1 = r0 + GS_ROWS < row_end ? r0 + GS_ROWS : row_end;
-        for (int c0 = r0; c0 < r1; ++c0) {
-            // same additions as the item-by-item scan: lut[0][c0] (+ lut[1][c1])
-            const float P = KF == 2 ? t0[c0] + t1 : t0[tid];
-            const bool hit = P < t;
-            const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
-            if (mask != 0) {
-                uint32_t base = 0;
-                const int leader = __builtin_ctzll(mask);
-                if ((int)lane == leader) base = atomicAdd(&s_nh, (uint32_t)__builtin_popcountll(mask));
-                base = __builtin_amdgcn_readlane(base, leader);
-                if (hit)
-                    hits[base + __builtin_popcountll(mask & ((1ull << lane) - 1))] =
-                        KF == 2 ? (uint32_t)c0 * 256u + (uint32_t)tid : (uint32_t)tid;
-            }
+    uint32_t nh = 0;                                       // wavefront-uniform
+    const int parts = gridDim.x;
+    int i = 0;
+    for (int row = KF == 2 ? (int)blockIdx.x : 0; row < (KF == 2 ? 256 : 1); row += parts, ++i) {
+        const uint32_t col = (uint32_t)(((wave + i) & (GS_WAVES - 1)) * 64) + lane;
+        const float P = KF == 2 ? t0[row] + t1[col] : t0[col];
+        const bool hit = P < t;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
+        if (mask == 0) continue;
+        if (nh > (uint32_t)(GS_WHITS - 64)) {
+            expand(nh);
+            nh = 0;
         }
-        if (r1 < row_end) {
-            // room for another GS_ROWS rows?  (uniform decision: read between two barriers)
-            __syncthreads();
-            const uint32_t nh = s_nh;
-            __syncthreads();
-            if (nh > (uint32_t)(GS_HITS - GS_ROWS * 256)) {
-                expand(nh);
-                __syncthreads();
-                if (tid == 0) s_nh = 0;
-                __syncthreads();
-            }
-        }
+        if (hit)
+            hits[__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, nh))] =
+                (uint16_t)((uint32_t)row * 256u + col);
+        nh += (uint32_t)__builtin_popcountll(mask);
     }
-    __syncthreads();
-    expand(s_nh);
+    expand(nh);
 }
 
 // ---- grouped stage 1 fused with stage 2
@@ -881,22 +912,23 @@ static int group_parts(const icq_index *ix, int Q) {
 }
 
 int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
-                          uint32_t *cand_ids, bool as_positions, uint32_t *cand_count, int64_t cap,
+                          uint32_t *cand_ids, float *cand_part, bool as_positions, uint32_t *cand_count, int64_t cap,
                           hipStream_t s) {
-    // cand_count is zero
-    const int parts = group_parts(ix, Q);
-    const int rows = (256 + parts - 1) / parts;
+    // cand_count is zero.  Four to eight blocks of four wavefronts per CU while the queries leave room for it; at
+    // most 64 parts: a row per wavefront and four tables' worth of columns is little for a block already
+    int parts = ix->Kf == 2 ? (int)((4ll * ix->num_cu + Q - 1) / Q) : 1;
+    if (parts > 64) parts = 64;
+    if (parts < 1) parts = 1;
     for (int q0 = 0; q0 < Q; q0 += 65535) {
         const int nq = Q - q0 < 65535 ? Q - q0 : 65535;
         dim3 grid((unsigned)parts, (unsigned)nq);
-        if (ix->Kf == 1)
-            group_scan_kernel<1><<<grid, GS_THREADS, 0, s>>>(
-                lut + (int64_t)q0 * ix->K * ICQ_LUT_W, ix->K, thr + q0, ix->group_start,
-                as_positions ? nullptr : ix->perm, cand_ids + (int64_t)q0 * cap, cand_count + q0, cap, rows);
-        else
-            group_scan_kernel<2><<<grid, GS_THREADS, 0, s>>>(
-                lut + (int64_t)q0 * ix->K * ICQ_LUT_W, ix->K, thr + q0, ix->group_start,
-                as_positions ? nullptr : ix->perm, cand_ids + (int64_t)q0 * cap, cand_count + q0, cap, rows);
+        auto launch = [&](auto kernel) {
+            kernel<<<grid, GS_THREADS, 0, s>>>(lut + (int64_t)q0 * ix->K * ICQ_LUT_W, ix->K, thr + q0, ix->group_start,
+                                               as_positions ? nullptr : ix->perm, cand_ids + (int64_t)q0 * cap,
+                                               cand_part ? cand_part + (int64_t)q0 * cap : nullptr, cand_count + q0, cap);
+        };
+        if (ix->Kf == 1) launch(group_scan_kernel<1>);
+        else launch(group_scan_kernel<2>);
     }
     return icq_check_launch();
 }

@@ -20,7 +20,9 @@
 
 namespace {
 
-constexpr int SP_THREADS = ICQ_SORT_THREADS;
+// the block's life is a chain of round trips (records, tables, histogram passes), so the sample is spread over
+// as many threads as a block can have: 19 us with 256 threads, 11 with 1024 (199 queries, 4096 items)
+constexpr int SP_THREADS = 1024;
 
 constexpr int SP_LPT = ICQ_MAX_SAMPLE / SP_THREADS;    // sample items per thread
 static_assert(ICQ_MAX_SAMPLE % SP_THREADS == 0 && SP_LPT <= 32, "one flag bit per item of a thread");
@@ -33,7 +35,7 @@ __global__ __launch_bounds__(SP_THREADS) void sample_threshold_kernel(
     const uint8_t *__restrict__ items, int stride, int K, int Kf, const float *__restrict__ lut,
     const float *__restrict__ sigma, int topk, int n, float *__restrict__ thr_out) {
     extern __shared__ __attribute__((aligned(16))) float sp_smem[];
-    __shared__ IcqKthShared kth;
+    __shared__ IcqKthSharedT<SP_THREADS> kth;
     __shared__ uint32_t s_below[SP_THREADS / 64];
     float *T = sp_smem;
     const int q = blockIdx.x, tid = threadIdx.x;

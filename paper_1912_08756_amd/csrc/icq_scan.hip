@@ -627,7 +627,6 @@ int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *t
     if (Q == 0) return ICQ_OK;
     if (ix->N == 0) return ICQ_OK;
 
-    const int bpq_fill = (int)((cap + 255) / 256 < 32 ? (cap + 255) / 256 : 32);
     if (icq_group_usable(ix, Q) && list_kind && !cand_part && ix->item_stride <= 16 &&
         (cand_keys || (out_ids && icq_group_fused(ix, Q, topk)))) {
         // the caller only wants the final lists: finish the distances (and, where one block
@@ -638,13 +637,9 @@ int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *t
     if (icq_group_usable(ix, Q)) {
         // positions only when the caller can take them and needs no crude distances
         const bool as_positions = list_kind != nullptr && cand_part == nullptr;
-        int rc = icq_launch_group_scan(ix, lut, Q, thr, cand_ids, as_positions, cand_count, cap, s);
-        if (rc != ICQ_OK) return rc;
-        if (as_positions) *list_kind = ICQ_LIST_POSITIONS;
-        if (!cand_part) return ICQ_OK;
-        fill_partials_kernel<<<(unsigned)Q * (unsigned)bpq_fill, 256, 0, s>>>(
-            ix->fast, ix->Npad, lut, ix->K, ix->Kf, cand_ids, cand_count, cap, bpq_fill, cand_part);
-        return icq_check_launch();
+        const int rc = icq_launch_group_scan(ix, lut, Q, thr, cand_ids, cand_part, as_positions, cand_count, cap, s);
+        if (rc == ICQ_OK && as_positions) *list_kind = ICQ_LIST_POSITIONS;
+        return rc;
     }
 
     if (ix->Kf <= 4) {

@@ -210,6 +210,29 @@ def test_scan_fast_special_thresholds_and_overflow(gpu, Q, mode):
         check_candidates(P[q], thr[q], ids[q], part[q], cnt[q], cap)
 
 
+@pytest.mark.parametrize("Q,Kf,m,N", [
+    (140, 2, 256, 70_001),     # every tuple below the threshold: a wavefront's buffer fills and is expanded more than once
+    (3, 2, 3, 40_003),         # nine tuples of 4445 items: windows of survivors far longer than a step
+    (2, 1, 256, 70_001), (70, 1, 2, 5_000),
+])
+def test_scan_fast_grouped_lists_at_the_edges_of_its_buffers(gpu, Q, Kf, m, N):
+    """Grouped lists against the item-by-item lists (same additions): equal as sets, crude distances bit for bit."""
+    cfg = small("C1", N, Q, d=16, Kf=Kf, m=m)
+    lists = []
+    for mode in (1, 2):
+        g = Gpu(gpu, cfg, mode)
+        lut = g.lut()
+        sums = np.sort(sum(lut.cpu().numpy()[:, k, cfg["codes"][k]] for k in range(Kf)), axis=1)
+        thr = np.where(np.arange(Q) % 2 == 0, np.inf, sums[:, N // 2]).astype(np.float32)
+        ids, part, cnt = g.scan(lut, thr, N)
+        ids, part, cnt = _u32(ids), part.cpu().numpy(), _u32(cnt)
+        order = np.argsort(np.where(np.arange(N) < cnt[:, None], ids, 0xFFFFFFFF), axis=1, kind="stable")
+        lists.append((cnt, [(ids[q][order[q, :cnt[q]]], part[q][order[q, :cnt[q]]]) for q in range(Q)]))
+    assert np.array_equal(lists[0][0], lists[1][0]) and (lists[0][0][::2] == N).all()
+    for a, b in zip(lists[0][1], lists[1][1]):
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
 # ------------------------------------------------------------------ stage 2 + list
 @pytest.mark.parametrize("name,N,Q,over,rule,topk", [
     ("C0", 10_000, 100, {}, ("kth", 20, 1.5), 10),
