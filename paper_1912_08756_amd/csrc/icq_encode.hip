@@ -4,17 +4,33 @@
 // codebook order:
 //     r_0 = x_i;  code_k(i) = argmin_j ||r_k - c_{k,j}||^2 (ties: smallest j);
 //     r_{k+1} = r_k - c_{k,code_k(i)}.
-// ||r - c||^2 = ||r||^2 - 2<r,c> + ||c||^2 and ||r||^2 does not depend on j, so a level
-// is one [N x d].[d x 256] contraction on the fp32 matrix cores with the epilogue
-// argmin_j (||c_j||^2 - 2<r,c_j>), followed by the residual update of the block's own
-// rows.
+// ||r - c||^2 = ||r||^2 - 2<r,c> + ||c||^2 and ||r||^2 does not depend on j, so a level is one
+// [N x d].[d x 256] contraction with the epilogue argmin_j (||c_j||^2 - 2<r,c_j>).
 //
 // icq_encode_refine revisits given codes by coordinate descent over the codebooks (iterated
 // conditional modes): with the other sub-codes of an item fixed, codebook k's codeword becomes the
 // nearest one to r = x - sum_{l != k} c_l, and only if that is strictly nearer than the current
-// one.  The kernel is the same contraction: the residual array holds x - xbar, a level adds the
-// current codeword back while staging its rows, the argmin prefers the current codeword among equal
-// scores, and only rows whose sub-code changed are rewritten.
+// one.  The residual holds x - xbar, a level adds the current codeword back, the argmin prefers the
+// current codeword among equal scores, and only items whose sub-code changed get a new residual.
+//
+// One kernel does both, all levels (and sweeps) of 128 items per block, in two steps per level:
+//  1. The contraction on half-precision copies of residual and codewords (v_mfma_f32_32x32x16_f16, sixteen
+//     times the rate of the fp32 instruction) leaves, with a bound E on its error, a SUPERSET of the
+//     codewords that can be the argmin: those whose score is within 2 E of the best.  E comes from
+//     Cauchy-Schwarz: |<r,c> - <r',c'>| <= ||r|| ||c - c'|| + ||r - r'|| ||c'||, with ||c - c'|| measured
+//     when the index is made, ||r - r'|| <= 2^-11 ||r||, and the accumulation's roundings.  All scales
+//     are powers of two, so nothing else is rounded.
+//  2. Items with more than one candidate (a few per cent) form the candidates' fp32 scores from the fp32
+//     residual and codewords and take the argmin of those.  The result is the fp32 argmin, as before.
+// Where more than eight codewords of an item are within the bound, the block repeats the level with both
+// operands split in two halves (three products, E smaller by 2^-10); more than eight after that -- equal
+// codewords -- and the item's scores are all formed in fp32.
+//
+// What bounds it: up to E_REG_D dimensions vector issue -- 800 instructions per wavefront and level (argmin 2.5
+// per score; residual, norms and conversion 5 per element) keep the vector units 64 % busy, the matrix
+// cores 20 % -- and, with more dimensions, the residuals' way through memory (4 TB/s at d = 256 and 960).
+// 10^6 x 128, K = 8: 1.25 ms; the fp32 contraction this replaces took 5.9 ms, 0.6 of the fp32 matrix
+// rate.  262147 x 96, K = 16, with two sweeps: 8.0 -> 2.0 ms.
 #include "icq_internal.h"
 #include "icq_sort.h"
 
@@ -22,198 +38,505 @@
 
 namespace {
 
-// the smaller of a lane's key and its DPP neighbour's (a lane without a source keeps its own)
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ u64 dpp_min64(u64 key) {
-    const uint32_t lo = icq_dpp<CTRL, ROW_MASK, 0xFFFFFFFFu>((uint32_t)key);
-    const uint32_t hi = icq_dpp<CTRL, ROW_MASK, 0xFFFFFFFFu>((uint32_t)(key >> 32));
-    const u64 o = ((u64)hi << 32) | lo;
-    return o < key ? o : key;
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+constexpr int EB = 128;           // items per block
+constexpr int E_THREADS = 512;
+constexpr int E_P = EB * 16 / E_THREADS;   // items per owner group of 16 threads
+constexpr int E_G = E_THREADS / 16;        // owner groups
+constexpr int E_REG_D = 128;      // up to this many dimensions the residual stays in registers
+constexpr int E_CAND = 8;         // candidates listed per item
+constexpr int E_FROW = EB + 1;    // 16-byte pieces per reduction group of the residual's fragments: one to spare, so
+                                  // that the 16 threads that write one row's groups meet different banks
+constexpr float E_U = 4.8828125e-4f;       // 2^-11: relative rounding error of a half
+
+struct EncShared {
+    uint4 frag[16 * E_FROW];               // a 128-wide slice of the residuals: [reduction index / 8][item]
+    uint4 cbs[2][4 * ICQ_LUT_W];           // a 32-wide slice of the codebook: [reduction index / 8][codeword]
+    float cnh[ICQ_LUT_W];                  // -||c||^2 / 2, scaled: what the accumulators start from
+    float nrm2[EB];                        // ||r||^2 (an item's entry, like its codes, belongs to its 16 threads)
+    float smax[4][EB];                     // best score among each 64 codewords
+    uint32_t ccount[EB];                   // candidates
+    uint8_t cand[EB][E_CAND];
+    uint8_t code[ICQ_MAX_K][EB];
+    uint8_t before[EB];                    // the sub-code the level before found
+    uint32_t over;                         // some item has more than E_CAND candidates
+};
+static_assert(sizeof(EncShared) <= 81920, "two blocks per CU");
+
+// x, from here on: what is derived from it is computed again instead of kept in a register since the kernel's start
+template <typename T>
+__device__ __forceinline__ T fresh(T x) {
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
-typedef float float16v __attribute__((ext_vector_type(16)));
-constexpr int EM = 64;            // items per block
-constexpr int EN = ICQ_LUT_W;     // codewords per level: the whole codebook (rows j >= m have norm +inf)
-constexpr int EK = 16;            // reduction slice staged in LDS
-constexpr int E_THREADS = 256;
+// sum over the 16 lanes of a DPP row, in every lane
+__device__ __forceinline__ float row_sum(float x) {
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x128, 0xf, 0xf, false));   // row_ror:8
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x124, 0xf, 0xf, false));
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x122, 0xf, 0xf, false));
+    x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x121, 0xf, 0xf, false));
+    return x;
+}
+// 2^(bits - e) with e the smallest integer for which x < 2^e (clamped): x times this is below 2^bits
+__device__ __forceinline__ float scale_below(float x, int bits) {
+    const int e = (int)((__float_as_uint(x) >> 23) & 255u) - 126;
+    int f = bits - e + 127;
+    f = f < 67 ? 67 : f > 187 ? 187 : f;                   // 2^-60 .. 2^60: products of two scales stay finite
+    return __uint_as_float((uint32_t)f << 23);
+}
 
-// One level for 64 items.  4 wavefronts, wavefront w owns codewords [64w, 64w + 64) as
-// 2x2 accumulators of 32x32 (MFMA 32x32x2 layout: lane l supplies A[l%32][l/32] and
-// B[l/32][l%32]; accumulator register v of lane l is C[(v%4) + 4*(l/32) + 8*(v/4)][l%32]).
-// src: x (row stride d, level 0) or the residuals (row stride d_pad); dst: residuals.
-// ICM: src = res holds x - xbar, codes_k holds the current sub-codes (in and out), *changed counts
-// the sub-codes replaced.
-template <bool ICM>
-__global__ __launch_bounds__(E_THREADS) void encode_level_kernel(
-    const float *src, int src_stride, int d, const float *__restrict__ cb_k, int d_pad,
-    const float *__restrict__ cnorm_k, int64_t N, uint8_t *codes_k, float *res, int vec_ok, uint32_t *changed) {
-    __shared__ float As[EK][EM + 1];
-    __shared__ float Bs[EK][EN + 1];
-    __shared__ u64 best[E_THREADS / 64][EM];
-    __shared__ uint32_t s_code[EM];
-    __shared__ uint32_t s_old[EM];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t i0 = (int64_t)blockIdx.x * EM;
-    const int le = tid & 15, lr = tid >> 4;       // reduction position and row (+16 per pass) of the staging loads
-    if (ICM && tid < EM) s_old[tid] = codes_k[i0 + tid < N ? i0 + tid : N - 1];     // visible after the first slice's barrier
+// x [N][d]; cb [K*256][d_pad] fp32; half_hi / half_lo: see
+// encode_pack_kernel; meta[k] = scale, largest ||c||, largest ||c - c'||.  REG: d <= E_REG_D, the residuals live in
+// registers; else in res [N][d_pad].  ICM: `codes` is in and out, `changed` (or nullptr) counts per sweep.
+//
+// Thread t owns the 8 dimensions from 8 (t % 16) on of the items t / 16 + 32 p, p = 0 .. 3 (of every 128-wide slice):
+// residual rows and codewords are read in whole pieces of 16 threads.  In the contraction the codewords are the rows of
+// the matrix instruction (wavefront w: the 64 from 64 (w % 4) on) and the items its columns (the 64 from 64 (w / 4) on),
+// so a lane holds 32 scores of one item per column block and the maximum is taken inside the lane.  64 x 64 scores per
+// wavefront are 64 registers, which with a thread's 32 residuals leave room for four wavefronts per SIMD (64 x 128 scores
+// by four wavefronts of 256 registers spilled: 3.8 ms at 10^6 x 128, K = 8, where this takes 1.25).
+template <bool REG, bool ICM>
+__global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
+    const float *__restrict__ x, int d, const float *__restrict__ cb, int d_pad, const float *__restrict__ cnorm,
+    const uint4 *__restrict__ half_hi, const uint4 *__restrict__ half_lo, const float4 *__restrict__ meta, int K, int m,
+    int64_t N, uint8_t *codes, int sweeps, float *res, uint32_t *changed) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char enc_smem[];
+    EncShared &sh = *reinterpret_cast<EncShared *>(enc_smem);
+    const int tid0 = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
+    const int64_t i0 = (int64_t)blockIdx.x * EB;
+    const int cw = wave & 3, ih = wave >> 2;
+    const int nks = (d_pad + 31) / 32;                     // 32-wide codebook slices
+    const int nsl = REG ? 1 : (nks + 3) / 4;               // 128-wide residual slices
+    // rows past N read the last row; their codes are never stored
+    auto row = [&](int rg, int p) { return i0 + rg + E_G * p < N ? i0 + rg + E_G * p : N - 1; };
 
-    float16v acc[2][2];
+    float r[REG ? E_P : 1][8];
+    float co[REG && ICM ? E_P : 1][8];                     // the current codewords of the level to come
+    auto load_x = [&](int rg, int p, int e0, float (&v)[8]) __attribute__((always_inline)) {
+        // Pieces need no alignment.  What lies outside the row is masked by bits: a select between a load and zero ends
+        // as a branch around the load, one wait per piece instead of all pieces in flight together.
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(4)));
+        const int64_t at = row(rg, p) * d + (e0 < d ? e0 : 0);
+        const uint32_t *s = reinterpret_cast<const uint32_t *>(x) + at;
+        if (at + 8 <= N * d) {
+            const u32x4 a = *reinterpret_cast<const u32x4 *>(s), b = *reinterpret_cast<const u32x4 *>(s + 4);
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 8; ++i) v[i] = __uint_as_float((i < 4 ? a[i & 3] : b[i & 3]) & (e0 + i < d ? ~0u : 0u));
+        } else {                                           // the end of x
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int i = 0; i < 8; ++i) v[i] = e0 + i < d ? __uint_as_float(s[i]) : 0.0f;
+        }
+    };
+    // eight values of a row of d_pad floats (a multiple of 16: the piece is inside or outside as a whole)
+    auto load8 = [&](const float *s, int e0, float (&v)[8]) __attribute__((always_inline)) {
+        const bool in = e0 < d_pad;
+        const uint4 a = *reinterpret_cast<const uint4 *>(s + (in ? e0 : 0));
+        const uint4 b = *reinterpret_cast<const uint4 *>(s + (in ? e0 + 4 : 4));
+        const uint32_t m = in ? ~0u : 0u;
+        const uint32_t w[8] = {a.x & m, a.y & m, a.z & m, a.w & m, b.x & m, b.y & m, b.z & m, b.w & m};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = __uint_as_float(w[i]);
+    };
+    auto codeword = [&](int k, uint32_t j) -> const float * {
+        if (REG) return cb + (((uint32_t)k * ICQ_LUT_W + j) * (uint32_t)d_pad);     // at most 2^21
+        return cb + ((int64_t)k * ICQ_LUT_W + j) * d_pad;
+    };
+    auto store_res = [&](int rg, int p, int e0, const float (&v)[8]) __attribute__((always_inline)) {
+        if (i0 + rg + E_G * p < N && e0 < d_pad) {
+            float *o = res + row(rg, p) * d_pad + e0;
+            *reinterpret_cast<float4v *>(o) = float4v{v[0], v[1], v[2], v[3]};
+            *reinterpret_cast<float4v *>(o + 4) = float4v{v[4], v[5], v[6], v[7]};
+        }
+    };
 
-    // Rows past N read the last row instead (their codes and residuals are never stored) and
-    // columns past d read column d - 1 (the codebook copy is zero there, the product vanishes):
-    // no load depends on a condition, so a slice's twenty are in flight together.
-    const float *arow[EM / 16];
-    const float *orow[EM / 16];                   // ICM: the row's current codeword, added back while staging
-#pragma unroll
-    for (int p = 0; p < EM / 16; ++p) {
-        const int64_t row = i0 + lr + 16 * p;
-        const int64_t rc = row < N ? row : N - 1;
-        arow[p] = src + rc * src_stride;
-        orow[p] = ICM ? cb_k + (int64_t)codes_k[rc] * d_pad : cb_k;
-    }
-    for (int k0 = 0; k0 < d_pad; k0 += EK) {
-        float a[EM / 16], b[EN / 16];
-        const int e = k0 + le;
-        const int ec = e < d ? e : d - 1;
-#pragma unroll
-        for (int p = 0; p < EM / 16; ++p) a[p] = ICM ? arow[p][ec] + orow[p][e] : arow[p][ec];
-#pragma unroll
-        for (int p = 0; p < EN / 16; ++p) b[p] = cb_k[(int64_t)(lr + 16 * p) * d_pad + e];
-        __syncthreads();   // previous slice fully consumed
-#pragma unroll
-        for (int p = 0; p < EM / 16; ++p) As[le][lr + 16 * p] = a[p];
-#pragma unroll
-        for (int p = 0; p < EN / 16; ++p) Bs[le][lr + 16 * p] = b[p];
+    if (ICM) {
+        for (int i = tid0; i < K * EB; i += E_THREADS) {
+            const int64_t at = i0 + i % EB;
+            sh.code[i / EB][i % EB] = codes[(int64_t)(i / EB) * N + (at < N ? at : N - 1)];
+        }
         __syncthreads();
-#pragma unroll
-        for (int s = 0; s < EK / 2; ++s) {
-            float av[2], bv[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                av[i] = As[2 * s + (lane >> 5)][i * 32 + (lane & 31)];
-                bv[i] = Bs[2 * s + (lane >> 5)][wave * 64 + i * 32 + (lane & 31)];
-            }
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-        }
     }
-    // argmin over the wavefront's 64 codewords for each of the 64 rows: key = (order-preserving bits
-    // of ||c||^2 - 2<r,c>, codeword index), the smaller key wins, so equal scores go to the smaller index
-    // (ICM: index + 1, and 0 for the row's current codeword, which so wins among equal scores)
-    float cn[2];
+    // the starting residuals and the largest norm among them (it sets the first level's scale)
+    auto add_norm = [&](int tid, int rg, int p, int sl, float x) __attribute__((always_inline)) {
+        x = row_sum(x);
+        const int item = rg + E_G * p;
+        if ((tid & 15) == 0) sh.nrm2[item] = sl == 0 ? x : sh.nrm2[item] + x;
+    };
+    for (int sl = 0; sl < nsl; ++sl) {
+        const int tid = fresh(tid0), e0 = sl * 128 + (tid & 15) * 8, rg = tid >> 4;
+        float v[E_P][8];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) cn[j] = cnorm_k[wave * 64 + j * 32 + (lane & 31)];
+        for (int p = 0; p < E_P; ++p) load_x(rg, p, e0, v[p]);
+        if (ICM) {                                         // x - sum_k c_k, k ascending
+            for (int k = 0; k < K; ++k) {
+                float c[E_P][8];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+                for (int p = 0; p < E_P; ++p) load8(codeword(k, sh.code[k][rg + E_G * p]), e0, c[p]);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            u64 key = ~0ull;
-            const uint32_t cur = ICM ? s_old[i * 32 + (v & 3) + 4 * (lane >> 5) + 8 * (v >> 2)] : 0u;
+                for (int p = 0; p < E_P; ++p)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const float score = cn[j] - 2.0f * acc[i][j][v];
-                const uint32_t col = (uint32_t)(wave * 64 + j * 32 + (lane & 31));
-                const uint32_t field = ICM ? (col == cur ? 0u : col + 1u) : col;
-                const u64 kj = ((u64)icq_order_bits(score) << 32) | field;
-                key = kj < key ? kj : key;
+                    for (int i = 0; i < 8; ++i) v[p][i] -= c[p][i];
             }
-            // minimum over each half of 32 lanes on the DPP path (row shifts, then lane 15 of rows 0 and 2
-            // into rows 1 and 3): lanes 31 and 63 end up with their half's smallest key
-            key = dpp_min64<0x111, 0xf>(key);
-            key = dpp_min64<0x112, 0xf>(key);
-            key = dpp_min64<0x114, 0xf>(key);
-            key = dpp_min64<0x118, 0xf>(key);
-            key = dpp_min64<0x142, 0xa>(key);
-            if ((lane & 31) == 31) best[wave][i * 32 + (v & 3) + 4 * (lane >> 5) + 8 * (v >> 2)] = key;
+        }
+#pragma unroll
+        for (int p = 0; p < E_P; ++p) {
+            float s = 0.0f;
+            if (ICM && !REG) store_res(rg, p, e0, v[p]);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (REG) r[REG ? p : 0][i] = v[p][i];
+                s = fmaf(v[p][i], v[p][i], s);
+            }
+            add_norm(tid, rg, p, sl, s);
+            if (REG && ICM) load8(codeword(0, sh.code[0][rg + E_G * p]), e0, co[REG && ICM ? p : 0]);
         }
     }
     __syncthreads();
-    if (tid < EM) {
-        u64 key = best[0][tid];
+    auto largest_norm = [&]() __attribute__((always_inline)) -> float {                   // behind a barrier after nrm2 was written
+        const int lane = fresh(tid0) & 63;
+        float v = fmaxf(sh.nrm2[lane], sh.nrm2[lane + 64]);
+        for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+        return __builtin_amdgcn_sqrtf(v) * 1.0001f;
+    };
+    float reach = largest_norm();                          // no residual of the block is longer
+    uint32_t nchanged = 0;
+
+    // slice g of codebook k's halves -> LDS, straight from memory
+    auto fetch = [&](const uint4 *src, int k, int g) __attribute__((always_inline)) {
+        const int lane = fresh(tid0) & 63;
+        const uint4 *s = src + ((int64_t)k * nks + g) * (4 * ICQ_LUT_W) + wave * 128;
+        uint4 *dst = sh.cbs[g & 1] + wave * 128;
 #pragma unroll
-        for (int w = 1; w < E_THREADS / 64; ++w) key = best[w][tid] < key ? best[w][tid] : key;
-        const uint32_t field = (uint32_t)key;
-        const uint32_t code = ICM ? (field == 0u ? s_old[tid] : field - 1u) : field;
-        s_code[tid] = code;
-        const bool store = i0 + tid < N && (!ICM || code != s_old[tid]);
-        if (store) codes_k[i0 + tid] = (uint8_t)code;
-        if (ICM && changed) {                      // tid < 64: the first wavefront, whole
-            const int n = __builtin_popcountll(__ballot(store));
-            if (tid == 0 && n > 0) atomicAdd(changed, (uint32_t)n);
-        }
-    }
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(s + i * 64 + lane),
+                                             (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
+    };
+    // what a level needs first: its first two slices, its codebook's scale and norms (asked for a level ahead)
+    float4 mt;
+    float cn = 0.0f;
+    auto ahead = [&](int k) __attribute__((always_inline)) {
+        fetch(half_hi, k, 0);
+        if (nks > 1) fetch(half_hi, k, 1);
+        mt = meta[k];
+        if (tid0 < ICQ_LUT_W) cn = cnorm[k * ICQ_LUT_W + tid0];
+    };
+    ahead(0);
+    // scale of the residuals of the level to come, and what its scores start from
+    float sr;
+    auto rescale = [&]() __attribute__((always_inline)) {
+        sr = scale_below(fmaxf(reach + (ICM ? mt.y : 0.0f), mt.y), 14);        // no r of that level is longer than this
+        if (tid0 < ICQ_LUT_W) sh.cnh[tid0] = -0.5f * (sr * mt.x) * cn;         // -inf beyond m
+    };
+    rescale();
     __syncthreads();
-    // residual update of the block's rows (zero beyond d, so later levels can read whole slices)
-    if (vec_ok && i0 + EM <= N) {
-        // whole block, d == d_pad, 16-byte aligned rows: 128-bit accesses, four of a thread's in flight
-        // together (one by one, each store would be waited for before the next load: stores count
-        // with the loads)
-        const int row4 = d_pad / 4;                       // 128-bit pieces per row; EM * row4 = 256 * (d_pad / 16)
-        const int nit = d_pad / 16;
-        const float4 *src4 = reinterpret_cast<const float4 *>(src);
-        const float4 *cb4 = reinterpret_cast<const float4 *>(cb_k);
-        float4 *res4 = reinterpret_cast<float4 *>(res);
-        const int src_row4 = src_stride / 4;
-        constexpr int U = 4;
-        for (int it = 0; it < nit; it += U) {
-            float4 xa[U], ca[U];
-            int64_t off[U];
-            bool keep[U];
+
+    const int levels = ICM ? K * sweeps : K;
+    for (int lev = 0; lev < levels; ++lev) {
+        const int k = ICM ? lev % K : lev;
+        const int kp = k == 0 ? K - 1 : k - 1, kn = k == K - 1 ? 0 : k + 1;        // the codebooks of the levels around it
+        const float cmax = mt.y, dmax = mt.z, sc = mt.x, S = sr * sc;
+
+        // the residual of this level in item p's piece at e0, before (ICM) the current codeword is added back
+        auto residual = [&](int rg, int p, int e0, float (&v)[8]) __attribute__((always_inline)) {
+            if (REG) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int idx = (it + u < nit ? it + u : it) * E_THREADS + tid;
-                const int r = idx / row4, e4 = idx % row4;
-                xa[u] = src4[(i0 + r) * src_row4 + e4];
-                ca[u] = cb4[(int64_t)s_code[r] * row4 + e4];
-                off[u] = (i0 + r) * row4 + e4;
-                keep[u] = ICM && s_code[r] == s_old[r];
-                if (ICM) {
-                    const float4 co = cb4[(int64_t)s_old[r] * row4 + e4];
-                    xa[u] = make_float4(xa[u].x + co.x, xa[u].y + co.y, xa[u].z + co.z, xa[u].w + co.w);
+                for (int i = 0; i < 8; ++i) v[i] = r[REG ? p : 0][i];
+            } else if (!ICM && lev == 0) {
+                load_x(rg, p, e0, v);
+            } else {
+                load8(res + row(rg, p) * d_pad, e0, v);
+            }
+        };
+        // the residuals of slice sl as halves -> LDS.  UPDATE: first bring them up to date with the level before
+        // (not REG) and sum their squares.  LOW: the second halves.
+        auto stage = [&](int sl, bool update, bool low) __attribute__((always_inline)) {
+            const int tid = fresh(tid0), rg = tid >> 4, e0 = sl * 128 + (tid & 15) * 8;
+            const float scale = fresh(sr), zero = fresh(0.0f);
+#pragma unroll REG ? E_P : 2
+            for (int p = 0; p < E_P; ++p) {
+                float v[8];
+                if (!REG && update && lev > 0) {
+                    const uint32_t oldc = sh.before[rg + E_G * p], newc = sh.code[kp][rg + E_G * p];
+                    const bool moved = !ICM || newc != oldc;
+                    if (!ICM && lev == 1) load_x(rg, p, e0, v);
+                    else load8(res + row(rg, p) * d_pad, e0, v);
+                    if (moved) {
+                        float c[8];
+                        if (ICM) {
+                            load8(codeword(kp, oldc), e0, c);
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) v[i] += c[i];
+                        }
+                        load8(codeword(kp, newc), e0, c);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) v[i] -= c[i];
+                        store_res(rg, p, e0, v);
+                    }
+                } else {
+                    residual(rg, p, e0, v);
+                }
+                if (ICM && REG && update) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] += co[REG && ICM ? p : 0][i];
+                } else if (ICM) {
+                    float c[8];
+                    load8(codeword(k, sh.code[k][rg + E_G * p]), e0, c);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] += c[i];
+                }
+                half8 h;
+                float n2 = zero;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    n2 = fmaf(v[i], v[i], n2);
+                    const float s = v[i] * scale;
+                    h[i] = (_Float16)s;
+                    if (low) h[i] = (_Float16)(s - (float)h[i]);
+                }
+                if (update) add_norm(tid, rg, p, sl, n2);
+                if (e0 < nks * 32) sh.frag[(tid & 15) * E_FROW + rg + E_G * p] = __builtin_bit_cast(uint4, h);
+            }
+        };
+        // acc += residual halves x codeword halves over all dimensions
+        auto contract = [&](float16v (&acc)[2][2], const uint4 *src, int pass, bool update) __attribute__((always_inline)) {
+            const int lane = fresh(tid0) & 63, half = lane >> 5, l32 = lane & 31;
+            if (!update || pass > 0) {
+                fetch(src, k, 0);
+                if (nks > 1) fetch(src, k, 1);
+            }
+            if (REG && pass > 0) stage(0, false, pass == 1);
+            for (int g = 0; g < nks; ++g) {
+                if (!REG && (g & 3) == 0) {
+                    if (g > 0) __syncthreads();            // the last slice's fragments are consumed
+                    stage(g >> 2, update, pass == 1);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // this thread's part of slice g is in LDS
+                __syncthreads();
+                if (g > 0 && g + 1 < nks) fetch(src, k, g + 1);
+#pragma unroll
+                for (int kk = 0; kk < 2; ++kk) {
+                    half8 a[2], b[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+                        a[t] = __builtin_bit_cast(half8, sh.cbs[g & 1][(kk * 2 + half) * ICQ_LUT_W + cw * 64 + t * 32 + l32]);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+                        b[u] = __builtin_bit_cast(half8, sh.frag[((g & 3) * 4 + kk * 2 + half) * E_FROW + ih * 64 + u * 32 + l32]);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[t], b[u], acc[u][t], 0, 0, 0);
                 }
             }
+        };
+
+        const int tid = fresh(tid0);
+        if (tid < EB) sh.ccount[tid] = 0;
+        if (tid == 0) sh.over = 0;
+        // ---- candidates: codewords whose score is within twice the error bound of the item's best
+        auto candidates = [&](const float16v (&acc)[2][2], float u_r, float d_c) __attribute__((always_inline)) {
+            const int lane = fresh(tid0) & 63, half = lane >> 5, l32 = lane & 31;
+            float best[2];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (it + u < nit && !keep[u])             // the first condition is block-uniform
-                    res4[off[u]] = make_float4(xa[u].x - ca[u].x, xa[u].y - ca[u].y, xa[u].z - ca[u].z, xa[u].w - ca[u].w);
+            for (int u = 0; u < 2; ++u) {
+                float b = acc[u][0][0];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) b = fmaxf(b, acc[u][t][v]);
+                b = fmaxf(b, __shfl_xor(b, 32, 64));
+                if (half == 0) sh.smax[cw][ih * 64 + u * 32 + l32] = b;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int item = ih * 64 + u * 32 + l32;
+                const float b = fmaxf(fmaxf(sh.smax[0][item], sh.smax[1][item]), fmaxf(sh.smax[2][item], sh.smax[3][item]));
+                const float rn = __builtin_amdgcn_sqrtf(sh.nrm2[item]) * 1.0001f;
+                // |<r,c> - <r',c'>|, scaled; the third term: halves below the normal range (2^-25 each at most)
+                const float E = S * rn * (u_r * cmax + (1.0f + u_r) * d_c) + __builtin_amdgcn_sqrtf((float)(nks * 32)) * 2.98e-8f * sc * cmax +
+                                (float)(nks * 32 + 8) * 1.2e-7f * S * cmax * (rn + cmax);
+                best[u] = b - 2.0f * E - fabsf(b) * 1e-6f - 1e-30f;
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int item = ih * 64 + u * 32 + l32;
+                uint32_t bits = 0;                         // the sign of bound - score, first score in bit 31
+#pragma unroll
+                for (int i = 0; i < 32; ++i)
+                    bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(best[u] - acc[u][i >> 4][i & 15]), 31);
+                while (bits != 0) {
+                    const int i = __builtin_clz(bits);
+                    bits &= ~(0x80000000u >> i);
+                    const uint32_t code = (uint32_t)(cw * 64 + (i >> 4) * 32 + (i & 3) + 4 * half + 8 * ((i & 15) >> 2));
+                    const uint32_t slot = atomicAdd(&sh.ccount[item], 1u);
+                    if (slot < (uint32_t)E_CAND) sh.cand[item][slot] = (uint8_t)code;
+                    else sh.over = 1;
+                }
+            }
+            __syncthreads();
+        };
+        // ---- first halves only; then, if that left some item too many candidates, both halves of both sides but the
+        // product of the two second ones
+        if (REG) stage(0, true, false);
+#pragma nounroll
+        for (int round = 0;; ++round) {
+            if (REG && round != 0) stage(0, false, false);
+            // accumulator register v of lane l is codeword (v % 4) + 4 (l / 32) + 8 (v / 4), item l % 32 of its tile
+            float16v acc[2][2];
+            const int half = (fresh(tid0) >> 5) & 1;
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const float4v c = *reinterpret_cast<const float4v *>(&sh.cnh[cw * 64 + t * 32 + w * 8 + half * 4]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[0][t][w * 4 + i] = acc[1][t][w * 4 + i] = c[i];
+                }
+#pragma nounroll
+            for (int pass = 0; pass < (round == 0 ? 1 : 3); ++pass) {
+                if (pass > 0) __syncthreads();             // the fragments of the pass before are consumed
+                contract(acc, pass == 2 ? half_lo : half_hi, pass, round == 0);
+            }
+            candidates(acc, round == 0 ? E_U : 4.0f * E_U * E_U, round == 0 ? dmax : 2.0f * E_U * dmax);
+            if (round != 0 || sh.over == 0) break;         // block-uniform: read between barriers
+            __syncthreads();
+            if (tid < EB) sh.ccount[tid] = 0;
+            if (tid == 0) sh.over = 0;
+        }
+        reach = largest_norm() + cmax;                     // of the residuals the level leaves
+        // ---- the sub-codes: the only candidate, or the argmin of the candidates' fp32 scores
+        const bool last = lev + 1 == levels;
+        if (!last) ahead(kn);
+        const int rg = tid >> 4, c8 = (tid & 15) * 8;
+        constexpr int CH = ICM ? 2 : E_P;                  // items whose codewords are loaded together (registers)
+        float ca[CH][8], cc[ICM ? CH : 1][8];              // REG: the first candidates, then the chosen codewords; the current ones
+#pragma unroll
+        for (int p = 0; p < E_P; ++p) {
+            if (REG && p % CH == 0) {
+#pragma unroll
+                for (int u = 0; u < CH; ++u) {
+                    const int it = rg + E_G * (p + u);
+                    const uint32_t now = ICM ? sh.code[k][it] : 0u;
+                    load8(codeword(k, sh.ccount[it] != 0 ? sh.cand[it][0] : now), c8, ca[u]);
+                    if (ICM) load8(codeword(k, now), c8, cc[ICM ? u : 0]);
+                }
+            }
+            const int item = rg + E_G * p;
+            const uint32_t n = sh.ccount[item];
+            const uint32_t old = ICM ? sh.code[k][item] : 0u;
+            uint32_t code = n != 0 ? sh.cand[item][0] : old;       // none: scores that are not numbers
+            const bool all = n > (uint32_t)E_CAND;
+            if (__builtin_amdgcn_ballot_w64(n > 1) != 0) {         // wavefront-uniform: four items at a time
+                float best = INFINITY;
+                uint32_t bf = 0xFFFFFFFFu;                         // ICM: 0 for the current codeword, else index + 1
+                const uint32_t todo = n > 1 ? (all ? (uint32_t)m : n) : 0u;
+                for (uint32_t i = 0; __builtin_amdgcn_ballot_w64(i < todo) != 0; ++i) {
+                    const uint32_t j = all ? (i < (uint32_t)m ? i : 0u) : sh.cand[item][i < n ? i & (E_CAND - 1) : 0];
+                    float dot = 0.0f, c[8];
+                    for (int sl = 0; sl < nsl; ++sl) {
+                        const int e0 = sl * 128 + c8;
+                        float v[8];
+                        load8(codeword(k, j), e0, c);
+                        residual(rg, p, e0, v);
+                        if (ICM) {
+                            float o[8];
+                            if (!REG) load8(codeword(k, old), e0, o);
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) v[q] += REG ? cc[ICM ? p % CH : 0][q] : o[q];
+                        }
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) dot = fmaf(v[q], c[q], dot);
+                    }
+                    dot = row_sum(dot);
+                    const float score = cnorm[k * ICQ_LUT_W + j] - 2.0f * dot;
+                    const uint32_t f = ICM && j == old ? 0u : j + 1u;
+                    if (i < todo && (score < best || (score == best && f < bf))) {
+                        best = score;
+                        bf = f;
+                        if (REG) {
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) ca[p % CH][q] = c[q];
+                        }
+                    }
+                }
+                if (todo != 0 && bf != 0xFFFFFFFFu) code = bf == 0u ? old : bf - 1u;
+            }
+            if ((tid & 15) == 0) {
+                if (ICM) sh.before[item] = (uint8_t)old;
+                sh.code[k][item] = (uint8_t)code;
+            }
+            if (ICM && code != old && (tid & 15) == 0 && i0 + item < N) ++nchanged;
+            if (REG && (!ICM || code != old)) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (ICM) r[REG ? p : 0][i] += cc[ICM ? p % CH : 0][i];
+                    r[REG ? p : 0][i] -= ca[p % CH][i];
+                }
             }
         }
-        return;
-    }
-    for (int idx = tid; idx < EM * d_pad; idx += E_THREADS) {
-        const int r = idx / d_pad, e = idx % d_pad;
-        const int64_t row = i0 + r;
-        if (row < N && !(ICM && s_code[r] == s_old[r])) {
-            float xv = e < d ? src[row * src_stride + e] : 0.0f;
-            if (ICM) xv += cb_k[(int64_t)s_old[r] * d_pad + e];
-            res[row * d_pad + e] = xv - cb_k[(int64_t)s_code[r] * d_pad + e];
+        // the sixteen lanes of an item read what one of them wrote: same wavefront, so in order, but not by the
+        // rules of one thread's memory
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        if (REG && ICM) {                                  // (after the last level too: a condition would keep the old values alive)
+#pragma unroll
+            for (int p = 0; p < E_P; ++p) load8(codeword(kn, sh.code[kn][rg + E_G * p]), c8, co[REG && ICM ? p : 0]);
         }
+        if (ICM && k == K - 1 && changed) {
+            const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(nchanged), 63);
+            if ((tid & 63) == 0 && n != 0) atomicAdd(&changed[lev / K], n);
+            nchanged = 0;
+        }
+        if (!last) rescale();
+        __syncthreads();
     }
+    for (int i = tid0; i < K * EB; i += E_THREADS)
+        if (i0 + i % EB < N) codes[(int64_t)(i / EB) * N + i0 + i % EB] = sh.code[i / EB][i % EB];
 }
 
-// res[n][e] = x[n][e] - sum_k c_{k,code_k(n)}[e] (k ascending), zero beyond d: what the refinement starts from.
-__global__ void residual_kernel(const float *__restrict__ x, int d, int d_pad, const float *__restrict__ cb, int K,
-                                const uint8_t *__restrict__ codes, int64_t N, float *__restrict__ res) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= N * d_pad) return;
-    const int64_t n = idx / d_pad;
-    const int e = (int)(idx % d_pad);
-    float r = e < d ? x[n * d + e] : 0.0f;
-    for (int k = 0; k < K; ++k) r -= cb[((int64_t)k * ICQ_LUT_W + codes[(int64_t)k * N + n]) * d_pad + e];
-    res[idx] = r;
-}
-
-__global__ void zero_words_kernel(uint32_t *p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
+// The codewords as halves, laid out as the contraction reads them: piece ((k * slices + e / 32) * 4 + e / 8 % 4) * 256 + j
+// holds the eight dimensions e .. e + 7 of codeword j (zero beyond d), times the codebook's scale, the first halves in
+// hi and what they leave in lo.  16 threads per codeword.  meta[k].z is zero on entry.
+__global__ __launch_bounds__(256) void encode_pack_kernel(const float *__restrict__ cb, int d_pad,
+                                                          const float *__restrict__ cnorm, uint4 *__restrict__ hi,
+                                                          uint4 *__restrict__ lo, float4 *__restrict__ meta) {
+    __shared__ float red[4];
+    const int tid = threadIdx.x, k = blockIdx.x / 16, j = (blockIdx.x % 16) * 16 + tid / 16;
+    float v = cnorm[k * ICQ_LUT_W + tid];
+    v = v < INFINITY ? v : 0.0f;
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    if ((tid & 63) == 0) red[tid >> 6] = v;
+    __syncthreads();
+    const float cmax = sqrtf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))) * 1.0001f;
+    const float sc = scale_below(cmax, 10);
+    const int nks = (d_pad + 31) / 32;
+    float err = 0.0f;
+    for (int c = tid & 15; c < nks * 4; c += 16) {
+        half8 a, b;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int e = c * 8 + i;
+            const float s = e < d_pad ? cb[((int64_t)k * ICQ_LUT_W + j) * d_pad + e] * sc : 0.0f;
+            a[i] = (_Float16)s;
+            const float rest = s - (float)a[i];
+            b[i] = (_Float16)rest;
+            err = fmaf(rest, rest, err);
+        }
+        const int64_t at = (((int64_t)k * nks + c / 4) * 4 + c % 4) * ICQ_LUT_W + j;
+        hi[at] = __builtin_bit_cast(uint4, a);
+        lo[at] = __builtin_bit_cast(uint4, b);
+    }
+    err = sqrtf(row_sum(err)) / sc * 1.0001f;
+    if ((tid & 15) == 0) atomicMax(reinterpret_cast<unsigned int *>(&meta[k].z), __float_as_uint(err));
+    if (blockIdx.x % 16 == 0 && tid == 0) {
+        meta[k].x = sc;
+        meta[k].y = cmax;
+    }
 }
 
 // One wavefront per item: ||x - sum_k c_{k,code_k}||^2 accumulated in double.
@@ -244,6 +567,25 @@ ICQ_EXPORT int icq_encode_workspace_bytes(const icq_index *ix, int64_t N, size_t
     return ICQ_OK;
 }
 
+template <bool ICM>
+static int launch_encode(const icq_index *ix, const float *x, int64_t N, uint8_t *codes, int sweeps, float *res,
+                         uint32_t *changed, hipStream_t s) {
+    const unsigned blocks = (unsigned)((N + EB - 1) / EB);
+    auto launch = [&](auto kernel) -> int {
+        ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(kernel), sizeof(EncShared)));
+        kernel<<<blocks, E_THREADS, sizeof(EncShared), s>>>(x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo,
+                                                            ix->enc_meta, ix->K, ix->m, N, codes, sweeps, res, changed);
+        return icq_check_launch();
+    };
+    if (ix->d <= E_REG_D) return launch(encode_kernel<true, ICM>);
+    return launch(encode_kernel<false, ICM>);
+}
+
+int icq_encode_pack(icq_index *ix, hipStream_t s) {
+    encode_pack_kernel<<<ix->K * 16, 256, 0, s>>>(ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo, ix->enc_meta);
+    return icq_check_launch();
+}
+
 ICQ_EXPORT int icq_encode(const icq_index *ix, const float *x, int64_t N, uint8_t *codes_out, void *workspace,
                           size_t workspace_bytes, void *stream) {
     if (!ix || N < 0 || N > ICQ_MAX_N) return ICQ_ERR_ARG;
@@ -252,21 +594,7 @@ ICQ_EXPORT int icq_encode(const icq_index *ix, const float *x, int64_t N, uint8_
     size_t need = 0;
     (void)icq_encode_workspace_bytes(ix, N, &need);
     if (!workspace || ((uintptr_t)workspace % ICQ_ALIGN) != 0 || workspace_bytes < need) return ICQ_ERR_WORKSPACE;
-    float *res = static_cast<float *>(workspace);
-    hipStream_t s = (hipStream_t)stream;
-    const unsigned blocks = (unsigned)((N + EM - 1) / EM);
-    for (int k = 0; k < ix->K; ++k) {
-        const float *src = k == 0 ? x : res;
-        const int stride = k == 0 ? ix->d : ix->d_pad;
-        // in place for k > 0: a block reads and writes only its own rows, and every read of a row
-        // (slices, then the update) precedes its write in program order behind a barrier
-        const float *cbk = ix->cb + (size_t)k * ICQ_LUT_W * ix->d_pad;
-        const int vec_ok = ix->d == ix->d_pad && stride % 4 == 0 && (uintptr_t)src % 16 == 0 && (uintptr_t)cbk % 16 == 0;
-        encode_level_kernel<false><<<blocks, E_THREADS, 0, s>>>(src, stride, ix->d, cbk, ix->d_pad,
-                                                                ix->cnorm + (size_t)k * ICQ_LUT_W, N,
-                                                                codes_out + (size_t)k * N, res, vec_ok, nullptr);
-    }
-    return icq_check_launch();
+    return launch_encode<false>(ix, x, N, codes_out, 1, static_cast<float *>(workspace), nullptr, (hipStream_t)stream);
 }
 
 ICQ_EXPORT int icq_encode_refine(const icq_index *ix, const float *x, int64_t N, uint8_t *codes, int sweeps,
@@ -277,24 +605,9 @@ ICQ_EXPORT int icq_encode_refine(const icq_index *ix, const float *x, int64_t N,
     size_t need = 0;
     (void)icq_encode_workspace_bytes(ix, N, &need);
     if (!workspace || ((uintptr_t)workspace % ICQ_ALIGN) != 0 || workspace_bytes < need) return ICQ_ERR_WORKSPACE;
-    float *res = static_cast<float *>(workspace);
     hipStream_t s = (hipStream_t)stream;
-    const int64_t total = N * ix->d_pad;
-    residual_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(x, ix->d, ix->d_pad, ix->cb, ix->K, codes, N, res);
-    if (changed_out) zero_words_kernel<<<(sweeps + 255) / 256, 256, 0, s>>>(changed_out, sweeps);
-    const unsigned blocks = (unsigned)((N + EM - 1) / EM);
-    for (int sw = 0; sw < sweeps; ++sw) {
-        for (int k = 0; k < ix->K; ++k) {
-            // in place: a block reads and writes only its own rows and sub-codes, reads first
-            const float *cbk = ix->cb + (size_t)k * ICQ_LUT_W * ix->d_pad;
-            const int vec_ok = ix->d == ix->d_pad && (uintptr_t)cbk % 16 == 0;
-            encode_level_kernel<true><<<blocks, E_THREADS, 0, s>>>(res, ix->d_pad, ix->d, cbk, ix->d_pad,
-                                                                   ix->cnorm + (size_t)k * ICQ_LUT_W, N,
-                                                                   codes + (size_t)k * N, res, vec_ok,
-                                                                   changed_out ? changed_out + sw : nullptr);
-        }
-    }
-    return icq_check_launch();
+    if (changed_out) icq_zero_words(changed_out, sweeps, s);
+    return launch_encode<true>(ix, x, N, codes, sweeps, static_cast<float *>(workspace), changed_out, s);
 }
 
 ICQ_EXPORT int icq_quantization_error(const icq_index *ix, const float *x, int64_t N, const uint8_t *codes,

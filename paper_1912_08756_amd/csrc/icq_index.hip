@@ -32,7 +32,7 @@ __global__ void copy_items_kernel(const uint8_t *__restrict__ codes, int64_t N, 
 // in d and store its squared norm (accumulated in double, rounded once).
 __global__ void copy_codebooks_kernel(const float *__restrict__ codebooks, int K, int m, int d,
                                       int d_pad, float *__restrict__ cb,
-                                      float *__restrict__ cnorm) {
+                                      float *__restrict__ cnorm, float4 *__restrict__ enc_meta) {
     int row = blockIdx.x * (blockDim.x / ICQ_WAVE) + threadIdx.x / ICQ_WAVE;
     int lane = threadIdx.x % ICQ_WAVE;
     if (row >= K * ICQ_LUT_W) return;
@@ -45,6 +45,7 @@ __global__ void copy_codebooks_kernel(const float *__restrict__ codebooks, int K
     }
     for (int off = ICQ_WAVE / 2; off > 0; off >>= 1) s += __shfl_down(s, off, ICQ_WAVE);
     if (lane == 0) cnorm[row] = j < m ? (float)s : INFINITY;
+    if (lane == 0 && j == 0) enc_meta[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
 // codes_out[k][perm[pos]] = items_grouped[pos][k]: the grouped layout written back in item order.
@@ -110,7 +111,6 @@ ICQ_EXPORT const char *icq_strerror(int code) {
 ICQ_EXPORT void icq_index_destroy(icq_index *ix) {
     if (!ix) return;
     (void)hipFree(ix->cb);
-    (void)hipFree(ix->cnorm);
     (void)hipFree(ix->fast);
     (void)hipFree(ix->items);
     (void)hipFree(ix->group_start);
@@ -154,19 +154,30 @@ ICQ_EXPORT int icq_index_create(icq_index **out, const float *codebooks, const u
     }
     ix->num_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
 
-    bool ok = hipMalloc(&ix->cb, sizeof(float) * (size_t)K * ICQ_LUT_W * ix->d_pad) == hipSuccess &&
-              hipMalloc(&ix->cnorm, sizeof(float) * (size_t)K * ICQ_LUT_W) == hipSuccess &&
-              hipMalloc(&ix->fast, (size_t)Kf * ix->Npad) == hipSuccess;
+    // codewords, their norms and the encoder's halves in one allocation
+    const size_t rows = (size_t)K * ICQ_LUT_W;
+    const size_t cb_bytes = icq_align_up(sizeof(float) * rows * ix->d_pad, ICQ_ALIGN);
+    const size_t norm_bytes = icq_align_up(sizeof(float) * rows, ICQ_ALIGN);
+    const size_t meta_bytes = icq_align_up(sizeof(float4) * (size_t)K, ICQ_ALIGN);
+    const size_t half_bytes = 2 * rows * ((size_t)(ix->d_pad + 31) / 32 * 32);      // a multiple of 16 KB
+    char *base = nullptr;
+    bool ok = hipMalloc(&base, cb_bytes + norm_bytes + meta_bytes + 2 * half_bytes) == hipSuccess;
+    ix->cb = reinterpret_cast<float *>(base);
+    ok = ok && hipMalloc(&ix->fast, (size_t)Kf * ix->Npad) == hipSuccess;
     if (ok && N > 0) ok = hipMalloc(&ix->items, (size_t)N * ix->item_stride) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         icq_index_destroy(ix);
         return ICQ_ERR_HIP;
     }
+    ix->cnorm = reinterpret_cast<float *>(base + cb_bytes);
+    ix->enc_meta = reinterpret_cast<float4 *>(base + cb_bytes + norm_bytes);
+    ix->half_hi = reinterpret_cast<uint4 *>(base + cb_bytes + norm_bytes + meta_bytes);
+    ix->half_lo = reinterpret_cast<uint4 *>(base + cb_bytes + norm_bytes + meta_bytes + half_bytes);
 
     const int T = 256;
     copy_codebooks_kernel<<<(K * ICQ_LUT_W + 3) / 4, T, 0, s>>>(codebooks, K, m, d, ix->d_pad,
-                                                                 ix->cb, ix->cnorm);
+                                                                 ix->cb, ix->cnorm, ix->enc_meta);
     {
         dim3 g((unsigned)((ix->Npad + T - 1) / T), (unsigned)Kf);
         copy_fast_kernel<<<g, T, 0, s>>>(codes, N, ix->Npad, ix->fast);
@@ -174,7 +185,7 @@ ICQ_EXPORT int icq_index_create(icq_index **out, const float *codebooks, const u
     if (N > 0)
         copy_items_kernel<<<(unsigned)((N + T - 1) / T), T, 0, s>>>(codes, N, K, ix->item_stride,
                                                                      ix->items);
-    if (icq_check_launch() != ICQ_OK || icq_group_build(ix, s) != ICQ_OK || icq_group2_build(ix, s) != ICQ_OK) {
+    if (icq_check_launch() != ICQ_OK || icq_encode_pack(ix, s) != ICQ_OK || icq_group_build(ix, s) != ICQ_OK || icq_group2_build(ix, s) != ICQ_OK) {
         icq_index_destroy(ix);
         return ICQ_ERR_HIP;
     }

@@ -26,7 +26,9 @@ struct icq_index {
     int num_cu;
     int64_t N, Npad;           // Npad: N rounded up to a multiple of 4096
     float *cb;                 // [K*256][d_pad] codewords, rows j >= m are zero
-    float *cnorm;              // [K*256] squared codeword norms, +inf for j >= m
+    float *cnorm;              // [K*256] squared codeword norms, +inf for j >= m (in cb's allocation, as the next three)
+    uint4 *half_hi, *half_lo;  // the codewords as two halves each, for the encoder (icq_encode.hip)
+    float4 *enc_meta;          // [K] scale of those, largest codeword norm, largest error of the first half
     uint8_t *fast;             // [Kf][Npad] fast sub-codes, zero padded
     uint8_t *items;            // [N][item_stride] all K sub-codes of an item, item-major
     // Grouping by fast-code tuple (Kf <= 2): items with the same fast sub-codes share their
@@ -62,6 +64,7 @@ static inline bool icq_g2_usable(const icq_index *ix) {
     if (!ix->g2 || ix->scan_mode == ICQ_SCAN_STREAMED) return false;
     return ix->scan_mode == ICQ_SCAN_GROUPED || ix->N >= 64ll * 65536;
 }
+int icq_encode_pack(icq_index *ix, hipStream_t s);             // enc_meta zero on entry
 int icq_group2_build(icq_index *ix, hipStream_t s);
 int icq_group2_export(const icq_index *ix, uint8_t *codes_out, hipStream_t s);
 

@@ -987,6 +987,57 @@ def test_encode_matches_oracle(gpu, K, m, d, N):
         b.icq_encode(index, _dev(torch, x), torch.empty((K, N), dtype=torch.uint8, device="cuda"), ws[:128])
 
 
+@pytest.mark.parametrize("K,m,d,N,kind", [
+    (3, 256, 128, 129, "plain"), (3, 256, 129, 257, "plain"),   # the residual in registers / in memory; blocks of 128 items
+    (2, 200, 255, 130, "plain"), (2, 256, 960, 200, "plain"),   # an odd end of the last row; several slices
+    (3, 256, 33, 300, "offset"), (2, 250, 200, 150, "offset"),  # half precision tells few codewords apart: both halves are taken
+    (3, 256, 40, 300, "equal"), (2, 256, 150, 150, "equal"),    # thirteen equal codewords each: the indices decide
+    (2, 256, 64, 130, "zero"), (2, 5, 3, 7, "equal"),
+])
+def test_encode_at_the_edges_of_its_forms(gpu, K, m, d, N, kind):
+    """Every level's codeword is a nearest one of the residual the GPU's own earlier choices leave (tolerance of fp32
+    scores: d roundings of terms up to ||r||^2 + ||c||^2), the smallest index among equal codewords; a sweep of
+    refinement from there keeps what is not strictly nearer."""
+    torch, b = gpu
+    rng = np.random.default_rng(K * 100_000 + d * 10 + m)
+    cb = rng.standard_normal((K, m, d)).astype(np.float32)
+    if kind == "offset":            # far from the origin, close to each other
+        cb = (3.0 + 0.01 * cb).astype(np.float32)
+    if kind == "equal":             # index j holds the codeword of j mod (m // 13 + 1)
+        cb = cb[:, np.arange(m) % (m // 13 + 1)].copy()
+    if kind == "zero":
+        cb[1] = 0.0
+    x = (sum(cb[k][rng.integers(0, m, N)] for k in range(K)) + 0.01 * rng.standard_normal((N, d))).astype(np.float32)
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), min(2, K))
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    codes = torch.full((K, N), 255, dtype=torch.uint8, device="cuda")
+    xd = _dev(torch, x)
+    b.icq_encode(index, xd, codes, ws)
+    refined = codes.clone()
+    b.icq_encode_refine(index, xd, refined, 1, None, ws)
+    torch.cuda.synchronize()
+    first, second = codes.cpu().numpy(), refined.cpu().numpy()
+    assert (first < m).all() and (second < m).all()
+    cb64, n, eps = cb.astype(np.float64), np.arange(N), d * 2.0 ** -23
+
+    def judge(r, k, chosen, old):
+        d2 = ((r[:, None, :] - cb64[k][None]) ** 2).sum(axis=2)
+        slack = eps * ((r * r).sum(axis=1) + (cb64[k] ** 2).sum(axis=1).max())
+        assert (d2[n, chosen] <= d2.min(axis=1) + slack).all(), "level %d: a clearly nearer codeword exists" % k
+        if kind == "equal":
+            g = m // 13 + 1
+            assert (np.where(chosen == old, 0, chosen) < g).all()      # a current codeword is kept, else the first of its equals
+    r = x.astype(np.float64)
+    for k in range(K):
+        judge(r, k, first[k], -1)
+        r = r - cb64[k][first[k]]
+    for k in range(K):
+        state = np.concatenate([second[:k], first[k:]])
+        judge(x - sum(cb64[l][state[l]] for l in range(K) if l != k), k, second[k], first[k])
+    if kind == "zero":
+        assert (first[1] == 0).all() and (second[1] == 0).all()
+
+
 def test_encode_on_disjoint_supports_recovers_the_codes(gpu):
     """Codebooks with pairwise-disjoint supports, vectors that are exact reconstructions: every
     greedy step has a codeword at distance zero, so the codes come back bit for bit; an index
