@@ -429,12 +429,13 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
             const int item = rg + E_G * p;
             const uint32_t n = sh.ccount[item];
             const uint32_t old = ICM ? sh.code[k][item] : 0u;
-            uint32_t code = n != 0 ? sh.cand[item][0] : old;       // none: scores that are not numbers
-            const bool all = n > (uint32_t)E_CAND;
-            if (__builtin_amdgcn_ballot_w64(n > 1) != 0) {         // wavefront-uniform: four items at a time
+            uint32_t code = n != 0 ? sh.cand[item][0] : old;
+            // none: a residual with infinities, NaN or components beyond the halves' range (its bound is no number)
+            const bool all = n == 0 || n > (uint32_t)E_CAND;
+            if (__builtin_amdgcn_ballot_w64(n != 1) != 0) {        // wavefront-uniform: four items at a time
                 float best = INFINITY;
                 uint32_t bf = 0xFFFFFFFFu;                         // ICM: 0 for the current codeword, else index + 1
-                const uint32_t todo = n > 1 ? (all ? (uint32_t)m : n) : 0u;
+                const uint32_t todo = n != 1 ? (all ? (uint32_t)m : n) : 0u;
                 for (uint32_t i = 0; __builtin_amdgcn_ballot_w64(i < todo) != 0; ++i) {
                     const uint32_t j = all ? (i < (uint32_t)m ? i : 0u) : sh.cand[item][i < n ? i & (E_CAND - 1) : 0];
                     float dot = 0.0f, c[8];

@@ -1038,6 +1038,41 @@ def test_encode_at_the_edges_of_its_forms(gpu, K, m, d, N, kind):
         assert (first[1] == 0).all() and (second[1] == 0).all()
 
 
+@pytest.mark.parametrize("K,m,d", [(2, 256, 48), (2, 201, 176)])
+def test_encode_of_vectors_beyond_the_halves_range(gpu, K, m, d):
+    """An infinite component decides by its sign alone (scores of -inf: the smallest index among them, a current
+    codeword kept), 1e24 by the products, NaN leaves index 0; the vectors beside them in the block stay what they are."""
+    torch, b = gpu
+    rng = np.random.default_rng(d)
+    N, e = 150, 5
+    cb = rng.standard_normal((K, m, d)).astype(np.float32)
+    x = (sum(cb[k][rng.integers(0, m, N)] for k in range(K)) + 0.01 * rng.standard_normal((N, d))).astype(np.float32)
+    x[3, e], x[4, e], x[70, e] = np.inf, -np.inf, np.nan
+    x[[9, 140]] *= 1e24
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    codes = torch.full((K, N), 255, dtype=torch.uint8, device="cuda")
+    xd = _dev(torch, x)
+    b.icq_encode(index, xd, codes, ws)
+    refined = codes.clone()
+    b.icq_encode_refine(index, xd, refined, 1, None, ws)
+    torch.cuda.synchronize()
+    first, second = codes.cpu().numpy(), refined.cpu().numpy()
+    plain = np.setdiff1d(np.arange(N), [3, 4, 70, 9, 140])
+    r = x.astype(np.float64)
+    for k in range(K):
+        c = cb[k].astype(np.float64)
+        assert first[k, 3] == np.argmax(c[:, e] > 0) and first[k, 4] == np.argmax(c[:, e] < 0) and first[k, 70] == 0
+        for i in (9, 140):
+            dot = c @ r[i]              # d roundings of terms up to ||r|| ||c||
+            assert dot[first[k, i]] >= dot.max() - d * 2.0 ** -23 * np.linalg.norm(r[i]) * np.linalg.norm(c, axis=1).max()
+        d2 = ((r[plain][:, None, :] - c[None]) ** 2).sum(axis=2)
+        slack = d * 2.0 ** -23 * ((r[plain] ** 2).sum(axis=1) + (c ** 2).sum(axis=1).max())
+        assert (d2[np.arange(plain.size), first[k, plain]] <= d2.min(axis=1) + slack).all()
+        r = r - c[first[k]]
+    assert (first[:, [3, 4, 70]] == second[:, [3, 4, 70]]).all()
+
+
 def test_encode_on_disjoint_supports_recovers_the_codes(gpu):
     """Codebooks with pairwise-disjoint supports, vectors that are exact reconstructions: every
     greedy step has a codeword at distance zero, so the codes come back bit for bit; an index
