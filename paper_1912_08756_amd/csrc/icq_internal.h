@@ -99,6 +99,9 @@ __device__ __forceinline__ uint32_t icq_order_bits(float x) {
     return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
 }
 
+// What the caller knows of the share of items that survive: nothing, that it is some per cent or more, that it is all.
+enum icq_share { ICQ_SHARE_UNKNOWN = 0, ICQ_SHARE_MANY = 1, ICQ_SHARE_ALL = 2 };
+
 // Sub-buffers carved out of the caller's workspace for one query batch.
 struct icq_ws_layout {
     size_t lut_off, ids_off, count_off, keycount_off, ticket_off, keys_off, total;
@@ -127,7 +130,7 @@ int64_t icq_mask_scan_end(const icq_index *ix);              // positions the hi
 // 2 * Q words of the workspace.
 int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_ext, int Q, const float *thresholds,
                     int64_t cap, int topk, uint32_t *out_ids, float *out_dist, uint32_t *out_survivors,
-                    void *workspace, size_t workspace_bytes, void *stream);
+                    void *workspace, size_t workspace_bytes, icq_share share, void *stream);
 // Stage 1 into hit bits.
 int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
                           size_t mask_stride, int64_t scan_end, bool *superset, hipStream_t s);
@@ -161,13 +164,17 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
 int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
                     uint32_t *cand_ids, float *cand_part, unsigned long long *cand_keys, int *list_kind,
                     uint32_t *cand_count, int64_t cap, int topk, uint32_t *out_ids, float *out_dist,
-                    hipStream_t s);
+                    icq_share share, hipStream_t s);
 // Grouped stage 1 fused with stage 2: the final lists when icq_group_fused() holds and
 // out_ids is given, else one 64-bit key per survivor in cand_keys.
 bool icq_group_fused(const icq_index *ix, int Q, int topk);
 int icq_launch_group_keys(const icq_index *ix, const float *lut, int Q, const float *thr,
                           unsigned long long *cand_keys, uint32_t *cand_count, int64_t cap, int topk,
                           uint32_t *out_ids, float *out_dist, hipStream_t s);
+// Both stages of a small index in one kernel (icq_small.hip): keys of the survivors in cand_keys.
+bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share);      // (calls that are not grouped by tuple)
+int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,
+                     uint32_t *cand_count, int64_t cap, hipStream_t s);
 // Where the per-candidate keys live inside the key area of the workspace.
 static inline unsigned long long *icq_cand_keys(unsigned long long *keys, int Q, int splits, int topk) {
     return keys + (splits > 1 ? (size_t)Q * splits * topk : 0);

@@ -173,7 +173,9 @@ ICQ_EXPORT int icq_search_running(const icq_index *const *tiles, const uint32_t 
     for (int r = 0; r < R; ++r) {
         const icq_index *t = tiles[r];
         const int64_t c = cap < t->N ? cap : t->N;
-        rc = icq_search_impl(t, nullptr, lut, Q, thr, c, topk, tids, tdist, tsurv, ws + L.inner_off, L.inner_bytes, stream);
+        // the list is empty before the first tile (every item's threshold is +inf) and its margin wide in the next ones
+        rc = icq_search_impl(t, nullptr, lut, Q, thr, c, topk, tids, tdist, tsurv, ws + L.inner_off, L.inner_bytes,
+                             r == 0 ? ICQ_SHARE_ALL : ICQ_SHARE_MANY, stream);
         if (rc != ICQ_OK) return rc;
         running_merge_kernel<<<Q, RM_T, lds, s>>>(out_ids, out_dist, crude, tids, tdist, tsurv, counters, id_base[r], t->items,
                                                   t->item_stride, t->K, t->Kf, lut, sigma, topk, thr, out_refined);

@@ -622,7 +622,7 @@ void icq_zero_words(uint32_t *p, int n, hipStream_t s) {
 }
 
 int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr, uint32_t *cand_ids, float *cand_part, unsigned long long *cand_keys, int *list_kind, uint32_t *cand_count, int64_t cap,
-                    int topk, uint32_t *out_ids, float *out_dist, hipStream_t s) {
+                    int topk, uint32_t *out_ids, float *out_dist, icq_share share, hipStream_t s) {
     if (list_kind) *list_kind = ICQ_LIST_IDS;
     if (Q == 0) return ICQ_OK;
     if (ix->N == 0) return ICQ_OK;
@@ -640,6 +640,11 @@ int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *t
         const int rc = icq_launch_group_scan(ix, lut, Q, thr, cand_ids, cand_part, as_positions, cand_count, cap, s);
         if (rc == ICQ_OK && as_positions) *list_kind = ICQ_LIST_POSITIONS;
         return rc;
+    }
+
+    if (cand_keys && list_kind && !cand_part && icq_small_usable(ix, Q, topk, share)) {
+        *list_kind = ICQ_LIST_KEYS;
+        return icq_launch_small(ix, lut, Q, thr, cand_keys, cand_count, cap, s);
     }
 
     if (ix->Kf <= 4) {
@@ -718,7 +723,7 @@ ICQ_EXPORT int icq_scan_fast(const icq_index *ix, const float *lut, int Q, const
     icq_zero_words(cand_count, Q, s);
     if (ev) ICQ_HIP_TRY(hipEventRecord(ev[1], s));
     const int rc = icq_launch_scan(ix, lut, Q, thresholds, cand_ids, cand_part, nullptr, nullptr, cand_count, cap,
-                                   0, nullptr, nullptr, s);
+                                   0, nullptr, nullptr, ICQ_SHARE_UNKNOWN, s);
     if (rc != ICQ_OK) return rc;
     if (ev) {
         ICQ_HIP_TRY(hipEventRecord(ev[2], s));

@@ -73,7 +73,7 @@ ICQ_EXPORT int icq_workspace_bytes(const icq_index *ix, int Q, int64_t cap, int 
 int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_ext, int Q, const float *thresholds,
                     int64_t cap, int topk, uint32_t *out_ids, float *out_dist,
                     uint32_t *out_survivors, void *workspace, size_t workspace_bytes,
-                    void *stream) {
+                    icq_share share, void *stream) {
     if (!ix || Q < 0 || Q > ICQ_MAX_Q || cap < 1 || topk < 1 || topk > ICQ_MAX_TOPK)
         return ICQ_ERR_ARG;
     if (Q == 0) return ICQ_OK;
@@ -139,7 +139,7 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
                                         : (ix->item_stride <= 16 && topk <= 512) ? icq_cand_keys(keys, nq, L.splits, topk)
                                                                                  : nullptr;
         rc = icq_launch_scan(ix, lut, nq, thresholds + q0, ids, nullptr, cand_keys, &list_kind, cnt,
-                             cap, topk, out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, s);
+                             cap, topk, out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, share, s);
         if (rc != ICQ_OK) return rc;
         if (timed) ICQ_HIP_TRY(hipEventRecord(ev[2], s));
         rc = icq_launch_refine(ix, lut, nq, ids, nullptr, list_kind, cnt, cap, topk, L.splits, keys, ticket,
@@ -156,7 +156,7 @@ ICQ_EXPORT int icq_search(const icq_index *ix, const float *queries, int Q, cons
                           uint32_t *out_survivors, void *workspace, size_t workspace_bytes,
                           void *stream) {
     return icq_search_impl(ix, queries, nullptr, Q, thresholds, cap, topk, out_ids, out_dist, out_survivors, workspace,
-                           workspace_bytes, stream);
+                           workspace_bytes, ICQ_SHARE_UNKNOWN, stream);
 }
 
 // ---- icq_search for callers that cannot allocate: the workspace is a fixed array in the
@@ -203,5 +203,5 @@ ICQ_EXPORT int icq_search_static(const icq_index *ix, const float *queries, int 
     const int rc = scratch_address(&ws);
     if (rc != ICQ_OK) return rc;
     return icq_search_impl(ix, queries, nullptr, Q, thresholds, cap, topk, out_ids, out_dist, out_survivors, ws,
-                       (size_t)ICQ_STATIC_SCRATCH_BYTES, stream);
+                       (size_t)ICQ_STATIC_SCRATCH_BYTES, ICQ_SHARE_UNKNOWN, stream);
 }

@@ -1317,6 +1317,53 @@ def test_search_sweep_against_oracle(gpu, case):
     _check_search(g, cfg, T, P, D, thr, topk, N + 1)
 
 
+@pytest.mark.parametrize("K,Kf,m,N,Q,topk,frac", [
+    (4, 1, 256, 1, 3, 5, 1.0), (16, 4, 256, 63, 8, 10, 0.5), (8, 3, 200, 2047, 5, 100, 0.1), (6, 2, 256, 2049, 4, 10, 0.01),
+    (12, 4, 256, 4096, 37, 257, 1.0), (3, 3, 77, 8191, 70, 100, 0.2), (16, 3, 256, 50_001, 33, 100, 0.02),
+    (5, 2, 256, 400_003, 4, 512, 0.01)])
+def test_search_of_a_small_index_in_one_kernel(gpu, K, Kf, m, N, Q, topk, frac):
+    """Both stages in one kernel (few items times queries): against the oracle, and bit for bit against the scan with
+    candidate lists (the sums are the same fp32 additions).  Sizes around a step of 2048 items, all record widths."""
+    rng = np.random.default_rng(K * 1000 + N)
+    cb = (rng.standard_normal((K, m, 24)) * (0.7 ** np.arange(K))[:, None, None]).astype(np.float32)
+    codes = rng.integers(0, m, size=(K, N), dtype=np.uint8)
+    src = rng.integers(0, N, size=Q)
+    queries = sum(cb[k][codes[k, src]] for k in range(K)) + 0.1 * rng.standard_normal((Q, 24))
+    cfg = dict(codebooks=cb, codes=codes, queries=np.ascontiguousarray(queries, dtype=np.float32),
+               K=K, Kf=Kf, d=24, N=N, Q=Q, topk=topk)
+    T, P, D = oracle_all(cfg)
+    thr = np.full(Q, np.inf, dtype=np.float32) if frac >= 1.0 else np.quantile(P, frac, axis=1).astype(np.float32)
+    if Q >= 5:
+        thr[1], thr[2], thr[3] = np.inf, np.nan, -np.inf
+    out = _check_search(Gpu(gpu, cfg), cfg, T, P, D, thr, topk, N + 1, min_equal=0.9 if topk <= 100 else 0.0)
+    for a, c in zip(out, Gpu(gpu, cfg, 1).search(thr, N + 1, topk)):
+        assert np.array_equal(a, c, equal_nan=True)
+
+
+@pytest.mark.parametrize("Kf,Q,bounds", [(4, 130, [0, 60_001, 63_000]), (2, 300, [0, 9_000, 20_001])])
+def test_running_search_with_a_long_first_tile(gpu, Kf, Q, bounds):
+    """Nothing is excluded from the first tile: a block of the one-kernel form takes several steps of it.  Bit for bit what
+    the scan with candidate lists gives."""
+    torch, b = gpu
+    cfg = small("C4", bounds[-1], Q, K=8, Kf=Kf)
+    cb, queries = _dev(torch, cfg["codebooks"]), _dev(torch, cfg["queries"])
+    sigma = torch.full((Q,), 5.0, dtype=torch.float32, device="cuda")
+    results = []
+    for mode in (0, 1):
+        tiles = [b.icq_index_create(cb, _dev(torch, cfg["codes"][:, a:e]), Kf) for a, e in zip(bounds[:-1], bounds[1:])]
+        for t in tiles:
+            b.icq_index_set_scan_mode(t, mode)
+        out = [torch.empty((Q, 100), dtype=torch.int32, device="cuda"), torch.empty((Q, 100), dtype=torch.float32, device="cuda"),
+               torch.empty((Q,), dtype=torch.int32, device="cuda")]
+        ws = torch.empty(b.icq_running_workspace_bytes(tiles, Q, bounds[1], 100), dtype=torch.uint8, device="cuda")
+        b.icq_search_running(tiles, bounds[:-1], queries, sigma, bounds[1], 100, *out, ws)
+        torch.cuda.synchronize()
+        results.append([o.cpu().numpy() for o in out])
+    assert (results[0][2] >= bounds[1]).all()
+    for a, c in zip(*results):
+        assert np.array_equal(a, c)
+
+
 def _hit_bit_cases():
     rng = np.random.default_rng(20241)
     cases = []
