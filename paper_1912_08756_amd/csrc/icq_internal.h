@@ -108,6 +108,7 @@ struct icq_ws_layout {
     int splits;                // parts a query's work in stage 2 is cut into
     // icq_search with the item-by-item stage 1: hit bits instead of candidate lists (ids_off holds them)
     bool masked;
+    bool tickets;              // the selection may take a query's keys in parts
     size_t mask_stride;        // 16-bit words of hit bits per query
     int64_t scan_end;          // scan positions the hit bits cover (whole chunks)
 };
@@ -120,14 +121,14 @@ static inline size_t icq_align_up(size_t x, size_t a) { return (x + a - 1) / a *
 icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool with_lut,
                          bool with_cands);
 int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk);
-int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk);
+bool icq_selects(const icq_index *ix, int topk);             // stage 2 selects from keys (else the generic kernel)
 // icq_search with the item-by-item stage 1 hands the survivors to stage 2 as one hit bit per scan
 // position and query instead of lists.
 bool icq_masks_usable(const icq_index *ix, int Q, int topk);
 int64_t icq_mask_scan_end(const icq_index *ix);              // positions the hit bits cover: whole stage-2 chunks
 // icq_search's body; lut_ext (device, [Q][K][256]) replaces the table build when not null.  The table build
 // zeroes the call's counters; with lut_ext the caller has done so: out_survivors (not null then) and the first
-// 2 * Q words of the workspace.
+// 2 * Q words of the workspace, which is at least that long.
 int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_ext, int Q, const float *thresholds,
                     int64_t cap, int topk, uint32_t *out_ids, float *out_dist, uint32_t *out_survivors,
                     void *workspace, size_t workspace_bytes, icq_share share, void *stream);
@@ -150,9 +151,9 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
 void icq_zero_words(uint32_t *p, int n, hipStream_t s);
 
 // Kernel launchers (each checks nothing; the extern "C" entry points validate).
-// zero0 / zero1 (may be nullptr): [Q] and [2 * Q] words the launch also sets to zero.
+// zero0, zero1, zero2 (may be nullptr): [Q] words each that the launch also sets to zero.
 int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float *lut, uint32_t *zero0,
-                         uint32_t *zero1, hipStream_t s);
+                         uint32_t *zero1, uint32_t *zero2, hipStream_t s);
 // cand_part == nullptr: the crude distances are not materialised (the fused path
 // recomputes the full sum in stage 2 from the item records).
 // list_kind == nullptr: the list must hold item ids (public contract).  Otherwise the

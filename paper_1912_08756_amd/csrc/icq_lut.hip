@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void build_lut_kernel(const float *queries, in
                                                         int d, const float *cb,
                                                         int d_pad, const float *__restrict__ cnorm,
                                                         int ncols, float *__restrict__ lut,
-                                                        uint32_t *zero0, uint32_t *zero1, int zero1_stride) {
+                                                        uint32_t *zero0, uint32_t *zero1, uint32_t *zero2) {
     __shared__ __attribute__((aligned(16))) float As[BM][LD];
     __shared__ __attribute__((aligned(16))) float Bs[NB * BN][LD];
     __shared__ float qn_s[BM];
@@ -49,7 +49,8 @@ __global__ __launch_bounds__(256) void build_lut_kernel(const float *queries, in
     // the table build of a few queries
     if (blockIdx.x == 0 && tid < BM && q0 + tid < Q) {
         if (zero0) zero0[q0 + tid] = 0u;
-        if (zero1) zero1[q0 + tid] = zero1[zero1_stride + q0 + tid] = 0u;
+        if (zero1) zero1[q0 + tid] = 0u;
+        if (zero2) zero2[q0 + tid] = 0u;
     }
 
     const int lq = tid & 3;     // which four of the slice's 16 values this thread moves
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(256) void build_lut_kernel(const float *queries, in
 }  // namespace
 
 int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float *lut, uint32_t *zero0,
-                         uint32_t *zero1, hipStream_t s) {
+                         uint32_t *zero1, uint32_t *zero2, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
     const int ncols = ix->K * ICQ_LUT_W;
     // two column blocks per wavefront: four are slower everywhere, one is within 3 % either way
@@ -180,7 +181,8 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
         const bool ahead = (int64_t)grid.x * grid.y < 4 * 256;
         auto launch = [&](auto kernel) {
             kernel<<<grid, 256, 0, s>>>(qs, nq, ix->d, ix->cb, ix->d_pad, ix->cnorm, ncols, out,
-                                        zero0 ? zero0 + q0 : nullptr, zero1 ? zero1 + q0 : nullptr, Q);
+                                        zero0 ? zero0 + q0 : nullptr, zero1 ? zero1 + q0 : nullptr,
+                                        zero2 ? zero2 + q0 : nullptr);
         };
         if (vec) { if (ahead) launch(build_lut_kernel<NB, true, true>); else launch(build_lut_kernel<NB, true, false>); }
         else     { if (ahead) launch(build_lut_kernel<NB, false, true>); else launch(build_lut_kernel<NB, false, false>); }
@@ -191,5 +193,5 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
 ICQ_EXPORT int icq_build_lut(const icq_index *ix, const float *queries, int Q, float *lut,
                              void *stream) {
     if (!ix || Q < 0 || Q > ICQ_MAX_Q || (Q > 0 && (!queries || !lut)) || ((uintptr_t)lut & 15) != 0) return ICQ_ERR_ARG;
-    return icq_launch_build_lut(ix, queries, Q, lut, nullptr, nullptr, (hipStream_t)stream);
+    return icq_launch_build_lut(ix, queries, Q, lut, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }

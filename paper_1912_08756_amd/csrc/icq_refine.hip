@@ -180,7 +180,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
     const int tid = threadIdx.x;
     u64 n = cand_count[q];
     if (n > (u64)cap) n = (u64)cap;
-    if (c0 == 0 && tid == 0) ticket[q] = 0;           // for the selection that follows
+    if (ticket && c0 == 0 && tid == 0) ticket[q] = 0; // for the selection that follows
     if (c0 >= n) return;                              // block-uniform
     const int k0 = cand_part ? Kf : 0;
     const uint32_t *ids = cand_ids + (int64_t)q * cap;
@@ -521,13 +521,13 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
 
 // Item records of at most 16 bytes take the bounded-stream kernel; wider records
 // (K > 16) the generic streaming kernel.
-static bool use_select(const icq_index *ix, int topk) { return ix->item_stride <= 16 && topk <= 512; }
+bool icq_selects(const icq_index *ix, int topk) { return ix->item_stride <= 16 && topk <= 512; }
 
 // Parts a query's work is cut into: the selection of the keys, or (wider records, longer results) the slices of
 // the generic kernel's candidate list.
 int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
     if (Q <= 0) return 1;
-    if (use_select(ix, topk)) return icq_select_splits(ix, Q, cap, topk);
+    if (icq_selects(ix, topk)) return icq_select_splits(ix, Q, cap, topk);
     int64_t s = (4LL * ix->num_cu + Q - 1) / Q;
     int64_t by_len = cap / 2048 + 1;            // do not slice short lists
     int64_t by_merge = 4096 / topk;             // merge buffer holds splits*topk keys
@@ -547,7 +547,7 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
     const uint32_t *perm = list_kind == ICQ_LIST_POSITIONS ? ix->perm : nullptr;
     const unsigned grid = (unsigned)Q * (unsigned)splits;
     const size_t tab = sizeof(float) * (size_t)(cand_part ? ix->Ks : ix->K) * ICQ_LUT_W;
-    if (use_select(ix, topk)) {
+    if (icq_selects(ix, topk)) {
         // distances for every candidate (flat), then the per-query select over the keys
         u64 *cand_keys = icq_cand_keys(keys, Q, splits, topk);   // [Q][cap], behind the slice lists
         int64_t len = cap < ix->N ? cap : ix->N;
@@ -598,7 +598,7 @@ ICQ_EXPORT int icq_refine(const icq_index *ix, const float *lut, int Q, const ui
         return ICQ_ERR_WORKSPACE;
     u64 *keys = reinterpret_cast<u64 *>(static_cast<char *>(workspace) + L.keys_off);
     return icq_launch_refine(ix, lut, Q, cand_ids, cand_part, ICQ_LIST_IDS, cand_count, cap, topk,
-                             L.splits, keys, reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + L.ticket_off),
+                             L.splits, keys, L.tickets ? reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + L.ticket_off) : nullptr,
                              out_ids, out_dist, (hipStream_t)stream);
 }
 
@@ -609,7 +609,7 @@ bool icq_masks_usable(const icq_index *ix, int Q, int topk) {
     // from 2^22 items on; with the 16-bit pre-filter (eight queries per pass of stage 1) and enough queries to
     // fill the chunk walk already from 2^19 (1000 queries, K = 16: lists are ahead up to 3e5 items, hit bits from 6e5)
     const bool large = ix->N >= (1ll << 22) || (ix->N >= (1ll << 19) && Q >= 32 && icq_scan_q16_usable(ix, Q));
-    return ix->Kf <= 4 && !icq_group_usable(ix, Q) && use_select(ix, topk) && large &&
+    return ix->Kf <= 4 && !icq_group_usable(ix, Q) && icq_selects(ix, topk) && large &&
            ix->N + 16ll * 65536 < (1ll << 31);
 }
 

@@ -119,7 +119,8 @@ int running_plan(const icq_index *const *tiles, int R, int Q, int64_t cap, int t
     L->tsurv_off = off; off = icq_align_up(off + sizeof(uint32_t) * (size_t)Q, ICQ_ALIGN);
     L->crude_off = off; off = icq_align_up(off + sizeof(float) * (size_t)Q * topk, ICQ_ALIGN);
     L->inner_off = off;
-    size_t inner = ICQ_ALIGN;
+    size_t inner = icq_align_up(2 * sizeof(uint32_t) * (size_t)Q, ICQ_ALIGN);      // the counters zeroed between two tiles
+    if (inner < ICQ_ALIGN) inner = ICQ_ALIGN;
     for (int r = 0; r < R; ++r) {
         // a tile needs room for at most its own items as candidates
         const int64_t c = cap < tiles[r]->N ? cap : tiles[r]->N;
@@ -164,7 +165,7 @@ ICQ_EXPORT int icq_search_running(const icq_index *const *tiles, const uint32_t 
     uint32_t *tsurv = reinterpret_cast<uint32_t *>(ws + L.tsurv_off);
     uint32_t *counters = reinterpret_cast<uint32_t *>(ws + L.inner_off);      // the tile searches' own, see icq_layout
     float *crude = reinterpret_cast<float *>(ws + L.crude_off);
-    rc = icq_launch_build_lut(tiles[0], queries, Q, lut, nullptr, nullptr, s);
+    rc = icq_launch_build_lut(tiles[0], queries, Q, lut, nullptr, nullptr, nullptr, s);
     if (rc != ICQ_OK) return rc;
     const int64_t n = (int64_t)Q * topk;
     running_init_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out_ids, out_dist, n, thr, out_refined, tsurv,

@@ -9,17 +9,22 @@
 icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool with_lut,
                          bool with_cands) {
     icq_ws_layout L = {};
-    // the counters first: a caller that zeroes them need not know the form the search takes
-    L.keycount_off = 0;                                    // [Q] keys written per query (hit-bit form)
-    L.ticket_off = sizeof(uint32_t) * (size_t)Q;           // [Q] parts of the selection that are done
-    size_t off = icq_align_up(2 * sizeof(uint32_t) * (size_t)Q, ICQ_ALIGN);
-    L.lut_off = off;
-    if (with_lut) off = icq_align_up(off + sizeof(float) * (size_t)Q * ix->K * ICQ_LUT_W, ICQ_ALIGN);
     // icq_search with the grouped stage 1 keeping the lists on chip: no candidate lists in the
     // workspace, only (few queries, several blocks per query) the parts' lists for the merge
     const bool on_chip = with_cands && icq_group_fused(ix, Q, topk);
     L.masked = with_cands && !on_chip && icq_masks_usable(ix, Q, topk);
     L.splits = icq_stage2_splits(ix, Q, cap, topk);
+    // The counters first, [Q] each and only those the call uses: a caller that zeroes the workspace's first 2 * Q
+    // words has zeroed them whatever form the search takes.  (A call that has neither takes no byte more than its
+    // tables, lists and counts: calls are sized to fill icq_search_static's fixed array.)
+    const size_t row = sizeof(uint32_t) * (size_t)Q;
+    L.keycount_off = 0;                                    // keys written per query (hit-bit form)
+    L.ticket_off = L.masked ? row : 0;                     // parts of the selection that are done
+    L.tickets = L.splits > 1 && !on_chip && icq_selects(ix, topk);
+    L.count_off = L.ticket_off + (L.tickets ? row : 0);
+    size_t off = icq_align_up(L.count_off + (with_cands ? row : 0), ICQ_ALIGN);
+    L.lut_off = off;
+    if (with_lut) off = icq_align_up(off + sizeof(float) * (size_t)Q * ix->K * ICQ_LUT_W, ICQ_ALIGN);
     L.ids_off = off;
     if (L.masked) {
         L.scan_end = icq_mask_scan_end(ix);
@@ -29,8 +34,6 @@ icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool
     } else if (with_cands && !on_chip) {
         off = icq_align_up(off + sizeof(uint32_t) * (size_t)Q * (size_t)cap, ICQ_ALIGN);
     }
-    L.count_off = off;
-    if (with_cands) off = icq_align_up(off + sizeof(uint32_t) * (size_t)Q, ICQ_ALIGN);
     L.keys_off = off;
     // slice lists [Q][splits][topk] (when sliced), then one 64-bit key per candidate [Q][cap]
     if (on_chip) {
@@ -110,13 +113,13 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
         unsigned long long *keys = reinterpret_cast<unsigned long long *>(ws + L.keys_off);
         if (timed) ICQ_HIP_TRY(hipEventRecord(ev[0], s));
         int rc = ICQ_OK;
-        uint32_t *key_count = reinterpret_cast<uint32_t *>(ws + L.keycount_off);
-        uint32_t *ticket = reinterpret_cast<uint32_t *>(ws + L.ticket_off);
+        uint32_t *key_count = L.masked ? reinterpret_cast<uint32_t *>(ws + L.keycount_off) : nullptr;
+        uint32_t *ticket = L.tickets ? reinterpret_cast<uint32_t *>(ws + L.ticket_off) : nullptr;
         if (own_lut)
             rc = icq_launch_build_lut(ix, queries + (int64_t)q0 * ix->d, nq, reinterpret_cast<float *>(ws + L.lut_off), cnt,
-                                      key_count, s);
-        else if (q0 > 0)
-            icq_zero_words(key_count, 2 * nq, s);
+                                      key_count, ticket, s);
+        else if (q0 > 0)      // (no table build to do it; the caller zeroed those of the first sub-batch)
+            icq_zero_words(reinterpret_cast<uint32_t *>(ws), (int)(L.masked + L.tickets) * nq, s);
         if (rc != ICQ_OK) return rc;
         if (timed) ICQ_HIP_TRY(hipEventRecord(ev[1], s));
         if (L.masked) {

@@ -67,3 +67,35 @@ def test_a_call_beyond_the_scratch_array_is_refused():
     with pytest.raises(b.IcqError) as e:
         b.icq_search_static(index, dev(cfg["queries"]), torch.zeros(Q, device="cuda"), cap, topk, ids, dist, None)
     assert e.value.code == b.ICQ_ERR_SCRATCH
+
+
+@pytest.mark.parametrize("K,Kf,Q,topk,cap", [(16, 4, 1024, 100, 1365), (16, 4, 2000, 100, 32), (4, 4, 3000, 10, 590),
+                                             (4, 2, 5000, 300, 217)])
+def test_calls_that_fill_the_scratch_array_to_its_end(K, Kf, Q, topk, cap):
+    """Tables, lists and counts take what they must and no byte more: [Q][K][256] floats, [Q][cap] ids and 64-bit keys,
+    [Q] counts, each rounded up to 256 bytes, are accepted as long as their sum is (cap + 1 no longer is)."""
+    import torch
+    from paper_1912_08756_amd import binding as b
+    up = lambda n: (n + 255) // 256 * 256
+    need = lambda c: up(4 * Q * K * 256) + up(4 * Q * c) + up(4 * Q) + up(8 * Q * c)
+    assert need(cap) <= b.ICQ_STATIC_SCRATCH_BYTES < need(cap + 1)
+    rng = np.random.default_rng(Q)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    cb, codes = rng.standard_normal((K, 256, 8)).astype(np.float32), rng.integers(0, 256, (K, 40_000), dtype=np.uint8)
+    index, queries = b.icq_index_create(dev(cb), dev(codes), Kf), dev(rng.standard_normal((Q, 8)).astype(np.float32))
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    at = dev(codes).long()                                # about half of cap items survive (items that tie do not)
+    thr = torch.cat([torch.kthvalue(sum(t[:, k].index_select(1, at[k]) for k in range(Kf)), cap // 2, dim=1).values
+                     for t in lut.split(256)])
+    out = [[torch.full((Q, topk), -7, dtype=torch.int32, device="cuda"), torch.full((Q, topk), -7.0, device="cuda"),
+            torch.full((Q,), -7, dtype=torch.int32, device="cuda")] for _ in range(2)]
+    b.icq_search_static(index, queries, thr, cap, topk, *out[0])
+    ws = torch.empty(b.icq_workspace_bytes(index, Q, cap, topk), dtype=torch.uint8, device="cuda")
+    b.icq_search(index, queries, thr, cap, topk, *out[1], ws)
+    torch.cuda.synchronize()
+    assert (out[0][2] <= cap).all() and (out[0][2] > 0).all()
+    assert all(torch.equal(x, y) for x, y in zip(*out))
+    with pytest.raises(b.IcqError) as e:
+        b.icq_search_static(index, queries, thr, cap + 1, topk, *out[0])
+    assert e.value.code == b.ICQ_ERR_SCRATCH
