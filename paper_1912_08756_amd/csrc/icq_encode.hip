@@ -23,8 +23,9 @@
 //  2. Items with more than one candidate (a few per cent) form the candidates' fp32 scores from the fp32
 //     residual and codewords and take the argmin of those.  The result is the fp32 argmin, as before.
 // Where more than eight codewords of an item are within the bound, the block repeats the level with both
-// operands split in two halves (three products, E smaller by 2^-10); more than eight after that -- equal
-// codewords -- and the item's scores are all formed in fp32.
+// operands split in two halves (three products: E's operand part is smaller by 2^-10, its accumulation part
+// three times as large); more than eight after that -- equal codewords -- and the item's scores are all
+// formed in fp32.
 //
 // What bounds it: up to E_REG_D dimensions vector issue -- 800 instructions per wavefront and level (argmin 2.5
 // per score; residual, norms and conversion 5 per element) keep the vector units 64 % busy, the matrix
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         if (tid < EB) sh.ccount[tid] = 0;
         if (tid == 0) sh.over = 0;
         // ---- candidates: codewords whose score is within twice the error bound of the item's best
-        auto candidates = [&](const float16v (&acc)[2][2], float u_r, float d_c) __attribute__((always_inline)) {
+        auto candidates = [&](const float16v (&acc)[2][2], float u_r, float d_c, int passes) __attribute__((always_inline)) {
             const int lane = fresh(tid0) & 63, half = lane >> 5, l32 = lane & 31;
             float best[2];
 #pragma unroll
@@ -357,9 +358,10 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 const int item = ih * 64 + u * 32 + l32;
                 const float b = fmaxf(fmaxf(sh.smax[0][item], sh.smax[1][item]), fmaxf(sh.smax[2][item], sh.smax[3][item]));
                 const float rn = __builtin_amdgcn_sqrtf(sh.nrm2[item]) * 1.0001f;
-                // |<r,c> - <r',c'>|, scaled; the third term: halves below the normal range (2^-25 each at most)
+                // |<r,c> - <r',c'>|, scaled; the third term: halves below the normal range (2^-25 each at most; of the
+                // codewords' second halves that is less than u_r * cmax allows); the last: every pass's roundings
                 const float E = S * rn * (u_r * cmax + (1.0f + u_r) * d_c) + __builtin_amdgcn_sqrtf((float)(nks * 32)) * 2.98e-8f * sc * cmax +
-                                (float)(nks * 32 + 8) * 1.2e-7f * S * cmax * (rn + cmax);
+                                (float)(passes * nks * 32 + 8) * 1.2e-7f * S * cmax * (rn + cmax);
                 best[u] = b - 2.0f * E - fabsf(b) * 1e-6f - 1e-30f;
             }
 #pragma unroll
@@ -402,7 +404,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 if (pass > 0) __syncthreads();             // the fragments of the pass before are consumed
                 contract(acc, pass == 2 ? half_lo : half_hi, pass, round == 0);
             }
-            candidates(acc, round == 0 ? E_U : 4.0f * E_U * E_U, round == 0 ? dmax : 2.0f * E_U * dmax);
+            candidates(acc, round == 0 ? E_U : 4.0f * E_U * E_U, round == 0 ? dmax : 2.0f * E_U * dmax, round == 0 ? 1 : 3);
             if (round != 0 || sh.over == 0) break;         // block-uniform: read between barriers
             __syncthreads();
             if (tid < EB) sh.ccount[tid] = 0;
