@@ -112,8 +112,12 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     const int cw = wave & 3, ih = wave >> 2;
     const int nks = (d_pad + 31) / 32;                     // 32-wide codebook slices
     const int nsl = REG ? 1 : (nks + 3) / 4;               // 128-wide residual slices
-    // rows past N read the last row; their codes are never stored
-    auto row = [&](int rg, int p) { return i0 + rg + E_G * p < N ? i0 + rg + E_G * p : N - 1; };
+    const int live = N - i0 < EB ? (int)(N - i0) : EB;     // items of this block; rows past them read the last one's x
+    auto row = [&](int rg, int p) { return i0 + (rg + E_G * p < live ? rg + E_G * p : live - 1); };
+    // a residual in memory is its owner's alone; rows past N read a codeword instead of racing with it
+    auto res_row = [&](int rg, int p) -> const float * {
+        return rg + E_G * p < live ? res + (i0 + rg + E_G * p) * d_pad : cb;
+    };
 
     float r[REG ? E_P : 1][8];
     float co[REG && ICM ? E_P : 1][8];                     // the current codewords of the level to come
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         return cb + ((int64_t)k * ICQ_LUT_W + j) * d_pad;
     };
     auto store_res = [&](int rg, int p, int e0, const float (&v)[8]) __attribute__((always_inline)) {
-        if (i0 + rg + E_G * p < N && e0 < d_pad) {
+        if (rg + E_G * p < live && e0 < d_pad) {
             float *o = res + row(rg, p) * d_pad + e0;
             *reinterpret_cast<float4v *>(o) = float4v{v[0], v[1], v[2], v[3]};
             *reinterpret_cast<float4v *>(o + 4) = float4v{v[4], v[5], v[6], v[7]};
@@ -165,7 +169,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     auto add_norm = [&](int tid, int rg, int p, int sl, float x) __attribute__((always_inline)) {
         x = row_sum(x);
         const int item = rg + E_G * p;
-        if ((tid & 15) == 0) sh.nrm2[item] = sl == 0 ? x : sh.nrm2[item] + x;
+        if ((tid & 15) == 0) sh.nrm2[item] = item >= live ? 0.0f : sl == 0 ? x : sh.nrm2[item] + x;
     };
     for (int sl = 0; sl < nsl; ++sl) {
         const int tid = fresh(tid0), e0 = sl * 128 + (tid & 15) * 8, rg = tid >> 4;
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
             } else if (!ICM && lev == 0) {
                 load_x(rg, p, e0, v);
             } else {
-                load8(res + row(rg, p) * d_pad, e0, v);
+                load8(res_row(rg, p), e0, v);
             }
         };
         // the residuals of slice sl as halves -> LDS.  UPDATE: first bring them up to date with the level before
@@ -264,7 +268,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                     const uint32_t oldc = sh.before[rg + E_G * p], newc = sh.code[kp][rg + E_G * p];
                     const bool moved = !ICM || newc != oldc;
                     if (!ICM && lev == 1) load_x(rg, p, e0, v);
-                    else load8(res + row(rg, p) * d_pad, e0, v);
+                    else load8(res_row(rg, p), e0, v);
                     if (moved) {
                         float c[8];
                         if (ICM) {
@@ -371,6 +375,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 #pragma unroll
                 for (int i = 0; i < 32; ++i)
                     bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(best[u] - acc[u][i >> 4][i & 15]), 31);
+                if (item >= live) bits = 0;
                 while (bits != 0) {
                     const int i = __builtin_clz(bits);
                     bits &= ~(0x80000000u >> i);
@@ -429,9 +434,9 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 }
             }
             const int item = rg + E_G * p;
-            const uint32_t n = sh.ccount[item];
+            const uint32_t n = item < live ? sh.ccount[item] : 1u;
             const uint32_t old = ICM ? sh.code[k][item] : 0u;
-            uint32_t code = n != 0 ? sh.cand[item][0] : old;
+            uint32_t code = sh.ccount[item] != 0 ? sh.cand[item][0] : old;
             // none: a residual with infinities, NaN or components beyond the halves' range (its bound is no number)
             const bool all = n == 0 || n > (uint32_t)E_CAND;
             if (__builtin_amdgcn_ballot_w64(n != 1) != 0) {        // wavefront-uniform: four items at a time
@@ -473,7 +478,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 if (ICM) sh.before[item] = (uint8_t)old;
                 sh.code[k][item] = (uint8_t)code;
             }
-            if (ICM && code != old && (tid & 15) == 0 && i0 + item < N) ++nchanged;
+            if (ICM && code != old && (tid & 15) == 0 && item < live) ++nchanged;
             if (REG && (!ICM || code != old)) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {

@@ -1073,6 +1073,35 @@ def test_encode_of_vectors_beyond_the_halves_range(gpu, K, m, d):
     assert (first[:, [3, 4, 70]] == second[:, [3, 4, 70]]).all()
 
 
+@pytest.mark.parametrize("N,d", [(1, 129), (2, 300), (129, 200), (130, 128), (257, 960), (383, 64)])
+def test_encode_of_a_last_block_with_few_items(gpu, N, d):
+    """The places past the last item take part in nothing: the last items get what they get in the middle of full blocks,
+    from vectors far from any tie, and the oracle's codes; twice the same, and with sweeps of refinement."""
+    torch, b = gpu
+    K, m, more = 4, 256, 512
+    rng = np.random.default_rng(N * 1000 + d)
+    cb = (rng.standard_normal((K, m, d)) * (0.5 ** np.arange(K))[:, None, None]).astype(np.float32)
+    src = rng.integers(0, m, (K, more))
+    x = (sum(cb[k][src[k]] for k in range(K)) + 0.001 * rng.standard_normal((more, d))).astype(np.float32)
+    x[:N] *= 1.0 + 0.001 * rng.random((N, 1), dtype=np.float32)
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    out = []
+    for n in (N, more, N):
+        ws = torch.empty(b.icq_encode_workspace_bytes(index, n), dtype=torch.uint8, device="cuda")
+        codes, changed = torch.full((K, n), 255, dtype=torch.uint8, device="cuda"), torch.full((2,), -1, dtype=torch.int32, device="cuda")
+        b.icq_encode(index, _dev(torch, x[:n]), codes, ws)
+        start = _dev(torch, rng.integers(0, m, (K, n), dtype=np.uint8) if not out else out[0][2][:, :n] if n == N else
+                     np.concatenate([out[0][2], rng.integers(0, m, (K, n - N), dtype=np.uint8)], axis=1))
+        refined = start.clone()
+        b.icq_encode_refine(index, _dev(torch, x[:n]), refined, 2, changed, ws)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (codes, refined, start, changed)])
+    want = orc.encode(cb, x[:N])
+    for o in out:
+        assert np.array_equal(o[0][:, :N], want) and np.array_equal(o[1][:, :N], out[0][1])
+    assert np.array_equal(out[0][3], out[2][3]) and out[0][3][0] <= K * N
+
+
 def test_encode_on_disjoint_supports_recovers_the_codes(gpu):
     """Codebooks with pairwise-disjoint supports, vectors that are exact reconstructions: every
     greedy step has a codeword at distance zero, so the codes come back bit for bit; an index
