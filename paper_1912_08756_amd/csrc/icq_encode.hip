@@ -366,7 +366,9 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 // codewords' second halves that is less than u_r * cmax allows); the last: every pass's roundings
                 const float E = S * rn * (u_r * cmax + (1.0f + u_r) * d_c) + __builtin_amdgcn_sqrtf((float)(nks * 32)) * 2.98e-8f * sc * cmax +
                                 (float)(passes * nks * 32 + 8) * 1.2e-7f * S * cmax * (rn + cmax);
-                best[u] = b - 2.0f * E - fabsf(b) * 1e-6f - 1e-30f;
+                // a bound that is no number (infinities, NaN, components beyond the halves' range) admits nobody: what its
+                // differences' signs say would be a matter of which NaN the instructions make
+                best[u] = E < INFINITY && item < live ? b - 2.0f * E - fabsf(b) * 1e-6f - 1e-30f : INFINITY;
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 #pragma unroll
                 for (int i = 0; i < 32; ++i)
                     bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(best[u] - acc[u][i >> 4][i & 15]), 31);
-                if (item >= live) bits = 0;
+                if (!(best[u] < INFINITY)) bits = 0;
                 while (bits != 0) {
                     const int i = __builtin_clz(bits);
                     bits &= ~(0x80000000u >> i);
@@ -429,16 +431,16 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 for (int u = 0; u < CH; ++u) {
                     const int it = rg + E_G * (p + u);
                     const uint32_t now = ICM ? sh.code[k][it] : 0u;
-                    load8(codeword(k, sh.ccount[it] != 0 ? sh.cand[it][0] : now), c8, ca[u]);
+                    load8(codeword(k, sh.ccount[it] - 1u < (uint32_t)E_CAND ? sh.cand[it][0] : now), c8, ca[u]);
                     if (ICM) load8(codeword(k, now), c8, cc[ICM ? u : 0]);
                 }
             }
             const int item = rg + E_G * p;
             const uint32_t n = item < live ? sh.ccount[item] : 1u;
             const uint32_t old = ICM ? sh.code[k][item] : 0u;
-            uint32_t code = sh.ccount[item] != 0 ? sh.cand[item][0] : old;
-            // none: a residual with infinities, NaN or components beyond the halves' range (its bound is no number)
+            // none: a bound that is no number.  If no fp32 score is one either, index 0 (ICM: the current one) stays
             const bool all = n == 0 || n > (uint32_t)E_CAND;
+            uint32_t code = sh.ccount[item] - 1u < (uint32_t)E_CAND ? sh.cand[item][0] : old;
             if (__builtin_amdgcn_ballot_w64(n != 1) != 0) {        // wavefront-uniform: four items at a time
                 float best = INFINITY;
                 uint32_t bf = 0xFFFFFFFFu;                         // ICM: 0 for the current codeword, else index + 1

@@ -1102,6 +1102,49 @@ def test_encode_of_a_last_block_with_few_items(gpu, N, d):
     assert np.array_equal(out[0][3], out[2][3]) and out[0][3][0] <= K * N
 
 
+@pytest.mark.parametrize("m,d", [(2, 2), (5, 40), (201, 128), (256, 130)])
+def test_encode_where_the_halves_overflow_for_few_codewords(gpu, m, d):
+    """Vectors whose halves are infinite, in a codebook in which few products then are +inf: these decide nothing.  1e30
+    in two components meets (1, -0.5) and (0.1, 0.1): 0.5e30 against 0.2e30, but inf - inf against inf in halves.  An
+    infinite component is decided by the codeword's sign there, also where the codeword is too small for a half.  NaN of
+    either sign: index 0, a current codeword kept."""
+    torch, b = gpu
+    K, N = 2, 140
+    rng = np.random.default_rng(m * 1000 + d)
+    cb = np.full((K, m, d), -1.0, np.float32)              # -1e30 - 1e30 and -inf: never the best
+    cb[:, :, 2:] = 0.01 * rng.standard_normal((K, m, max(d - 2, 0))).astype(np.float32)
+    cb[:, m - 1, :2] = 0.1, 0.1
+    cb[:, m - 2, :2] = 1.0, -0.5
+    x = np.zeros((N, d), np.float32)
+    x[:, 0] = -1.0                                         # plain vectors around them
+    x[7, :2] = x[139, :2] = 1e30
+    x[20, d - 1] = np.nan
+    x[21, d - 1] = np.copysign(np.float32(np.nan), np.float32(-1.0))
+    assert np.signbit(x[21, d - 1]) and not np.signbit(x[20, d - 1])
+    tiny = cb.copy()                                       # the first positive one is no half: 1e-12 against 1
+    tiny[:, :, 0] = -1.0
+    tiny[:, m - 2, 0], tiny[:, m - 1, 0] = 1e-12, 1.0
+    y = x.copy()
+    y[:, 0] = -1.0
+    y[7, 0] = y[139, 0] = np.inf
+
+    def both(cb, x, start):
+        index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+        ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+        codes = torch.full((K, N), 255, dtype=torch.uint8, device="cuda")
+        refined = torch.full((K, N), start, dtype=torch.uint8, device="cuda")
+        b.icq_encode(index, _dev(torch, x), codes, ws)
+        b.icq_encode_refine(index, _dev(torch, x), refined, 1, None, ws)
+        torch.cuda.synchronize()
+        return codes.cpu().numpy(), refined.cpu().numpy()
+    first, second = both(cb, x, m - 1)
+    assert (first[:, [7, 139]] == m - 2).all() and (second[:, [7, 139]] == m - 2).all()
+    assert (first[:, 20:22] == 0).all() and (second[:, 20:22] == m - 1).all()
+    first, second = both(tiny, y, 0)
+    assert (first[:, [7, 139]] == m - 2).all()
+    assert (second[:, [7, 139]] == (0 if m == 2 else m - 2)).all()
+
+
 def test_encode_on_disjoint_supports_recovers_the_codes(gpu):
     """Codebooks with pairwise-disjoint supports, vectors that are exact reconstructions: every
     greedy step has a codeword at distance zero, so the codes come back bit for bit; an index
