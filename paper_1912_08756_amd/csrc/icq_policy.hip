@@ -20,34 +20,30 @@
 
 namespace {
 
-// the block's life is a chain of round trips (records, tables, histogram passes), so the sample is spread over
-// as many threads as a block can have: 19 us with 256 threads, 11 with 1024 (199 queries, 4096 items)
-constexpr int SP_THREADS = 1024;
-
-constexpr int SP_LPT = ICQ_MAX_SAMPLE / SP_THREADS;    // sample items per thread
-static_assert(ICQ_MAX_SAMPLE % SP_THREADS == 0 && SP_LPT <= 32, "one flag bit per item of a thread");
-
-// One block per query; thread t owns sample items u * SP_THREADS + t.  LDS: the K tables.
+// One block of T threads per query; thread t owns sample items u * T + t.  LDS: the K tables.
 // The topk-th nearest by (D, id) comes from two exact radix selects: the topk-th smallest
 // distance word, then -- among the items at exactly that distance -- the id that completes
 // the count (usually the only one).
-__global__ __launch_bounds__(SP_THREADS) void sample_threshold_kernel(
+template <int T>
+__global__ __launch_bounds__(T) void sample_threshold_kernel(
     const uint8_t *__restrict__ items, int stride, int K, int Kf, const float *__restrict__ lut,
     const float *__restrict__ sigma, int topk, int n, float *__restrict__ thr_out) {
+    constexpr int LPT = ICQ_MAX_SAMPLE / T;                // sample items per thread
+    static_assert(ICQ_MAX_SAMPLE % T == 0 && LPT <= 32, "one flag bit per item of a thread");
     extern __shared__ __attribute__((aligned(16))) float sp_smem[];
-    __shared__ IcqKthSharedT<SP_THREADS> kth;
-    __shared__ uint32_t s_below[SP_THREADS / 64];
-    float *T = sp_smem;
+    __shared__ IcqKthSharedT<T> kth;
+    __shared__ uint32_t s_below[T / 64];
+    float *tab = sp_smem;
     const int q = blockIdx.x, tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = tid >> 6;
     const float *Tq = lut + (int64_t)q * K * ICQ_LUT_W;
-    for (int i = tid; i < K * ICQ_LUT_W; i += SP_THREADS) T[i] = Tq[i];
+    for (int i = tid; i < K * ICQ_LUT_W; i += T) tab[i] = Tq[i];
     __syncthreads();
-    uint32_t v[SP_LPT], ok = 0;
+    uint32_t v[LPT], ok = 0;
 #pragma unroll
-    for (int u = 0; u < SP_LPT; ++u) {
-        const int i = u * SP_THREADS + tid;
+    for (int u = 0; u < LPT; ++u) {
+        const int i = u * T + tid;
         v[u] = 0;
         if (i < n) {
             // the record word by word (records are 4-byte aligned); k ascending, as in the search kernels
@@ -59,7 +55,7 @@ __global__ __launch_bounds__(SP_THREADS) void sample_threshold_kernel(
                 for (int b = 0; b < 4; ++b) {
                     const int k = w * 4 + b;
                     if (k < K) {
-                        const float e = T[k * ICQ_LUT_W + ((word >> (8 * b)) & 0xffu)];
+                        const float e = tab[k * ICQ_LUT_W + ((word >> (8 * b)) & 0xffu)];
                         d = k == 0 ? e : d + e;
                     }
                 }
@@ -68,12 +64,12 @@ __global__ __launch_bounds__(SP_THREADS) void sample_threshold_kernel(
             ok |= 1u << u;
         }
     }
-    const uint32_t cut = block_kth<SP_LPT>(kth, v, ok, (uint32_t)topk, true, tid, lane, wave);
+    const uint32_t cut = block_kth<LPT>(kth, v, ok, (uint32_t)topk, true, tid, lane, wave);
     // items nearer than the cut, and the ids of those at it
-    uint32_t below = 0, eq = 0, ids[SP_LPT];
+    uint32_t below = 0, eq = 0, ids[LPT];
 #pragma unroll
-    for (int u = 0; u < SP_LPT; ++u) {
-        ids[u] = (uint32_t)(u * SP_THREADS + tid);
+    for (int u = 0; u < LPT; ++u) {
+        ids[u] = (uint32_t)(u * T + tid);
         if (((ok >> u) & 1u) && v[u] < cut) ++below;
         if (((ok >> u) & 1u) && v[u] == cut) eq |= 1u << u;
     }
@@ -84,12 +80,12 @@ __global__ __launch_bounds__(SP_THREADS) void sample_threshold_kernel(
     __syncthreads();
     uint32_t total_below = 0;
 #pragma unroll
-    for (int w = 0; w < SP_THREADS / 64; ++w) total_below += s_below[w];
-    const uint32_t f = block_kth<SP_LPT>(kth, ids, eq, (uint32_t)topk - total_below, true, tid, lane, wave);
+    for (int w = 0; w < T / 64; ++w) total_below += s_below[w];
+    const uint32_t f = block_kth<LPT>(kth, ids, eq, (uint32_t)topk - total_below, true, tid, lane, wave);
     if (tid == 0) {
         const uint8_t *rec = items + (size_t)f * stride;
-        float p = T[rec[0]];
-        for (int k = 1; k < Kf; ++k) p += T[k * ICQ_LUT_W + rec[k]];
+        float p = tab[rec[0]];
+        for (int k = 1; k < Kf; ++k) p += tab[k * ICQ_LUT_W + rec[k]];
         thr_out[q] = p + (sigma ? sigma[q] : 0.0f);
     }
 }
@@ -239,10 +235,19 @@ ICQ_EXPORT int icq_sample_thresholds(const icq_index *ix, const float *lut, int 
         return icq_check_launch();
     }
     const size_t lds = sizeof(float) * (size_t)ix->K * ICQ_LUT_W;
-    ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(&sample_threshold_kernel), 65536));
-    sample_threshold_kernel<<<Q, SP_THREADS, lds, s>>>(ix->items, ix->item_stride, ix->K, ix->Kf, lut, sigma,
-                                                       topk, n, thresholds_out);
-    return icq_check_launch();
+    auto launch = [&](auto kernel, int threads) -> int {
+        ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(kernel), 65536));
+        kernel<<<Q, threads, lds, s>>>(ix->items, ix->item_stride, ix->K, ix->Kf, lut, sigma, topk, n, thresholds_out);
+        return icq_check_launch();
+    };
+    // A block's life is a chain of round trips (records, tables, histogram passes), so while the queries leave room a
+    // sample is spread over many threads; from some queries per CU on what counts is that a CU holds more blocks.
+    // us with 256 / 512 / 1024 threads, K = 8: 100 queries, 4096 items 15.5 / 10.3 / 9.0 (2000: 10.8 / 8.0 / 8.2);
+    // 512 queries 16.3 / 11.9 / 12.0 (11.6 / 9.1 / 10.0); 1024 queries 18.4 / 16.3 / 22.2, and with 500 items
+    // 9.4 / 9.6 / 15.5; 4000 queries 53.7 / 56.5 / 81.5.  K = 4 and 16: the same lines.
+    if (Q <= 2 * ix->num_cu && n > 2048) return launch(sample_threshold_kernel<1024>, 1024);
+    if (Q <= 2 * ix->num_cu || (Q <= 4 * ix->num_cu && n > 1024)) return launch(sample_threshold_kernel<512>, 512);
+    return launch(sample_threshold_kernel<256>, 256);
 }
 
 ICQ_EXPORT int icq_op_counts(const icq_index *ix, const uint32_t *refined, int Q, unsigned long long *ops_out,

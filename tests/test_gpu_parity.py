@@ -733,6 +733,10 @@ def test_stream_scan_of_an_array_beyond_the_last_level_cache(gpu):
     ("C1", 30_000, 9, {}, 10, 1000),                    # sample length not a power of two
     ("C2", 9_000, 33, dict(d=64), 100, 2048),           # K = 16, Kf = 4
     ("C0", 10_000, 100, {}, 10, 4096),                  # K = 4, Kf = 1
+    ("C1", 5_000, 513, {}, 10, 4096),                   # more queries than 1024-thread blocks have room for
+    ("C1", 5_000, 520, {}, 7, 1025),
+    ("C1", 2_000, 1100, {}, 20, 1500),                  # small blocks
+    ("C0", 700, 600, {}, 700, 1024),                    # every sample item
     ("C1", 700, 5, {}, 100, 4096),                      # sample = the whole index
     ("C1", 60, 5, {}, 100, 4096),                       # fewer items than topk: nothing is pruned
 ])
