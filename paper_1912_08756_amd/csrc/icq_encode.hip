@@ -489,10 +489,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 }
             }
         }
-        // the sixteen lanes of an item read what one of them wrote: same wavefront, so in order, but not by the
-        // rules of one thread's memory
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();                                  // the sixteen lanes of an item read what one of them wrote
         if (REG && ICM) {                                  // (after the last level too: a condition would keep the old values alive)
 #pragma unroll
             for (int p = 0; p < E_P; ++p) load8(codeword(kn, sh.code[kn][rg + E_G * p]), c8, co[REG && ICM ? p : 0]);

@@ -128,7 +128,7 @@ __global__ __launch_bounds__(GS_THREADS) void group_scan_kernel(
     __syncthreads();                                       // the only barrier
 
     auto expand = [&](uint32_t nh) {                       // nh <= GS_WHITS, wavefront-uniform
-        __builtin_amdgcn_wave_barrier();                   // LDS runs a wavefront's accesses in order
+        wave_lds_order();
         uint32_t tot = 0;
         for (uint32_t h0 = 0; h0 < nh; h0 += 64) {
             const uint32_t h = h0 + lane;
@@ -150,14 +150,14 @@ __global__ __launch_bounds__(GS_THREADS) void group_scan_kernel(
             const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
             // same additions as the item-by-item scan: lut[0][c0] (+ lut[1][c1])
             const float P = KF == 2 ? t0[g >> 8] + t1[g & 255u] : t0[g];
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
             tuple[lane] = make_uint2(s - excl, __float_as_uint(P));
             uint32_t carry = 0;                            // tuple (lane + 1) that holds the survivor before the window
             for (uint32_t w0 = 0; w0 < m; w0 += GS_AHEAD * 64) {
                 // marks of the tuples that start inside these windows
                 const bool starts = n != 0 && excl >= w0 && excl < w0 + GS_AHEAD * 64;
                 if (starts) mark[excl - w0] = lane + 1;
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_order();
                 uint32_t id[GS_AHEAD], pb[GS_AHEAD];
 #pragma unroll
                 for (int u = 0; u < GS_AHEAD; ++u) {
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(GS_THREADS) void group_scan_kernel(
                     id[u] = perm ? perm[pos] : pos;
                     pb[u] = tu.y;
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_order();
                 if (starts) mark[excl - w0] = 0;
 #pragma unroll
                 for (int u = 0; u < GS_AHEAD; ++u) {
@@ -669,7 +669,7 @@ __global__ __launch_bounds__(GS_THREADS) __attribute__((amdgpu_waves_per_eu(WORD
                 const uint32_t bnd = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(hx) + (bi4 < nhc4 ? bi4 : nhc4));
                 ++stamp;
                 if (bnd <= pl) flag[bnd - pf] = stamp;              // pf < bnd: tuple ha holds pf
-                __builtin_amdgcn_wave_barrier();                    // LDS runs a wavefront's accesses in order
+                wave_lds_order();
                 const uint64_t marks = __builtin_amdgcn_ballot_w64(flag[lane] == stamp);
                 // flags at or below this lane: lane 0 never holds one (a flagged tuple starts after pf), so
                 // that is the count below the lane in the flags moved down by one -- two mbcnt, ha added in

@@ -410,7 +410,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         }
         const uint32_t cbase = c * RM_CHUNK, p0 = lane * 32u;
         for (uint32_t lo = 0; lo < total; lo += RM_LIST) {      // wavefront-uniform; one round unless the chunk is dense
-            __builtin_amdgcn_wave_barrier();          // LDS runs a wavefront's accesses in order: the last round's reads are done
+            wave_lds_order();                         // the last round's reads are done
             if (off + mine > lo && off < lo + RM_LIST) {
                 uint32_t idx = off - lo;              // wraps below the window: fails the test until it is inside
 #pragma unroll
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
                     }
                 }
             }
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_order();
             const uint32_t n = total - lo < (uint32_t)RM_LIST ? total - lo : (uint32_t)RM_LIST;
             for (uint32_t base = 0; base < n; base += 64 * RM_PER) {
                 uint32_t id[RM_PER], rec[RM_PER][RW];

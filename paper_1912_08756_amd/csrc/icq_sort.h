@@ -67,6 +67,14 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
+// What the lanes of a wavefront wrote to LDS is theirs to read from here on, and what they read may be overwritten.  The
+// hardware runs a wavefront's LDS accesses in order; the fence says so to the compiler, which by one thread's rules
+// may move a read of another lane's word over the barrier or reuse an earlier one.  No instruction comes of it.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Compare-exchange steps j = jmax, jmax/2, .., 1 of bitonic stage k on the element
 // a lane holds, against lanes lane^j of its own wavefront (no LDS, no barrier).
 __device__ __forceinline__ u64 wave_bitonic_steps(u64 x, int e, int k, int jmax) {
