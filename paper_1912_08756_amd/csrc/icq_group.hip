@@ -93,7 +93,7 @@ constexpr int GS_AHEAD = 4;       // windows of 64 survivors whose ids are loade
 // grid (parts, Q): a block takes the tuples (c0, c1) of one query whose c0 is congruent to its part's number;
 // at its i-th row wavefront w evaluates the 64 columns of group (w + i) mod 4, so that the rows and columns
 // of a query's nearest codewords -- where its survivors sit -- are dealt out evenly (Kf == 1: one row, tuple
-// c0 = column).  A wavefront is on its own once the tables are in LDS: the tuples below the threshold go to
+// c0 = column; a block takes the columns congruent to its part's number).  A wavefront is on its own once the tables are in LDS: the tuples below the threshold go to
 // its own buffer (ballot, no atomics); expanding it takes one atomic on the query's counter for all their
 // items and then writes them 64 at a time, whatever the tuple sizes: a tuple that starts inside a window
 // marks its first survivor's lane, a running maximum over the lanes carries it to the others.  One tuple at
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(GS_THREADS) void group_scan_kernel(
     for (int row = KF == 2 ? (int)blockIdx.x : 0; row < (KF == 2 ? 256 : 1); row += parts, ++i) {
         const uint32_t col = (uint32_t)(((wave + i) & (GS_WAVES - 1)) * 64) + lane;
         const float P = KF == 2 ? t0[row] + t1[col] : t0[col];
-        const bool hit = P < t;
+        const bool hit = P < t && (KF == 2 || lane % (uint32_t)parts == blockIdx.x);
         const uint64_t mask = __builtin_amdgcn_ballot_w64(hit);
         if (mask == 0) continue;
         if (nh > (uint32_t)(GS_WHITS - 64)) {
@@ -915,8 +915,10 @@ int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const fl
                           uint32_t *cand_ids, float *cand_part, bool as_positions, uint32_t *cand_count, int64_t cap,
                           hipStream_t s) {
     // cand_count is zero.  Four to eight blocks of four wavefronts per CU while the queries leave room for it; at
-    // most 64 parts: a row per wavefront and four tables' worth of columns is little for a block already
-    int parts = ix->Kf == 2 ? (int)((4ll * ix->num_cu + Q - 1) / Q) : 1;
+    // most 64 parts: a row per wavefront and four tables' worth of columns is little for a block already.  Kf == 1:
+    // the 256 tuples are long, so that even one column per wavefront is work (7 queries, 10^5 items that all survive,
+    // one block per query / 64: 90 / 27 us)
+    int parts = (int)((4ll * ix->num_cu + Q - 1) / Q);
     if (parts > 64) parts = 64;
     if (parts < 1) parts = 1;
     for (int q0 = 0; q0 < Q; q0 += 65535) {
