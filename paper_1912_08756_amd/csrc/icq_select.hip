@@ -32,7 +32,7 @@ constexpr int SEL_RANK = 256;      // up to so many keys are ranked by counting,
 template <int T>
 struct SelShared {
     IcqKthSharedT<T> kth;
-    uint32_t cnt, total, minima, last;
+    uint32_t cnt, minima, below, last;
     uint32_t rank[SEL_RANK];
 };
 
@@ -56,41 +56,31 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
             if (base + (u64)j * T + tid >= n) r[j] = KEY_PAD;
     };
     const bool once = n <= (u64)PER * T;
-    uint32_t m = 0xFFFFFFFFu, real = 0;
-    bool any = false;
-    if (tid == 0) sh.cnt = sh.total = sh.minima = 0;
+    u64 least = KEY_PAD;               // the smallest key of this thread's share
     for (u64 base = 0; base < n; base += (u64)PER * T) {
         load(base);
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const uint32_t d = (uint32_t)(r[j] >> 32);
-            const bool ok = r[j] != KEY_PAD;
-            m = ok && d < m ? d : m;
-            any |= ok;
-            real += ok ? 1u : 0u;
-        }
+        for (int j = 0; j < PER; ++j) least = r[j] < least ? r[j] : least;
     }
+    const bool any = least != KEY_PAD;
+    const uint32_t high[1] = {(uint32_t)(least >> 32)}, low[1] = {(uint32_t)least};
+    if (tid == 0) sh.cnt = sh.minima = sh.below = 0;
     __syncthreads();
     {
-        const uint32_t wr = wave_scan_add(real);
-        const uint64_t wm = __builtin_amdgcn_ballot_w64(any);
-        if (lane == 63) {
-            atomicAdd(&sh.total, wr);
-            atomicAdd(&sh.minima, (uint32_t)__builtin_popcountll(wm));
-        }
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(any);
+        if (lane == 0) atomicAdd(&sh.minima, (uint32_t)__builtin_popcountll(mask));
     }
     __syncthreads();
-    const uint32_t total = sh.total, minima = sh.minima;
-    uint32_t bound = 0xFFFFFFFFu;
-    if (total > (uint32_t)topk && minima >= (uint32_t)topk) {
-        const uint32_t v[1] = {m};
-        bound = block_kth<1>(sh.kth, v, any ? 1u : 0u, (uint32_t)topk, false, tid, lane, wave);
+    const bool bounded = n > (u64)topk && sh.minima >= (uint32_t)topk;
+    u64 limit = KEY_PAD - 1;           // the largest key that is collected
+    if (bounded) {
+        const u64 top = ((u64)block_kth<1>(sh.kth, high, any ? 1u : 0u, (uint32_t)topk, false, tid, lane, wave) << 32) | 0xFFFFFFFFu;
+        limit = top < limit ? top : limit;
     }
-    // collect: keys at or below the bound
     auto collect = [&]() {
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const bool keep = r[j] != KEY_PAD && (uint32_t)(r[j] >> 32) <= bound;
+            const bool keep = r[j] <= limit;
             const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
             if (mask == 0) continue;                       // wavefront-uniform
             uint32_t slot = 0;
@@ -100,16 +90,30 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
             if (keep && slot < (uint32_t)SEL_LIST) list[slot] = r[j];
         }
     };
-    if (once) {
-        collect();
-    } else {
-        for (u64 base = 0; base < n; base += (u64)PER * T) {
-            load(base);
+    uint32_t cnt;
+    for (bool exact = false;; exact = true) {
+        if (once) {
             collect();
+        } else {
+            for (u64 base = 0; base < n; base += (u64)PER * T) {
+                load(base);
+                collect();
+            }
         }
+        __syncthreads();
+        cnt = sh.cnt;
+        if (cnt <= (uint32_t)SEL_LIST || exact || !bounded) break;     // block-uniform
+        // Masses of equal distances, or a histogram bin wide enough to hold hundreds of keys: the topk-th smallest of the
+        // minima as whole keys, the id deciding among equal distances, bounds as well and lets through about as few as
+        // distinct distances would.  icq_refine of one query, 16 different distances among 20000 / 120000 candidates,
+        // topk = 100: 30 / 71 us, where the digit passes below, taken at once, made it 70 / 316.
+        const uint32_t kth = block_kth<1>(sh.kth, high, any ? 1u : 0u, (uint32_t)topk, true, tid, lane, wave);
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(any && high[0] < kth);
+        if (lane == 0) atomicAdd(&sh.below, (uint32_t)__builtin_popcountll(mask));
+        if (tid == 0) sh.cnt = 0;
+        __syncthreads();
+        limit = ((u64)kth << 32) | block_kth<1>(sh.kth, low, any && high[0] == kth ? 1u : 0u, (uint32_t)topk - sh.below, true, tid, lane, wave);
     }
-    __syncthreads();
-    uint32_t cnt = sh.cnt;
     if (cnt > (uint32_t)SEL_RANK && cnt <= (uint32_t)SEL_LIST && cnt > (uint32_t)topk) {
         // a fat histogram bin: cut the list exactly at the topk-th smallest distance (ties stay)
         constexpr int LPT = SEL_LIST / T;
@@ -132,11 +136,10 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
         cnt = sh.cnt;
     }
     if (cnt > (uint32_t)SEL_LIST) {
-        // Masses of equal distances, or too few threads with a key: exact radix select over whole keys (the
-        // id decides among equal distances), 8 bits at a time, re-reading the keys for every digit.
-        const uint32_t want = total < (uint32_t)topk ? total : (uint32_t)topk;
+        // Few threads hold most of the smallest keys (or any at all), or a key is there many times: exact radix select
+        // over whole keys, 8 bits at a time, re-reading the keys for every digit.  More than topk keys are there.
         u64 prefix = 0;
-        uint32_t kr = want;
+        uint32_t kr = (uint32_t)topk;
         for (int shift = 56; shift >= 0; shift -= 8) {
             __syncthreads();
             if (tid < 256) sh.kth.hist[tid] = 0;
@@ -168,7 +171,7 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
             prefix = (prefix << 8) | (uint32_t)__builtin_amdgcn_readlane((int)my_bin, L);
             kr -= (uint32_t)__builtin_amdgcn_readlane((int)my_below, L);
         }
-        // the keys below the cut, then copies of it (a caller's list may name an item twice) up to `want`
+        // the keys below the cut, then copies of it (a caller's list may name an item twice) up to topk
         __syncthreads();
         if (tid == 0) sh.cnt = 0;
         __syncthreads();
@@ -177,9 +180,9 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
             if (k < prefix) list[atomicAdd(&sh.cnt, 1u)] = k;
         }
         __syncthreads();
-        for (uint32_t i = sh.cnt + (uint32_t)tid; i < want; i += T) list[i] = prefix;
+        for (uint32_t i = sh.cnt + (uint32_t)tid; i < (uint32_t)topk; i += T) list[i] = prefix;
         __syncthreads();
-        cnt = want;
+        cnt = (uint32_t)topk;
     }
     const int kept = (int)cnt < topk ? (int)cnt : topk;
     if (cnt <= (uint32_t)SEL_RANK) {

@@ -265,6 +265,7 @@ def test_refine_matches_oracle(gpu, name, N, Q, over, rule, topk):
     (3, 20_000, 512, "few"), (2, 140_000, 64, "few"),      # masses of equal distances: the ids decide
     (600, 700, 256, "real"), (5, 1000, 257, "few"),        # the two block sizes at their longest result
     (4, 300, 1, "real"), (40, 257, 300, "real"),           # shortest result; fewer keys than the result holds
+    (530, 5_000, 30, "few"), (2, 20_000, 150, "few threads"),      # 512 threads; 100 of 1024 threads hold the 1954 smallest
 ])
 def test_refine_lists_are_the_exact_smallest_keys(gpu, Q, n, topk, values):
     """The list of every query = the first topk of its candidates ordered by (D, id), D the fp32 sum in codebook
@@ -276,8 +277,13 @@ def test_refine_lists_are_the_exact_smallest_keys(gpu, Q, n, topk, values):
                codes=rng.integers(0, m, (K, N), dtype=np.uint8), queries=np.zeros((Q, d), np.float32))
     g = Gpu(gpu, cfg)
     lut = rng.random((Q, K, 256), dtype=np.float32) if values == "real" else \
-        rng.integers(0, 2, (Q, K, 256)).astype(np.float32)
+        rng.integers(0, 2 if values == "few" else 50, (Q, K, 256)).astype(np.float32)
     ids = np.stack([rng.permutation(N)[:n] for _ in range(Q)]).astype(np.int32)
+    if values == "few threads":
+        for q in range(Q):
+            D = sum(lut[q, k, cfg["codes"][k, ids[q]]] for k in range(K))
+            at = np.argsort(np.arange(n) % 1024 >= 100, kind="stable")
+            ids[q, at] = ids[q, np.lexsort((ids[q], D))]
     cnt = np.array([n if q % 4 == 0 else n // (q % 4 + 1) * (q % 7 != 3) for q in range(Q)], np.int32)
     out_ids, out_dist = g.refine(_dev(torch, lut), _dev(torch, ids), None, _dev(torch, cnt), topk)
     for q in range(Q):
