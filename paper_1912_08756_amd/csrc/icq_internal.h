@@ -176,20 +176,16 @@ int icq_launch_group_keys(const icq_index *ix, const float *lut, int Q, const fl
 bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share);      // (calls that are not grouped by tuple)
 int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,
                      uint32_t *cand_count, int64_t cap, hipStream_t s);
-// Where the per-candidate keys live inside the key area of the workspace.
-static inline unsigned long long *icq_cand_keys(unsigned long long *keys, int Q, int splits, int topk) {
-    return keys + (splits > 1 ? (size_t)Q * splits * topk : 0);
-}
 // Grouped stage 1 (icq_group.hip); as_positions: list grouped positions instead of ids; cand_part may be nullptr.
 bool icq_group_usable(const icq_index *ix, int Q);
 int icq_group_fused_parts(const icq_index *ix, int Q);
 // The topk smallest keys of every query (icq_select.hip; topk <= 512).  count != nullptr: count[q] <= cap keys at
-// keys + q * cap, selected in up to `splits` parts (part_lists [Q][splits][topk], ticket [Q] zero, left zero);
+// keys + q * cap, selected in up to `splits` parts (ticket [Q] zero, left zero; not read if splits == 1) and used up;
 // count == nullptr: cap keys at keys + q * cap, KEY_PAD where there is none, splits = 1.
 int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk);
 // compact: the result's keys also replace the query's keys (and count[q] their number).
 int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
-                      unsigned long long *part_lists, uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
+                      uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
 int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
                           uint32_t *cand_ids, float *cand_part, bool as_positions, uint32_t *cand_count, int64_t cap,
                           hipStream_t s);

@@ -549,14 +549,13 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
     const size_t tab = sizeof(float) * (size_t)(cand_part ? ix->Ks : ix->K) * ICQ_LUT_W;
     if (icq_selects(ix, topk)) {
         // distances for every candidate (flat), then the per-query select over the keys
-        u64 *cand_keys = icq_cand_keys(keys, Q, splits, topk);   // [Q][cap], behind the slice lists
         int64_t len = cap < ix->N ? cap : ix->N;
         const int bpq = len > 0 ? (int)((len + RD_BLOCK - 1) / RD_BLOCK) : 1;
         const unsigned dgrid = (unsigned)Q * (unsigned)bpq;
         if (list_kind != ICQ_LIST_KEYS) {
 #define ICQ_RD_LAUNCH(W)                                                                          \
     refine_dist_kernel<W><<<dgrid, RF_THREADS, 0, s>>>(items, ix->K, ix->Kf, lut, cand_ids,       \
-                                                       cand_part, cand_count, cap, bpq, cand_keys, ticket)
+                                                       cand_part, cand_count, cap, bpq, keys, ticket)
         switch (ix->item_stride) {
             case 4: ICQ_RD_LAUNCH(1); break;
             case 8: ICQ_RD_LAUNCH(2); break;
@@ -565,7 +564,7 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
 #undef ICQ_RD_LAUNCH
         if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
         }
-        return icq_launch_select(cand_keys, const_cast<uint32_t *>(cand_count), cap, Q, topk, splits, false, keys, ticket, out_ids, out_dist, s);
+        return icq_launch_select(keys, const_cast<uint32_t *>(cand_count), cap, Q, topk, splits, false, ticket, out_ids, out_dist, s);
     }
     const int bufn = bufn_for(topk);
     const size_t lds = sizeof(u64) * bufn + tab;
@@ -576,7 +575,7 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
     if (splits == 1) return ICQ_OK;
     // join the slices' lists, KEY_PAD where one is short (splits * topk <= 4096)
     if (topk <= 512)
-        return icq_launch_select(keys, nullptr, (int64_t)splits * topk, Q, topk, 1, false, nullptr, nullptr, out_ids, out_dist, s);
+        return icq_launch_select(keys, nullptr, (int64_t)splits * topk, Q, topk, 1, false, nullptr, out_ids, out_dist, s);
     int len = 2;
     while (len < splits * topk) len <<= 1;
     merge_kernel<<<Q, RF_THREADS, sizeof(u64) * len, s>>>(keys, splits, topk, len, out_ids, out_dist);
@@ -626,13 +625,12 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     const bool g2 = icq_g2_usable(ix);
     const uint8_t *items = g2 ? ix->items_grouped : ix->items;
     const uint32_t *perm = g2 ? ix->perm : nullptr;
-    u64 *cand_keys = icq_cand_keys(keys, Q, splits, topk);     // [Q][cap], behind the slice lists
     const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
     // few chunks: one unfiltered launch over all of them (a bound would save less than its second launch costs)
     const uint32_t seed_every = chunks < 2 * RM_SEED_EVERY ? 1u : (uint32_t)RM_SEED_EVERY;
     const uint32_t nseed = (chunks + seed_every - 1) / seed_every, nmain = chunks - nseed;
     auto select = [&](bool more) -> int {
-        return icq_launch_select(cand_keys, key_count, cap, Q, topk, splits, more, keys, ticket, out_ids, out_dist, s);
+        return icq_launch_select(keys, key_count, cap, Q, topk, splits, more, ticket, out_ids, out_dist, s);
     };
     // Chunks per block: few, so that the blocks in flight (two windows' worth when the queries fill the
     // chip) keep to a few chunks per XCD; more when there are so few queries that the table load would weigh.
@@ -664,11 +662,11 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         if (thr)                                                                                             \
             refine_mask_kernel<W, FILTER, RM_QPB, true><<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(           \
                 items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, window, xs_shift, Q, out_dist, topk,     \
-                cand_keys, key_count, cap, cand_count, thr, ix->Kf);                                         \
+                keys, key_count, cap, cand_count, thr, ix->Kf);                                         \
         else                                                                                                 \
             refine_mask_kernel<W, FILTER, RM_QPB, false><<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(          \
                 items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, window, xs_shift, Q, out_dist, topk,     \
-                cand_keys, key_count, cap, cand_count, nullptr, ix->Kf);                                     \
+                keys, key_count, cap, cand_count, nullptr, ix->Kf);                                     \
     } while (0)
     switch (ix->item_stride) {
         case 4: ICQ_RM_LAUNCH(1, false, nseed); break;

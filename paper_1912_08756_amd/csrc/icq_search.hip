@@ -35,12 +35,12 @@ icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool
         off = icq_align_up(off + sizeof(uint32_t) * (size_t)Q * (size_t)cap, ICQ_ALIGN);
     }
     L.keys_off = off;
-    // slice lists [Q][splits][topk] (when sliced), then one 64-bit key per candidate [Q][cap]
+    // the generic kernel's slice lists [Q][splits][topk], or one 64-bit key per candidate [Q][cap]
     if (on_chip) {
         const int parts = icq_group_fused_parts(ix, Q);
         if (parts > 1) off = icq_align_up(off + sizeof(unsigned long long) * (size_t)Q * parts * topk, ICQ_ALIGN);
     } else {
-        if (L.splits > 1)
+        if (L.splits > 1 && !icq_selects(ix, topk))
             off = icq_align_up(off + sizeof(unsigned long long) * (size_t)Q * L.splits * topk, 8);
         if (ix->item_stride <= 16)
             off = icq_align_up(off + sizeof(unsigned long long) * (size_t)Q * (size_t)cap, ICQ_ALIGN);
@@ -137,10 +137,8 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
             continue;
         }
         int list_kind = ICQ_LIST_IDS;
-        // keys of the survivors behind the slice lists, or (on-chip lists) the parts' lists
-        unsigned long long *cand_keys = icq_group_fused(ix, nq, topk) ? keys
-                                        : (ix->item_stride <= 16 && topk <= 512) ? icq_cand_keys(keys, nq, L.splits, topk)
-                                                                                 : nullptr;
+        // keys of the survivors, or (on-chip lists) the parts' lists
+        unsigned long long *cand_keys = icq_group_fused(ix, nq, topk) || icq_selects(ix, topk) ? keys : nullptr;
         rc = icq_launch_scan(ix, lut, nq, thresholds + q0, ids, nullptr, cand_keys, &list_kind, cnt,
                              cap, topk, out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, share, s);
         if (rc != ICQ_OK) return rc;

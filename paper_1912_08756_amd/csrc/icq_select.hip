@@ -16,7 +16,7 @@
 // 20 + 198 us, now 16.
 //
 // A query with very many keys is cut into up to `splits` parts, as many as its count asks for; each
-// part leaves its ascending list and the last block to finish selects again from those.
+// part leaves its ascending list in place of its keys and the last block to finish selects again from those.
 #include "icq_internal.h"
 #include "icq_sort.h"
 
@@ -25,8 +25,7 @@
 namespace {
 
 constexpr int SEL_LIST = 1024;     // keys the LDS list holds; topk <= 512
-constexpr int SEL_PART = 131072;   // keys a block takes alone: joining parts costs two device-wide fences, several
-                                   // passes' worth (Q = 128, 15000 keys each in one / two parts: 20 / 218 us)
+constexpr int SEL_PART = 16384;    // keys of a part, once a query's keys are cut into parts (SEL_ALONE)
 constexpr int SEL_RANK = 256;      // up to so many keys are ranked by counting, more are sorted
 
 template <int T>
@@ -37,9 +36,11 @@ struct SelShared {
 };
 
 // The topk smallest keys of in[0..n) (KEY_PAD entries are skipped) -> list[0..kept) ascending;
-// returns kept = min(topk, number of keys).  PER: keys per thread held in registers.  Every thread of the block calls.
-template <int T, int PER>
-__device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, int topk) {
+// returns kept = min(topk, number of keys).  PER: keys per thread held in registers.  LISTS: n is a multiple of topk, and
+// each run of topk keys starts `stride` after the one before.  Every thread of the block calls.
+template <int T, int PER, bool LISTS>
+__device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u64 stride, int topk) {
+    auto key = [&](u64 i) { return LISTS ? in[(uint32_t)i / (uint32_t)topk * stride + (uint32_t)i % (uint32_t)topk] : in[i]; };
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = tid >> 6;
@@ -49,7 +50,7 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const u64 i = base + (u64)j * T + tid;
-            r[j] = in[i < n ? i : n - 1];
+            r[j] = key(i < n ? i : n - 1);
         }
 #pragma unroll
         for (int j = 0; j < PER; ++j)
@@ -145,7 +146,7 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
             if (tid < 256) sh.kth.hist[tid] = 0;
             __syncthreads();
             for (u64 i = tid; i < n; i += T) {
-                const u64 k = in[i];
+                const u64 k = key(i);
                 if (k != KEY_PAD && (shift == 56 || (k >> (shift + 8)) == prefix))
                     atomicAdd(&sh.kth.hist[(uint32_t)(k >> shift) & 255u], 1u);
             }
@@ -176,7 +177,7 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
         if (tid == 0) sh.cnt = 0;
         __syncthreads();
         for (u64 i = tid; i < n; i += T) {
-            const u64 k = in[i];
+            const u64 k = key(i);
             if (k < prefix) list[atomicAdd(&sh.cnt, 1u)] = k;
         }
         __syncthreads();
@@ -226,12 +227,12 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, i
 }
 
 // Grid: Q * splits blocks.  count != nullptr: count[q] keys (at most cap) at keys_in + q * cap, worked off
-// by one of the query's blocks per SEL_PART keys; count == nullptr: cap keys,
+// by one of the query's blocks, or if they are more than `alone` by one per SEL_PART keys; count == nullptr: cap keys,
 // splits == 1.  compact: the result's keys also replace the query's keys, and their number count[q] (more keys
 // are going to be appended; what is left out here cannot reach the result).
 template <int T, int PER>
 __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count, int64_t cap, int topk, int splits,
-                                                   int compact, u64 *part_lists, uint32_t *ticket,
+                                                   uint32_t alone, int compact, uint32_t *ticket,
                                                    uint32_t *__restrict__ out_ids, float *__restrict__ out_dist) {
     __shared__ SelShared<T> sh;
     __shared__ __attribute__((aligned(16))) u64 list[SEL_LIST];
@@ -243,47 +244,62 @@ __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count
         n = count[q];
         if (n > (u64)cap) n = (u64)cap;
         const u64 want = (n + (u64)SEL_PART - 1) / (u64)SEL_PART;
-        used = want > (u64)splits ? splits : want > 1 ? (int)want : 1;
+        used = n <= (u64)alone ? 1 : want > (u64)splits ? splits : (int)want;
     }
     if (sp >= used) return;                                // block-uniform
-    const u64 lo = n * (u64)sp / (u64)used, hi = n * (u64)(sp + 1) / (u64)used;
-    int kept = block_select<T, PER>(sh, list, keys_in + (int64_t)q * cap + lo, hi - lo, topk);
+    u64 *mine = keys_in + (int64_t)q * cap;
+    const u64 per = used == 1 ? n : (n + (u64)used - 1) / (u64)used, lo = (u64)sp * per;
+    int kept = block_select<T, PER, false>(sh, list, mine + lo, n - lo < per ? n - lo : per, 0, topk);
     if (used > 1) {
-        u64 *mine = part_lists + ((int64_t)q * splits + sp) * topk;
-        for (int i = tid; i < topk; i += T) mine[i] = i < kept ? list[i] : KEY_PAD;
-        __threadfence();                                   // the list is visible before the ticket is
+        for (int i = tid; i < topk; i += T) mine[lo + i] = i < kept ? list[i] : KEY_PAD;     // parts are longer than topk
+        // One thread makes the block's list visible to the device and the other blocks' visible to the block: a fence
+        // writes back and invalidates the chiplet's L2, and one per wavefront was sixteen of each.  Every wavefront
+        // waits for its own stores first: the barrier alone need not order them before another wavefront's fence.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (tid == 0) sh.last = atomicAdd(&ticket[q], 1u) == (uint32_t)(used - 1) ? 1u : 0u;
+        if (tid == 0) {
+            __threadfence();
+            sh.last = atomicAdd(&ticket[q], 1u) == (uint32_t)(used - 1) ? 1u : 0u;
+            __threadfence();
+        }
         __syncthreads();
         if (sh.last == 0) return;                          // block-uniform
-        __threadfence();
         if (tid == 0) ticket[q] = 0;                       // for the call's next selection
-        __syncthreads();
-        kept = block_select<T, PER>(sh, list, part_lists + (int64_t)q * splits * topk, (u64)used * topk, topk);
+        kept = block_select<T, PER, true>(sh, list, mine, (u64)used * topk, per, topk);
     }
     for (int i = tid; i < topk; i += T) {
         const bool have = i < kept;
         const u64 k = list[have ? i : 0];
         out_ids[(int64_t)q * topk + i] = have ? (uint32_t)k : ICQ_PAD_ID;
         out_dist[(int64_t)q * topk + i] = have ? icq_unorder_bits((uint32_t)(k >> 32)) : INFINITY;
-        if (compact && have) keys_in[(int64_t)q * cap + i] = k;        // kept <= count[q]: inside the query's keys
+        if (compact && have) mine[i] = k;                      // kept <= count[q]: inside the query's keys
     }
     if (compact && tid == 0) count[q] = (uint32_t)kept;
 }
 
 template <int T, int PER>
-int launch_select(u64 *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact, u64 *part_lists,
+int launch_select(u64 *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, uint32_t alone, bool compact,
                   uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
-    select_kernel<T, PER><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, compact ? 1 : 0, part_lists, ticket,
-                                                                       out_ids, out_dist);
+    select_kernel<T, PER><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, alone, compact ? 1 : 0,
+                                                                       ticket, out_ids, out_dist);
     return icq_check_launch();
 }
 
 }  // namespace
 
+// Keys a block takes alone.  Joining parts takes 10 us (25 where lists of more than 256 keys are sorted), a block a
+// microsecond per 4000 keys: icq_refine of one query, topk = 100, 40000 / 120000 / 400000 candidates in one part
+// 22 / 43 / - us, in parts of SEL_PART 22 / 23 / 27 us; topk = 400: 34 / 53 / - and 43 / 44 / 55 us.  (128 queries of
+// 20000 / 80000, one part 46 / 147, several 58 / 158 us: they fill the chip as they are.)  The line by queries lies where
+// the ticket each of them needs no longer fits the 256 bytes that the counters take anyway.
+static uint32_t select_alone(int Q, int topk) {
+    if (3 * sizeof(uint32_t) * (size_t)Q > ICQ_ALIGN) return 131072;
+    return topk <= 256 ? 40960 : 98304;
+}
+
 // Parts a query's keys may be cut into: more than one only where the queries leave the chip mostly idle.
 int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
-    if (Q <= 0) return 1;
+    if (Q <= 0 || cap <= (int64_t)select_alone(Q, topk)) return 1;
     int64_t s = ix->num_cu / Q;
     const int64_t by_len = cap / SEL_PART + 1;
     const int64_t by_merge = 4096 / topk;       // the parts' lists fit one block's registers again
@@ -294,13 +310,14 @@ int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
 }
 
 int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
-                      unsigned long long *part_lists, uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
+                      uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
     // 1024 threads while every query's block finds a CU to itself or to share with one other, or where the list is
     // longer than the minima of 512 threads bound well; else 512 threads, of which a CU runs four blocks (1000
     // queries of 10^4 keys: 34 us against 45).  Eight keys per thread in registers: sixteen gain nothing on lists
     // that fit and hold twice the registers on those that do not.
+    const uint32_t alone = select_alone(Q, topk);
     const bool wide = topk > 256 || (count && (int64_t)Q * splits <= 512);
-    if (wide) return launch_select<1024, 8>(keys, count, cap, Q, topk, splits, compact, part_lists, ticket, out_ids, out_dist, s);
-    return launch_select<512, 8>(keys, count, cap, Q, topk, splits, compact, part_lists, ticket, out_ids, out_dist, s);
+    if (wide) return launch_select<1024, 8>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s);
+    return launch_select<512, 8>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s);
 }

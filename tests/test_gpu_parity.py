@@ -262,6 +262,8 @@ def test_refine_matches_oracle(gpu, name, N, Q, over, rule, topk):
 @pytest.mark.parametrize("Q,n,topk,values", [
     (1, 8192, 100, "real"), (1, 8193, 100, "real"),        # one load of a block's registers, and one key more
     (2, 131_073, 20, "real"), (1, 300_001, 512, "real"),   # several parts per query, joined
+    (3, 40_961, 256, "real"), (21, 40_961, 10, "few"), (2, 98_305, 257, "real"), (22, 131_073, 9, "real"),     # one key more than
+    (2, 40_960, 30, "real"), (2, 98_304, 400, "few"),      # a block takes alone, and just as many
     (3, 20_000, 512, "few"), (2, 140_000, 64, "few"),      # masses of equal distances: the ids decide
     (600, 700, 256, "real"), (5, 1000, 257, "few"),        # the two block sizes at their longest result
     (4, 300, 1, "real"), (40, 257, 300, "real"),           # shortest result; fewer keys than the result holds
@@ -295,6 +297,33 @@ def test_refine_lists_are_the_exact_smallest_keys(gpu, Q, n, topk, values):
         kept = order.size
         assert np.array_equal(out_ids[q, :kept], mine[order].astype(np.uint32)) and np.array_equal(out_dist[q, :kept], D[order])
         assert (out_ids[q, kept:] == 0xFFFFFFFF).all() and np.isinf(out_dist[q, kept:]).all()
+
+
+@pytest.mark.parametrize("topk,m", [(100, 256), (400, 256), (20, 3)])
+def test_search_whose_first_selection_is_joined_from_parts(gpu, topk, m):
+    """More than 98304 keys per query before the first selection of the hit-bit form, which leaves its result in place of the
+    keys for the rest of the search: lists exact by (D, id), D the fp32 sums of the library's own tables."""
+    torch, b = gpu
+    Q, K, Kf, d, N = 3, 4, 3, 8, 130 * 2 * 32768 + 777
+    g = torch.Generator(device="cuda"); g.manual_seed(topk)
+    cb = torch.randn((K, m, d), device="cuda", generator=g)
+    codes = torch.randint(0, m, (K, N), dtype=torch.uint8, device="cuda", generator=g)
+    queries = torch.randn((Q, d), device="cuda", generator=g)
+    index = b.icq_index_create(cb, codes, Kf)
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    ids, dist = torch.full((Q, topk), -7, dtype=torch.int32, device="cuda"), torch.zeros((Q, topk), device="cuda")
+    count = torch.full((Q,), -7, dtype=torch.int32, device="cuda")
+    ws = torch.empty(b.icq_workspace_bytes(index, Q, N, topk), dtype=torch.uint8, device="cuda")
+    for _ in range(2):
+        b.icq_search(index, queries, torch.full((Q,), np.inf, device="cuda"), N, topk, ids, dist, count, ws)
+        assert (count == N).all()
+        for q in range(Q):
+            D = lut[q, 0][codes[0].long()]
+            for k in range(1, K):
+                D = D + lut[q, k][codes[k].long()]
+            want = torch.sort(D, stable=True)
+            assert torch.equal(ids[q].long(), want.indices[:topk]) and torch.equal(dist[q], want.values[:topk])
 
 
 # ------------------------------------------------------------------ whole path
