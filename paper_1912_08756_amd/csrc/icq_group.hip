@@ -991,7 +991,7 @@ int icq_launch_group_keys(const icq_index *ix, const float *lut, int Q, const fl
     }
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     if (fused && parts > 1)
-        return icq_launch_select(cand_keys, nullptr, (int64_t)parts * topk, Q, topk, 1, false, nullptr, out_ids, out_dist, s);
+        return icq_launch_join(cand_keys, Q, parts, topk, out_ids, out_dist, s);
     return ICQ_OK;
 }
 

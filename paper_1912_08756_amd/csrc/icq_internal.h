@@ -186,6 +186,8 @@ int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk);
 // compact: the result's keys also replace the query's keys (and count[q] their number).
 int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
                       uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
+// The same from `parts` ascending lists of topk distinct keys per query, KEY_PAD where one is short.
+int icq_launch_join(const unsigned long long *lists, int Q, int parts, int topk, uint32_t *out_ids, float *out_dist, hipStream_t s);
 int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const float *thr,
                           uint32_t *cand_ids, float *cand_part, bool as_positions, uint32_t *cand_count, int64_t cap,
                           hipStream_t s);

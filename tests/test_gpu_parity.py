@@ -326,6 +326,35 @@ def test_search_whose_first_selection_is_joined_from_parts(gpu, topk, m):
             assert torch.equal(ids[q].long(), want.indices[:topk]) and torch.equal(dist[q], want.values[:topk])
 
 
+@pytest.mark.parametrize("Q,topk", [(500, 256), (260, 1), (180, 47), (130, 256), (100, 30)])     # 2, 2, 3, 4, 6 lists per query
+def test_grouped_lists_joined_from_several_blocks(gpu, Q, topk):
+    """The same lists, bit for bit, as from the item-by-item form; none, one, few and all items survive; with ties."""
+    torch, b = gpu
+    K, Kf, d, N, m = 6, 2, 8, 40_000, 200
+    g = torch.Generator(device="cuda"); g.manual_seed(Q)
+    cb = torch.randn((K, m, d), device="cuda", generator=g)
+    codes = torch.randint(0, m, (K, N), dtype=torch.uint8, device="cuda", generator=g)
+    codes[:, N // 2:] = codes[:, :N // 2]
+    queries = torch.randn((Q, d), device="cuda", generator=g)
+    index = b.icq_index_create(cb, codes, Kf)
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = torch.sort(lut[:, 0][:, codes[0].long()] + lut[:, 1][:, codes[1].long()], dim=1).values
+    rank = torch.tensor([0, 2, topk // 2 * 2, topk + 40, 4000, N - 1], device="cuda")[torch.arange(Q, device="cuda") % 6]
+    thr = P.gather(1, rank[:, None])[:, 0].contiguous()
+    thr[5::12] = np.inf
+    out = []
+    for mode in (b.ICQ_SCAN_GROUPED, b.ICQ_SCAN_STREAMED):
+        b.icq_index_set_scan_mode(index, mode)
+        ids, dist = torch.full((Q, topk), -7, dtype=torch.int32, device="cuda"), torch.zeros((Q, topk), device="cuda")
+        count = torch.full((Q,), -7, dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.icq_workspace_bytes(index, Q, N, topk), dtype=torch.uint8, device="cuda")
+        b.icq_search(index, queries, thr, N, topk, ids, dist, count, ws)
+        out.append((ids, dist, count))
+    assert all(torch.equal(x, y) for x, y in zip(*out))
+    assert (out[0][2][0::6] == 0).all() and (out[0][0][0::6] == -1).all() and (out[0][2][5::12] == N).all()
+
+
 # ------------------------------------------------------------------ whole path
 def _check_search(g, cfg, T, P, D, thr, topk, cap, min_equal=0.9):
     out_ids, out_dist, surv = g.search(thr, cap, topk)
