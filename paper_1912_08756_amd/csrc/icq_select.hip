@@ -116,23 +116,44 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u
         limit = ((u64)kth << 32) | block_kth<1>(sh.kth, low, any && high[0] == kth ? 1u : 0u, (uint32_t)topk - sh.below, true, tid, lane, wave);
     }
     if (cnt > (uint32_t)SEL_RANK && cnt <= (uint32_t)SEL_LIST && cnt > (uint32_t)topk) {
-        // a fat histogram bin: cut the list exactly at the topk-th smallest distance (ties stay)
+        // a fat histogram bin, or ties: cut the list exactly at the topk-th smallest distance and, where too many keys have
+        // that one for the ranks, at the topk-th smallest key
         constexpr int LPT = SEL_LIST / T;
         u64 e[LPT];
-        uint32_t v[LPT], ok = 0;
+        uint32_t v[LPT], id[LPT], ok = 0;
 #pragma unroll
         for (int u = 0; u < LPT; ++u) {
             const uint32_t i = (uint32_t)u * T + tid;
             e[u] = list[i];
             v[u] = (uint32_t)(e[u] >> 32);
+            id[u] = (uint32_t)e[u];
             if (i < cnt) ok |= 1u << u;
         }
         const uint32_t cut = block_kth<LPT>(sh.kth, v, ok, (uint32_t)topk, true, tid, lane, wave);
+        if (tid == 0) sh.cnt = sh.below = 0;
+        __syncthreads();                                   // the list has been read, the counters are zero
+        uint32_t tie = 0, below = 0, upto = 0;
+#pragma unroll
+        for (int u = 0; u < LPT; ++u) {
+            const bool in = (ok >> u) & 1u;
+            if (in && v[u] == cut) tie |= 1u << u;
+            below += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] < cut));
+            upto += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(in && v[u] <= cut));
+        }
+        if (lane == 0) {
+            atomicAdd(&sh.below, below);
+            atomicAdd(&sh.cnt, upto);
+        }
+        __syncthreads();
+        uint32_t last_id = 0xFFFFFFFFu;
+        if (sh.cnt > (uint32_t)SEL_RANK && topk <= SEL_RANK)       // block-uniform
+            last_id = block_kth<LPT>(sh.kth, id, tie, (uint32_t)topk - sh.below, true, tid, lane, wave);
+        __syncthreads();
         if (tid == 0) sh.cnt = 0;
-        __syncthreads();                                   // the list has been read, the counter is zero
+        __syncthreads();
 #pragma unroll
         for (int u = 0; u < LPT; ++u)
-            if (((ok >> u) & 1u) && v[u] <= cut) list[atomicAdd(&sh.cnt, 1u)] = e[u];
+            if (((ok >> u) & 1u) && (v[u] < cut || (v[u] == cut && id[u] <= last_id))) list[atomicAdd(&sh.cnt, 1u)] = e[u];
         __syncthreads();
         cnt = sh.cnt;
     }
