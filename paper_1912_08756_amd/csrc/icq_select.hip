@@ -352,13 +352,12 @@ int launch_select(u64 *keys, uint32_t *count, int64_t cap, int Q, int topk, int 
 }  // namespace
 
 // Keys a block takes alone.  Joining parts takes 10 us (25 where lists of more than 256 keys are sorted), a block a
-// microsecond per 4000 keys: icq_refine of one query, topk = 100, 40000 / 120000 / 400000 candidates in one part
-// 22 / 43 / - us, in parts of SEL_PART 22 / 23 / 27 us; topk = 400: 34 / 53 / - and 43 / 44 / 55 us.  (128 queries of
-// 20000 / 80000, one part 46 / 147, several 58 / 158 us: they fill the chip as they are.)  The line by queries lies where
-// the ticket each of them needs no longer fits the 256 bytes that the counters take anyway.
+// microsecond per 4000 keys: icq_refine of one query, topk = 100, 40000 / 120000 candidates in one part 22 / 43 us, in
+// parts of SEL_PART 22 / 23 us; topk = 512, 120000 candidates: 58 / 64 us.  (128 queries of 20000 / 80000, one part
+// 46 / 147, several 58 / 158 us: they fill the chip as they are.)  The line by queries lies where the ticket each of them
+// needs no longer fits the 256 bytes that the counters take anyway.
 static uint32_t select_alone(int Q, int topk) {
-    if (3 * sizeof(uint32_t) * (size_t)Q > ICQ_ALIGN) return 131072;
-    return topk <= 256 ? 40960 : 98304;
+    return topk <= 256 && 3 * sizeof(uint32_t) * (size_t)Q <= ICQ_ALIGN ? 40960 : 131072;
 }
 
 // Parts a query's keys may be cut into: more than one only where the queries leave the chip mostly idle.

@@ -262,8 +262,8 @@ def test_refine_matches_oracle(gpu, name, N, Q, over, rule, topk):
 @pytest.mark.parametrize("Q,n,topk,values", [
     (1, 8192, 100, "real"), (1, 8193, 100, "real"),        # one load of a block's registers, and one key more
     (2, 131_073, 20, "real"), (1, 300_001, 512, "real"),   # several parts per query, joined
-    (3, 40_961, 256, "real"), (21, 40_961, 10, "few"), (2, 98_305, 257, "real"), (22, 131_073, 9, "real"),     # one key more than
-    (2, 40_960, 30, "real"), (2, 98_304, 400, "few"),      # a block takes alone, and just as many
+    (3, 40_961, 256, "real"), (21, 40_961, 10, "few"), (2, 131_073, 257, "real"), (22, 131_073, 9, "real"),    # one key more than
+    (2, 40_960, 30, "real"), (2, 131_072, 400, "few"),     # a block takes alone, and just as many
     (3, 20_000, 512, "few"), (2, 140_000, 64, "few"),      # masses of equal distances: the ids decide
     (600, 700, 256, "real"), (5, 1000, 257, "few"),        # the two block sizes at their longest result
     (4, 300, 1, "real"), (40, 257, 300, "real"),           # shortest result; fewer keys than the result holds
@@ -301,7 +301,7 @@ def test_refine_lists_are_the_exact_smallest_keys(gpu, Q, n, topk, values):
 
 @pytest.mark.parametrize("topk,m", [(100, 256), (400, 256), (20, 3)])
 def test_search_whose_first_selection_is_joined_from_parts(gpu, topk, m):
-    """More than 98304 keys per query before the first selection of the hit-bit form, which leaves its result in place of the
+    """More than 131072 keys per query before the first selection of the hit-bit form, which leaves its result in place of the
     keys for the rest of the search: lists exact by (D, id), D the fp32 sums of the library's own tables."""
     torch, b = gpu
     Q, K, Kf, d, N = 3, 4, 3, 8, 130 * 2 * 32768 + 777
