@@ -36,9 +36,9 @@ struct SelShared {
 };
 
 // The topk smallest keys of in[0..n) (KEY_PAD entries are skipped) -> list[0..kept) ascending;
-// returns kept = min(topk, number of keys).  PER: keys per thread held in registers.  LISTS: n is a multiple of topk, and
+// returns kept = min(topk, number of keys).  PER: keys per thread held in registers; MIN: shares of a thread, a minimum each.  LISTS: n is a multiple of topk, and
 // each run of topk keys starts `stride` after the one before.  Every thread of the block calls.
-template <int T, int PER, bool LISTS>
+template <int T, int PER, int MIN, bool LISTS>
 __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u64 stride, int topk) {
     auto key = [&](u64 i) { return LISTS ? in[(uint32_t)i / (uint32_t)topk * stride + (uint32_t)i % (uint32_t)topk] : in[i]; };
     const int tid = threadIdx.x;
@@ -57,25 +57,36 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u
             if (base + (u64)j * T + tid >= n) r[j] = KEY_PAD;
     };
     const bool once = n <= (u64)PER * T;
-    u64 least = KEY_PAD;               // the smallest key of this thread's share
+    u64 least[MIN];                    // the smallest keys of this thread's shares
+#pragma unroll
+    for (int u = 0; u < MIN; ++u) least[u] = KEY_PAD;
     for (u64 base = 0; base < n; base += (u64)PER * T) {
         load(base);
 #pragma unroll
-        for (int j = 0; j < PER; ++j) least = r[j] < least ? r[j] : least;
+        for (int j = 0; j < PER; ++j) least[j % MIN] = r[j] < least[j % MIN] ? r[j] : least[j % MIN];
     }
-    const bool any = least != KEY_PAD;
-    const uint32_t high[1] = {(uint32_t)(least >> 32)}, low[1] = {(uint32_t)least};
+    uint32_t high[MIN], low[MIN], any = 0;
+#pragma unroll
+    for (int u = 0; u < MIN; ++u) {
+        high[u] = (uint32_t)(least[u] >> 32);
+        low[u] = (uint32_t)least[u];
+        if (least[u] != KEY_PAD) any |= 1u << u;
+    }
     if (tid == 0) sh.cnt = sh.minima = sh.below = 0;
     __syncthreads();
-    {
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(any);
-        if (lane == 0) atomicAdd(&sh.minima, (uint32_t)__builtin_popcountll(mask));
-    }
+    // the lanes' flagged minima, as one count per wavefront
+    auto count = [&](uint32_t flags, uint32_t *to) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int u = 0; u < MIN; ++u) n += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64((flags >> u) & 1u));
+        if (lane == 0) atomicAdd(to, n);
+    };
+    count(any, &sh.minima);
     __syncthreads();
     const bool bounded = n > (u64)topk && sh.minima >= (uint32_t)topk;
     u64 limit = KEY_PAD - 1;           // the largest key that is collected
     if (bounded) {
-        const u64 top = ((u64)block_kth<1>(sh.kth, high, any ? 1u : 0u, (uint32_t)topk, false, tid, lane, wave) << 32) | 0xFFFFFFFFu;
+        const u64 top = ((u64)block_kth<MIN>(sh.kth, high, any, (uint32_t)topk, false, tid, lane, wave) << 32) | 0xFFFFFFFFu;
         limit = top < limit ? top : limit;
     }
     auto collect = [&]() {
@@ -108,12 +119,17 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u
         // minima as whole keys, the id deciding among equal distances, bounds as well and lets through about as few as
         // distinct distances would.  icq_refine of one query, 16 different distances among 20000 / 120000 candidates,
         // topk = 100: 30 / 71 us, where the digit passes below, taken at once, made it 70 / 316.
-        const uint32_t kth = block_kth<1>(sh.kth, high, any ? 1u : 0u, (uint32_t)topk, true, tid, lane, wave);
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(any && high[0] < kth);
-        if (lane == 0) atomicAdd(&sh.below, (uint32_t)__builtin_popcountll(mask));
+        const uint32_t kth = block_kth<MIN>(sh.kth, high, any, (uint32_t)topk, true, tid, lane, wave);
+        uint32_t under = 0, at = 0;
+#pragma unroll
+        for (int u = 0; u < MIN; ++u) {
+            if (((any >> u) & 1u) && high[u] < kth) under |= 1u << u;
+            if (((any >> u) & 1u) && high[u] == kth) at |= 1u << u;
+        }
+        count(under, &sh.below);
         if (tid == 0) sh.cnt = 0;
         __syncthreads();
-        limit = ((u64)kth << 32) | block_kth<1>(sh.kth, low, any && high[0] == kth ? 1u : 0u, (uint32_t)topk - sh.below, true, tid, lane, wave);
+        limit = ((u64)kth << 32) | block_kth<MIN>(sh.kth, low, at, (uint32_t)topk - sh.below, true, tid, lane, wave);
     }
     if (cnt > (uint32_t)SEL_RANK && cnt <= (uint32_t)SEL_LIST && cnt > (uint32_t)topk) {
         // a fat histogram bin, or ties: cut the list exactly at the topk-th smallest distance and, where too many keys have
@@ -251,7 +267,7 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u
 // by one of the query's blocks, or if they are more than `alone` by one per SEL_PART keys; count == nullptr: cap keys,
 // splits == 1.  compact: the result's keys also replace the query's keys, and their number count[q] (more keys
 // are going to be appended; what is left out here cannot reach the result).
-template <int T, int PER>
+template <int T, int PER, int MIN>
 __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count, int64_t cap, int topk, int splits,
                                                    uint32_t alone, int compact, uint32_t *ticket,
                                                    uint32_t *__restrict__ out_ids, float *__restrict__ out_dist) {
@@ -270,7 +286,7 @@ __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count
     if (sp >= used) return;                                // block-uniform
     u64 *mine = keys_in + (int64_t)q * cap;
     const u64 per = used == 1 ? n : (n + (u64)used - 1) / (u64)used, lo = (u64)sp * per;
-    int kept = block_select<T, PER, false>(sh, list, mine + lo, n - lo < per ? n - lo : per, 0, topk);
+    int kept = block_select<T, PER, MIN, false>(sh, list, mine + lo, n - lo < per ? n - lo : per, 0, topk);
     if (used > 1) {
         for (int i = tid; i < topk; i += T) mine[lo + i] = i < kept ? list[i] : KEY_PAD;     // parts are longer than topk
         // One thread makes the block's list visible to the device and the other blocks' visible to the block: a fence
@@ -286,7 +302,7 @@ __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count
         __syncthreads();
         if (sh.last == 0) return;                          // block-uniform
         if (tid == 0) ticket[q] = 0;                       // for the call's next selection
-        kept = block_select<T, PER, true>(sh, list, mine, (u64)used * topk, per, topk);
+        kept = block_select<T, PER, MIN, true>(sh, list, mine, (u64)used * topk, per, topk);
     }
     for (int i = tid; i < topk; i += T) {
         const bool have = i < kept;
@@ -341,10 +357,10 @@ __global__ __launch_bounds__(JOIN_THREADS) void join_kernel(const u64 *__restric
     }
 }
 
-template <int T, int PER>
+template <int T, int PER, int MIN>
 int launch_select(u64 *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, uint32_t alone, bool compact,
                   uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
-    select_kernel<T, PER><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, alone, compact ? 1 : 0,
+    select_kernel<T, PER, MIN><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, alone, compact ? 1 : 0,
                                                                        ticket, out_ids, out_dist);
     return icq_check_launch();
 }
@@ -375,14 +391,19 @@ int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
 int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
                       uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
-    // 1024 threads while every query's block finds a CU to itself or to share with one other, or where the list is
-    // longer than the minima of 512 threads bound well; else 512 threads, of which a CU runs four blocks (1000
-    // queries of 10^4 keys: 34 us against 45).  Eight keys per thread in registers: sixteen gain nothing on lists
-    // that fit and hold twice the registers on those that do not.
+    // 1024 threads while every query's block finds a CU to itself or to share with one other; else 512 threads, of which
+    // a CU runs four blocks (1000 queries of 10^4 keys: 34 us against 45), with two minima each where one each would
+    // bound the list badly (icq_refine, 2000 queries of 3000 candidates, topk = 512: 1024 threads 167 us, 512 with one
+    // minimum 143, with two 91), and 256 threads for lists whose keys all fit (2000 queries of 200, topk = 100: 27 / 21 us,
+    // of 1000, topk = 400: 67 / 44 us).  Eight keys per thread in registers: sixteen gain nothing on lists that fit and
+    // hold twice the registers on those that do not.
     const uint32_t alone = select_alone(Q, topk);
-    const bool wide = topk > 256 || (count && (int64_t)Q * splits <= 512);
-    if (wide) return launch_select<1024, 8>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s);
-    return launch_select<512, 8>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s);
+#define ICQ_SEL(T, PER, MIN) launch_select<T, PER, MIN>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s)
+    if (count && (int64_t)Q * splits <= 512) return ICQ_SEL(1024, 8, 1);
+    if (cap <= SEL_LIST) return ICQ_SEL(256, 4, 2);
+    if (topk > 256) return ICQ_SEL(512, 8, 2);
+    return ICQ_SEL(512, 8, 1);
+#undef ICQ_SEL
 }
 
 int icq_launch_join(const unsigned long long *lists, int Q, int parts, int topk, uint32_t *out_ids, float *out_dist, hipStream_t s) {

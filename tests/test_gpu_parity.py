@@ -265,7 +265,8 @@ def test_refine_matches_oracle(gpu, name, N, Q, over, rule, topk):
     (3, 40_961, 256, "real"), (21, 40_961, 10, "few"), (2, 131_073, 257, "real"), (22, 131_073, 9, "real"),    # one key more than
     (2, 40_960, 30, "real"), (2, 131_072, 400, "few"),     # a block takes alone, and just as many
     (3, 20_000, 512, "few"), (2, 140_000, 64, "few"),      # masses of equal distances: the ids decide
-    (600, 700, 256, "real"), (5, 1000, 257, "few"),        # the two block sizes at their longest result
+    (600, 700, 256, "real"), (5, 1000, 257, "few"),        # block sizes, at their longest results
+    (600, 1024, 512, "real"), (513, 1025, 300, "few"), (600, 4097, 512, "real"), (530, 1000, 100, "few"),
     (4, 300, 1, "real"), (40, 257, 300, "real"),           # shortest result; fewer keys than the result holds
     (530, 5_000, 30, "few"), (2, 20_000, 150, "few threads"),      # 512 threads; 100 of 1024 threads hold the 1954 smallest
 ])
