@@ -24,8 +24,8 @@
 //     residual and codewords and take the argmin of those.  The result is the fp32 argmin, as before.
 // Where more than eight codewords of an item are within the bound, the block repeats the level with both
 // operands split in two halves (three products: E's operand part is smaller by 2^-10, its accumulation part
-// three times as large); more than eight after that -- equal codewords -- and the item's scores are all
-// formed in fp32.
+// three times as large).  Where it is more than eight after that (equal codewords), or the bound is no number
+// (infinities, NaN, norms beyond fp32), the block forms all its scores in fp32 on the matrix cores.
 //
 // What bounds it: up to E_REG_D dimensions vector issue -- 800 instructions per wavefront and level (argmin 2.5
 // per score; residual, norms and conversion 5 per element) keep the vector units 64 % busy, the matrix
@@ -63,6 +63,7 @@ struct EncShared {
     uint8_t code[ICQ_MAX_K][EB];
     uint8_t before[EB];                    // the sub-code the level before found
     uint32_t over;                         // some item has more than E_CAND candidates
+    uint32_t wild;                         // some item's bound is no number
 };
 static_assert(sizeof(EncShared) <= 81920, "two blocks per CU");
 
@@ -203,8 +204,11 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     __syncthreads();
     auto largest_norm = [&]() __attribute__((always_inline)) -> float {                   // behind a barrier after nrm2 was written
         const int lane = fresh(tid0) & 63;
-        float v = fmaxf(sh.nrm2[lane], sh.nrm2[lane + 64]);
-        for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+        // as bits, which order as the squares do; an item whose norm is no number would take the others' halves from
+        // them and has no bound anyway
+        const uint32_t a = __float_as_uint(sh.nrm2[lane]), b = __float_as_uint(sh.nrm2[lane + 64]);
+        const uint32_t a1 = a < 0x7f800000u ? a : 0u, b1 = b < 0x7f800000u ? b : 0u;
+        const float v = __uint_as_float(wave_max_u32(a1 > b1 ? a1 : b1));
         return __builtin_amdgcn_sqrtf(v) * 1.0001f;
     };
     float reach = largest_norm();                          // no residual of the block is longer
@@ -240,6 +244,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     __syncthreads();
 
     const int levels = ICM ? K * sweeps : K;
+    bool equal = false;                                    // the second round left too many candidates at some level: no use
     for (int lev = 0; lev < levels; ++lev) {
         const int k = ICM ? lev % K : lev;
         const int kp = k == 0 ? K - 1 : k - 1, kn = k == K - 1 ? 0 : k + 1;        // the codebooks of the levels around it
@@ -341,7 +346,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 
         const int tid = fresh(tid0);
         if (tid < EB) sh.ccount[tid] = 0;
-        if (tid == 0) sh.over = 0;
+        if (tid == 0) sh.over = sh.wild = 0;
         // ---- candidates: codewords whose score is within twice the error bound of the item's best
         auto candidates = [&](const float16v (&acc)[2][2], float u_r, float d_c, int passes) __attribute__((always_inline)) {
             const int lane = fresh(tid0) & 63, half = lane >> 5, l32 = lane & 31;
@@ -377,7 +382,10 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 #pragma unroll
                 for (int i = 0; i < 32; ++i)
                     bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(best[u] - acc[u][i >> 4][i & 15]), 31);
-                if (!(best[u] < INFINITY)) bits = 0;
+                if (!(best[u] < INFINITY)) {
+                    bits = 0;
+                    if (item < live) sh.wild = 1;
+                }
                 while (bits != 0) {
                     const int i = __builtin_clz(bits);
                     bits &= ~(0x80000000u >> i);
@@ -389,9 +397,112 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
             }
             __syncthreads();
         };
+        // ---- for the items whose candidates say nothing: the fp32 argmin over all codewords as the only candidate.  The
+        // 256 scores one by one instead, sixteen threads an item, took 0.35 us each: 20000 x 128, K = 8, every codeword
+        // there 16 times 2.76 ms, one infinite vector in each block 2.91 ms; now 0.24 and 0.25 ms (0.064 ms
+        // without them; with more than 128 dimensions 6.9 ms both, now 0.54).
+        auto exact = [&]() __attribute__((always_inline)) {
+            const int tid = fresh(tid0), lane = tid & 63, half = lane >> 5, l32 = lane & 31, rg = tid >> 4;
+            float *F = reinterpret_cast<float *>(sh.frag);                 // [64 dimensions][E_FROW]
+            float *C = reinterpret_cast<float *>(sh.cbs);                  // [256 codewords][17]: 16 dimensions
+            u64 *best = reinterpret_cast<u64 *>(sh.frag);                  // [4][EB]
+            static_assert(64 * E_FROW * sizeof(float) <= sizeof(sh.frag) && ICQ_LUT_W * 17 * sizeof(float) <= sizeof(sh.cbs), "");
+            float16v acc[2][2];
+#pragma unroll
+            for (int i = 0; i < 64; ++i) acc[i >> 5][(i >> 4) & 1][i & 15] = 0.0f;
+#pragma nounroll
+            for (int e = 0; e < d_pad; e += 16) {
+                __syncthreads();                           // the slice before is consumed
+                const int e0 = (e & ~127) + (tid & 15) * 8;
+                if ((e & 63) == 0 && (e0 & ~63) == e) {
+#pragma unroll
+                    for (int p = 0; p < E_P; ++p) {
+                        asm volatile("" ::: "memory");
+                        float v[8];
+                        residual(rg, p, e0, v);
+                        if (ICM) {
+                            float c[8];
+                            load8(codeword(k, sh.code[k][rg + E_G * p]), e0, c);
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) v[i] += c[i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) F[((e0 & 63) + i) * E_FROW + rg + E_G * p] = v[i];
+                    }
+                }
+                {
+                    float c[8];
+                    load8(codeword(k, (uint32_t)tid >> 1), e + (tid & 1) * 8, c);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) C[(tid >> 1) * 17 + (tid & 1) * 8 + i] = c[i];
+                }
+                __syncthreads();
+#pragma unroll 2
+                for (int s = 0; s < 8; ++s) {
+                    float a[2], b[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) a[t] = C[(cw * 64 + t * 32 + l32) * 17 + 2 * s + half];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) b[u] = F[((e & 63) + 2 * s + half) * E_FROW + ih * 64 + u * 32 + l32];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) acc[u][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[t], b[u], acc[u][t], 0, 0, 0);
+                }
+            }
+            __syncthreads();                               // the fragments are consumed
+            // key: order-preserving bits of the score, index + 1 (ICM: 0 for the current codeword); no number, no key
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int item = ih * 64 + u * 32 + l32;
+                const uint32_t old = ICM ? sh.code[k][item] : ~0u;
+                float b = INFINITY;                        // the least score and, below, the first field that has it
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        asm volatile("" ::: "memory");     // (four norms at a time: all 32 would push residuals out of registers)
+                        const float4v cn = *reinterpret_cast<const float4v *>(cnorm + k * ICQ_LUT_W + cw * 64 + t * 32 + w * 8 + half * 4);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            acc[u][t][w * 4 + i] = cn[i] - 2.0f * acc[u][t][w * 4 + i];
+                            b = fminf(b, acc[u][t][w * 4 + i]);            // not NaN
+                        }
+                    }
+                const uint32_t first = (uint32_t)(cw * 64 + 4 * half);
+                uint32_t f = 0;
+                bool keep = false;                         // the current codeword has it
+#pragma unroll
+                for (int i = 31; i >= 0; --i) {
+                    const uint32_t at = (uint32_t)((i >> 4) * 32 + (i & 3) + 8 * ((i & 15) >> 2));
+                    f = acc[u][i >> 4][i & 15] == b ? at : f;
+                    if (ICM) keep |= acc[u][i >> 4][i & 15] == b && old == first + at;
+                }
+                f = keep ? 0u : first + f + 1u;
+                u64 key = b < INFINITY ? ((u64)icq_order_bits(b + 0.0f) << 32) | f : ~0ull;
+                const u64 other = __shfl_xor(key, 32, 64);
+                key = other < key ? other : key;
+                if (half == 0) best[cw * EB + item] = key;
+            }
+            __syncthreads();
+            if (tid < live) {
+                const uint32_t n = sh.ccount[tid];
+                if (n == 0 || n > (uint32_t)E_CAND) {
+                    u64 key = best[tid];
+#pragma unroll
+                    for (int w = 1; w < 4; ++w) key = best[w * EB + tid] < key ? best[w * EB + tid] : key;
+                    // no score a number: index 0 (ICM: the current one) stays
+                    const uint32_t old = ICM ? sh.code[k][tid] : 0u;
+                    sh.cand[tid][0] = (uint8_t)(key == ~0ull || (uint32_t)key == 0u ? old : (uint32_t)key - 1u);
+                    sh.ccount[tid] = 1;
+                }
+            }
+            __syncthreads();
+        };
         // ---- first halves only; then, if that left some item too many candidates, both halves of both sides but the
         // product of the two second ones
         if (REG) stage(0, true, false);
+        uint32_t stuck;
 #pragma nounroll
         for (int round = 0;; ++round) {
             if (REG && round != 0) stage(0, false, false);
@@ -412,11 +523,15 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 contract(acc, pass == 2 ? half_lo : half_hi, pass, round == 0);
             }
             candidates(acc, round == 0 ? E_U : 4.0f * E_U * E_U, round == 0 ? dmax : 2.0f * E_U * dmax, round == 0 ? 1 : 3);
-            if (round != 0 || sh.over == 0) break;         // block-uniform: read between barriers
+            const uint32_t over = __builtin_amdgcn_readfirstlane(sh.over), wild = __builtin_amdgcn_readfirstlane(sh.wild);
+            if (round != 0) equal |= over != 0;
+            stuck = over | wild;
+            if (round != 0 || over == 0 || equal) break;   // block-uniform: read between barriers
             __syncthreads();
             if (tid < EB) sh.ccount[tid] = 0;
-            if (tid == 0) sh.over = 0;
+            if (tid == 0) sh.over = sh.wild = 0;
         }
+        if (stuck != 0) exact();                           // block-uniform
         reach = largest_norm() + cmax;                     // of the residuals the level leaves
         // ---- the sub-codes: the only candidate, or the argmin of the candidates' fp32 scores
         const bool last = lev + 1 == levels;
@@ -438,15 +553,13 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
             const int item = rg + E_G * p;
             const uint32_t n = item < live ? sh.ccount[item] : 1u;
             const uint32_t old = ICM ? sh.code[k][item] : 0u;
-            // none: a bound that is no number.  If no fp32 score is one either, index 0 (ICM: the current one) stays
-            const bool all = n == 0 || n > (uint32_t)E_CAND;
-            uint32_t code = sh.ccount[item] - 1u < (uint32_t)E_CAND ? sh.cand[item][0] : old;
+            uint32_t code = n - 1u < (uint32_t)E_CAND && item < live ? sh.cand[item][0] : old;
             if (__builtin_amdgcn_ballot_w64(n != 1) != 0) {        // wavefront-uniform: four items at a time
                 float best = INFINITY;
                 uint32_t bf = 0xFFFFFFFFu;                         // ICM: 0 for the current codeword, else index + 1
-                const uint32_t todo = n != 1 ? (all ? (uint32_t)m : n) : 0u;
+                const uint32_t todo = n != 1 ? n : 0u;             // at most E_CAND
                 for (uint32_t i = 0; __builtin_amdgcn_ballot_w64(i < todo) != 0; ++i) {
-                    const uint32_t j = all ? (i < (uint32_t)m ? i : 0u) : sh.cand[item][i < n ? i & (E_CAND - 1) : 0];
+                    const uint32_t j = sh.cand[item][i < n ? i : 0];
                     float dot = 0.0f, c[8];
                     for (int sl = 0; sl < nsl; ++sl) {
                         const int e0 = sl * 128 + c8;

@@ -1214,6 +1214,44 @@ def test_encode_where_the_halves_overflow_for_few_codewords(gpu, m, d):
     assert (second[:, [7, 139]] == (0 if m == 2 else m - 2)).all()
 
 
+@pytest.mark.parametrize("m,distinct,d,N", [(256, 16, 40, 300), (256, 1, 128, 129), (200, 19, 130, 140), (90, 9, 99, 128),
+                                            (256, 28, 960, 257)])
+def test_encode_with_masses_of_equal_codewords(gpu, m, distinct, d, N):
+    """Codebooks whose codewords are there nine times or more, beside vectors that have infinities, NaN or a norm beyond
+    fp32 in every block: the smallest index of the nearest (the oracle's), a current codeword kept among equal ones, and
+    the neighbours' codes as without them."""
+    torch, b = gpu
+    K = 3
+    rng = np.random.default_rng(m * 1000 + d)
+    base = (rng.standard_normal((K, distinct, d)) * (0.5 ** np.arange(K))[:, None, None]).astype(np.float32)
+    cb = base[:, np.arange(m) % distinct]
+    src = rng.integers(0, distinct, (K, N))
+    x = (sum(base[k][src[k]] for k in range(K)) + 0.01 * rng.standard_normal((N, d))).astype(np.float32)
+    bad = np.arange(5, N, 64)
+    y = x.copy()
+    y[bad[0::3], 0] = np.inf
+    y[bad[1::3], d - 1] = np.nan
+    y[bad[2::3]] *= 1e20
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    start = rng.integers(0, m, (K, N), dtype=np.uint8)
+    out = []
+    for v in (x, y):
+        codes = torch.full((K, N), 255, dtype=torch.uint8, device="cuda")
+        refined, changed = _dev(torch, start), torch.full((2,), -1, dtype=torch.int32, device="cuda")
+        b.icq_encode(index, _dev(torch, v), codes, ws)
+        b.icq_encode_refine(index, _dev(torch, v), refined, 2, changed, ws)
+        torch.cuda.synchronize()
+        out.append([t.cpu().numpy() for t in (codes, refined, changed)])
+    good = np.setdiff1d(np.arange(N), bad)
+    want = orc.encode(cb, x)
+    assert (want < distinct).all() and np.array_equal(out[0][0], want)
+    assert np.array_equal(out[1][0][:, good], want[:, good]) and (out[1][0] < m).all()
+    assert np.array_equal(out[1][1][:, good], out[0][1][:, good]) and (out[1][1] < m).all()
+    want, moved = orc.encode_icm(cb, x, start, 2)
+    assert np.array_equal(out[0][1], want) and np.array_equal(out[0][2], moved)
+
+
 def test_encode_on_disjoint_supports_recovers_the_codes(gpu):
     """Codebooks with pairwise-disjoint supports, vectors that are exact reconstructions: every
     greedy step has a codeword at distance zero, so the codes come back bit for bit; an index
