@@ -916,9 +916,11 @@ int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const fl
                           hipStream_t s) {
     // cand_count is zero.  Four to eight blocks of four wavefronts per CU while the queries leave room for it; at
     // most 64 parts: a row per wavefront and four tables' worth of columns is little for a block already.  Kf == 1:
-    // the 256 tuples are long, so that even one column per wavefront is work (7 queries, 10^5 items that all survive,
-    // one block per query / 64: 90 / 27 us)
+    // the 256 tuples are long, so that even one column per wavefront is work, as long as a block's items outweigh its
+    // wavefronts' turns at the query's counter (all items surviving, one block per query / 64 / a block per 4096 items:
+    // 17 queries, 10^5 items 97 / 53 / 28 us; 64 queries, 5000 items 13 / 34 / 13 us, 20000 items 25 / 37 / 15 us)
     int parts = (int)((4ll * ix->num_cu + Q - 1) / Q);
+    if (ix->Kf == 1 && parts > ix->N / 4096) parts = (int)(ix->N / 4096);
     if (parts > 64) parts = 64;
     if (parts < 1) parts = 1;
     for (int q0 = 0; q0 < Q; q0 += 65535) {

@@ -213,7 +213,7 @@ def test_scan_fast_special_thresholds_and_overflow(gpu, Q, mode):
 @pytest.mark.parametrize("Q,Kf,m,N", [
     (140, 2, 256, 70_001),     # every tuple below the threshold: a wavefront's buffer fills and is expanded more than once
     (3, 2, 3, 40_003),         # nine tuples of 4445 items: windows of survivors far longer than a step
-    (2, 1, 256, 70_001), (70, 1, 2, 5_000), (29, 1, 256, 20_001), (1030, 1, 100, 2_000),     # 64, 15, 36 blocks per query, one
+    (2, 1, 256, 270_001), (70, 1, 2, 70_000), (29, 1, 256, 20_001), (1030, 1, 100, 2_000),     # 64, 15, 4 blocks per query, one
 ])
 def test_scan_fast_grouped_lists_at_the_edges_of_its_buffers(gpu, Q, Kf, m, N):
     """Grouped lists against the item-by-item lists (same additions): equal as sets, crude distances bit for bit."""
