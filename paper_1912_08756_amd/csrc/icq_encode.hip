@@ -63,7 +63,6 @@ struct EncShared {
     uint8_t code[ICQ_MAX_K][EB];
     uint8_t before[EB];                    // the sub-code the level before found
     uint32_t over;                         // some item has more than E_CAND candidates
-    uint32_t wild;                         // some item's bound is no number
 };
 static_assert(sizeof(EncShared) <= 81920, "two blocks per CU");
 
@@ -202,12 +201,14 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         }
     }
     __syncthreads();
+    bool wild = false;                                     // some norm of the block is no number
     auto largest_norm = [&]() __attribute__((always_inline)) -> float {                   // behind a barrier after nrm2 was written
         const int lane = fresh(tid0) & 63;
         // as bits, which order as the squares do; an item whose norm is no number would take the others' halves from
         // them and has no bound anyway
         const uint32_t a = __float_as_uint(sh.nrm2[lane]), b = __float_as_uint(sh.nrm2[lane + 64]);
         const uint32_t a1 = a < 0x7f800000u ? a : 0u, b1 = b < 0x7f800000u ? b : 0u;
+        wild = __builtin_amdgcn_ballot_w64(a1 != a || b1 != b) != 0;
         const float v = __uint_as_float(wave_max_u32(a1 > b1 ? a1 : b1));
         return __builtin_amdgcn_sqrtf(v) * 1.0001f;
     };
@@ -346,7 +347,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 
         const int tid = fresh(tid0);
         if (tid < EB) sh.ccount[tid] = 0;
-        if (tid == 0) sh.over = sh.wild = 0;
+        if (tid == 0) sh.over = 0;
         // ---- candidates: codewords whose score is within twice the error bound of the item's best
         auto candidates = [&](const float16v (&acc)[2][2], float u_r, float d_c, int passes) __attribute__((always_inline)) {
             const int lane = fresh(tid0) & 63, half = lane >> 5, l32 = lane & 31;
@@ -382,10 +383,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 #pragma unroll
                 for (int i = 0; i < 32; ++i)
                     bits = __builtin_amdgcn_alignbit(bits, __float_as_uint(best[u] - acc[u][i >> 4][i & 15]), 31);
-                if (!(best[u] < INFINITY)) {
-                    bits = 0;
-                    if (item < live) sh.wild = 1;
-                }
+                if (!(best[u] < INFINITY)) bits = 0;
                 while (bits != 0) {
                     const int i = __builtin_clz(bits);
                     bits &= ~(0x80000000u >> i);
@@ -502,7 +500,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         // ---- first halves only; then, if that left some item too many candidates, both halves of both sides but the
         // product of the two second ones
         if (REG) stage(0, true, false);
-        uint32_t stuck;
+        bool over;
 #pragma nounroll
         for (int round = 0;; ++round) {
             if (REG && round != 0) stage(0, false, false);
@@ -523,16 +521,17 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 contract(acc, pass == 2 ? half_lo : half_hi, pass, round == 0);
             }
             candidates(acc, round == 0 ? E_U : 4.0f * E_U * E_U, round == 0 ? dmax : 2.0f * E_U * dmax, round == 0 ? 1 : 3);
-            const uint32_t over = __builtin_amdgcn_readfirstlane(sh.over), wild = __builtin_amdgcn_readfirstlane(sh.wild);
-            if (round != 0) equal |= over != 0;
-            stuck = over | wild;
-            if (round != 0 || over == 0 || equal) break;   // block-uniform: read between barriers
+            over = sh.over != 0;
+            if (round != 0) equal |= over;
+            if (round != 0 || !over || equal) break;   // block-uniform: read between barriers
             __syncthreads();
             if (tid < EB) sh.ccount[tid] = 0;
-            if (tid == 0) sh.over = sh.wild = 0;
+            if (tid == 0) sh.over = 0;
         }
-        if (stuck != 0) exact();                           // block-uniform
         reach = largest_norm() + cmax;                     // of the residuals the level leaves
+        // some item has no bound: a norm or (for all items) a codeword is no number.  All else is finite: what the scales
+        // multiply is below 2^14 and 2^10
+        if (over || wild || !(dmax < INFINITY)) exact();   // block-uniform
         // ---- the sub-codes: the only candidate, or the argmin of the candidates' fp32 scores
         const bool last = lev + 1 == levels;
         if (!last) ahead(kn);

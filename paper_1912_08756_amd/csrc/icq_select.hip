@@ -400,7 +400,7 @@ int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, in
     const uint32_t alone = select_alone(Q, topk);
 #define ICQ_SEL(T, PER, MIN) launch_select<T, PER, MIN>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s)
     if (count && (int64_t)Q * splits <= 512) return ICQ_SEL(1024, 8, 1);
-    if (cap <= SEL_LIST) return ICQ_SEL(256, 4, 2);
+    if (Q > 512 && cap <= SEL_LIST) return ICQ_SEL(256, 4, 2);
     if (topk > 256) return ICQ_SEL(512, 8, 2);
     return ICQ_SEL(512, 8, 1);
 #undef ICQ_SEL

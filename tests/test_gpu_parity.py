@@ -1252,6 +1252,28 @@ def test_encode_with_masses_of_equal_codewords(gpu, m, distinct, d, N):
     assert np.array_equal(out[0][1], want) and np.array_equal(out[0][2], moved)
 
 
+@pytest.mark.parametrize("d", [40, 130])
+def test_encode_with_codewords_that_are_no_numbers(gpu, d):
+    """Codewords with an infinity or NaN are nobody's nearest: the codes are those of a codebook with far codewords there."""
+    torch, b = gpu
+    K, m, N = 3, 100, 200
+    rng = np.random.default_rng(d)
+    far = rng.standard_normal((K, m, d)).astype(np.float32)
+    x = (sum(far[k][rng.integers(8, m, N)] for k in range(K)) + 0.01 * rng.standard_normal((N, d))).astype(np.float32)
+    far[1, 3:6] = 1e6
+    cb = far.copy()
+    cb[1, 3, 0], cb[1, 4, d - 1], cb[1, 5, 2] = np.inf, np.nan, -np.inf
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    codes = torch.full((K, N), 255, dtype=torch.uint8, device="cuda")
+    b.icq_encode(index, _dev(torch, x), codes, ws)
+    want = orc.encode(far, x)
+    assert np.array_equal(codes.cpu().numpy(), want)
+    refined = _dev(torch, want)
+    b.icq_encode_refine(index, _dev(torch, x), refined, 2, None, ws)
+    assert np.array_equal(refined.cpu().numpy(), orc.encode_icm(far, x, want, 2)[0])
+
+
 def test_encode_on_disjoint_supports_recovers_the_codes(gpu):
     """Codebooks with pairwise-disjoint supports, vectors that are exact reconstructions: every
     greedy step has a codeword at distance zero, so the codes come back bit for bit; an index
