@@ -312,7 +312,8 @@ int icq_op_counts(const icq_index *index, const uint32_t *refined, int Q, unsign
  * codebook order:  r_0 = x_i;  code_k(i) = argmin_j ||r_k - c_{k,j}||^2
  * (ties: smallest j);  r_{k+1} = r_k - c_{k,code_k(i)}.  On codebooks with
  * pairwise-disjoint supports every step is the exact nearest codeword in its
- * subspace.  Scores are formed in fp32 on the matrix cores.
+ * subspace.  The argmin is that of fp32 scores; products of half-precision
+ * copies, with a bound on their error, only rule out codewords that cannot be it.
  * index: any index over the codebooks (it may hold no items: N = 0 at create).
  * x [N][d] fp32, codes_out [K][N] (the layout icq_index_create takes),
  * workspace of icq_encode_workspace_bytes(index, N) bytes (the residuals).

@@ -27,11 +27,14 @@
 // three times as large).  Where it is more than eight after that (equal codewords), or the bound is no number
 // (infinities, NaN, norms beyond fp32), the block forms all its scores in fp32 on the matrix cores.
 //
-// What bounds it: up to E_REG_D dimensions vector issue -- 800 instructions per wavefront and level (argmin 2.5
-// per score; residual, norms and conversion 5 per element) keep the vector units 64 % busy, the matrix
-// cores 20 % -- and, with more dimensions, the residuals' way through memory (4 TB/s at d = 256 and 960).
-// 10^6 x 128, K = 8: 1.25 ms; the fp32 contraction this replaces took 5.9 ms, 0.6 of the fp32 matrix
-// rate.  262147 x 96, K = 16, with two sweeps: 8.0 -> 2.0 ms.
+// What bounds it: up to E_REG_D dimensions vector issue -- 813 vector instructions per wavefront and level at 128 dimensions
+// keep the vector units 65 % busy, the matrix cores 20 %.  By the listing: halves and norms of the 32 residuals of a thread 150,
+// their update 32, the contraction's 32 matrix instructions, start values and addresses 120, maxima and bounds 100, the
+// comparison of 64 scores a lane 130, loading the chosen codewords and choosing 150; the rest is second looks, taken by a
+// wavefront when one of its items has several candidates.  With more dimensions it is the residuals' way through memory
+// (4 TB/s at d = 256 and 960).
+// 10^6 x 128, K = 8: 1.02 ms; the fp32 contraction this replaces took 5.9 ms, 0.6 of the fp32 matrix
+// rate.  262147 x 96, K = 16, with two sweeps: 8.0 -> 1.74 ms.
 #include "icq_internal.h"
 #include "icq_sort.h"
 
@@ -89,16 +92,16 @@ __device__ __forceinline__ float scale_below(float x, int bits) {
     return __uint_as_float((uint32_t)f << 23);
 }
 
-// x [N][d]; cb [K*256][d_pad] fp32; half_hi / half_lo: see
-// encode_pack_kernel; meta[k] = scale, largest ||c||, largest ||c - c'||.  REG: d <= E_REG_D, the residuals live in
+// x [N][d]; cb [K*256][d_pad] fp32; half_hi / half_lo: see encode_pack_kernel; meta[k] = scale, largest ||c||, largest ||c - c'||.  REG: d <= E_REG_D, the residuals live in
 // registers; else in res [N][d_pad].  ICM: `codes` is in and out, `changed` (or nullptr) counts per sweep.
 //
 // Thread t owns the 8 dimensions from 8 (t % 16) on of the items t / 16 + 32 p, p = 0 .. 3 (of every 128-wide slice):
 // residual rows and codewords are read in whole pieces of 16 threads.  In the contraction the codewords are the rows of
 // the matrix instruction (wavefront w: the 64 from 64 (w % 4) on) and the items its columns (the 64 from 64 (w / 4) on),
 // so a lane holds 32 scores of one item per column block and the maximum is taken inside the lane.  64 x 64 scores per
-// wavefront are 64 registers, which with a thread's 32 residuals leave room for four wavefronts per SIMD (64 x 128 scores
-// by four wavefronts of 256 registers spilled: 3.8 ms at 10^6 x 128, K = 8, where this takes 1.25).
+// wavefront are 64 registers, which with a thread's 32 residuals leave room for four wavefronts per SIMD.  7 of the 128
+// registers' values are spilled (ICM: 47 and 41, mostly around the round of fp32 scores); 64 x 128 scores by four
+// wavefronts of 256 registers spilled inside the contraction: three times the time.
 template <bool REG, bool ICM>
 __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     const float *__restrict__ x, int d, const float *__restrict__ cb, int d_pad, const float *__restrict__ cnorm,

@@ -553,18 +553,19 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
         const int bpq = len > 0 ? (int)((len + RD_BLOCK - 1) / RD_BLOCK) : 1;
         const unsigned dgrid = (unsigned)Q * (unsigned)bpq;
         if (list_kind != ICQ_LIST_KEYS) {
-#define ICQ_RD_LAUNCH(W)                                                                          \
-    refine_dist_kernel<W><<<dgrid, RF_THREADS, 0, s>>>(items, ix->K, ix->Kf, lut, cand_ids,       \
-                                                       cand_part, cand_count, cap, bpq, keys, ticket)
-        switch (ix->item_stride) {
-            case 4: ICQ_RD_LAUNCH(1); break;
-            case 8: ICQ_RD_LAUNCH(2); break;
-            default: ICQ_RD_LAUNCH(4); break;
+            auto launch = [&](auto kernel) {
+                kernel<<<dgrid, RF_THREADS, 0, s>>>(items, ix->K, ix->Kf, lut, cand_ids, cand_part, cand_count, cap, bpq, keys,
+                                                    ticket);
+            };
+            switch (ix->item_stride) {
+                case 4: launch(refine_dist_kernel<1>); break;
+                case 8: launch(refine_dist_kernel<2>); break;
+                default: launch(refine_dist_kernel<4>); break;
+            }
+            if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
         }
-#undef ICQ_RD_LAUNCH
-        if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-        }
-        return icq_launch_select(keys, const_cast<uint32_t *>(cand_count), cap, Q, topk, splits, false, ticket, out_ids, out_dist, s);
+        return icq_launch_select(keys, const_cast<uint32_t *>(cand_count), cap, Q, topk, splits, false, ticket, out_ids,
+                                 out_dist, s);
     }
     const int bufn = bufn_for(topk);
     const size_t lds = sizeof(u64) * bufn + tab;

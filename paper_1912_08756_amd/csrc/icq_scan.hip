@@ -621,8 +621,9 @@ void icq_zero_words(uint32_t *p, int n, hipStream_t s) {
     if (n > 0) zero_counts_kernel<<<(n + 255) / 256, 256, 0, s>>>(p, n);
 }
 
-int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr, uint32_t *cand_ids, float *cand_part, unsigned long long *cand_keys, int *list_kind, uint32_t *cand_count, int64_t cap,
-                    int topk, uint32_t *out_ids, float *out_dist, icq_share share, hipStream_t s) {
+int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *thr, uint32_t *cand_ids, float *cand_part,
+                    unsigned long long *cand_keys, int *list_kind, uint32_t *cand_count, int64_t cap, int topk,
+                    uint32_t *out_ids, float *out_dist, icq_share share, hipStream_t s) {
     if (list_kind) *list_kind = ICQ_LIST_IDS;
     if (Q == 0) return ICQ_OK;
     if (ix->N == 0) return ICQ_OK;

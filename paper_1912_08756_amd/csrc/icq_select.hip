@@ -2,12 +2,12 @@
 // query's 64-bit keys (order-preserving bits of D, item id), ascending.  The keys are either the
 // survivors' (count[q] of them) or the ascending lists that several blocks left for one query.
 //
-// One block per query.  Every thread takes the smallest distance of its share of the keys; the
+// One block per query.  Every thread takes the smallest key of its share (or of two shares); the
 // topk-th smallest of those minima (one histogram pass) bounds the topk-th smallest key from above,
 // because at least topk keys are at or below it -- and hardly more are: with 10^4 keys, 1024 threads
 // and topk = 100 some 110.  Those are collected into LDS and ranked by counting.  The keys stay in
 // registers between the two looks while there are at most PER per thread (8192 with 1024 threads),
-// else they are read again from the caches.
+// else they are read again from the caches.  Where equal distances let hundreds through, the ids decide as well.
 //
 // What bounds it is latency: three dependent trips to memory (count, keys, results) and a dozen
 // barriers; 128 queries of 15000 keys also take the time their keys need to come from another

@@ -21,7 +21,8 @@ constexpr int SM_PER = 4;                            // items per thread and ste
 constexpr int SM_STEP = SM_THREADS * SM_PER;
 static_assert(SM_STEP <= 65536, "the list holds 16-bit offsets");
 
-// items [N] records of WORDS words; thr [Q], Q = gridDim.y; keys [Q][cap]; count [Q] zero on entry, N <= 2^31.
+// items [N] records of WORDS words; thr [Q], Q = gridDim.y; keys [Q][cap]; count [Q] zero on entry, N <= ICQ_MAX_N
+// (a step past it still fits 32 bits).
 // Block x takes the items [x * per, (x + 1) * per), per a multiple of SM_STEP.
 template <int WORDS>
 __global__ __launch_bounds__(SM_THREADS) void small_search_kernel(

@@ -943,6 +943,31 @@ def test_running_search_in_tiles_matches_oracle(gpu, name, N, Q, over, topk, bou
         b.icq_index_destroy(t)
 
 
+def test_running_search_of_more_queries_than_one_batch(gpu):
+    """33 000 queries: each tile's search takes them in two sub-batches over the caller's tables.  Lists and counts are those of
+    the queries searched by themselves."""
+    torch, b = gpu
+    Q, K, Kf, d, topk = 33_000, 4, 3, 8, 20
+    g = torch.Generator(device="cuda"); g.manual_seed(5)
+    cb = torch.randn((K, 256, d), device="cuda", generator=g) * (0.6 ** torch.arange(K, device="cuda"))[:, None, None]
+    bounds = [0, 300, 1300, 3000]
+    codes = torch.randint(0, 256, (K, bounds[-1]), dtype=torch.uint8, device="cuda", generator=g)
+    queries = torch.randn((Q, d), device="cuda", generator=g)
+    tiles = [b.icq_index_create(cb, codes[:, x:y].contiguous(), Kf) for x, y in zip(bounds, bounds[1:])]
+
+    def run(q):
+        n = q.shape[0]
+        ids, dist = torch.full((n, topk), -7, dtype=torch.int32, device="cuda"), torch.zeros((n, topk), device="cuda")
+        count = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.icq_running_workspace_bytes(tiles, n, bounds[-1], topk), dtype=torch.uint8, device="cuda")
+        b.icq_search_running(tiles, bounds[:-1], q, torch.full((n,), 2.0, device="cuda"), bounds[-1], topk, ids, dist, count, ws)
+        return ids, dist, count
+    whole = run(queries)
+    assert (whole[2] >= 300).all() and (whole[2] < bounds[-1]).any()
+    for x, y in ((0, 50), (32_700, 32_850), (Q - 40, Q)):
+        assert all(torch.equal(w[x:y], p) for w, p in zip(whole, run(queries[x:y].contiguous())))
+
+
 def test_running_search_at_full_size_sampled_against_oracle(gpu):
     """The largest workload (N = 1e8, K = 16, Kf = 4) in the launch configuration bench.py times: 8 tiles
     growing fourfold from 8192 items, one batch of 128 queries; four of them against the oracle's tiled loop, the rest by
