@@ -118,7 +118,7 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u
         // Masses of equal distances, or a histogram bin wide enough to hold hundreds of keys: the topk-th smallest of the
         // minima as whole keys, the id deciding among equal distances, bounds as well and lets through about as few as
         // distinct distances would.  icq_refine of one query, 16 different distances among 20000 / 120000 candidates,
-        // topk = 100: 30 / 71 us, where the digit passes below, taken at once, made it 70 / 316.
+        // topk = 100: 30 / 71 us (in parts 31), where the digit passes below, taken at once, made it 70 / 316.
         const uint32_t kth = block_kth<MIN>(sh.kth, high, any, (uint32_t)topk, true, tid, lane, wave);
         uint32_t under = 0, at = 0;
 #pragma unroll
