@@ -13,7 +13,9 @@
 // one.  The residual holds x - xbar, a level adds the current codeword back, the argmin prefers the
 // current codeword among equal scores, and only items whose sub-code changed get a new residual.
 //
-// One kernel does both, all levels (and sweeps) of 128 items per block, in two steps per level:
+// Two kernels do both, all levels (and sweeps) of a block's items in one launch: encode_wave_kernel (icq_encode_wave.hip) holds
+// the residuals in registers, up to 256 dimensions always and up to 512 for few items; encode_kernel below keeps them in
+// memory.  Two steps per level:
 //  1. The contraction on half-precision copies of residual and codewords (v_mfma_f32_32x32x16_f16, sixteen
 //     times the rate of the fp32 instruction) leaves, with a bound E on its error, a SUPERSET of the
 //     codewords that can be the argmin: those whose score is within 2 E of the best.  E comes from
@@ -22,21 +24,16 @@
 //     are powers of two, so nothing else is rounded.
 //  2. Items with more than one candidate (a few per cent) form the candidates' fp32 scores from the fp32
 //     residual and codewords and take the argmin of those.  The result is the fp32 argmin, as before.
-// Where more than eight codewords of an item are within the bound, the block repeats the level with both
+// Where more than eight codewords of an item are within the bound, encode_kernel repeats the level with both
 // operands split in two halves (three products: E's operand part is smaller by 2^-10, its accumulation part
 // three times as large).  Where it is more than eight after that (equal codewords), or the bound is no number
 // (infinities, NaN, norms beyond fp32), the block forms all its scores in fp32 on the matrix cores.
+// (encode_wave_kernel does so at once: its fp32 products cost a wavefront about what a second round would.)
 //
-// What bounds it: up to E_REG_D dimensions vector issue -- 813 vector instructions per wavefront and level at 128 dimensions
-// keep the vector units 65 % busy, the matrix cores 20 %.  By the listing: halves and norms of the 32 residuals of a thread 150,
-// their update 32, the contraction's 32 matrix instructions, start values and addresses 120, maxima and bounds 100, the
-// comparison of 64 scores a lane 130, loading the chosen codewords and choosing 150; the rest is second looks, taken by a
-// wavefront when one of its items has several candidates.  With more dimensions it is the residuals' way through memory
-// (4 TB/s at d = 256 and 960).
-// 10^6 x 128, K = 8: 1.02 ms; the fp32 contraction this replaces took 5.9 ms, 0.6 of the fp32 matrix
-// rate.  262147 x 96, K = 16, with two sweeps: 8.0 -> 1.74 ms.
+// What bounds encode_kernel: the residuals' way through memory (4 TB/s at d = 960).
 #include "icq_internal.h"
 #include "icq_sort.h"
+#include "icq_encode.h"
 
 #include <math.h>
 
@@ -49,7 +46,6 @@ constexpr int EB = 128;           // items per block
 constexpr int E_THREADS = 512;
 constexpr int E_P = EB * 16 / E_THREADS;   // items per owner group of 16 threads
 constexpr int E_G = E_THREADS / 16;        // owner groups
-constexpr int E_REG_D = 128;      // up to this many dimensions the residual stays in registers
 constexpr int E_CAND = 8;         // candidates listed per item
 constexpr int E_FROW = EB + 1;    // 16-byte pieces per reduction group of the residual's fragments: one to spare, so
                                   // that the 16 threads that write one row's groups meet different banks
@@ -84,28 +80,20 @@ __device__ __forceinline__ float row_sum(float x) {
     x += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x121, 0xf, 0xf, false));
     return x;
 }
-// 2^(bits - e) with e the smallest integer for which x < 2^e (clamped): x times this is below 2^bits
-__device__ __forceinline__ float scale_below(float x, int bits) {
-    const int e = (int)((__float_as_uint(x) >> 23) & 255u) - 126;
-    int f = bits - e + 127;
-    f = f < 67 ? 67 : f > 187 ? 187 : f;                   // 2^-60 .. 2^60: products of two scales stay finite
-    return __uint_as_float((uint32_t)f << 23);
-}
 
-// x [N][d]; cb [K*256][d_pad] fp32; half_hi / half_lo: see encode_pack_kernel; meta[k] = scale, largest ||c||, largest ||c - c'||.  REG: d <= E_REG_D, the residuals live in
-// registers; else in res [N][d_pad].  ICM: `codes` is in and out, `changed` (or nullptr) counts per sweep.
+// x [N][d]; cb [K*256][d_pad] fp32; half_hi / half_lo: see encode_pack_kernel; meta[k] = scale, largest ||c||, largest ||c - c'||;
+// the residuals in res [N][d_pad].  ICM: `codes` is in and out, `changed` (or nullptr) counts per sweep.
 //
 // Thread t owns the 8 dimensions from 8 (t % 16) on of the items t / 16 + 32 p, p = 0 .. 3 (of every 128-wide slice):
 // residual rows and codewords are read in whole pieces of 16 threads.  In the contraction the codewords are the rows of
 // the matrix instruction (wavefront w: the 64 from 64 (w % 4) on) and the items its columns (the 64 from 64 (w / 4) on),
 // so a lane holds 32 scores of one item per column block and the maximum is taken inside the lane.  64 x 64 scores per
-// wavefront are 64 registers, which with a thread's 32 residuals leave room for four wavefronts per SIMD.  7 of the 128
-// registers' values are spilled (ICM: 47 and 41, mostly around the round of fp32 scores); 64 x 128 scores by four
-// wavefronts of 256 registers spilled inside the contraction: three times the time.
-template <bool REG, bool ICM>
+// wavefront are 64 registers, which leave room for four wavefronts per SIMD.  7 of the 128 registers' values are spilled
+// (ICM: 41, mostly around the round of fp32 scores).
+template <bool ICM>
 __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     const float *__restrict__ x, int d, const float *__restrict__ cb, int d_pad, const float *__restrict__ cnorm,
-    const uint4 *__restrict__ half_hi, const uint4 *__restrict__ half_lo, const float4 *__restrict__ meta, int K, int m,
+    const uint4 *__restrict__ half_hi, const uint4 *__restrict__ half_lo, const float4 *__restrict__ meta, int K, int slices,
     int64_t N, uint8_t *codes, int sweeps, float *res, uint32_t *changed) {
     extern __shared__ __attribute__((aligned(16))) unsigned char enc_smem[];
     EncShared &sh = *reinterpret_cast<EncShared *>(enc_smem);
@@ -114,7 +102,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     const int64_t i0 = (int64_t)blockIdx.x * EB;
     const int cw = wave & 3, ih = wave >> 2;
     const int nks = (d_pad + 31) / 32;                     // 32-wide codebook slices
-    const int nsl = REG ? 1 : (nks + 3) / 4;               // 128-wide residual slices
+    const int nsl = (nks + 3) / 4;                         // 128-wide residual slices
     const int live = N - i0 < EB ? (int)(N - i0) : EB;     // items of this block; rows past them read the last one's x
     auto row = [&](int rg, int p) { return i0 + (rg + E_G * p < live ? rg + E_G * p : live - 1); };
     // a residual in memory is its owner's alone; rows past N read a codeword instead of racing with it
@@ -122,8 +110,6 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         return rg + E_G * p < live ? res + (i0 + rg + E_G * p) * d_pad : cb;
     };
 
-    float r[REG ? E_P : 1][8];
-    float co[REG && ICM ? E_P : 1][8];                     // the current codewords of the level to come
     auto load_x = [&](int rg, int p, int e0, float (&v)[8]) __attribute__((always_inline)) {
         // Pieces need no alignment.  What lies outside the row is masked by bits: a select between a load and zero ends
         // as a branch around the load, one wait per piece instead of all pieces in flight together.
@@ -150,7 +136,6 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         for (int i = 0; i < 8; ++i) v[i] = __uint_as_float(w[i]);
     };
     auto codeword = [&](int k, uint32_t j) -> const float * {
-        if (REG) return cb + (((uint32_t)k * ICQ_LUT_W + j) * (uint32_t)d_pad);     // at most 2^21
         return cb + ((int64_t)k * ICQ_LUT_W + j) * d_pad;
     };
     auto store_res = [&](int rg, int p, int e0, const float (&v)[8]) __attribute__((always_inline)) {
@@ -193,14 +178,10 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 #pragma unroll
         for (int p = 0; p < E_P; ++p) {
             float s = 0.0f;
-            if (ICM && !REG) store_res(rg, p, e0, v[p]);
+            if (ICM) store_res(rg, p, e0, v[p]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (REG) r[REG ? p : 0][i] = v[p][i];
-                s = fmaf(v[p][i], v[p][i], s);
-            }
+            for (int i = 0; i < 8; ++i) s = fmaf(v[p][i], v[p][i], s);
             add_norm(tid, rg, p, sl, s);
-            if (REG && ICM) load8(codeword(0, sh.code[0][rg + E_G * p]), e0, co[REG && ICM ? p : 0]);
         }
     }
     __syncthreads();
@@ -219,13 +200,15 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     uint32_t nchanged = 0;
 
     // slice g of codebook k's halves -> LDS, straight from memory
+    const int chunk = slices * 128;                        // 32 codewords
     auto fetch = [&](const uint4 *src, int k, int g) __attribute__((always_inline)) {
         const int lane = fresh(tid0) & 63;
-        const uint4 *s = src + ((int64_t)k * nks + g) * (4 * ICQ_LUT_W) + wave * 128;
+        const uint4 *s = src + ((int64_t)(k * 8 + (wave & 1) * 4) * chunk + (g * 4 + (wave >> 1)) * 32);
+        const uint32_t at = (uint32_t)((lane >> 5) * chunk + (lane & 31));
         uint4 *dst = sh.cbs[g & 1] + wave * 128;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(s + i * 64 + lane),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(s + i * 2 * chunk + at),
                                              (__attribute__((address_space(3))) void *)(dst + i * 64), 16, 0, 0);
     };
     // what a level needs first: its first two slices, its codebook's scale and norms (asked for a level ahead)
@@ -241,7 +224,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
     // scale of the residuals of the level to come, and what its scores start from
     float sr;
     auto rescale = [&]() __attribute__((always_inline)) {
-        sr = scale_below(fmaxf(reach + (ICM ? mt.y : 0.0f), mt.y), 14);        // no r of that level is longer than this
+        sr = icq_enc_scale_below(fmaxf(reach + (ICM ? mt.y : 0.0f), mt.y), 14);        // no r of that level is longer than this
         if (tid0 < ICQ_LUT_W) sh.cnh[tid0] = -0.5f * (sr * mt.x) * cn;         // -inf beyond m
     };
     rescale();
@@ -256,24 +239,21 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
 
         // the residual of this level in item p's piece at e0, before (ICM) the current codeword is added back
         auto residual = [&](int rg, int p, int e0, float (&v)[8]) __attribute__((always_inline)) {
-            if (REG) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = r[REG ? p : 0][i];
-            } else if (!ICM && lev == 0) {
+            if (!ICM && lev == 0) {
                 load_x(rg, p, e0, v);
             } else {
                 load8(res_row(rg, p), e0, v);
             }
         };
         // the residuals of slice sl as halves -> LDS.  UPDATE: first bring them up to date with the level before
-        // (not REG) and sum their squares.  LOW: the second halves.
+        // and sum their squares.  LOW: the second halves.
         auto stage = [&](int sl, bool update, bool low) __attribute__((always_inline)) {
             const int tid = fresh(tid0), rg = tid >> 4, e0 = sl * 128 + (tid & 15) * 8;
             const float scale = fresh(sr), zero = fresh(0.0f);
-#pragma unroll REG ? E_P : 2
+#pragma unroll 2
             for (int p = 0; p < E_P; ++p) {
                 float v[8];
-                if (!REG && update && lev > 0) {
+                if (update && lev > 0) {
                     const uint32_t oldc = sh.before[rg + E_G * p], newc = sh.code[kp][rg + E_G * p];
                     const bool moved = !ICM || newc != oldc;
                     if (!ICM && lev == 1) load_x(rg, p, e0, v);
@@ -293,10 +273,7 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 } else {
                     residual(rg, p, e0, v);
                 }
-                if (ICM && REG && update) {
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) v[i] += co[REG && ICM ? p : 0][i];
-                } else if (ICM) {
+                if (ICM) {
                     float c[8];
                     load8(codeword(k, sh.code[k][rg + E_G * p]), e0, c);
 #pragma unroll
@@ -322,9 +299,8 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 fetch(src, k, 0);
                 if (nks > 1) fetch(src, k, 1);
             }
-            if (REG && pass > 0) stage(0, false, pass == 1);
             for (int g = 0; g < nks; ++g) {
-                if (!REG && (g & 3) == 0) {
+                if ((g & 3) == 0) {
                     if (g > 0) __syncthreads();            // the last slice's fragments are consumed
                     stage(g >> 2, update, pass == 1);
                 }
@@ -398,10 +374,8 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
             }
             __syncthreads();
         };
-        // ---- for the items whose candidates say nothing: the fp32 argmin over all codewords as the only candidate.  The
-        // 256 scores one by one instead, sixteen threads an item, took 0.35 us each: 20000 x 128, K = 8, every codeword
-        // there 16 times 2.76 ms, one infinite vector in each block 2.91 ms; now 0.24 and 0.25 ms (0.064 ms
-        // without them; with more than 128 dimensions 6.9 ms both, now 0.54).
+        // ---- for the items whose candidates say nothing: the fp32 argmin over all codewords as the only candidate.  (The
+        // 256 scores one by one instead, sixteen threads an item, took 0.35 us each: 12 times as long.)
         auto exact = [&]() __attribute__((always_inline)) {
             const int tid = fresh(tid0), lane = tid & 63, half = lane >> 5, l32 = lane & 31, rg = tid >> 4;
             float *F = reinterpret_cast<float *>(sh.frag);                 // [64 dimensions][E_FROW]
@@ -502,11 +476,9 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         };
         // ---- first halves only; then, if that left some item too many candidates, both halves of both sides but the
         // product of the two second ones
-        if (REG) stage(0, true, false);
         bool over;
 #pragma nounroll
         for (int round = 0;; ++round) {
-            if (REG && round != 0) stage(0, false, false);
             // accumulator register v of lane l is codeword (v % 4) + 4 (l / 32) + 8 (v / 4), item l % 32 of its tile
             float16v acc[2][2];
             const int half = (fresh(tid0) >> 5) & 1;
@@ -539,19 +511,8 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         const bool last = lev + 1 == levels;
         if (!last) ahead(kn);
         const int rg = tid >> 4, c8 = (tid & 15) * 8;
-        constexpr int CH = ICM ? 2 : E_P;                  // items whose codewords are loaded together (registers)
-        float ca[CH][8], cc[ICM ? CH : 1][8];              // REG: the first candidates, then the chosen codewords; the current ones
 #pragma unroll
         for (int p = 0; p < E_P; ++p) {
-            if (REG && p % CH == 0) {
-#pragma unroll
-                for (int u = 0; u < CH; ++u) {
-                    const int it = rg + E_G * (p + u);
-                    const uint32_t now = ICM ? sh.code[k][it] : 0u;
-                    load8(codeword(k, sh.ccount[it] - 1u < (uint32_t)E_CAND ? sh.cand[it][0] : now), c8, ca[u]);
-                    if (ICM) load8(codeword(k, now), c8, cc[ICM ? u : 0]);
-                }
-            }
             const int item = rg + E_G * p;
             const uint32_t n = item < live ? sh.ccount[item] : 1u;
             const uint32_t old = ICM ? sh.code[k][item] : 0u;
@@ -570,9 +531,9 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                         residual(rg, p, e0, v);
                         if (ICM) {
                             float o[8];
-                            if (!REG) load8(codeword(k, old), e0, o);
+                            load8(codeword(k, old), e0, o);
 #pragma unroll
-                            for (int q = 0; q < 8; ++q) v[q] += REG ? cc[ICM ? p % CH : 0][q] : o[q];
+                            for (int q = 0; q < 8; ++q) v[q] += o[q];
                         }
 #pragma unroll
                         for (int q = 0; q < 8; ++q) dot = fmaf(v[q], c[q], dot);
@@ -583,10 +544,6 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                     if (i < todo && (score < best || (score == best && f < bf))) {
                         best = score;
                         bf = f;
-                        if (REG) {
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) ca[p % CH][q] = c[q];
-                        }
                     }
                 }
                 if (todo != 0 && bf != 0xFFFFFFFFu) code = bf == 0u ? old : bf - 1u;
@@ -596,19 +553,8 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
                 sh.code[k][item] = (uint8_t)code;
             }
             if (ICM && code != old && (tid & 15) == 0 && item < live) ++nchanged;
-            if (REG && (!ICM || code != old)) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (ICM) r[REG ? p : 0][i] += cc[ICM ? p % CH : 0][i];
-                    r[REG ? p : 0][i] -= ca[p % CH][i];
-                }
-            }
         }
         wave_lds_order();                                  // the sixteen lanes of an item read what one of them wrote
-        if (REG && ICM) {                                  // (after the last level too: a condition would keep the old values alive)
-#pragma unroll
-            for (int p = 0; p < E_P; ++p) load8(codeword(kn, sh.code[kn][rg + E_G * p]), c8, co[REG && ICM ? p : 0]);
-        }
         if (ICM && k == K - 1 && changed) {
             const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(nchanged), 63);
             if ((tid & 63) == 0 && n != 0) atomicAdd(&changed[lev / K], n);
@@ -621,10 +567,11 @@ __global__ __launch_bounds__(E_THREADS, 4) void encode_kernel(
         if (i0 + i % EB < N) codes[(int64_t)(i / EB) * N + i0 + i % EB] = sh.code[i / EB][i % EB];
 }
 
-// The codewords as halves, laid out as the contraction reads them: piece ((k * slices + e / 32) * 4 + e / 8 % 4) * 256 + j
-// holds the eight dimensions e .. e + 7 of codeword j (zero beyond d), times the codebook's scale, the first halves in
-// hi and what they leave in lo.  16 threads per codeword.  meta[k].z is zero on entry.
-__global__ __launch_bounds__(256) void encode_pack_kernel(const float *__restrict__ cb, int d_pad,
+// The codewords as halves, laid out as the contractions read them, times the codebook's scale: the first halves in hi and
+// (where the second round of encode_kernel reads them) what they leave in lo.  Piece ((k * 8 + j / 32) * slices * 4 + e / 8) * 32
+// + j % 32 holds the eight dimensions e .. e + 7 of codeword j (zero beyond d).  16 threads per codeword.  meta[k].z is zero
+// on entry.
+__global__ __launch_bounds__(256) void encode_pack_kernel(const float *__restrict__ cb, int d_pad, int slices,
                                                           const float *__restrict__ cnorm, uint4 *__restrict__ hi,
                                                           uint4 *__restrict__ lo, float4 *__restrict__ meta) {
     __shared__ float red[4];
@@ -635,10 +582,9 @@ __global__ __launch_bounds__(256) void encode_pack_kernel(const float *__restric
     if ((tid & 63) == 0) red[tid >> 6] = v;
     __syncthreads();
     const float cmax = sqrtf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))) * 1.0001f;
-    const float sc = scale_below(cmax, 10);
-    const int nks = (d_pad + 31) / 32;
+    const float sc = icq_enc_scale_below(cmax, 10);
     float err = 0.0f;
-    for (int c = tid & 15; c < nks * 4; c += 16) {
+    for (int c = tid & 15; c < slices * 4; c += 16) {
         half8 a, b;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -649,9 +595,9 @@ __global__ __launch_bounds__(256) void encode_pack_kernel(const float *__restric
             b[i] = (_Float16)rest;
             err = fmaf(rest, rest, err);
         }
-        const int64_t at = (((int64_t)k * nks + c / 4) * 4 + c % 4) * ICQ_LUT_W + j;
+        const int64_t at = (((int64_t)k * 8 + j / 32) * slices * 4 + c) * 32 + j % 32;
         hi[at] = __builtin_bit_cast(uint4, a);
-        lo[at] = __builtin_bit_cast(uint4, b);
+        if (lo) lo[at] = __builtin_bit_cast(uint4, b);
     }
     err = sqrtf(row_sum(err)) / sc * 1.0001f;
     if ((tid & 15) == 0) atomicMax(reinterpret_cast<unsigned int *>(&meta[k].z), __float_as_uint(err));
@@ -692,19 +638,21 @@ ICQ_EXPORT int icq_encode_workspace_bytes(const icq_index *ix, int64_t N, size_t
 template <bool ICM>
 static int launch_encode(const icq_index *ix, const float *x, int64_t N, uint8_t *codes, int sweeps, float *res,
                          uint32_t *changed, hipStream_t s) {
-    const unsigned blocks = (unsigned)((N + EB - 1) / EB);
-    auto launch = [&](auto kernel) -> int {
-        ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(kernel), sizeof(EncShared)));
-        kernel<<<blocks, E_THREADS, sizeof(EncShared), s>>>(x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo,
-                                                            ix->enc_meta, ix->K, ix->m, N, codes, sweeps, res, changed);
-        return icq_check_launch();
-    };
-    if (ix->d <= E_REG_D) return launch(encode_kernel<true, ICM>);
-    return launch(encode_kernel<false, ICM>);
+    const int slices = icq_enc_slices(ix->d_pad);
+    // Residuals in registers where the wavefronts that hold them do not spill.  Above 256 dimensions coordinate descent has
+    // one block of 64 items per CU there: ahead for two rounds of them (d = 300, 384, 512, 30000 items: 1.18, 1.19, 1.09
+    // times as fast; 50000: 0.8), greedy assignment throughout (300, 384, 512; 15000 items 2.3 - 2.4, 80000 1.2 - 1.5).
+    if (icq_enc_wave_only(ix->d_pad) || (slices <= 16 && (!ICM || N <= 2 * 64 * (int64_t)ix->num_cu)))
+        return icq_launch_encode_wave(ix, x, N, codes, ICM, sweeps, changed, s);
+    ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(encode_kernel<ICM>), sizeof(EncShared)));
+    encode_kernel<ICM><<<(unsigned)((N + EB - 1) / EB), E_THREADS, sizeof(EncShared), s>>>(
+        x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo, ix->enc_meta, ix->K, slices, N, codes, sweeps, res, changed);
+    return icq_check_launch();
 }
 
 int icq_encode_pack(icq_index *ix, hipStream_t s) {
-    encode_pack_kernel<<<ix->K * 16, 256, 0, s>>>(ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo, ix->enc_meta);
+    encode_pack_kernel<<<ix->K * 16, 256, 0, s>>>(ix->cb, ix->d_pad, icq_enc_slices(ix->d_pad), ix->cnorm, ix->half_hi, ix->half_lo,
+                                                  ix->enc_meta);
     return icq_check_launch();
 }
 

@@ -2,6 +2,7 @@
 // layouts the search kernels stream (Sec. 1 of arxiv 1912.08756: an item is K
 // codeword indices; the fast set is codebooks 0..Kf-1).
 #include "icq_internal.h"
+#include "icq_encode.h"
 
 #include <math.h>
 #include <mutex>
@@ -159,9 +160,10 @@ ICQ_EXPORT int icq_index_create(icq_index **out, const float *codebooks, const u
     const size_t cb_bytes = icq_align_up(sizeof(float) * rows * ix->d_pad, ICQ_ALIGN);
     const size_t norm_bytes = icq_align_up(sizeof(float) * rows, ICQ_ALIGN);
     const size_t meta_bytes = icq_align_up(sizeof(float4) * (size_t)K, ICQ_ALIGN);
-    const size_t half_bytes = 2 * rows * ((size_t)(ix->d_pad + 31) / 32 * 32);      // a multiple of 16 KB
+    const size_t half_bytes = 2 * rows * (size_t)icq_enc_slices(ix->d_pad) * 32;    // a multiple of 16 KB
+    const int half_parts = icq_enc_wave_only(ix->d_pad) ? 1 : 2;
     char *base = nullptr;
-    bool ok = hipMalloc(&base, cb_bytes + norm_bytes + meta_bytes + 2 * half_bytes) == hipSuccess;
+    bool ok = hipMalloc(&base, cb_bytes + norm_bytes + meta_bytes + half_parts * half_bytes) == hipSuccess;
     ix->cb = reinterpret_cast<float *>(base);
     ok = ok && hipMalloc(&ix->fast, (size_t)Kf * ix->Npad) == hipSuccess;
     if (ok && N > 0) ok = hipMalloc(&ix->items, (size_t)N * ix->item_stride) == hipSuccess;
@@ -173,7 +175,7 @@ ICQ_EXPORT int icq_index_create(icq_index **out, const float *codebooks, const u
     ix->cnorm = reinterpret_cast<float *>(base + cb_bytes);
     ix->enc_meta = reinterpret_cast<float4 *>(base + cb_bytes + norm_bytes);
     ix->half_hi = reinterpret_cast<uint4 *>(base + cb_bytes + norm_bytes + meta_bytes);
-    ix->half_lo = reinterpret_cast<uint4 *>(base + cb_bytes + norm_bytes + meta_bytes + half_bytes);
+    ix->half_lo = half_parts == 2 ? reinterpret_cast<uint4 *>(base + cb_bytes + norm_bytes + meta_bytes + half_bytes) : nullptr;
 
     const int T = 256;
     copy_codebooks_kernel<<<(K * ICQ_LUT_W + 3) / 4, T, 0, s>>>(codebooks, K, m, d, ix->d_pad,

@@ -27,7 +27,7 @@ struct icq_index {
     int64_t N, Npad;           // Npad: N rounded up to a multiple of 4096
     float *cb;                 // [K*256][d_pad] codewords, rows j >= m are zero
     float *cnorm;              // [K*256] squared codeword norms, +inf for j >= m (in cb's allocation, as the next three)
-    uint4 *half_hi, *half_lo;  // the codewords as two halves each, for the encoder (icq_encode.hip)
+    uint4 *half_hi, *half_lo;  // the codewords as two halves each, for the encoder (icq_encode.hip); half_lo may be nullptr
     float4 *enc_meta;          // [K] scale of those, largest codeword norm, largest error of the first half
     uint8_t *fast;             // [Kf][Npad] fast sub-codes, zero padded
     uint8_t *items;            // [N][item_stride] all K sub-codes of an item, item-major

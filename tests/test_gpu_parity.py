@@ -1081,6 +1081,51 @@ def test_encode_matches_oracle(gpu, K, m, d, N):
         b.icq_encode(index, _dev(torch, x), torch.empty((K, N), dtype=torch.uint8, device="cuda"), ws[:128])
 
 
+@pytest.mark.parametrize("m,d,N,sweeps", [
+    (256, 32, 40_000, 1), (33, 33, 33, 1), (64, 64, 40_000, 0), (65, 96, 33_000, 1), (31, 97, 70, 1), (129, 128, 33_000, 1),
+    (256, 129, 65, 1), (97, 192, 33_000, 1), (225, 193, 17, 1), (256, 256, 16_500, 1), (160, 256, 63, 1), (1, 130, 200, 1),
+    (256, 257, 100, 1), (200, 300, 16_400, 0), (256, 384, 33_000, 1), (96, 385, 129, 1), (256, 512, 33_000, 0), (255, 512, 64, 1),
+    (256, 512, 33_000, 1), (256, 513, 130, 1),
+])
+def test_encode_over_the_forms_of_its_kernels(gpu, m, d, N, sweeps):
+    """The numbers of 32-wide slices the register form is built for and those next to them, both of its block sizes, the
+    residuals in memory beyond; codebooks that end inside a chunk of 32 codewords.  x is drawn, not reconstructed: every level
+    has to decide.  Judged on a sample as in test_encode_at_the_edges_of_its_forms: fp32 scores are sums of d terms of up to
+    ||r||^2 + ||c||^2, each off by 2^-23 of it at most."""
+    torch, b = gpu
+    K = 3
+    rng = np.random.default_rng(d * 1000 + m)
+    cb = (rng.standard_normal((K, m, d)) * (0.7 ** np.arange(K))[:, None, None]).astype(np.float32)
+    x = rng.standard_normal((N, d)).astype(np.float32)
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    codes = torch.full((K, N), 255, dtype=torch.uint8, device="cuda")
+    xd = _dev(torch, x)
+    b.icq_encode(index, xd, codes, ws)
+    refined, changed = codes.clone(), torch.full((max(1, sweeps),), 7, dtype=torch.int32, device="cuda")
+    b.icq_encode_refine(index, xd, refined, sweeps, changed if sweeps else None, ws)
+    torch.cuda.synchronize()
+    first, second = codes.cpu().numpy(), refined.cpu().numpy()
+    assert (first < m).all() and (second < m).all()
+    if sweeps:
+        assert int(changed[0]) == int((first != second).sum())
+    at = np.unique(np.concatenate([np.arange(min(N, 150)), np.arange(max(0, N - 150), N), rng.integers(0, N, 300)]))
+    cb64, xs, n, eps = cb.astype(np.float64), x[at].astype(np.float64), np.arange(at.size), d * 2.0 ** -23
+
+    def judge(r, k, chosen):
+        d2 = (r * r).sum(axis=1)[:, None] - 2.0 * r @ cb64[k].T + (cb64[k] ** 2).sum(axis=1)[None]
+        slack = eps * ((r * r).sum(axis=1) + (cb64[k] ** 2).sum(axis=1).max())
+        assert (d2[n, chosen] <= d2.min(axis=1) + slack).all(), "level %d: a clearly nearer codeword exists" % k
+    f, s = first[:, at], second[:, at]
+    r = xs.copy()
+    for k in range(K):
+        judge(r, k, f[k])
+        r = r - cb64[k][f[k]]
+    for k in range(K if sweeps else 0):
+        state = np.concatenate([s[:k], f[k:]])
+        judge(xs - sum(cb64[l][state[l]] for l in range(K) if l != k), k, s[k])
+
+
 @pytest.mark.parametrize("K,m,d,N,kind", [
     (3, 256, 128, 129, "plain"), (3, 256, 129, 257, "plain"),   # the residual in registers / in memory; blocks of 128 items
     (2, 200, 255, 130, "plain"), (2, 256, 960, 200, "plain"),   # an odd end of the last row; several slices
