@@ -276,15 +276,16 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
 // bits (one 128-bit load per lane, two chunks ahead), a prefix of their popcounts, the set bits
 // expanded into a position list in the wavefront's part of LDS, then per position the record
 // gather, the K table reads and the key, as in refine_dist_kernel.
+// (Few queries: a wavefront takes half or a quarter of a chunk, see icq_launch_refine_masks; what follows says chunk for either.)
 // Every 65th chunk is done in a first launch, unfiltered (!FILTER); the select kernel's topk-th
 // distance of those keys then bounds what the other chunks add in a second launch (FILTER: keys
 // above it are dropped; ties at it are kept, the final select decides).  The final lists are
 // unchanged -- at least topk keys at or below the bound are already there -- and the key lists
-// shrink to a few per cent.  Survivors are counted from the popcounts.
+// shrink to a few per cent.  Survivors are counted from the popcounts, added up per block.
 constexpr int RM_THREADS = 256;
 constexpr int RM_WAVES = RM_THREADS / 64;
 constexpr uint32_t RM_CHUNK = 32768;                  // positions per chunk; a multiple of the scan kernel's block step
-constexpr int RM_WORDS = RM_CHUNK / 32 / 64;          // 32-bit words of hit bits per lane and chunk
+constexpr int RM_FULL = RM_CHUNK / 32 / 64;           // 32-bit words of hit bits per lane and chunk (pieces of chunks: fewer)
 constexpr int RM_PER = 4;                             // records a lane gathers together
 constexpr int RM_LIST = 512;                          // positions a wavefront expands per round
 constexpr int RM_QPB = 1;                             // queries per block (two: 1.39 against 1.25 ms at N = 1e8, 128 queries)
@@ -299,7 +300,7 @@ static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into th
 // stage 1 makes item by item -- are below thr[q].  Only survivors are counted and get keys.
 // The filtered launch is held to the registers of five wavefronts per SIMD (the exact comparison's few
 // more would cost the fifth: 1.17 -> 1.29 ms for the stage at N = 1e8).
-template <int WORDS, bool FILTER, int QPB, bool EXACT>
+template <int WORDS, bool FILTER, int QPB, bool EXACT, int RM_WORDS>
 __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel(
     const uint8_t *__restrict__ items, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
     size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, uint32_t seed_every, int window, int xs_shift, int Q,
@@ -307,7 +308,9 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
     int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
     __shared__ __attribute__((aligned(16))) float T_all[QPB][4 * WORDS * ICQ_LUT_W];
     __shared__ uint16_t cand_all[RM_WAVES][RM_LIST];  // positions inside the chunk (RM_CHUNK <= 65536)
+    __shared__ uint32_t sum_all[QPB], done_all[QPB];  // survivors of the block, wavefronts that have added theirs
     constexpr int RW = WORDS;
+    constexpr uint32_t PIECE = RM_WORDS * 2048;       // positions
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         return FILTER ? i + i / (seed_every - 1u) + 1u : i * seed_every;   // the others : every seed_every-th
     };
     if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
-    // Word r of this lane covers the 32 positions from c * RM_CHUNK + (r * 64 + lane) * 32: neighbouring
+    // Word r of this lane covers the 32 positions from c * PIECE + (r * 64 + lane) * 32: neighbouring
     // words sit in neighbouring lanes, so a dense stretch of hits is shared out among many lanes.
     // The wavefront's work is the sequence (chunk j, query qq), qq fastest; the next one's hit bits travel
     // while the current one is worked on.
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
     {
         const uint32_t c0 = c != 0xFFFFFFFFu ? c : 0u;
 #pragma unroll
-        for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mq + (size_t)c0 * (RM_CHUNK / 32) + r * 64);
+        for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mq + (size_t)c0 * (PIECE / 32) + r * 64);
     }
     // the queries' tables -> LDS, one table per record byte, zero beyond K
 #pragma unroll
@@ -364,6 +367,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
             if (ob < 0xFF800000u) bound_all[g] = ob;  // a finite topk-th distance; else the list is still open
         }
     }
+    if (tid < QPB) sum_all[tid] = done_all[tid] = 0;
     __syncthreads();                                  // the only barrier: from here on every wavefront is on its own
     uint32_t survivors[QPB];                          // of this wavefront's chunks (wavefront-uniform)
     uint32_t lane_survivors[QPB];                     // EXACT: counted per lane, summed at the end
@@ -381,7 +385,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
             cn = chunk_of(jn);
         }
         if (cn != 0xFFFFFFFFu) {
-            const uint32_t *mn = mq + (size_t)qn * mask_words + (size_t)cn * (RM_CHUNK / 32);
+            const uint32_t *mn = mq + (size_t)qn * mask_words + (size_t)cn * (PIECE / 32);
 #pragma unroll
             for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mn + r * 64);
         }
@@ -408,7 +412,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         if (!FILTER && !EXACT && total != 0) {
             if (lane == 0) chunk_slot = atomicAdd(&key_count[q], total);
         }
-        const uint32_t cbase = c * RM_CHUNK, p0 = lane * 32u;
+        const uint32_t cbase = c * PIECE, p0 = lane * 32u;
         for (uint32_t lo = 0; lo < total; lo += RM_LIST) {      // wavefront-uniform; one round unless the chunk is dense
             wave_lds_order();                         // the last round's reads are done
             if (off + mine > lo && off < lo + RM_LIST) {
@@ -512,9 +516,17 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         for (int g = 0; g < QPB; ++g)
             survivors[g] = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors[g]), 63);
     }
+    // one addition per block: thousands of wavefronts of one query at one counter would take 11 ns each.  The last of the four
+    // to come here makes it.
 #pragma unroll
-    for (int g = 0; g < QPB; ++g)
-        if (lane == 0 && (uint32_t)g < nq && survivors[g] != 0) atomicAdd(&cand_count[q0 + g], survivors[g]);
+    for (int g = 0; g < QPB; ++g) {
+        if (lane != 0) continue;
+        atomicAdd(&sum_all[g], survivors[g]);
+        __threadfence_block();
+        if (atomicAdd(&done_all[g], 1u) != RM_WAVES - 1) continue;
+        const uint32_t sum = atomicAdd(&sum_all[g], 0u);
+        if ((uint32_t)g < nq && sum != 0) atomicAdd(&cand_count[q0 + g], sum);
+    }
 }
 
 }  // namespace
@@ -620,28 +632,38 @@ int64_t icq_mask_scan_end(const icq_index *ix) {
 
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, u64 *keys, uint32_t *key_count,
-                            uint32_t *ticket, uint32_t *cand_count, const float *thr, uint32_t *out_ids, float *out_dist,
-                            hipStream_t s) {
+                            uint32_t *ticket, uint32_t *cand_count, const float *thr, bool few, uint32_t *out_ids,
+                            float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
     const bool g2 = icq_g2_usable(ix);
     const uint8_t *items = g2 ? ix->items_grouped : ix->items;
     const uint32_t *perm = g2 ? ix->perm : nullptr;
-    const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
     // few chunks: one unfiltered launch over all of them (a bound would save less than its second launch costs)
-    const uint32_t seed_every = chunks < 2 * RM_SEED_EVERY ? 1u : (uint32_t)RM_SEED_EVERY;
+    const uint32_t seed_every = scan_end / RM_CHUNK < 2 * RM_SEED_EVERY ? 1u : (uint32_t)RM_SEED_EVERY;
+    // A wavefront takes a chunk at a time, or a piece of one: half a chunk while the (chunk, query) pairs are few enough that
+    // the chip is not full of whole ones (1e8 items, 1 / 8 / 64 / 128 queries, whole call: 184 / 386 / 1080 / 1800 us with whole
+    // chunks, 156 / 320 / 1028 / 1831 with halves; 2e7 items, 128 queries: 481 / 455), a quarter for the very few (5e6 items,
+    // 1 query: 59 / 48 / 43 us with whole ones, halves, quarters; 8: 101 / 88 / 95).  Where little is found in a chunk (few:
+    // 7e6 items, 128 queries, 0.1 % 89 / 104 us) or a block's tables serve one launch over all of them (1e6 items, 200
+    // queries: 154 / 163) whole ones pay sooner.
+    const uint64_t pairs = (uint64_t)(scan_end / RM_CHUNK) * (uint64_t)Q;
+    const uint64_t halves = seed_every == 1u ? 512u : few ? 8192u : Q <= 64 ? 262144u : 131072u;
+    const int words = pairs <= 320 ? RM_FULL / 4 : pairs <= halves ? RM_FULL / 2 : RM_FULL;
+    const uint32_t chunks = (uint32_t)(scan_end / (2048 * words));
     const uint32_t nseed = (chunks + seed_every - 1) / seed_every, nmain = chunks - nseed;
     auto select = [&](bool more) -> int {
         return icq_launch_select(keys, key_count, cap, Q, topk, splits, more, ticket, out_ids, out_dist, s);
     };
-    // Chunks per block: few, so that the blocks in flight (two windows' worth when the queries fill the
-    // chip) keep to a few chunks per XCD; more when there are so few queries that the table load would weigh.
+    // Pieces per block: few, so that the blocks in flight (two windows' worth when the queries fill the
+    // chip) keep to a few chunks per XCD.  With few queries one per wavefront.
     // An unfiltered launch with little work for the chip (the first part of a large index: one chunk per
     // wavefront is all the parallelism there is) is spread over as many blocks as possible; one that is the
     // whole stage (a small index, many queries) takes full windows, and the chunks are cut fewer than 8
     // ways when 8 windows' worth do not exist: 16 MB of records stay in the caches wherever the blocks run.
     auto plan_for = [&](uint32_t nsel, bool filtered, int *xs_shift) -> int {
-        int w = Q >= 8 ? (g2 ? 12 : 8) : 16;          // at N = 1e8, 128 queries, pair ordering: 16 / 12 / 8 / 6 / 4: 1.105 / 1.090 / 1.109 / 1.18 / 1.31 ms
-        if (!filtered && Q >= 8) w = (uint64_t)nsel * (uint64_t)Q <= 16384u ? 4 : 16;
+        int w = words == RM_FULL && g2 ? 12 : 8;      // at N = 1e8, 128 queries, pair ordering: 16 / 12 / 8 / 6 / 4: 1.105 / 1.090 / 1.109 / 1.18 / 1.31 ms
+        if ((uint64_t)nsel * (uint64_t)Q <= 16384u && (!filtered || Q < 8)) w = 4;
+        else if (!filtered) w = 16 * RM_FULL / words;
         // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
         // keeps a chunk's records in ONE L2 is worth more than the longer windows: 1e4 queries, 1e6 items,
         // 8-byte records: 0.80 ms with it, 0.83 without)
@@ -660,14 +682,14 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         const unsigned per_win = (unsigned)window << xs_shift;                                               \
         const unsigned nwin = ((NSEL) + per_win - 1) / per_win;                                              \
         const unsigned ngroups = ((unsigned)Q + RM_QPB - 1) / RM_QPB;                                        \
-        if (thr)                                                                                             \
-            refine_mask_kernel<W, FILTER, RM_QPB, true><<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(           \
+        auto go = [&](auto kernel) {                                                                         \
+            kernel<<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(                                      \
                 items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, window, xs_shift, Q, out_dist, topk,     \
-                keys, key_count, cap, cand_count, thr, ix->Kf);                                         \
-        else                                                                                                 \
-            refine_mask_kernel<W, FILTER, RM_QPB, false><<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(          \
-                items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, window, xs_shift, Q, out_dist, topk,     \
-                keys, key_count, cap, cand_count, nullptr, ix->Kf);                                     \
+                keys, key_count, cap, cand_count, thr, ix->Kf);                                              \
+        };                                                                                                   \
+        if (words == RM_FULL / 4) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 4>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 4>); } \
+        else if (words == RM_FULL / 2) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 2>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 2>); } \
+        else { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL>); }         \
     } while (0)
     switch (ix->item_stride) {
         case 4: ICQ_RM_LAUNCH(1, false, nseed); break;

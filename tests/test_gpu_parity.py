@@ -1026,6 +1026,43 @@ def test_running_search_at_full_size_sampled_against_oracle(gpu):
         del P, D
 
 
+@pytest.mark.parametrize("K,Kf,mode", [(4, 3, 0), (12, 4, 0), (4, 3, 1)])
+def test_search_from_hit_bits_in_pieces_of_chunks(gpu, K, Kf, mode):
+    """Stage 2 takes whole, half or quarter chunks of hit bits by the number of (chunk, query) pairs: 2100 queries at once, in
+    twos and in forties have the same lists, distances and counts, bit for bit (a query's work does not depend on the others)."""
+    torch, b = gpu
+    N, Q, d, topk = (1 << 22) + 4097, 2100, 16, 12
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    cb = torch.randn((K, 256, d), device="cuda", generator=gen) * torch.tensor([0.8 ** k for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, 256, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    index = b.icq_index_create(cb.contiguous(), codes, Kf)
+    b.icq_index_set_scan_mode(index, mode)
+    queries = 1.5 * torch.randn((Q, d), device="cuda", generator=gen)
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = sum(lut[:, k].index_select(1, codes[k, :20_000].long()) for k in range(Kf))
+    thr = P.kthvalue(30, dim=1).values.contiguous()            # 0.15 % of the items
+    thr[3], thr[4] = -1.0, float("nan")                        # nothing survives
+    cap = 20_000
+
+    def run(step):
+        ids = torch.empty((Q, topk), dtype=torch.int32, device="cuda")
+        dist = torch.empty((Q, topk), device="cuda")
+        count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.icq_workspace_bytes(index, min(Q, step), cap, topk), dtype=torch.uint8, device="cuda")
+        for q in range(0, Q if step >= 40 else 24, step):
+            at = slice(q, min(Q, q + step))
+            b.icq_search(index, queries[at], thr[at], cap, topk, ids[at], dist[at], count[at], ws)
+        torch.cuda.synchronize()
+        return ids, dist, count
+    want = run(Q)
+    assert (want[2][3:5] == 0).all() and want[2].float().mean() > 1000
+    for step, upto in ((40, Q), (2, 24)):
+        for x, y in zip(run(step), want):
+            assert torch.equal(x[:upto], y[:upto])
+
+
 def test_op_counts_match_oracle(gpu):
     torch, b = gpu
     cfg = small("C1", 5_000, 300)
