@@ -476,11 +476,8 @@ int launch_stream_as(const icq_index *ix, const float *lut, int Q, const float *
     const uint32_t step = (uint32_t)(threads / 64) * 1024u;
     const int64_t nitems = G2 ? ix->g2_npos : ix->N;          // scan positions that can hold an item
     const int64_t npos = MASK ? scan_end : nitems;            // positions to walk
-    // one wave of equally loaded blocks: the chip is filled once and every block streams a long run
-    int64_t chunks = ((int64_t)ix->num_cu + groups - 1) / groups;
-    int64_t max_chunks = (npos + step - 1) / step;
-    if (chunks > max_chunks) chunks = max_chunks;
-    if (chunks < 1) chunks = 1;
+    // whole rounds of equally loaded blocks that stream long runs
+    int64_t chunks = icq_scan_pieces(ix->num_cu, groups, (npos + step - 1) / step, 2);
     uint32_t per = (uint32_t)(((npos + chunks - 1) / chunks + step - 1) / step * step);
     chunks = (npos + per - 1) / per;
     // query groups along grid.y, at most 65535 per launch
