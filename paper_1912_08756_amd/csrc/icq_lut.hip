@@ -154,6 +154,81 @@ __global__ __launch_bounds__(256) void build_lut_kernel(const float *queries, in
     }
 }
 
+// The same table by single wavefronts, 32 queries x 32 entries each, operands straight from memory, eight slices ahead: no LDS
+// staging and no barrier.  Every sum has the terms of build_lut_kernel in the same order, so the tables are the same bit for bit.
+// What bounds it: the latency of a launch's loads and of a chain of d / 2 matrix instructions.  Against build_lut_kernel, whole
+// searches: one query over 1e6 items (d = 128, K = 8) 26.9 -> 23.3 us, 40 queries over 2e5 (d = 200, K = 16) 34.8 -> 30.9.
+constexpr int FD = 8;    // slices under way (four: one microsecond more from 64 to 256 dimensions)
+template <bool VEC>
+__global__ __launch_bounds__(64) void build_lut_few_kernel(const float *__restrict__ queries, int Q, int d,
+                                                           const float *__restrict__ cb, int d_pad,
+                                                           const float *__restrict__ cnorm, int ncols, float *__restrict__ lut,
+                                                           uint32_t *zero0, uint32_t *zero1, uint32_t *zero2) {
+    __shared__ __attribute__((aligned(16))) float qn_s[32];
+    const int lane = threadIdx.x, half = lane >> 5, l32 = lane & 31;
+    const int n0 = blockIdx.x * 32, q0 = blockIdx.y * 32;
+    const int qr = q0 + l32 < Q ? q0 + l32 : Q - 1;        // a row past Q reads the last query, its results are not stored
+    const float *qrow = queries + (int64_t)qr * d;
+    const float *brow = cb + (int64_t)(n0 + l32) * d_pad;
+    float4v a[FD][2], b[FD][2];
+    auto load = [&](int k0, float4v (&x)[2], float4v (&y)[2]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int e = k0 + 8 * half + 4 * h;           // values past d: see build_lut_kernel
+            if (VEC) {
+                x[h] = *reinterpret_cast<const float4v *>(qrow + (e < d ? e : d - 4));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[h][i] = qrow[e + i < d ? e + i : d - 1];
+            }
+            y[h] = *reinterpret_cast<const float4v *>(brow + e);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < FD; ++u) load(u * BK < d_pad ? u * BK : 0, a[u], b[u]);
+    const float cn = cnorm[n0 + l32];
+    if (blockIdx.x == 0 && half == 0 && q0 + l32 < Q) {    // the counters of a search call, see build_lut_kernel
+        if (zero0) zero0[q0 + l32] = 0u;
+        if (zero1) zero1[q0 + l32] = 0u;
+        if (zero2) zero2[q0 + l32] = 0u;
+    }
+    float16v acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+    float qn[2] = {0.0f, 0.0f};
+    for (int k0 = 0; k0 < d_pad; k0 += FD * BK) {
+#pragma unroll
+        for (int u = 0; u < FD; ++u) {
+            const int at = k0 + u * BK;
+            if (at >= d_pad) break;                        // uniform
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (at + 8 * half + 4 * h + i < d) qn[h] = fmaf(a[u][h][i], a[u][h][i], qn[h]);
+#pragma unroll
+            for (int s = 0; s < BK / 2; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][s >> 2][s & 3], b[u][s >> 2][s & 3], acc, 0, 0, 0);
+            const int next = at + FD * BK;
+            if (next < d_pad) load(next, a[u], b[u]);      // uniform
+        }
+    }
+    // ||q||^2: the four partial sums of a row, those of its upper half first
+    {
+        const float x = qn[1] + qn[0];
+        const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        if (half == 0) qn_s[l32] = __uint_as_float(p[1]) + __uint_as_float(p[0]);
+    }
+    wave_lds_order();
+    float *out = lut + (int64_t)(q0 + 4 * half) * ncols + n0 + l32;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const float4v q = *reinterpret_cast<const float4v *>(&qn_s[4 * half + 8 * w]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (q0 + 4 * half + 8 * w + i < Q) out[(int64_t)(8 * w + i) * ncols] = (q[i] + cn) - 2.0f * acc[4 * w + i];
+    }
+}
+
 }  // namespace
 
 int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float *lut, uint32_t *zero0,
@@ -179,6 +254,18 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
         // Slower: the entries as rows of the matrix instruction (16-byte stores of 32-byte pieces in 32
         // rows instead of 4-byte stores of whole 128-byte lines).
         const bool ahead = (int64_t)grid.x * grid.y < 4 * 256;
+        // Up to three wavefronts per CU; with more, the blocks that stage in LDS read the codebooks less often (K = 8, d = 256, table
+        // alone, 256 / 600 queries: 11 / 18 us against 13.5 / 15; K = 16, d = 960, whole search of 1e6 items, 10 / 37 / 130 / 200
+        // queries -- 128 / 256 / 640 / 896 wavefronts: 66 / 84 / 113 / 136 us against 77 / 93 / 121 / 131).
+        if ((int64_t)(nq + 31) / 32 * (ncols / 32) <= 3 * (int64_t)ix->num_cu) {
+            dim3 few((unsigned)(ncols / 32), (unsigned)((nq + 31) / 32));
+            auto go = [&](auto kernel) {
+                kernel<<<few, 64, 0, s>>>(qs, nq, ix->d, ix->cb, ix->d_pad, ix->cnorm, ncols, out, zero0 ? zero0 + q0 : nullptr,
+                                          zero1 ? zero1 + q0 : nullptr, zero2 ? zero2 + q0 : nullptr);
+            };
+            if (vec) go(build_lut_few_kernel<true>); else go(build_lut_few_kernel<false>);
+            continue;
+        }
         auto launch = [&](auto kernel) {
             kernel<<<grid, 256, 0, s>>>(qs, nq, ix->d, ix->cb, ix->d_pad, ix->cnorm, ncols, out,
                                         zero0 ? zero0 + q0 : nullptr, zero1 ? zero1 + q0 : nullptr,

@@ -1063,6 +1063,31 @@ def test_search_from_hit_bits_in_pieces_of_chunks(gpu, K, Kf, mode):
             assert torch.equal(x[:upto], y[:upto])
 
 
+@pytest.mark.parametrize("K,d", [(1, 1), (4, 17), (8, 100), (8, 128), (8, 132), (16, 33), (3, 260)])
+def test_tables_of_few_queries_equal_those_of_many(gpu, K, d):
+    """Few queries' tables come from wavefronts of their own, many queries' from blocks that stage in LDS: the same sums in the
+    same order, hence the same bits -- also of rows that are not 16-byte aligned, and with infinities and NaN."""
+    torch, b = gpu
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    cb = torch.randn((K, 200, d), device="cuda", generator=gen)
+    index = b.icq_index_create(cb, torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    many = 32 * (3 * 256 // (8 * K)) + 65
+    flat = torch.randn((many * d + 1,), device="cuda", generator=gen)
+    queries = flat[1:].view(many, d)
+    queries[5, d - 1], queries[7, 0], queries[40, d // 2] = float("inf"), float("nan"), -float("inf")
+    want = torch.empty((many, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, want)
+    for first, Q in ((0, 1), (0, 31), (3, 32), (5, 33), (1, 65)):
+        for aligned in (False, True):
+            q = queries[first:first + Q]
+            q = q.clone() if aligned else q.contiguous()
+            got = torch.full((Q, K, 256), 7.0, device="cuda")
+            b.icq_build_lut(index, q, got)
+            assert torch.equal(got.view(torch.int32), want[first:first + Q].view(torch.int32)) or \
+                ((got == want[first:first + Q]) | (got.isnan() & want[first:first + Q].isnan())).all()
+
+
 def test_op_counts_match_oracle(gpu):
     torch, b = gpu
     cfg = small("C1", 5_000, 300)
