@@ -1,11 +1,12 @@
 // Both stages of the two-step search (arxiv 1912.08756, Eq. 2 and Eq. 1) in one kernel, for an index of few items:
 // a small database, or the first tiles of the running search, where every item or every fifth one survives.
 //
-// A block takes 2048 items at a time for one query: their crude distances from the query's tables in LDS, the
+// A block takes 4096 items at a time for one query: their crude distances from the query's tables in LDS, the
 // survivors compacted into a list in LDS, and that list's exact distances as keys (order-preserving bits of D, id)
 // for the selection.  No candidate list goes through memory, the codes are read from the item records that the
-// second stage needs as well, and a list slot in memory is reserved once per 2048 items instead of once per
-// wavefront.  The table reads collide in LDS banks (codes are random, one copy of the tables, about five clocks per 64
+// second stage needs as well, and a list slot in memory is reserved once per 4096 items instead of once per
+// wavefront (one query's reservations go to one counter at 11 ns each: with 2048 items a step 10^6 items took 23.6 us, now 20.8; 8192
+// a step leave too few blocks, 3e5 items 15.8 / 17.6).  The table reads collide in LDS banks (codes are random, one copy of the tables, about five clocks per 64
 // reads); scan_stream_kernel's copies avoid that, but its block of 16384 items and its 128 KB of tables leave most of the
 // chip idle here and its lists cost atomics.
 // What bounds it: the LDS while survivors are few, the keys' stores when all survive (both sides: icq_small_usable).
@@ -16,7 +17,7 @@
 
 namespace {
 
-constexpr int SM_THREADS = 512;
+constexpr int SM_THREADS = 1024;
 constexpr int SM_PER = 4;                            // items per thread and step
 constexpr int SM_STEP = SM_THREADS * SM_PER;
 static_assert(SM_STEP <= 65536, "the list holds 16-bit offsets");
@@ -107,11 +108,14 @@ __global__ __launch_bounds__(SM_THREADS) void small_search_kernel(
 // survivors, K = 16, Kf = 4, lists / this: 1 x 131072 26.0 / 18.5, 8 x 131072 30.0 / 23.9, 128 x 8192 27.3 / 20.7,
 // 8 x 200000 30.9 / 27.5, 37 x 65536 29.4 / 31.5, 128 x 32768 29.2 / 31.4, 1000 x 32768 63 / 90; at 20 %: 128 x 8192
 // 35.6 / 21.9, 128 x 32768 47.4 / 35.2, 1000 x 32768 117 / 108; all surviving: 128 x 8192 75.5 / 27.3,
-// 1000 x 131072 2253 / 900.  Kf = 1, 2, 3: the same line within 20 %).
+// 1000 x 131072 2253 / 900.  Kf = 1, 2, 3: the same line within 20 %.  Those with 2048 items a step; with 4096, lists / this:
+// 1 x 2.5e6 33.6 / 29.0, 1 x 4e6 35.4 / 34.2, 4 x 5e5 29.0 / 21.1, 3 x 10^6 28.0 / 25.5, 5 x 10^6 33.6 / 37.0, 8 x 5e5 29.3 / 29.7,
+// 100 x 30000 25.3 / 23.9, 700 x 5000 31.5 / 31.7; at 0.1 %: 4 x 7e5 23.0 / 24.5, 28 x 10^5 24.1 / 22.4; at 5 %: 39.7 / 33.5,
+// 30.7 / 24.1).
 bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share) {
     const double pairs = (double)Q * (double)ix->N;
     return ix->scan_mode == ICQ_SCAN_AUTO && ix->Kf <= 4 && ix->item_stride <= 16 && topk <= 512 &&
-           (share == ICQ_SHARE_ALL || pairs <= (share == ICQ_SHARE_MANY ? 5.0e6 : 1.8e6));
+           (share == ICQ_SHARE_ALL || pairs <= (share == ICQ_SHARE_MANY ? 5.0e6 : 3.0e6));
 }
 
 int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,

@@ -1088,6 +1088,36 @@ def test_tables_of_few_queries_equal_those_of_many(gpu, K, d):
                 ((got == want[first:first + Q]) | (got.isnan() & want[first:first + Q].isnan())).all()
 
 
+@pytest.mark.parametrize("K,Kf,N,Q", [(4, 3, 4095, 7), (4, 1, 4096, 1), (8, 2, 4097, 3), (12, 4, 8191, 40), (16, 4, 8193, 350), (16, 3, 1_000_003, 2)])
+def test_small_index_in_one_kernel_equals_the_streamed_form(gpu, K, Kf, N, Q):
+    """Both stages of a small index in one kernel, 4096 items a step, against the forms for larger ones: the same additions, the
+    same lists, distances and counts bit for bit."""
+    torch, b = gpu
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    d, topk = 24, 33
+    cb = torch.randn((K, 256, d), device="cuda", generator=gen) * torch.tensor([0.7 ** k for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, 256, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    index = b.icq_index_create(cb.contiguous(), codes, Kf)
+    queries = torch.randn((Q, d), device="cuda", generator=gen)
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = sum(lut[:, k].index_select(1, codes[k, :4000].long()) for k in range(Kf))
+    thr = P.kthvalue(200, dim=1).values.contiguous()
+    thr[0] = float("inf") if N < 10_000 else thr[0]
+    out = []
+    for mode in (b.ICQ_SCAN_AUTO, b.ICQ_SCAN_STREAMED):
+        b.icq_index_set_scan_mode(index, mode)
+        ids, dist = torch.empty((Q, topk), dtype=torch.int32, device="cuda"), torch.empty((Q, topk), device="cuda")
+        count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.icq_workspace_bytes(index, Q, N, topk), dtype=torch.uint8, device="cuda")
+        b.icq_search(index, queries, thr, N, topk, ids, dist, count, ws)
+        out.append((ids, dist, count))
+    torch.cuda.synchronize()
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
+
+
 def test_op_counts_match_oracle(gpu):
     torch, b = gpu
     cfg = small("C1", 5_000, 300)
