@@ -937,8 +937,14 @@ int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const fl
     return icq_check_launch();
 }
 
+// Up to four queries as well, where the lists stay on chip, from the (query, item) pairs on at which icq_small_usable ends: its
+// 65536 evaluations per query and the pruned items against a pass over all items (1 / 2 / 4 queries, K = 8: N = 1.2e7
+// 27 / 28 / 28 us, the pass 45 / 56 / 77, clustered codes 27 / 37 / 37 against 45 / 56 / 78; N = 4e6 24 / 25 / 25 against
+// 36 / 37 / 41; four queries, N = 1e6: 26, clustered 29.4, against 29.5).
 bool icq_group_fused(const icq_index *ix, int Q, int topk) {
-    return icq_group_usable(ix, Q) && ix->item_stride <= 16 && topk <= GD_TOPK;
+    const bool few = ix->scan_mode == ICQ_SCAN_AUTO && ix->Kf == 2 && ix->N >= (int64_t)ix->groups / 2 &&
+                     (double)Q * (double)ix->N > ICQ_SMALL_PAIRS;
+    return (icq_group_usable(ix, Q) || (few && Q > 0)) && ix->item_stride <= 16 && topk <= GD_TOPK;
 }
 
 // Blocks per query in the fused form: one when the queries alone fill the chip; else each block

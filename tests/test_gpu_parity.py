@@ -1118,6 +1118,38 @@ def test_small_index_in_one_kernel_equals_the_streamed_form(gpu, K, Kf, N, Q):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("K,m,N,Q,clustered", [(8, 256, 3_000_001, 1, False), (4, 256, 1_500_001, 2, True), (12, 200, 1_100_000, 3, False),
+                                               (8, 256, 4_300_000, 4, True), (8, 256, 4_300_000, 1, False)])
+def test_search_of_few_queries_grouped_by_tuple(gpu, K, m, N, Q, clustered):
+    """One to four queries over an index grouped by two fast codes, just above the line where the grouped kernel takes them (and
+    where hit bits did): lists, distances and counts of the streamed form, bit for bit; no survivors, too."""
+    torch, b = gpu
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + Q)
+    d, topk = 16, 100
+    cb = torch.randn((K, m, d), device="cuda", generator=gen) * torch.tensor([0.6 ** k for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, m, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    if clustered:
+        codes[:2, : N // 2] = codes[:2, :500].repeat(1, N // 1000 + 1)[:, : N // 2]
+    index = b.icq_index_create(cb.contiguous(), codes, 2)
+    queries = torch.randn((Q, d), device="cuda", generator=gen)
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = sum(lut[:, k].index_select(1, codes[k].long()) for k in range(2))
+    for thr in (P.kthvalue(N // 200, dim=1).values.contiguous(), torch.full((Q,), -1.0, device="cuda")):
+        out = []
+        for mode in (b.ICQ_SCAN_AUTO, b.ICQ_SCAN_STREAMED):
+            b.icq_index_set_scan_mode(index, mode)
+            ids, dist = torch.empty((Q, topk), dtype=torch.int32, device="cuda"), torch.empty((Q, topk), device="cuda")
+            count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+            ws = torch.empty(b.icq_workspace_bytes(index, Q, N // 10, topk), dtype=torch.uint8, device="cuda")
+            b.icq_search(index, queries, thr, N // 10, topk, ids, dist, count, ws)
+            out.append((ids, dist, count))
+        torch.cuda.synchronize()
+        for x, y in zip(*out):
+            assert torch.equal(x, y)
+
+
 def test_op_counts_match_oracle(gpu):
     torch, b = gpu
     cfg = small("C1", 5_000, 300)
