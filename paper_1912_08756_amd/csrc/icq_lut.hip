@@ -154,12 +154,13 @@ __global__ __launch_bounds__(256) void build_lut_kernel(const float *queries, in
     }
 }
 
-// The same table by single wavefronts, 32 queries x 32 entries each, operands straight from memory, eight slices ahead: no LDS
+// The same table by single wavefronts, 32 queries x 32 entries each, operands straight from memory, up to eight slices ahead: no LDS
 // staging and no barrier.  Every sum has the terms of build_lut_kernel in the same order, so the tables are the same bit for bit.
 // What bounds it: the latency of a launch's loads and of a chain of d / 2 matrix instructions.  Against build_lut_kernel, whole
 // searches: one query over 1e6 items (d = 128, K = 8) 26.9 -> 23.3 us, 40 queries over 2e5 (d = 200, K = 16) 34.8 -> 30.9.
-constexpr int FD = 8;    // slices under way (four: one microsecond more from 64 to 256 dimensions)
-template <bool VEC>
+// FD: slices under way (four instead of eight: one microsecond more from 64 to 256 dimensions; a row of fewer slices has no more).
+// Each store in a branch of its own instead of the values first: 256 queries (K = 8, d = 43) 6.1 instead of 4.4 us.
+template <bool VEC, int FD>
 __global__ __launch_bounds__(64) void build_lut_few_kernel(const float *__restrict__ queries, int Q, int d,
                                                            const float *__restrict__ cb, int d_pad,
                                                            const float *__restrict__ cnorm, int ncols, float *__restrict__ lut,
@@ -220,12 +221,20 @@ __global__ __launch_bounds__(64) void build_lut_few_kernel(const float *__restri
     }
     wave_lds_order();
     float *out = lut + (int64_t)(q0 + 4 * half) * ncols + n0 + l32;
+    float r[16];                                           // values first, then the stores, see build_lut_kernel
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         const float4v q = *reinterpret_cast<const float4v *>(&qn_s[4 * half + 8 * w]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (q0 + 4 * half + 8 * w + i < Q) out[(int64_t)(8 * w + i) * ncols] = (q[i] + cn) - 2.0f * acc[4 * w + i];
+        for (int i = 0; i < 4; ++i) r[4 * w + i] = (q[i] + cn) - 2.0f * acc[4 * w + i];
+    }
+    if (q0 + 32 <= Q) {                                    // uniform
+#pragma unroll
+        for (int v = 0; v < 16; ++v) out[(int64_t)((v & 3) + 8 * (v >> 2)) * ncols] = r[v];
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (q0 + 4 * half + (v & 3) + 8 * (v >> 2) < Q) out[(int64_t)((v & 3) + 8 * (v >> 2)) * ncols] = r[v];
     }
 }
 
@@ -254,16 +263,24 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
         // Slower: the entries as rows of the matrix instruction (16-byte stores of 32-byte pieces in 32
         // rows instead of 4-byte stores of whole 128-byte lines).
         const bool ahead = (int64_t)grid.x * grid.y < 4 * 256;
-        // Up to three wavefronts per CU; with more, the blocks that stage in LDS read the codebooks less often (K = 8, d = 256, table
-        // alone, 256 / 600 queries: 11 / 18 us against 13.5 / 15; K = 16, d = 960, whole search of 1e6 items, 10 / 37 / 130 / 200
-        // queries -- 128 / 256 / 640 / 896 wavefronts: 66 / 84 / 113 / 136 us against 77 / 93 / 121 / 131).
-        if ((int64_t)(nq + 31) / 32 * (ncols / 32) <= 3 * (int64_t)ix->num_cu) {
+        // Up to three wavefronts per CU (six where a row has at most 32 values); with more, the blocks that stage in LDS read the
+        // codebooks less often.  Table alone, build_lut_kernel / build_lut_few_kernel, us:
+        //   wavefronts            64         256 or 320    512          640 or 768   1024         1280        1600
+        //   K =  8, d = 32     4.3 / 3.0   4.5 / 3.3    4.3 / 3.4    4.5 / 3.8    5.1 / 4.3   4.9 / 4.5   5.5 / 5.1
+        //   K =  8, d = 43     5.3 / 3.6   5.5 / 4.1    5.3 / 4.4    5.5 / 5.1    6.1 / 5.8   5.9 / 7.0   6.5 / 8.5
+        //   K =  8, d = 128    8.3 / 5.2   8.2 / 5.2    8.3 / 6.3    8.6 / 7.4    9.3 / 8.7   9.1 / 10.9  9.8 / 12.2
+        //   K =  8, d = 960                             43.4 / 32.4  43.7 / 34.5  44.8 / 36.8 46.0 / 51.9 47.5 / 60.7
+        //   K = 16, d = 99                 8.5 / 5.6    8.4 / 7.2    8.7 / 7.9    8.9 / 10.0  9.4 / 12.7
+        const int64_t waves = (int64_t)(nq + 31) / 32 * (ncols / 32);
+        if (waves <= (ix->d_pad <= 2 * BK ? 6 : 3) * (int64_t)ix->num_cu) {
             dim3 few((unsigned)(ncols / 32), (unsigned)((nq + 31) / 32));
             auto go = [&](auto kernel) {
                 kernel<<<few, 64, 0, s>>>(qs, nq, ix->d, ix->cb, ix->d_pad, ix->cnorm, ncols, out, zero0 ? zero0 + q0 : nullptr,
                                           zero1 ? zero1 + q0 : nullptr, zero2 ? zero2 + q0 : nullptr);
             };
-            if (vec) go(build_lut_few_kernel<true>); else go(build_lut_few_kernel<false>);
+            if (ix->d_pad <= 2 * BK) { if (vec) go(build_lut_few_kernel<true, 2>); else go(build_lut_few_kernel<false, 2>); }
+            else if (ix->d_pad <= 4 * BK) { if (vec) go(build_lut_few_kernel<true, 4>); else go(build_lut_few_kernel<false, 4>); }
+            else { if (vec) go(build_lut_few_kernel<true, 8>); else go(build_lut_few_kernel<false, 8>); }
             continue;
         }
         auto launch = [&](auto kernel) {

@@ -1063,7 +1063,7 @@ def test_search_from_hit_bits_in_pieces_of_chunks(gpu, K, Kf, mode):
             assert torch.equal(x[:upto], y[:upto])
 
 
-@pytest.mark.parametrize("K,d", [(1, 1), (4, 17), (8, 100), (8, 128), (8, 132), (16, 33), (3, 260)])
+@pytest.mark.parametrize("K,d", [(1, 1), (4, 17), (8, 100), (8, 128), (8, 132), (8, 64), (16, 33), (3, 260)])
 def test_tables_of_few_queries_equal_those_of_many(gpu, K, d):
     """Few queries' tables come from wavefronts of their own, many queries' from blocks that stage in LDS: the same sums in the
     same order, hence the same bits -- also of rows that are not 16-byte aligned, and with infinities and NaN."""
@@ -1072,7 +1072,7 @@ def test_tables_of_few_queries_equal_those_of_many(gpu, K, d):
     gen.manual_seed(d)
     cb = torch.randn((K, 200, d), device="cuda", generator=gen)
     index = b.icq_index_create(cb, torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
-    many = 32 * (3 * 256 // (8 * K)) + 65
+    many = 32 * (6 * 256 // (8 * K)) + 65
     flat = torch.randn((many * d + 1,), device="cuda", generator=gen)
     queries = flat[1:].view(many, d)
     queries[5, d - 1], queries[7, 0], queries[40, d // 2] = float("inf"), float("nan"), -float("inf")
