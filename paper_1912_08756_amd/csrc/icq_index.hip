@@ -5,10 +5,7 @@
 #include "icq_encode.h"
 
 #include <math.h>
-#include <mutex>
 #include <new>
-#include <set>
-#include <utility>
 
 namespace {
 
@@ -77,25 +74,6 @@ int item_stride_for(int K) {
 }
 
 }  // namespace
-
-hipError_t icq_allow_lds(const void *fn, int bytes, bool no_static_lds) {
-    static std::mutex mu;
-    static std::set<std::pair<int, const void *>> done;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lock(mu);
-    if (done.count({dev, fn})) return hipSuccess;
-    if (no_static_lds) {
-        hipFuncAttributes attr;
-        e = hipFuncGetAttributes(&attr, fn);
-        if (e != hipSuccess) return e;
-        if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;
-    }
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) done.insert({dev, fn});
-    return e;
-}
 
 ICQ_EXPORT const char *icq_strerror(int code) {
     switch (code) {

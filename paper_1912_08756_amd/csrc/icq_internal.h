@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "icq.h"
+#include "icq_lds.h"
 
 #define ICQ_EXPORT extern "C" __attribute__((visibility("default")))
 #define ICQ_LUT_W 256          // table row width (entries j >= m hold +inf)
@@ -67,10 +68,6 @@ static inline bool icq_g2_usable(const icq_index *ix) {
 int icq_encode_pack(icq_index *ix, hipStream_t s);             // enc_meta zero on entry
 int icq_group2_build(icq_index *ix, hipStream_t s);
 int icq_group2_export(const icq_index *ix, uint8_t *codes_out, hipStream_t s);
-
-// hipFuncSetAttribute(fn, MaxDynamicSharedMemorySize, bytes), once per (device, kernel); thread-safe.
-// no_static_lds: also refuse (hipErrorInvalidValue) a kernel whose code object holds static LDS.
-hipError_t icq_allow_lds(const void *fn, int bytes, bool no_static_lds = false);
 
 // What a candidate list holds.
 enum icq_list_kind {

@@ -1250,6 +1250,33 @@ def test_encode_over_the_forms_of_its_kernels(gpu, m, d, N, sweeps):
         judge(xs - sum(cb64[l][state[l]] for l in range(K) if l != k), k, s[k])
 
 
+@pytest.mark.parametrize("d", [160, 256, 384, 512])
+def test_encode_with_few_codebooks_and_then_many(gpu, d):
+    """The register form's LDS grows with the number of codebooks: 64 of them after 2, on one kernel.  Greedy assignment takes
+    the codebooks one after another, so the first codes of the long list are those of the short one."""
+    torch, b = gpu
+    rng = np.random.default_rng(d)
+    cb = (rng.standard_normal((64, 256, d)) * (0.9 ** np.arange(64))[:, None, None]).astype(np.float32)
+    x = _dev(torch, rng.standard_normal((130, d)).astype(np.float32))
+    out = []
+    for K in (2, 64):
+        index = b.icq_index_create(_dev(torch, cb[:K]), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+        ws = torch.empty(b.icq_encode_workspace_bytes(index, 130), dtype=torch.uint8, device="cuda")
+        codes = torch.empty((K, 130), dtype=torch.uint8, device="cuda")
+        b.icq_encode(index, x, codes, ws)
+        refined = codes.clone()
+        b.icq_encode_refine(index, x, refined, 1, None, ws)
+        err = [torch.empty((130,), dtype=torch.float64, device="cuda") for _ in range(2)]
+        b.icq_quantization_error(index, x, codes, err[0])
+        b.icq_quantization_error(index, x, refined, err[1])
+        torch.cuda.synchronize()
+        # a replaced sub-code is nearer up to the rounding of its fp32 score, a sum of d terms within ||v||^2 + ||c||^2
+        slack = K * d * 2.0 ** -23 * ((x.double() ** 2).sum(1) + float((cb[0] ** 2).sum(1).max()))
+        assert (err[1] <= err[0] + slack).all()
+        out.append(codes.cpu().numpy())
+    assert np.array_equal(out[0], out[1][:2])
+
+
 @pytest.mark.parametrize("K,m,d,N,kind", [
     (3, 256, 128, 129, "plain"), (3, 256, 129, 257, "plain"),   # the residual in registers / in memory; blocks of 128 items
     (2, 200, 255, 130, "plain"), (2, 256, 960, 200, "plain"),   # an odd end of the last row; several slices
