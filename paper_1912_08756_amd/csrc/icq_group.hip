@@ -897,7 +897,12 @@ int icq_group_build(icq_index *ix, hipStream_t s) {
 bool icq_group_usable(const icq_index *ix, int Q) {
     if (ix->groups == 0 || ix->scan_mode == ICQ_SCAN_STREAMED) return false;
     if (ix->scan_mode == ICQ_SCAN_GROUPED) return true;
-    // automatic: the grouped form costs 256^Kf evaluations per query whatever N is
+    // automatic: the grouped form costs 256^Kf evaluations per query whatever N is.  One to four queries go item by item: their
+    // few blocks (at most 8 per query, each listing every tuple) are ahead where little survives and lose badly where much
+    // does, which the call does not know.  Hit bits / grouped on chip, us, N = 1.3e7, K = 8, one query, 1 / 10 / 40 % and all
+    // surviving: codebooks halving 47 / 28, 107 / 103, 344 / 664, 1297 / 2073; of one size 48 / 49, 111 / 378, 350 / 1814,
+    // 1348 / 4642; four queries 82 / 29, 246 / 120, 511 / 690, 1457 / 2084; of one size 83 / 51, 242 / 397, 496 / 1819, 1480 / 4580.
+    // N = 3.5e6, lists: 37 / 23 at 1 %, 43 / 267 at 20 %, 114 / 2070 for all.
     return Q > 4 && ix->N >= (int64_t)ix->groups / 2;
 }
 
@@ -937,14 +942,8 @@ int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const fl
     return icq_check_launch();
 }
 
-// Up to four queries as well, where the lists stay on chip, from the (query, item) pairs on at which icq_small_usable ends: its
-// 65536 evaluations per query and the pruned items against a pass over all items (1 / 2 / 4 queries, K = 8: N = 1.2e7
-// 27 / 28 / 28 us, the pass 45 / 56 / 77, clustered codes 27 / 37 / 37 against 45 / 56 / 78; N = 4e6 24 / 25 / 25 against
-// 36 / 37 / 41; four queries, N = 1e6: 26, clustered 29.4, against 29.5).
 bool icq_group_fused(const icq_index *ix, int Q, int topk) {
-    const bool few = ix->scan_mode == ICQ_SCAN_AUTO && ix->Kf == 2 && ix->N >= (int64_t)ix->groups / 2 &&
-                     (double)Q * (double)ix->N > ICQ_SMALL_PAIRS;
-    return (icq_group_usable(ix, Q) || (few && Q > 0)) && ix->item_stride <= 16 && topk <= GD_TOPK;
+    return icq_group_usable(ix, Q) && ix->item_stride <= 16 && topk <= GD_TOPK;
 }
 
 // Blocks per query in the fused form: one when the queries alone fill the chip; else each block

@@ -170,7 +170,6 @@ int icq_launch_group_keys(const icq_index *ix, const float *lut, int Q, const fl
                           unsigned long long *cand_keys, uint32_t *cand_count, int64_t cap, int topk,
                           uint32_t *out_ids, float *out_dist, hipStream_t s);
 // Both stages of a small index in one kernel (icq_small.hip): keys of the survivors in cand_keys.
-#define ICQ_SMALL_PAIRS 3.0e6  // (query, item) pairs, share not known
 bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share);      // (calls that are not grouped by tuple)
 int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,
                      uint32_t *cand_count, int64_t cap, hipStream_t s);

@@ -625,11 +625,11 @@ int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *t
     if (Q == 0) return ICQ_OK;
     if (ix->N == 0) return ICQ_OK;
 
-    const bool fused = out_ids && icq_group_fused(ix, Q, topk);
-    if ((icq_group_usable(ix, Q) || fused) && list_kind && !cand_part && ix->item_stride <= 16 && (cand_keys || fused)) {
+    if (icq_group_usable(ix, Q) && list_kind && !cand_part && ix->item_stride <= 16 &&
+        (cand_keys || (out_ids && icq_group_fused(ix, Q, topk)))) {
         // the caller only wants the final lists: finish the distances (and, where one block
         // owns a query, the lists) right here
-        *list_kind = fused ? ICQ_LIST_DONE : ICQ_LIST_KEYS;
+        *list_kind = out_ids && icq_group_fused(ix, Q, topk) ? ICQ_LIST_DONE : ICQ_LIST_KEYS;
         return icq_launch_group_keys(ix, lut, Q, thr, cand_keys, cand_count, cap, topk, out_ids, out_dist, s);
     }
     if (icq_group_usable(ix, Q)) {

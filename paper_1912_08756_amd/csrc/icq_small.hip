@@ -115,7 +115,7 @@ __global__ __launch_bounds__(SM_THREADS) void small_search_kernel(
 bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share) {
     const double pairs = (double)Q * (double)ix->N;
     return ix->scan_mode == ICQ_SCAN_AUTO && ix->Kf <= 4 && ix->item_stride <= 16 && topk <= 512 &&
-           (share == ICQ_SHARE_ALL || pairs <= (share == ICQ_SHARE_MANY ? 5.0e6 : ICQ_SMALL_PAIRS));
+           (share == ICQ_SHARE_ALL || pairs <= (share == ICQ_SHARE_MANY ? 5.0e6 : 3.0e6));
 }
 
 int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,

@@ -1121,8 +1121,9 @@ def test_small_index_in_one_kernel_equals_the_streamed_form(gpu, K, Kf, N, Q):
 @pytest.mark.parametrize("K,m,N,Q,clustered", [(8, 256, 3_000_001, 1, False), (4, 256, 1_500_001, 2, True), (12, 200, 1_100_000, 3, False),
                                                (8, 256, 4_300_000, 4, True), (8, 256, 4_300_000, 1, False)])
 def test_search_of_few_queries_grouped_by_tuple(gpu, K, m, N, Q, clustered):
-    """One to four queries over an index grouped by two fast codes, just above the line where the grouped kernel takes them (and
-    where hit bits did): lists, distances and counts of the streamed form, bit for bit; no survivors, too."""
+    """One to four queries over an index grouped by two fast codes, next to the lines between the small-index kernel, lists and hit
+    bits: lists, distances and counts of the streamed form, bit for bit; no survivors, too, and all of them, where the
+    call must not take long either (the grouped kernel with its blocks per query took 10 to 25 times the streamed form's time)."""
     torch, b = gpu
     gen = torch.Generator(device="cuda")
     gen.manual_seed(N + Q)
@@ -1136,18 +1137,27 @@ def test_search_of_few_queries_grouped_by_tuple(gpu, K, m, N, Q, clustered):
     lut = torch.empty((Q, K, 256), device="cuda")
     b.icq_build_lut(index, queries, lut)
     P = sum(lut[:, k].index_select(1, codes[k].long()) for k in range(2))
-    for thr in (P.kthvalue(N // 200, dim=1).values.contiguous(), torch.full((Q,), -1.0, device="cuda")):
-        out = []
+    for thr in (P.kthvalue(N // 200, dim=1).values.contiguous(), torch.full((Q,), -1.0, device="cuda"), torch.full((Q,), float("inf"), device="cuda")):
+        cap = N if torch.isinf(thr[0]) else N // 10
+        out, times = [], []
         for mode in (b.ICQ_SCAN_AUTO, b.ICQ_SCAN_STREAMED):
             b.icq_index_set_scan_mode(index, mode)
             ids, dist = torch.empty((Q, topk), dtype=torch.int32, device="cuda"), torch.empty((Q, topk), device="cuda")
             count = torch.empty((Q,), dtype=torch.int32, device="cuda")
-            ws = torch.empty(b.icq_workspace_bytes(index, Q, N // 10, topk), dtype=torch.uint8, device="cuda")
-            b.icq_search(index, queries, thr, N // 10, topk, ids, dist, count, ws)
+            ws = torch.empty(b.icq_workspace_bytes(index, Q, cap, topk), dtype=torch.uint8, device="cuda")
+            best = float("inf")
+            for _ in range(3):
+                e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+                e0.record()
+                b.icq_search(index, queries, thr, cap, topk, ids, dist, count, ws)
+                e1.record()
+                torch.cuda.synchronize()
+                best = min(best, e0.elapsed_time(e1))
             out.append((ids, dist, count))
-        torch.cuda.synchronize()
+            times.append(best)
         for x, y in zip(*out):
             assert torch.equal(x, y)
+        assert times[0] < 3 * times[1] + 0.05, times
 
 
 def test_op_counts_match_oracle(gpu):
