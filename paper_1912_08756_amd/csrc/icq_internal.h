@@ -6,6 +6,7 @@
 
 #include "icq.h"
 #include "icq_lds.h"
+#include "icq_pieces.h"
 
 #define ICQ_EXPORT extern "C" __attribute__((visibility("default")))
 #define ICQ_LUT_W 256          // table row width (entries j >= m hold +inf)
@@ -195,22 +196,6 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
                       const float *cand_part, int list_kind,
                       const uint32_t *cand_count, int64_t cap, int topk, int splits,
                       unsigned long long *keys, uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
-
-// Pieces the scan positions (`steps` block steps) are cut into for `groups` groups of queries, one block per CU at a time: the
-// number for which whole rounds of blocks take least, a block's tables costing it as much as `fill` steps.  (As many
-// pieces as fill the chip, rounded up, can leave a second round nearly empty: 125 groups in 3 pieces each.)
-static inline int64_t icq_scan_pieces(int num_cu, int64_t groups, int64_t steps, int64_t fill) {
-    int64_t best = 1, least = -1;
-    const int64_t most = 2 * ((num_cu + groups - 1) / groups) + 2;
-    for (int64_t c = 1; c <= most && c <= steps; ++c) {
-        const int64_t cost = (groups * c + num_cu - 1) / num_cu * ((steps + c - 1) / c + fill);
-        if (least < 0 || cost < least) {
-            least = cost;
-            best = c;
-        }
-    }
-    return best;
-}
 
 #define ICQ_HIP_TRY(expr)                      \
     do {                                       \

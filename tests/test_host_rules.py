@@ -40,3 +40,43 @@ int main() {
 }
 """, "icq_lds.hip")
     assert out == ["0:a:100", "0:a:300", "0:a:301", "0:b:50", "1:a:70", "1:a:80", "1:a:75"]
+
+
+def test_scan_pieces_are_those_of_the_search_over_every_number(tmp_path):
+    """The steps per block that follow from the rule are those that looking at every number of pieces gives (of equal costs the
+    fewest rounds), for a handful of queries to thousands of groups; and it looks at few of them."""
+    out = _run(tmp_path, """
+#include "icq_pieces.h"
+#include <chrono>
+#include <initializer_list>
+#include <stdio.h>
+static int64_t every(int num_cu, int64_t groups, int64_t steps, int64_t fill) {
+    int64_t best = 1, least = -1;
+    const int64_t most = 2 * ((num_cu + groups - 1) / groups) + 2;
+    for (int64_t c = 1; c <= most && c <= steps; ++c) {
+        const int64_t cost = (groups * c + num_cu - 1) / num_cu * ((steps + c - 1) / c + fill);
+        if (least < 0 || cost < least) { least = cost; best = c; }
+    }
+    return best;
+}
+int main() {
+    long n = 0;
+    for (int cu : {256, 304, 7}) for (int64_t g = 1; g < 2200; g = g < 600 ? g + 1 : g + 61)
+        for (int64_t steps = 0; steps < 9000; steps = steps < 70 ? steps + 1 : steps * 9 / 8 + 1)
+            for (int64_t fill : {1, 2, 8}) {
+                const int64_t a = icq_scan_pieces(cu, g, steps, fill), b = every(cu, g, steps, fill);
+                if (a < 1 || (steps > 0 && a > steps)) return 1;
+                if ((steps + a - 1) / a != (steps + b - 1) / b) return 2;
+                ++n;
+            }
+    volatile int64_t sink = 0;
+    double t[2];
+    for (int w = 0; w < 2; ++w) {
+        const auto t0 = std::chrono::steady_clock::now();
+        for (int i = 0; i < 3000; ++i) sink += w ? every(256, 1 + sink % 2, 6000 + i, 2) : icq_scan_pieces(256, 1 + sink % 2, 6000 + i, 2);
+        t[w] = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+    }
+    printf("%ld %d\\n", n, t[0] * 10 < t[1]);
+}
+""")
+    assert int(out[0]) > 100_000 and out[1] == "1"
