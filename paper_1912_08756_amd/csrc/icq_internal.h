@@ -139,10 +139,10 @@ int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, cons
                               size_t mask_stride, int64_t scan_end, hipStream_t s);
 // Stage 2 from hit bits; keys [Q][cap] (+ slice lists in front, see icq_cand_keys); adds the survivors to cand_count.
 // thr != nullptr: the bits mark a superset of the survivors, and an item counts only if its crude distance
-// (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].  few: less than a per cent will survive.
+// (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, unsigned long long *keys,
-                            uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr, bool few,
+                            uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr,
                             uint32_t *out_ids, float *out_dist, hipStream_t s);
 
 // p[0..n) = 0, by a kernel (the call can sit inside a captured graph).

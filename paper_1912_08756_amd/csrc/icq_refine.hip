@@ -276,8 +276,9 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
 // bits (one 128-bit load per lane, two chunks ahead), a prefix of their popcounts, the set bits
 // expanded into a position list in the wavefront's part of LDS, then per position the record
 // gather, the K table reads and the key, as in refine_dist_kernel.
-// (Few queries: a wavefront takes half or a quarter of a chunk, see icq_launch_refine_masks; what follows says chunk for either.)
-// Every 65th chunk is done in a first launch, unfiltered (!FILTER); the select kernel's topk-th
+// (A wavefront may take half or a quarter of a chunk, see icq_launch_refine_masks; what follows says chunk for either.)
+// Every 65th chunk -- where the others are taken whole, every 65th quarter of one -- is done in a first launch, unfiltered
+// (!FILTER); the select kernel's topk-th
 // distance of those keys then bounds what the other chunks add in a second launch (FILTER: keys
 // above it are dropped; ties at it are kept, the final select decides).  The final lists are
 // unchanged -- at least topk keys at or below the bound are already there -- and the key lists
@@ -290,6 +291,8 @@ constexpr int RM_PER = 4;                             // records a lane gathers 
 constexpr int RM_LIST = 512;                          // positions a wavefront expands per round
 constexpr int RM_QPB = 1;                             // queries per block (two: 1.39 against 1.25 ms at N = 1e8, 128 queries)
 constexpr int RM_SEED_EVERY = 65;                     // odd: the first launch's chunks are spread over all XCDs
+// 32-bit words per lane of the first launch's pieces, by those of the second's
+constexpr int rm_seed_words(int words) { return words == RM_FULL ? RM_FULL / 4 : words; }
 static_assert(RM_LIST % (64 * RM_PER) == 0, "a round of the list is whole steps of gathers");
 static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into the chunk");
 
@@ -311,6 +314,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
     __shared__ uint32_t sum_all[QPB], done_all[QPB];  // survivors of the block, wavefronts that have added theirs
     constexpr int RW = WORDS;
     constexpr uint32_t PIECE = RM_WORDS * 2048;       // positions
+    constexpr uint32_t SEED_PARTS = RM_WORDS / rm_seed_words(RM_WORDS);
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -325,7 +329,8 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
     auto chunk_of = [&](uint32_t j) -> uint32_t {
         const uint32_t i = ((win * (uint32_t)window + j) << xs_shift) + xcd;
         if (j >= (uint32_t)window || i >= nsel) return 0xFFFFFFFFu;
-        return FILTER ? i + i / (seed_every - 1u) + 1u : i * seed_every;   // the others : every seed_every-th
+        if (!FILTER) return i * seed_every;
+        return SEED_PARTS == 1u ? i + i / (RM_SEED_EVERY - 1u) + 1u : i;   // all but every 65th : all
     };
     if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
     // Word r of this lane covers the 32 positions from c * PIECE + (r * 64 + lane) * 32: neighbouring
@@ -377,6 +382,11 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         uint32_t w[RM_WORDS];
 #pragma unroll
         for (int r = 0; r < RM_WORDS; ++r) w[r] = nxt[r];
+        if (FILTER && SEED_PARTS > 1u) {              // what the first launch has done is out
+            const uint32_t at = c * SEED_PARTS % RM_SEED_EVERY, done = at == 0u ? 0u : RM_SEED_EVERY - at;
+#pragma unroll
+            for (int r = 0; r < RM_WORDS; ++r) w[r] = (uint32_t)(r / rm_seed_words(RM_WORDS)) == done ? 0u : w[r];
+        }
         // next piece of work: the next query of this chunk, else the wavefront's next chunk
         uint32_t qn = qq + 1, jn = j, cn = c;
         if (qn >= nq) {
@@ -632,25 +642,42 @@ int64_t icq_mask_scan_end(const icq_index *ix) {
 
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, u64 *keys, uint32_t *key_count,
-                            uint32_t *ticket, uint32_t *cand_count, const float *thr, bool few, uint32_t *out_ids,
-                            float *out_dist, hipStream_t s) {
+                            uint32_t *ticket, uint32_t *cand_count, const float *thr, uint32_t *out_ids, float *out_dist,
+                            hipStream_t s) {
     if (Q == 0) return ICQ_OK;
     const bool g2 = icq_g2_usable(ix);
     const uint8_t *items = g2 ? ix->items_grouped : ix->items;
     const uint32_t *perm = g2 ? ix->perm : nullptr;
     // few chunks: one unfiltered launch over all of them (a bound would save less than its second launch costs)
     const uint32_t seed_every = scan_end / RM_CHUNK < 2 * RM_SEED_EVERY ? 1u : (uint32_t)RM_SEED_EVERY;
-    // A wavefront takes a chunk at a time, or a piece of one: half a chunk while the (chunk, query) pairs are few enough that
-    // the chip is not full of whole ones (1e8 items, 1 / 8 / 64 / 128 queries, whole call: 184 / 386 / 1080 / 1800 us with whole
-    // chunks, 156 / 320 / 1028 / 1831 with halves; 2e7 items, 128 queries: 481 / 455), a quarter for the very few (5e6 items,
-    // 1 query: 59 / 48 / 43 us with whole ones, halves, quarters; 8: 101 / 88 / 95).  Where little is found in a chunk (few:
-    // 7e6 items, 128 queries, 0.1 % 89 / 104 us) or a block's tables serve one launch over all of them (1e6 items, 200
-    // queries: 154 / 163) whole ones pay sooner.
-    const uint64_t pairs = (uint64_t)(scan_end / RM_CHUNK) * (uint64_t)Q;
-    const uint64_t halves = seed_every == 1u ? 512u : few ? 8192u : Q <= 64 ? 262144u : 131072u;
-    const int words = pairs <= 320 ? RM_FULL / 4 : pairs <= halves ? RM_FULL / 2 : RM_FULL;
-    const uint32_t chunks = (uint32_t)(scan_end / (2048 * words));
-    const uint32_t nseed = (chunks + seed_every - 1) / seed_every, nmain = chunks - nseed;
+    // A wavefront takes a chunk at a time, or half or a quarter of one.  What a call spends its time on depends on what survives:
+    // with little, on each piece's chain of steps and each block's tables, so that smaller pieces cost; with much, on the first
+    // launch, whose few wavefronts then hold long lists, and on records that leave the caches before the other queries'
+    // blocks come to them, so that smaller pieces and windows gain.  Whole chunks with a first launch of quarters and windows of
+    // four chunks lose to larger pieces at no share; smaller pieces stand where they do not lose at a low share either.  Whole
+    // calls, us, at 0.05 / 1 / 5 / 30 % (K = 16, Kf = 4; whole chunks in both launches, windows of 16, 12 from eight queries on | halves
+    // in both, windows of 8 | quarters, windows of 8 | this):
+    //   4.3e6 items, 1 query     44/102/317/2300 |  34/46/82/335   |  33/44/58/146     quarters
+    //   4.3e6, 3 queries        48/109/353/2339  |  45/56/107/330  |  46/62/88/183     halves
+    //   4.3e6, 8                57/106/302/1709  |  64/85/165/514  |  70/98/148/289    whole  53/74/156/509
+    //   9e6, 16                 100/162/375/1575 | 114/172/335/708 | 129/221/335/570   whole  97/152/342/734
+    //   2e7, 5                  80/158/395       |  84/127/207     |  85/123/167       halves
+    //   2e7, 64                 228/409/742/3756 | 254/413/645/2258| 266/439/607/1751  whole  222/399/665/3399
+    //   6e7, 8                  152/322/617/2274 | 133/248/373/1244| 152/243/356/859   halves
+    //   1e8, 1                  90/205/540/3472  |  90/166/260/753 |  87/184/252/473   halves
+    //   1e8, 64                 669/1220/2318    | 649/1088/1985   | 714/1178/2068     halves
+    // Codes not ordered by their first two (K = 8, Kf = 2): 9e6, 1 query 45/67/209/2055 | 37/41/67/248 | 42/45/63/142; 1.3e7, 4
+    // queries 63/91/233/1933 | 75/81/174/428 | 108/114/173 | whole 58/80/167/380.
+    const uint64_t whole = (uint64_t)(scan_end / RM_CHUNK), pairs = whole * (uint64_t)Q;
+    int words = RM_FULL;
+    if (seed_every != 1u) {
+        if (pairs <= 320) words = RM_FULL / 4;
+        else if (pairs <= 700 || (g2 && Q < 8 && whole >= 600) || (g2 && whole >= 1700 && pairs <= 200000)) words = RM_FULL / 2;
+    }
+    const int seed_words = seed_every == 1u ? RM_FULL : rm_seed_words(words);
+    const uint32_t chunks = (uint32_t)(scan_end / (2048 * words)), seed_chunks = (uint32_t)(scan_end / (2048 * seed_words));
+    const uint32_t nseed = (seed_chunks + seed_every - 1) / seed_every;
+    const uint32_t nmain = seed_every == 1u ? 0u : words == seed_words ? chunks - nseed : chunks;
     auto select = [&](bool more) -> int {
         return icq_launch_select(keys, key_count, cap, Q, topk, splits, more, ticket, out_ids, out_dist, s);
     };
@@ -661,9 +688,12 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // whole stage (a small index, many queries) takes full windows, and the chunks are cut fewer than 8
     // ways when 8 windows' worth do not exist: 16 MB of records stay in the caches wherever the blocks run.
     auto plan_for = [&](uint32_t nsel, bool filtered, int *xs_shift) -> int {
-        int w = words == RM_FULL && g2 ? 12 : 8;      // at N = 1e8, 128 queries, pair ordering: 16 / 12 / 8 / 6 / 4: 1.105 / 1.090 / 1.109 / 1.18 / 1.31 ms
+        // whole chunks: 4, with more blocks than the chip holds for long 12 or 8 (at N = 1e8, 128 queries, pair ordering:
+        // 16 / 12 / 8 / 6 / 4: 1.105 / 1.090 / 1.109 / 1.18 / 1.31 ms; whole calls at 1 %, windows of 4 / 12: 2e7 items, 128 queries
+        // 512 / 529 us, 3e7, 200 queries (K = 8) 804 / 769)
+        int w = words != RM_FULL ? 8 : pairs <= 131072u ? 4 : g2 ? 12 : 8;
         if ((uint64_t)nsel * (uint64_t)Q <= 16384u && (!filtered || Q < 8)) w = 4;
-        else if (!filtered) w = 16 * RM_FULL / words;
+        else if (!filtered) w = 16 * RM_FULL / seed_words;
         // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
         // keeps a chunk's records in ONE L2 is worth more than the longer windows: 1e4 queries, 1e6 items,
         // 8-byte records: 0.80 ms with it, 0.83 without)
@@ -687,8 +717,9 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                 items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, window, xs_shift, Q, out_dist, topk,     \
                 keys, key_count, cap, cand_count, thr, ix->Kf);                                              \
         };                                                                                                   \
-        if (words == RM_FULL / 4) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 4>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 4>); } \
-        else if (words == RM_FULL / 2) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 2>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 2>); } \
+        const int piece = FILTER ? words : seed_words;                                                       \
+        if (piece == RM_FULL / 4) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 4>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 4>); } \
+        else if (piece == RM_FULL / 2) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 2>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 2>); } \
         else { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL>); }         \
     } while (0)
     switch (ix->item_stride) {

@@ -1063,6 +1063,45 @@ def test_search_from_hit_bits_in_pieces_of_chunks(gpu, K, Kf, mode):
             assert torch.equal(x[:upto], y[:upto])
 
 
+@pytest.mark.parametrize("K,Kf,mode,N", [(8, 3, 0, (1 << 22) + 70_001), (8, 2, 1, (1 << 22) + 65_537), (16, 4, 0, (1 << 22) + 1), (4, 3, 0, 20_000_003)])
+def test_search_from_hit_bits_in_pieces_over_the_shares(gpu, K, Kf, mode, N):
+    """Whole chunks after a first launch of quarters, halves in both, quarters in both: the same lists and counts, bit for bit,
+    whether nothing, a thousandth, a third or all of the items survive, and counts that are those of the crude distances
+    (a chunk's quarter that the first launch has done is not done again, and none is left out)."""
+    torch, b = gpu
+    Q, d, topk = 24, 16, 100
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    cb = torch.randn((K, 256, d), device="cuda", generator=gen) * torch.tensor([0.8 ** k for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, 256, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    index = b.icq_index_create(cb.contiguous(), codes, Kf)
+    b.icq_index_set_scan_mode(index, mode)
+    queries = 1.5 * torch.randn((Q, d), device="cuda", generator=gen)
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    thr, survivors = torch.empty((Q,), device="cuda"), torch.empty((Q,), dtype=torch.int32, device="cuda")
+    for q in range(Q):
+        P = sum(lut[q, k].index_select(0, codes[k].long()) for k in range(Kf))
+        thr[q] = (float("-inf"), P[:20_000].kthvalue(20).values, P[:20_000].kthvalue(300).values, P[:20_000].kthvalue(6000).values, float("inf"))[q % 5]
+        survivors[q] = (P < thr[q]).sum()
+
+    def run(step):
+        ids = torch.empty((Q, topk), dtype=torch.int32, device="cuda")
+        dist = torch.empty((Q, topk), device="cuda")
+        count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.icq_workspace_bytes(index, step, N, topk), dtype=torch.uint8, device="cuda")
+        for q in range(0, Q, step):
+            at = slice(q, min(Q, q + step))
+            b.icq_search(index, queries[at], thr[at], N, topk, ids[at], dist[at], count[at], ws)
+        torch.cuda.synchronize()
+        return ids, dist, count
+    want = run(Q)
+    assert torch.equal(want[2], survivors)
+    for step in (1, 5, 8):
+        for x, y in zip(run(step), want):
+            assert torch.equal(x, y), step
+
+
 @pytest.mark.parametrize("K,d", [(1, 1), (4, 17), (8, 100), (8, 128), (8, 132), (8, 64), (16, 33), (3, 260)])
 def test_tables_of_few_queries_equal_those_of_many(gpu, K, d):
     """Few queries' tables come from wavefronts of their own, many queries' from blocks that stage in LDS: the same sums in the
