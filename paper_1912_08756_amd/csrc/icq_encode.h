@@ -19,6 +19,6 @@ __device__ __forceinline__ float icq_enc_scale_below(float x, int bits) {
     return __uint_as_float((uint32_t)f << 23);
 }
 
-// At most 16 slices.  icm: coordinate descent from the codes there, else greedy assignment (sweeps = 1).
+// At most 16 slices.  icm: coordinate descent from the codes there, else greedy assignment (sweeps = 1).  res [N][d_pad].
 int icq_launch_encode_wave(const icq_index *ix, const float *x, int64_t N, uint8_t *codes, bool icm, int sweeps,
-                           uint32_t *changed, hipStream_t s);
+                           float *res, uint32_t *changed, hipStream_t s);

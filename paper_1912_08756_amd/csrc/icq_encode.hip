@@ -643,7 +643,7 @@ static int launch_encode(const icq_index *ix, const float *x, int64_t N, uint8_t
     // one block of 64 items per CU there: ahead for two rounds of them (d = 300, 384, 512, 30000 items: 1.18, 1.19, 1.09
     // times as fast; 50000: 0.8), greedy assignment throughout (300, 384, 512; 15000 items 2.3 - 2.4, 80000 1.2 - 1.5).
     if (icq_enc_wave_only(ix->d_pad) || (slices <= 16 && (!ICM || N <= 2 * 64 * (int64_t)ix->num_cu)))
-        return icq_launch_encode_wave(ix, x, N, codes, ICM, sweeps, changed, s);
+        return icq_launch_encode_wave(ix, x, N, codes, ICM, sweeps, res, changed, s);
     ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(encode_kernel<ICM>), sizeof(EncShared)));
     encode_kernel<ICM><<<(unsigned)((N + EB - 1) / EB), E_THREADS, sizeof(EncShared), s>>>(
         x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo, ix->enc_meta, ix->K, slices, N, codes, sweeps, res, changed);

@@ -30,9 +30,16 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half2 __attribute__((ext_vector_type(2)));
 typedef float float4v __attribute__((ext_vector_type(4)));
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 constexpr int W_THREADS = 256;             // four wavefronts, each with items of its own
-constexpr int W_CAND = 8;                  // candidates looked at one by one
+// Candidates of an item looked at one by one, beyond that all codewords are scored on the matrix cores; and items of a wavefront
+// without a usable list that are taken one after another instead.  Above 128 dimensions a level's codewords come from memory
+// for each such item as they do for all of them together.  10^5 items, K = 8, 16 equal codewords each, 8 / 32: 128 dimensions,
+// greedy 840 / 760 us, a sweep 1520 / 950; 32 dimensions, greedy 311 / 362, a sweep 592 / 450; 256, greedy 1925 / 2495.  One infinite vector
+// in 128 items, a sweep, without / with: 128 dimensions 1130 / 480 us.
+constexpr int w_cand(int ns, bool icm) { return ns > 4 || (ns == 1 && !icm) ? 8 : 32; }
+constexpr int w_lone(int ns) { return ns <= 4 ? 4 : 0; }
 constexpr float W_U = 4.8828125e-4f;       // 2^-11: relative rounding error of a half
 
 // NS: 32-wide slices of the dimensions.  A chunk is 32 codewords of one codebook as halves, all dimensions: 2 NS KiB.
@@ -49,18 +56,18 @@ constexpr int w_waves(int it, int ns, bool icm) {
 }
 
 // What a wavefront keeps in LDS for itself.
-template <int IT>
+template <int IT, int NS, bool ICM>
 struct WaveOwn {
     uint4 piece[4][IT + 8];                // a slice of the halves: [reduction index / 8][item]; of the residuals: 16 dimensions.
                                            // (128 bytes to spare: the rows that owners write together meet different banks)
     float nrm2[IT];                        // ||v||^2
     uint32_t count[IT];                    // candidates
-    uint2 cand[IT];                        // the first eight, a byte each
+    alignas(8) uint8_t cand[IT][w_cand(NS, ICM)];          // the first of them
 };
-template <int IT, int NS>
+template <int IT, int NS, bool ICM>
 struct WaveShared {
     uint4 ring[w_ring(NS)][w_stage(NS) * NS * 128];        // chunk: [reduction index / 8][codeword]
-    WaveOwn<IT> own[4];
+    WaveOwn<IT, NS, ICM> own[4];
     float cnh[2][ICQ_LUT_W];               // -||c||^2 / 2, scaled: what the accumulators of a level start from
     uint32_t reach[3];                     // largest ||v||^2 of the block's items, as bits, of three levels in turn
     uint32_t wild;                         // whether some item of the block has a norm that is no number
@@ -105,12 +112,12 @@ template <> struct Tile<16> {
 };
 
 // x [N][d]; cb [K*256][d_pad] fp32; halves: see encode_pack_kernel; meta[k] = scale, largest ||c||, largest ||c - c'||.  ICM: `codes`
-// is in and out, `changed` (or nullptr) counts per sweep.
+// is in and out, `changed` (or nullptr) counts per sweep; res [N][d_pad] is scratch.
 template <int IT, int NS, bool ICM>
 __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_kernel(
     const float *__restrict__ x, int d, const float *__restrict__ cb, int d_pad, const float *__restrict__ cnorm,
     const uint4 *__restrict__ halves, const float4 *__restrict__ meta, int K, int m, int64_t N, uint8_t *codes, int sweeps,
-    uint32_t *changed) {
+    float *res, uint32_t *changed) {
     constexpr int P = IT / 8;              // items per owner group of eight lanes
     constexpr int LPI = 64 / IT;           // lanes of an item in the contraction
     constexpr int KS = 4 / LPI;            // matrix instructions a slice takes per tile
@@ -128,7 +135,7 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
     constexpr int PG = NS * P * 4 <= 128 ? P : NS * 4 <= 64 ? 2 : 1;     // items whose new codewords are (128 registers)
     typedef typename Tile<IT>::acc acc_t;
     extern __shared__ __attribute__((aligned(16))) unsigned char enc_smem[];
-    auto &sh = *reinterpret_cast<WaveShared<IT, NS> *>(enc_smem);
+    auto &sh = *reinterpret_cast<WaveShared<IT, NS, ICM> *>(enc_smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     auto &own = sh.own[wave];
@@ -414,9 +421,9 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                 all = q[0] + q[1];
             }
             if (sub == 0) own.count[col] = all;
-            hard = col < live && all - 1u >= (uint32_t)W_CAND;
+            hard = col < live && all - 1u >= (uint32_t)w_cand(NS, ICM);
             several = __builtin_amdgcn_ballot_w64(all > 1) != 0;
-            uint8_t *list = reinterpret_cast<uint8_t *>(&own.cand[col]);
+            uint8_t *list = own.cand[col];
             for (; n != 0; --n, ++before) {                // mostly once
                 uint32_t b = bits[NW - 1], j = (NW - 1) * (IT == 32 ? 64 : 128);
 #pragma unroll
@@ -426,7 +433,7 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                 }
                 const uint32_t i = (uint32_t)__builtin_clz(b), cut = ~(0x80000000u >> i);
                 j += (i & 3u) + ((i >> 2) << (IT == 32 ? 3 : 4)) + (uint32_t)(4 * sub);
-                if (before < (uint32_t)W_CAND) list[before] = (uint8_t)j;
+                if (before < (uint32_t)w_cand(NS, ICM)) list[before] = (uint8_t)j;
                 if (n > 1) {
                     uint32_t done = 0;
 #pragma unroll
@@ -439,19 +446,107 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
             }
         }
         wave_lds_order();
-        // ---- items whose candidates say nothing (none or too many): all scores in fp32 on the matrix cores
+        // ---- items whose candidates say nothing (none or too many): all scores in fp32; a few items one after another, eight
+        // codewords at a time by the eight owner groups, more of them on the matrix cores
         {
-            if (__builtin_amdgcn_ballot_w64(hard) != 0) {
+            uint64_t left = __builtin_amdgcn_ballot_w64(hard) & (IT == 32 ? 0xFFFFFFFFull : 0xFFFFull);
+            if (left != 0 && __builtin_popcountll(left) <= w_lone(NS)) {
+                const int lane = fresh(tid) & 63, og = lane >> 3, ol = lane & 7;
+                constexpr int U = NS <= 1 ? 4 : NS <= 3 ? 2 : 1;           // codewords of a group under way (registers)
+                do {
+                    const uint32_t item = (uint32_t)__builtin_ctzll(left), p1 = item >> 3;
+                    const uint32_t cur = ICM ? code[k][wave * IT + item] : 0u;
+                    float v[NS][4];
+#pragma unroll
+                    for (int g = 0; g < NS; ++g) {
+                        float o[4];
+                        if (ICM) load4(codeword(k, cur), g, o, ol);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            uint32_t w = __float_as_uint(r[0][g][e]);
+#pragma unroll
+                            for (int p = 1; p < P; ++p) {
+                                const uint32_t is = p1 == (uint32_t)p ? ~0u : 0u;          // by bits, see below
+                                w = (w & ~is) | (__float_as_uint(r[p][g][e]) & is);
+                            }
+                            w = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((item & 7u) * 8u + (uint32_t)ol) * 4, (int)w);
+                            v[g][e] = ICM ? fmaf(o[e], sr, __uint_as_float(w)) : __uint_as_float(w);
+                        }
+                    }
+                    float least = INFINITY;
+                    uint32_t f = 0;                        // 0 for the current codeword (ICM), else index + 1
+                    for (int s = 0; s < m; s += 8 * U) {
+                        float y[U][NS][4], cq[U], dot[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            cq[u] = cnorm[k * ICQ_LUT_W + s + 8 * u + og];
+#pragma unroll
+                            for (int g = 0; g < NS; ++g) load4(codeword(k, (uint32_t)(s + 8 * u + og)), g, y[u][g], ol);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            dot[u] = 0.0f;
+#pragma unroll
+                            for (int g = 0; g < NS; ++g)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) dot[u] = fmaf(v[g][e], y[u][g][e], dot[u]);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const uint32_t j = (uint32_t)(s + 8 * u + og), fq = ICM && j == cur ? 0u : j + 1u;
+                            const float score = cq[u] - twice * group_add(dot[u]);
+                            if (score < least || (score == least && fq < f)) {
+                                least = score;
+                                f = fq;
+                            }
+                        }
+                    }
+                    u64 key = least < INFINITY ? ((u64)icq_order_bits(least + 0.0f) << 32) | f : ~0ull;
+#pragma unroll
+                    for (int o = 8; o < 64; o *= 2) {
+                        const u64 other = __shfl_xor(key, o, 64);
+                        key = other < key ? other : key;
+                    }
+                    // no score a number: index 0 (ICM: the current one) stays
+                    if (lane == 0) {
+                        own.cand[item][0] = (uint8_t)(key == ~0ull || (uint32_t)key == 0u ? cur : (uint32_t)key - 1u);
+                        own.count[item] = 1;
+                    }
+                    left &= left - 1;
+                } while (left != 0);
+                wave_lds_order();
+            } else if (left != 0) {
                 const int lane = fresh(tid) & 63, col = lane % IT, sub = lane / IT, og = lane >> 3, ol = lane & 7;
                 // least score and the first index that has it (ICM: or the current codeword); no number, no key
                 const uint32_t cur = ICM ? code[k][wave * IT + col] : 0u;
                 float least = INFINITY;
                 uint32_t f = 0;
                 bool keep = false;
-                // One or two tiles at a time; 16 dimensions go from the owners through LDS, lane (item, sub) multiplies those from
+                // One tile or two at a time; 16 dimensions go from the owners through LDS, lane (item, sub) multiplies those from
                 // 16 sub / LPI on.  The codewords of the next 16 are asked for before the products of these.
-                constexpr int Q = 16 / LPI, U = IT == 16 ? 2 : 1;          // (registers)
+                constexpr int Q = 16 / LPI, U = IT == 16 || !ICM ? 2 : 1;          // (registers)
                 float *F = reinterpret_cast<float *>(own.piece);           // [16 dimensions][IT]
+                // ICM: the residuals wait in the workspace while v takes their registers.  Through a buffer that ends with the
+                // wavefront's last item, with no branch: where `if (item < live)` stood, the compiler put copies of other values
+                // in front of the point at which the lanes of missing items join again, and those lanes were left without them.
+                const auto rows = __builtin_amdgcn_make_buffer_rsrc(res + i0 * d_pad, 0, live * d_pad * 4, 0x00027000);
+                auto place = [&](int p, int g) -> int {
+                    const int e = g * 32 + ol * 4;
+                    return e < d_pad ? ((og + 8 * p) * d_pad + e) * 4 : 1 << 30;           // past the buffer: not written, read as zero
+                };
+                if (ICM) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p)
+#pragma unroll
+                        for (int g = 0; g < NS; ++g) {
+                            float o[4];
+                            load4(codeword(k, old[p]), g, o, ol);
+                            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint32x4, float4v{r[p][g][0], r[p][g][1], r[p][g][2], r[p][g][3]}),
+                                                                   rows, place(p, g), 0, 0);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) r[p][g][i] = fmaf(o[i], sr, r[p][g][i]);
+                        }
+                }
                 auto half_slice = [&](int t, int q, float (&c)[U][Q]) __attribute__((always_inline)) {
                     const int e = q * 16 + sub * Q;
 #pragma unroll
@@ -478,11 +573,9 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                         if ((ol >> 2) == (q & 1)) {
 #pragma unroll
                             for (int p = 0; p < P; ++p) {
-                                float o[4];
-                                if (ICM) load4(codeword(k, old[p]), g, o, ol);
 #pragma unroll
                                 for (int i = 0; i < 4; ++i)
-                                    F[((ol & 3) * 4 + i) * IT + og + 8 * p] = ICM ? fmaf(o[i], sr, r[p][g][i]) : r[p][g][i];
+                                    F[((ol & 3) * 4 + i) * IT + og + 8 * p] = r[p][g][i];
                             }
                         }
                         if (q + 1 < 2 * NS) half_slice(t, q + 1, c[(q + 1) & 1]);
@@ -521,8 +614,18 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                     key = other < key ? other : key;
                 }
                 // no score a number: index 0 (ICM: the current one) stays
+                if (ICM) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p)
+#pragma unroll
+                        for (int g = 0; g < NS; ++g) {
+                            const float4v v = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, place(p, g), 0, 0));
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) r[p][g][i] = v[i];
+                        }
+                }
                 if (hard && sub == 0) {
-                    own.cand[col].x = (key == ~0ull || (uint32_t)key == 0u ? cur : (uint32_t)key - 1u);
+                    own.cand[col][0] = (uint8_t)(key == ~0ull || (uint32_t)key == 0u ? cur : (uint32_t)key - 1u);
                     own.count[col] = 1;
                 }
                 wave_lds_order();
@@ -537,8 +640,8 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
             for (int p = 0; p < P; ++p) many |= own.count[og + 8 * p] > 1 ? 1u << p : 0u;
             while (__builtin_amdgcn_ballot_w64(many != 0) != 0) {
                 const uint32_t p1 = many != 0 ? (uint32_t)__builtin_ctz(many) : 0u;
-                const uint32_t item = og + 8 * p1, n = many != 0 ? own.count[item] : 0u;   // at most W_CAND
-                uint8_t *list = reinterpret_cast<uint8_t *>(&own.cand[item]);
+                const uint32_t item = og + 8 * p1, n = many != 0 ? own.count[item] : 0u;   // at most w_cand(NS, ICM)
+                uint8_t *list = own.cand[item];
                 uint32_t cur = old[0], is[P];
 #pragma unroll
                 for (int p = 1; p < P; ++p) {
@@ -589,7 +692,7 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
         // ---- the sub-codes, and the residual that is left
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const uint32_t q = own.cand[og + 8 * p].x & 255u;
+            const uint32_t q = own.cand[og + 8 * p][0];
             now[p] = own.count[og + 8 * p] != 0 ? q : old[p];
             if (ol == 0) code[k][wave * IT + og + 8 * p] = (uint8_t)now[p];
         }
@@ -656,16 +759,15 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
 }  // namespace
 
 int icq_launch_encode_wave(const icq_index *ix, const float *x, int64_t N, uint8_t *codes, bool icm, int sweeps,
-                           uint32_t *changed, hipStream_t s) {
+                           float *res, uint32_t *changed, hipStream_t s) {
     auto launch = [&](auto kernel, int it, size_t lds) -> int {
         ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(kernel), (int)lds));
         kernel<<<(unsigned)((N + 4 * it - 1) / (4 * it)), W_THREADS, lds, s>>>(
-            x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->enc_meta, ix->K, ix->m, N, codes, sweeps, changed);
+            x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->enc_meta, ix->K, ix->m, N, codes, sweeps, res, changed);
         return icq_check_launch();
     };
-#define ICQ_ENC(IT, NS)                                                                                               \
-    return icm ? launch(encode_wave_kernel<IT, NS, true>, IT, sizeof(WaveShared<IT, NS>) + (size_t)ix->K * 4 * IT)   \
-               : launch(encode_wave_kernel<IT, NS, false>, IT, sizeof(WaveShared<IT, NS>) + (size_t)ix->K * 4 * IT)
+#define ICQ_ENC_AS(IT, NS, ICM) launch(encode_wave_kernel<IT, NS, ICM>, IT, sizeof(WaveShared<IT, NS, ICM>) + (size_t)ix->K * 4 * IT)
+#define ICQ_ENC(IT, NS) return icm ? ICQ_ENC_AS(IT, NS, true) : ICQ_ENC_AS(IT, NS, false)
 #define ICQ_ENC_BOTH(NS, FEW) do { if (FEW) { ICQ_ENC(16, NS); } ICQ_ENC(32, NS); } while (0)
     // 16 items a wavefront while such blocks find room beside each other (two per CU; one from 8 slices on): a level's chain of
     // steps is shorter (30000 x 128: 47 against 57 us; 15000 x 256: 61 / 83), but every codeword is read from LDS for half as
@@ -682,11 +784,12 @@ int icq_launch_encode_wave(const icq_index *ix, const float *x, int64_t N, uint8
         case 8: ICQ_ENC_BOTH(8, blocks <= cu);
         case 12:
             if (icm || blocks <= cu) { ICQ_ENC(16, 12); }
-            return launch(encode_wave_kernel<32, 12, false>, 32, sizeof(WaveShared<32, 12>) + (size_t)ix->K * 128);
+            return ICQ_ENC_AS(32, 12, false);
         default:
             if (icm || (blocks + cu - 1) / cu * 20 <= ((blocks + 1) / 2 + cu - 1) / cu * 39) { ICQ_ENC(16, 16); }
-            return launch(encode_wave_kernel<32, 16, false>, 32, sizeof(WaveShared<32, 16>) + (size_t)ix->K * 128);
+            return ICQ_ENC_AS(32, 16, false);
     }
 #undef ICQ_ENC_BOTH
 #undef ICQ_ENC
+#undef ICQ_ENC_AS
 }

@@ -1299,6 +1299,85 @@ def test_encode_over_the_forms_of_its_kernels(gpu, m, d, N, sweeps):
         judge(xs - sum(cb64[l][state[l]] for l in range(K) if l != k), k, s[k])
 
 
+@pytest.mark.parametrize("d,N", [(32, 400), (64, 40_000), (96, 33_000), (128, 700), (192, 300), (256, 33_000), (300, 200), (512, 130)])
+@pytest.mark.parametrize("equal,wild", [(8, 0), (9, 128), (16, 7), (32, 16), (33, 300), (128, 2)])
+def test_encode_where_lists_of_candidates_say_little(gpu, d, N, equal, wild):
+    """Up to eight or 32 candidates are looked at one by one, more are scored with all other codewords on the matrix cores, and so
+    are items that have no bound, a few of them by themselves: codebooks of `equal` equal codewords each, every `wild`-th vector
+    with a component that is infinite.  Among equal codewords the first is taken, refinement keeps a current one; the
+    vectors next to a wild one are not disturbed.  Judged as in test_encode_over_the_forms_of_its_kernels."""
+    torch, b = gpu
+    K, m = 3, 256
+    few = m // equal
+    rng = np.random.default_rng(d * 1000 + equal)
+    cb = (rng.standard_normal((K, few, d)) * (0.7 ** np.arange(K))[:, None, None]).astype(np.float32)
+    cb = np.concatenate([cb] * (m // few + 1), axis=1)[:, :m]
+    x = rng.standard_normal((N, d)).astype(np.float32)
+    strange = np.arange(0, N, wild) if wild else np.zeros(0, dtype=int)
+    plain = np.setdiff1d(np.arange(N), strange)
+    x[strange, 0] = np.inf
+    index = b.icq_index_create(_dev(torch, cb), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    codes, changed = torch.empty((K, N), dtype=torch.uint8, device="cuda"), torch.empty((1,), dtype=torch.int32, device="cuda")
+    xd = _dev(torch, x)
+    b.icq_encode(index, xd, codes, ws)
+    start = rng.integers(0, m, (K, N), dtype=np.uint8)
+    refined = _dev(torch, start)
+    b.icq_encode_refine(index, xd, refined, 1, changed, ws)
+    torch.cuda.synchronize()
+    first, second = codes.cpu().numpy(), refined.cpu().numpy()
+    assert (first < few).all()
+    assert ((second < few) | (second == start)).all() and int(changed[0]) == int((second != start).sum())
+    # an infinite component: the score is -inf where the codeword has that sign, the first of those is taken
+    up = cb[0][:, 0] > 0
+    if up.any():
+        assert (first[0, strange] == np.argmax(up)).all()
+        assert (second[0, strange] == np.where(up[start[0, strange]], start[0, strange], np.argmax(up))).all()
+    at = plain[np.unique(np.concatenate([np.arange(min(plain.size, 150)), np.arange(max(0, plain.size - 150), plain.size), rng.integers(0, plain.size, 300)]))]
+    cb64, xs, n, eps = cb.astype(np.float64), x[at].astype(np.float64), np.arange(at.size), d * 2.0 ** -23
+
+    def judge(r, k, chosen):
+        d2 = (r * r).sum(axis=1)[:, None] - 2.0 * r @ cb64[k].T + (cb64[k] ** 2).sum(axis=1)[None]
+        slack = eps * ((r * r).sum(axis=1) + (cb64[k] ** 2).sum(axis=1).max())
+        assert (d2[n, chosen] <= d2.min(axis=1) + slack).all(), "level %d: a clearly nearer codeword exists" % k
+    r = xs.copy()
+    for k in range(K):
+        judge(r, k, first[k, at])
+        r = r - cb64[k][first[k, at]]
+    for k in range(K):
+        state = np.concatenate([second[:k, at], start[k:, at]])
+        judge(xs - sum(cb64[l][state[l]] for l in range(K) if l != k), k, second[k, at])
+
+
+def test_encode_refine_does_not_take_long_over_a_few_wild_vectors(gpu):
+    """One vector in 128 without a bound costs its wavefront a look at each codeword, not its neighbours a contraction in
+    fp32 (with which a sweep took 5.6 times as long as without such vectors; 1.6 now)."""
+    torch, b = gpu
+    N, d, K = 100_000, 128, 8
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    cb = torch.randn((K, 256, d), device="cuda", generator=gen) * torch.tensor([0.6 ** k for k in range(K)], device="cuda")[:, None, None]
+    index = b.icq_index_create(cb.contiguous(), torch.empty((K, 0), dtype=torch.uint8, device="cuda"), 1)
+    x = torch.randn((N, d), device="cuda", generator=gen)
+    y = x.clone()
+    y[::128, 3] = float("inf")
+    ws = torch.empty(b.icq_encode_workspace_bytes(index, N), dtype=torch.uint8, device="cuda")
+    start = torch.randint(0, 256, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    times = []
+    for v in (x, y):
+        best = float("inf")
+        for _ in range(6):
+            codes = start.clone()
+            e0, e1 = torch.cuda.Event(True), torch.cuda.Event(True)
+            e0.record()
+            b.icq_encode_refine(index, v, codes, 4, None, ws)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    assert times[1] < 3.5 * times[0], times
+
+
 @pytest.mark.parametrize("d", [160, 256, 384, 512])
 def test_encode_with_few_codebooks_and_then_many(gpu, d):
     """The register form's LDS grows with the number of codebooks: 64 of them after 2, on one kernel.  Greedy assignment takes
