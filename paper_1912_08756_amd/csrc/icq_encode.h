@@ -9,7 +9,7 @@ static inline int icq_enc_slices(int d_pad) {
     return n <= 4 || n > 16 ? n : n <= 6 ? 6 : n <= 8 ? 8 : n <= 12 ? 12 : 16;
 }
 // Whether encode_wave_kernel takes every call on such codebooks; then nothing reads the halves' remainders.
-static inline bool icq_enc_wave_only(int d_pad) { return d_pad <= 256; }
+static inline bool icq_enc_wave_only(int d_pad) { return d_pad <= 128; }
 
 // 2^(bits - e) with e the smallest integer for which x < 2^e (clamped): x times this is below 2^bits
 __device__ __forceinline__ float icq_enc_scale_below(float x, int bits) {

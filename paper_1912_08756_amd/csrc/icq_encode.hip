@@ -14,8 +14,8 @@
 // current codeword among equal scores, and only items whose sub-code changed get a new residual.
 //
 // Two kernels do both, all levels (and sweeps) of a block's items in one launch: encode_wave_kernel (icq_encode_wave.hip) holds
-// the residuals in registers, up to 256 dimensions always and up to 512 for few items; encode_kernel below keeps them in
-// memory.  Two steps per level:
+// the residuals in registers, up to 128 dimensions always and up to 512 where launch_encode says so; encode_kernel below keeps
+// them in memory.  Two steps per level:
 //  1. The contraction on half-precision copies of residual and codewords (v_mfma_f32_32x32x16_f16, sixteen
 //     times the rate of the fp32 instruction) leaves, with a bound E on its error, a SUPERSET of the
 //     codewords that can be the argmin: those whose score is within 2 E of the best.  E comes from
@@ -639,13 +639,24 @@ template <bool ICM>
 static int launch_encode(const icq_index *ix, const float *x, int64_t N, uint8_t *codes, int sweeps, float *res,
                          uint32_t *changed, hipStream_t s) {
     const int slices = icq_enc_slices(ix->d_pad);
-    // Residuals in registers where the wavefronts that hold them do not spill.  Above 256 dimensions coordinate descent has
-    // one block of 64 items per CU there: ahead for two rounds of them (d = 300, 384, 512, 30000 items: 1.18, 1.19, 1.09
-    // times as fast; 50000: 0.8), greedy assignment throughout (300, 384, 512; 15000 items 2.3 - 2.4, 80000 1.2 - 1.5).
-    if (icq_enc_wave_only(ix->d_pad) || (slices <= 16 && (!ICM || N <= 2 * 64 * (int64_t)ix->num_cu)))
+    // Residuals in registers: always up to 128 dimensions (icq_enc_wave_only).  Above, by what a CU then holds (the register form's
+    // time over encode_kernel's):
+    //  - coordinate descent has one wavefront per SIMD there, two with few items.  Up to 256 dimensions while blocks find room in one
+    //    round (d = 144, 192, 200, 256, K = 8; 16384 items 0.44 .. 0.51, 32768 0.52, 0.49, 0.79, 0.79; 33000 1.08, 1.01, 1.05,
+    //    1.04, K = 16 1.05, 1.12, 1.26, 1.33, 131000 1.0 .. 1.1; with vectors that have no bound 1.3 to 1.6), beyond that while
+    //    blocks of 64 items do (d = 288, 384, 512, K = 8; 16384 items 0.60, 0.55, 0.58; 17000 1.10, 1.08, 1.28);
+    //  - greedy assignment up to 256 dimensions throughout.  Beyond that one block of 128 items per CU against two of
+    //    encode_kernel's: ahead in the first round of blocks, in those that leave the CUs a single block there and (12 slices) in
+    //    well filled others (d = 320, 384, 448, K = 16; 32768 items 0.71, 0.65, 0.70; 1.03, 1.15, 1.45, 1.9 rounds 1.22 .. 0.97,
+    //    1.20 .. 0.93, 1.01 .. 1.05; 2.05, 2.9 rounds 1.00, 0.97, 0.92 and 0.84, 0.82, 0.90; 3.05 .. 3.6 1.13 .. 1.00, 1.05 .. 0.94,
+    //    1.09 .. 1.02).  With 15 or 16 slices, of which the register form wastes none, throughout (d = 512: 0.81 .. 1.08).
+    const int64_t cu = ix->num_cu, blocks = (N + EB - 1) / EB, rounds = (blocks + cu - 1) / cu;
+    const bool full = slices == 12 && 5 * (blocks - (rounds - 1) * cu) > 3 * cu;
+    const bool wave = ICM ? N <= (slices <= 8 ? 128 : 64) * cu : slices <= 8 || rounds % 2 == 1 || full || ix->d_pad > 448;
+    if (icq_enc_wave_only(ix->d_pad) || (slices <= 16 && wave))
         return icq_launch_encode_wave(ix, x, N, codes, ICM, sweeps, res, changed, s);
     ICQ_HIP_TRY(icq_allow_lds(reinterpret_cast<const void *>(encode_kernel<ICM>), sizeof(EncShared)));
-    encode_kernel<ICM><<<(unsigned)((N + EB - 1) / EB), E_THREADS, sizeof(EncShared), s>>>(
+    encode_kernel<ICM><<<(unsigned)blocks, E_THREADS, sizeof(EncShared), s>>>(
         x, ix->d, ix->cb, ix->d_pad, ix->cnorm, ix->half_hi, ix->half_lo, ix->enc_meta, ix->K, slices, N, codes, sweeps, res, changed);
     return icq_check_launch();
 }

@@ -1,5 +1,5 @@
 // Encoding with the residuals in registers (arxiv 1912.08756; the method -- candidates from half precision with an error
-// bound, decided by fp32 scores -- stands in icq_encode.hip): up to 256 dimensions always, up to 512 where launch_encode
+// bound, decided by fp32 scores -- stands in icq_encode.hip): up to 128 dimensions always, up to 512 where launch_encode
 // there says so.
 //
 // A wavefront owns its 32 (few items: 16) vectors alone and sees all 256 codewords, so nothing is exchanged with the rest of
@@ -530,9 +530,9 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                 // wavefront's last item, with no branch: where `if (item < live)` stood, the compiler put copies of other values
                 // in front of the point at which the lanes of missing items join again, and those lanes were left without them.
                 const auto rows = __builtin_amdgcn_make_buffer_rsrc(res + i0 * d_pad, 0, live * d_pad * 4, 0x00027000);
-                auto place = [&](int p, int g) -> int {
-                    const int e = g * 32 + ol * 4;
-                    return e < d_pad ? ((og + 8 * p) * d_pad + e) * 4 : 1 << 30;           // past the buffer: not written, read as zero
+                auto place = [&](int l, int p, int g) -> int {
+                    const int e = g * 32 + (l & 7) * 4;
+                    return e < d_pad ? (((l >> 3) + 8 * p) * d_pad + e) * 4 : 1 << 30;     // past the buffer: not written, read as zero
                 };
                 if (ICM) {
 #pragma unroll
@@ -542,7 +542,7 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                             float o[4];
                             load4(codeword(k, old[p]), g, o, ol);
                             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uint32x4, float4v{r[p][g][0], r[p][g][1], r[p][g][2], r[p][g][3]}),
-                                                                   rows, place(p, g), 0, 0);
+                                                                   rows, place(lane, p, g), 0, 0);
 #pragma unroll
                             for (int i = 0; i < 4; ++i) r[p][g][i] = fmaf(o[i], sr, r[p][g][i]);
                         }
@@ -615,11 +615,12 @@ __global__ __launch_bounds__(W_THREADS, w_waves(IT, NS, ICM)) void encode_wave_k
                 }
                 // no score a number: index 0 (ICM: the current one) stays
                 if (ICM) {
+                    const int lane = fresh(tid) & 63;
 #pragma unroll
                     for (int p = 0; p < P; ++p)
 #pragma unroll
                         for (int g = 0; g < NS; ++g) {
-                            const float4v v = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, place(p, g), 0, 0));
+                            const float4v v = __builtin_bit_cast(float4v, __builtin_amdgcn_raw_buffer_load_b128(rows, place(lane, p, g), 0, 0));
 #pragma unroll
                             for (int i = 0; i < 4; ++i) r[p][g][i] = v[i];
                         }
@@ -780,7 +781,9 @@ int icq_launch_encode_wave(const icq_index *ix, const float *x, int64_t N, uint8
         case 2: ICQ_ENC_BOTH(2, blocks <= 2 * cu);
         case 3: ICQ_ENC_BOTH(3, blocks <= 2 * cu);
         case 4: ICQ_ENC_BOTH(4, blocks <= 2 * cu);
-        case 6: ICQ_ENC_BOTH(6, blocks <= 2 * cu);
+        case 6:
+            if (icm || blocks <= 2 * cu) { ICQ_ENC(16, 6); }
+            return ICQ_ENC_AS(32, 6, false);
         case 8: ICQ_ENC_BOTH(8, blocks <= cu);
         case 12:
             if (icm || blocks <= cu) { ICQ_ENC(16, 12); }
