@@ -277,9 +277,9 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
 // expanded into a position list in the wavefront's part of LDS, then per position the record
 // gather, the K table reads and the key, as in refine_dist_kernel.
 // (A wavefront may take half or a quarter of a chunk, see icq_launch_refine_masks; what follows says chunk for either.)
-// Every 65th chunk -- where the others are taken whole, every 65th quarter of one -- is done in a first launch, unfiltered
+// Every 65th chunk (or every 65th quarter of one, seed_parts = 4) is done in a first launch, unfiltered
 // (!FILTER); the select kernel's topk-th
-// distance of those keys then bounds what the other chunks add in a second launch (FILTER: keys
+// distance of those keys then bounds what the others add in a second launch (FILTER: keys
 // above it are dropped; ties at it are kept, the final select decides).  The final lists are
 // unchanged -- at least topk keys at or below the bound are already there -- and the key lists
 // shrink to a few per cent.  Survivors are counted from the popcounts, added up per block.
@@ -291,8 +291,7 @@ constexpr int RM_PER = 4;                             // records a lane gathers 
 constexpr int RM_LIST = 512;                          // positions a wavefront expands per round
 constexpr int RM_QPB = 1;                             // queries per block (two: 1.39 against 1.25 ms at N = 1e8, 128 queries)
 constexpr int RM_SEED_EVERY = 65;                     // odd: the first launch's chunks are spread over all XCDs
-// 32-bit words per lane of the first launch's pieces, by those of the second's
-constexpr int rm_seed_words(int words) { return words == RM_FULL ? RM_FULL / 4 : words; }
+constexpr uint32_t RM_SEED_PARTS = 4;                 // of whole chunks the first launch may take quarters
 static_assert(RM_LIST % (64 * RM_PER) == 0, "a round of the list is whole steps of gathers");
 static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into the chunk");
 
@@ -306,7 +305,7 @@ static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into th
 template <int WORDS, bool FILTER, int QPB, bool EXACT, int RM_WORDS>
 __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel(
     const uint8_t *__restrict__ items, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
-    size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, uint32_t seed_every, int window, int xs_shift, int Q,
+    size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, uint32_t seed_every, uint32_t seed_parts, int window, int xs_shift, int Q,
     const float *__restrict__ kth_dist, int topk, u64 *__restrict__ keys, uint32_t *__restrict__ key_count,
     int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
     __shared__ __attribute__((aligned(16))) float T_all[QPB][4 * WORDS * ICQ_LUT_W];
@@ -314,7 +313,6 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
     __shared__ uint32_t sum_all[QPB], done_all[QPB];  // survivors of the block, wavefronts that have added theirs
     constexpr int RW = WORDS;
     constexpr uint32_t PIECE = RM_WORDS * 2048;       // positions
-    constexpr uint32_t SEED_PARTS = RM_WORDS / rm_seed_words(RM_WORDS);
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -330,7 +328,7 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         const uint32_t i = ((win * (uint32_t)window + j) << xs_shift) + xcd;
         if (j >= (uint32_t)window || i >= nsel) return 0xFFFFFFFFu;
         if (!FILTER) return i * seed_every;
-        return SEED_PARTS == 1u ? i + i / (RM_SEED_EVERY - 1u) + 1u : i;   // all but every 65th : all
+        return seed_parts == 1u ? i + i / (RM_SEED_EVERY - 1u) + 1u : i;   // all but every 65th : all
     };
     if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
     // Word r of this lane covers the 32 positions from c * PIECE + (r * 64 + lane) * 32: neighbouring
@@ -382,10 +380,12 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
         uint32_t w[RM_WORDS];
 #pragma unroll
         for (int r = 0; r < RM_WORDS; ++r) w[r] = nxt[r];
-        if (FILTER && SEED_PARTS > 1u) {              // what the first launch has done is out
-            const uint32_t at = c * SEED_PARTS % RM_SEED_EVERY, done = at == 0u ? 0u : RM_SEED_EVERY - at;
+        if (FILTER && RM_WORDS == RM_FULL && seed_parts > 1u) {       // the quarter that the first launch has done is out
+            const uint32_t at = c * RM_SEED_PARTS % RM_SEED_EVERY, done = at == 0u ? 0u : RM_SEED_EVERY - at;
+            if (done < RM_SEED_PARTS) {               // wavefront-uniform
 #pragma unroll
-            for (int r = 0; r < RM_WORDS; ++r) w[r] = (uint32_t)(r / rm_seed_words(RM_WORDS)) == done ? 0u : w[r];
+                for (int r = 0; r < RM_WORDS; ++r) w[r] = (uint32_t)r / (RM_FULL / RM_SEED_PARTS) == done ? 0u : w[r];
+            }
         }
         // next piece of work: the next query of this chunk, else the wavefront's next chunk
         uint32_t qn = qq + 1, jn = j, cn = c;
@@ -674,10 +674,12 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         if (pairs <= 320) words = RM_FULL / 4;
         else if (pairs <= 700 || (g2 && Q < 8 && whole >= 600) || (g2 && whole >= 1700 && pairs <= 200000)) words = RM_FULL / 2;
     }
-    const int seed_words = seed_every == 1u ? RM_FULL : rm_seed_words(words);
+    // (the largest calls have wavefronts enough for whole ones: 1e8 items, 128 queries 1802 us, with quarters 1823)
+    const uint32_t seed_parts = seed_every != 1u && words == RM_FULL && pairs <= 200000 ? RM_SEED_PARTS : 1u;
+    const int seed_words = words / (int)seed_parts;
     const uint32_t chunks = (uint32_t)(scan_end / (2048 * words)), seed_chunks = (uint32_t)(scan_end / (2048 * seed_words));
     const uint32_t nseed = (seed_chunks + seed_every - 1) / seed_every;
-    const uint32_t nmain = seed_every == 1u ? 0u : words == seed_words ? chunks - nseed : chunks;
+    const uint32_t nmain = seed_every == 1u ? 0u : seed_parts == 1u ? chunks - nseed : chunks;
     auto select = [&](bool more) -> int {
         return icq_launch_select(keys, key_count, cap, Q, topk, splits, more, ticket, out_ids, out_dist, s);
     };
@@ -714,7 +716,7 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         const unsigned ngroups = ((unsigned)Q + RM_QPB - 1) / RM_QPB;                                        \
         auto go = [&](auto kernel) {                                                                         \
             kernel<<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(                                      \
-                items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, window, xs_shift, Q, out_dist, topk,     \
+                items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, seed_parts, window, xs_shift, Q, out_dist, topk,     \
                 keys, key_count, cap, cand_count, thr, ix->Kf);                                              \
         };                                                                                                   \
         const int piece = FILTER ? words : seed_words;                                                       \
