@@ -372,7 +372,7 @@ def encode_leg(torch, b, cfg, steps):
     e_refined = mean_err(refined)
     same_r = float((refined == src.to(torch.uint8)).all(dim=0).float().mean().item())
     x_norm2 = float((x.double() ** 2).sum(dim=1).mean().item())
-    return {"bound": "mfma", "kernel": "encode_kernel", "achieved": round(ach, 2), "peak": 2500.0,
+    return {"bound": "mfma", "kernel": "encode_wave_kernel", "achieved": round(ach, 2), "peak": 2500.0,
             "unit": "TFLOP/s", "frac": round(ach / 2500.0, 4), "traffic": None, "ms": round(ms, 4),
             "items_per_s": round(N / (ms * 1e-3), 1), "N": N, "codes_recovered_frac": round(same, 4),
             "mean_sq_error": {"planted_codes": round(e_planted, 4), "greedy": round(e_greedy, 4),

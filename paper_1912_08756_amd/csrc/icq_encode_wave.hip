@@ -14,8 +14,8 @@
 // What the running bound admits too many is dropped when a later chunk lifts it by more than that margin.  The residuals are
 // kept times a power of two of the block (see sr), so making halves of them is one instruction for two.
 //
-// What bounds it (10^6 x 128, K = 8): vector issue, 54 % busy with 1008 instructions per wavefront and level (32 items; the
-// form before spent 3252 on as many), beside the matrix cores' 26 %; three wavefronts a SIMD overlap the two.
+// What bounds it (10^6 x 128, K = 8): vector issue, 53 % busy with 1002 instructions per wavefront and level (32 items; the
+// form before spent 3252 on as many), beside the matrix cores' 27 %; three wavefronts a SIMD overlap the two.
 // Contraction and candidates are about half of the instructions (per chunk 16 differences, 16 sign collections, 8
 // maxima of three), halves and norms 130, the update 64, second looks 250.  Leaving out single parts gained 3 - 5 % each.
 // Before / now: 10^6 x 128, K = 8: 1.03 / 0.84 ms; 262147 x 96, K = 16, two sweeps: 1.74 / 1.21 ms; 5000 x 128, K = 8:
@@ -36,8 +36,8 @@ constexpr int W_THREADS = 256;             // four wavefronts, each with items o
 // Candidates of an item looked at one by one, beyond that all codewords are scored on the matrix cores; and items of a wavefront
 // without a usable list that are taken one after another instead.  Above 128 dimensions a level's codewords come from memory
 // for each such item as they do for all of them together.  10^5 items, K = 8, 16 equal codewords each, 8 / 32: 128 dimensions,
-// greedy 840 / 760 us, a sweep 1520 / 950; 32 dimensions, greedy 311 / 362, a sweep 592 / 450; 256, greedy 1925 / 2495.  One infinite vector
-// in 128 items, a sweep, without / with: 128 dimensions 1130 / 480 us.
+// greedy 849 / 705 us, a sweep 1516 / 923; 32 dimensions, greedy 311 / 362, a sweep 592 / 450; 256, greedy 1925 / 2495.  One infinite vector
+// in 128 items, a sweep, without / with: 128 dimensions 1130 / 316 us.
 constexpr int w_cand(int ns, bool icm) { return ns > 4 || (ns == 1 && !icm) ? 8 : 32; }
 constexpr int w_lone(int ns) { return ns <= 4 ? 4 : 0; }
 constexpr float W_U = 4.8828125e-4f;       // 2^-11: relative rounding error of a half
@@ -47,8 +47,10 @@ constexpr int w_step(int ns) { return ns > 4 ? 2 : 1; }                         
 constexpr int w_stage(int ns) { return ns == 1 ? 8 : ns == 2 ? 4 : 2; }                   // and fetched together
 constexpr int w_ring(int ns) { return ns == 8 ? 4 : 2; }                                  // such stages in LDS
 
-// Wavefronts per SIMD that the registers allow without spilling: a spilled register costs more than a missing wavefront
-// (128 dimensions, greedy: 106 spilled at two wavefronts 1.9 ms, none 0.94; 51 at three 1.5, none 0.84).
+// Wavefronts per SIMD that the registers allow with next to no spilling: a spilled register costs more than a missing wavefront
+// (128 dimensions, greedy: 106 spilled at two wavefronts 1.9 ms, none 0.94; 51 at three 1.5, none 0.84; 262147 x 96, 16
+// codebooks, greedy and two sweeps, three wavefronts: 57 spilled 1.53, 13 1.27, 5 1.21).  Spilled by <items, slices, ICM>: <32, 3, true> 5, <32, 4, false> 9,
+// <16, 16, true> 10, <32, 16, false> 63; the others none.
 constexpr int w_waves(int it, int ns, bool icm) {
     if (ns <= 4) return ns == 4 && it == 32 && icm ? 2 : 3;
     if (ns <= 8) return it == 16 ? (ns == 8 && icm ? 1 : 2) : (ns == 6 && !icm ? 2 : 1);

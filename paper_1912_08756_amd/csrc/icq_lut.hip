@@ -271,6 +271,8 @@ int icq_launch_build_lut(const icq_index *ix, const float *queries, int Q, float
         //   K =  8, d = 128    8.3 / 5.2   8.2 / 5.2    8.3 / 6.3    8.6 / 7.4    9.3 / 8.7   9.1 / 10.9  9.8 / 12.2
         //   K =  8, d = 960                             43.4 / 32.4  43.7 / 34.5  44.8 / 36.8 46.0 / 51.9 47.5 / 60.7
         //   K = 16, d = 99                 8.5 / 5.6    8.4 / 7.2    8.7 / 7.9    8.9 / 10.0  9.4 / 12.7
+        // With the codebooks out of the caches (K = 8; 1 and 200 queries) d = 32 7.9 / 6.1, 7.6 / 6.2, d = 128 12.1 / 7.7, 12.0 / 8.8,
+        // d = 960 50.4 / 39.2, 50.3 / 42.6; of 270 such calls none slower.
         const int64_t waves = (int64_t)(nq + 31) / 32 * (ncols / 32);
         if (waves <= (ix->d_pad <= 2 * BK ? 6 : 3) * (int64_t)ix->num_cu) {
             dim3 few((unsigned)(ncols / 32), (unsigned)((nq + 31) / 32));

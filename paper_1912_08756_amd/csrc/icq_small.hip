@@ -111,7 +111,8 @@ __global__ __launch_bounds__(SM_THREADS) void small_search_kernel(
 // 1000 x 131072 2253 / 900.  Kf = 1, 2, 3: the same line within 20 %.  Those with 2048 items a step; with 4096, lists / this:
 // 1 x 2.5e6 33.6 / 29.0, 1 x 4e6 35.4 / 34.2, 4 x 5e5 29.0 / 21.1, 3 x 10^6 28.0 / 25.5, 5 x 10^6 33.6 / 37.0, 8 x 5e5 29.3 / 29.7,
 // 100 x 30000 25.3 / 23.9, 700 x 5000 31.5 / 31.7; at 0.1 %: 4 x 7e5 23.0 / 24.5, 28 x 10^5 24.1 / 22.4; at 5 %: 39.7 / 33.5,
-// 30.7 / 24.1).
+// 30.7 / 24.1: next to the line lists may be ahead by 6 % where next to nothing survives.  Against 2048 items a step and a line at
+// 1.8e6 pairs, 816 calls of 1.5e6 to 2.9e6 pairs at 0.05 % to all surviving: 0.69 of the time, none 4 % slower).
 bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share) {
     const double pairs = (double)Q * (double)ix->N;
     return ix->scan_mode == ICQ_SCAN_AUTO && ix->Kf <= 4 && ix->item_stride <= 16 && topk <= 512 &&
@@ -120,7 +121,7 @@ bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share) {
 
 int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,
                      uint32_t *cand_count, int64_t cap, hipStream_t s) {
-    // about eight blocks per CU; beyond that a block takes more steps with the tables it has loaded
+    // about eight blocks per CU, of which two run at a time; beyond that a block takes more steps with the tables it has loaded
     int64_t chunks = (8ll * ix->num_cu + Q - 1) / Q;
     const int64_t most = (ix->N + SM_STEP - 1) / SM_STEP;
     if (chunks > most) chunks = most;
