@@ -1,7 +1,7 @@
 // Both stages of the two-step search (arxiv 1912.08756, Eq. 2 and Eq. 1) in one kernel, for an index of few items:
 // a small database, or the first tiles of the running search, where every item or every fifth one survives.
 //
-// A block takes 4096 items at a time for one query: their crude distances from the query's tables in LDS, the
+// A block takes 4096 items at a time for one query (2048 where many queries meet few items: icq_launch_small): their crude distances from the query's tables in LDS, the
 // survivors compacted into a list in LDS, and that list's exact distances as keys (order-preserving bits of D, id)
 // for the selection.  No candidate list goes through memory, the codes are read from the item records that the
 // second stage needs as well, and a list slot in memory is reserved once per 4096 items instead of once per
@@ -17,18 +17,17 @@
 
 namespace {
 
-constexpr int SM_THREADS = 1024;
 constexpr int SM_PER = 4;                            // items per thread and step
-constexpr int SM_STEP = SM_THREADS * SM_PER;
-static_assert(SM_STEP <= 65536, "the list holds 16-bit offsets");
 
 // items [N] records of WORDS words; thr [Q], Q = gridDim.y; keys [Q][cap]; count [Q] zero on entry, N <= ICQ_MAX_N
 // (a step past it still fits 32 bits).
-// Block x takes the items [x * per, (x + 1) * per), per a multiple of SM_STEP.
-template <int WORDS>
+// Block x takes the items [x * per, (x + 1) * per), per a multiple of the step.
+template <int WORDS, int SM_THREADS>
 __global__ __launch_bounds__(SM_THREADS) void small_search_kernel(
     const uint8_t *__restrict__ items, uint32_t N, int K, int Kf, const float *__restrict__ lut,
     const float *__restrict__ thr, uint32_t per, u64 *__restrict__ keys, int64_t cap, uint32_t *__restrict__ count) {
+    constexpr int SM_STEP = SM_THREADS * SM_PER;
+    static_assert(SM_STEP <= 65536, "the list holds 16-bit offsets");
     __shared__ __attribute__((aligned(16))) float T[4 * WORDS * ICQ_LUT_W];      // a table per record byte, zero beyond K
     __shared__ float list_p[SM_STEP];
     __shared__ uint16_t list_i[SM_STEP];
@@ -121,20 +120,29 @@ bool icq_small_usable(const icq_index *ix, int Q, int topk, icq_share share) {
 
 int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *thr, unsigned long long *cand_keys,
                      uint32_t *cand_count, int64_t cap, hipStream_t s) {
+    // 1024 threads, or 512 where those cover the index in one step (the other half would only wait at the barriers) and the
+    // blocks are more than two per CU, the most that run at a time with 1024: then the next ones start earlier.  K = 12, 2 %
+    // surviving, 1024 / 512 threads in us: 520 queries over 700, 1300, 2048 items 18.0 / 16.3, 19.8 / 18.0, 20.1 / 18.6; 1000
+    // queries 23.5 / 21.3, 26.4 / 24.3, 27.8 / 26.1; 3000 over 700 47.7 / 41.2.  Up to 512 queries the two are within 2 %, and past
+    // 2048 items (to 4096) 512 threads take 7 to 15 % longer for 300 to 1000 queries.
+    const int threads = ix->N <= 512 * SM_PER && Q > 2 * ix->num_cu ? 512 : 1024;
+    const int64_t step = threads * SM_PER;
     // about eight blocks per CU, of which two run at a time; beyond that a block takes more steps with the tables it has loaded
     int64_t chunks = (8ll * ix->num_cu + Q - 1) / Q;
-    const int64_t most = (ix->N + SM_STEP - 1) / SM_STEP;
+    const int64_t most = (ix->N + step - 1) / step;
     if (chunks > most) chunks = most;
-    const uint32_t per = (uint32_t)(((ix->N + chunks - 1) / chunks + SM_STEP - 1) / SM_STEP * SM_STEP);
+    const uint32_t per = (uint32_t)(((ix->N + chunks - 1) / chunks + step - 1) / step * step);
     const dim3 grid((unsigned)((ix->N + per - 1) / per), (unsigned)Q);
-#define ICQ_SM_LAUNCH(W)                                                                                           \
-    small_search_kernel<W><<<grid, SM_THREADS, 0, s>>>(ix->items, (uint32_t)ix->N, ix->K, ix->Kf, lut, thr, per, cand_keys, \
-                                                       cap, cand_count)
+#define ICQ_SM_AS(W, THREADS)                                                                                      \
+    small_search_kernel<W, THREADS><<<grid, THREADS, 0, s>>>(ix->items, (uint32_t)ix->N, ix->K, ix->Kf, lut, thr, per, cand_keys, \
+                                                             cap, cand_count)
+#define ICQ_SM_LAUNCH(W) do { if (threads == 512) ICQ_SM_AS(W, 512); else ICQ_SM_AS(W, 1024); } while (0)
     switch (ix->item_stride) {
         case 4: ICQ_SM_LAUNCH(1); break;
         case 8: ICQ_SM_LAUNCH(2); break;
         default: ICQ_SM_LAUNCH(4); break;
     }
 #undef ICQ_SM_LAUNCH
+#undef ICQ_SM_AS
     return icq_check_launch();
 }

@@ -1870,10 +1870,12 @@ def test_search_sweep_against_oracle(gpu, case):
 @pytest.mark.parametrize("K,Kf,m,N,Q,topk,frac", [
     (4, 1, 256, 1, 3, 5, 1.0), (16, 4, 256, 63, 8, 10, 0.5), (8, 3, 200, 2047, 5, 100, 0.1), (6, 2, 256, 2049, 4, 10, 0.01),
     (12, 4, 256, 4096, 37, 257, 1.0), (3, 3, 77, 8191, 70, 100, 0.2), (16, 3, 256, 50_001, 33, 100, 0.02),
-    (5, 2, 256, 400_003, 4, 512, 0.01), (16, 4, 256, 4095, 5, 100, 1.0), (8, 3, 256, 4097, 7, 20, 0.3), (4, 3, 130, 8193, 3, 50, 1.0)])
+    (5, 2, 256, 400_003, 4, 512, 0.01), (16, 4, 256, 4095, 5, 100, 1.0), (8, 3, 256, 4097, 7, 20, 0.3), (4, 3, 130, 8193, 3, 50, 1.0),
+    (8, 3, 256, 2048, 600, 20, 0.2), (16, 4, 256, 2049, 513, 10, 0.1), (4, 2, 256, 700, 1030, 30, 1.0)])
 def test_search_of_a_small_index_in_one_kernel(gpu, K, Kf, m, N, Q, topk, frac):
     """Both stages in one kernel (few items times queries): against the oracle, and bit for bit against the scan with
-    candidate lists (the sums are the same fp32 additions).  Sizes around a step of 4096 items and half of it, all record widths."""
+    candidate lists (the sums are the same fp32 additions).  Sizes around a step of 4096 items and half of it, all record widths;
+    600, 513 and 1030 queries: either side of the line where a block is half as large."""
     rng = np.random.default_rng(K * 1000 + N)
     cb = (rng.standard_normal((K, m, 24)) * (0.7 ** np.arange(K))[:, None, None]).astype(np.float32)
     codes = rng.integers(0, m, size=(K, N), dtype=np.uint8)
