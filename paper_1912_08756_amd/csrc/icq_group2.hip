@@ -6,7 +6,7 @@
 //
 // Layout (built once by a counting sort): the 65536 pairs in the scattered order of
 // icq_g2_pair_of_slot, every pair's run padded to whole 16 positions; per position the item id (perm),
-// the item's record (items_grouped) and its remaining fast sub-codes as rows of their own (g2_rows);
+// the item's record (items_grouped; 16-byte records as two planes, the halves of all positions behind each other) and its remaining fast sub-codes as rows of their own (g2_rows);
 // per 16 positions the pair and the number of real items (g2_info).
 #include "icq_internal.h"
 
@@ -53,13 +53,19 @@ __global__ __launch_bounds__(1024) void g2_offsets_kernel(uint32_t *__restrict__
 
 __global__ void g2_scatter_kernel(const uint8_t *__restrict__ fast, int64_t Npad, int Kf, int64_t N,
                                   uint32_t *__restrict__ cursor, const uint8_t *__restrict__ items, int stride,
-                                  uint32_t *__restrict__ perm, uint8_t *__restrict__ items_grouped,
+                                  uint32_t *__restrict__ perm, uint8_t *__restrict__ items_grouped, bool planes,
                                   uint8_t *__restrict__ rows, int64_t g2_npad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
     const uint32_t pos = atomicAdd(&cursor[slot_of_item(fast, Npad, i)], 1u);
     perm[pos] = (uint32_t)i;
     for (int r = 0; r < Kf - 2; ++r) rows[(int64_t)r * g2_npad + pos] = fast[(int64_t)(r + 2) * Npad + i];
+    if (planes) {                            // 16-byte records: first and second halves apart
+        const uint4 v = *reinterpret_cast<const uint4 *>(items + (size_t)i * 16);
+        reinterpret_cast<uint2 *>(items_grouped)[pos] = make_uint2(v.x, v.y);
+        reinterpret_cast<uint2 *>(items_grouped)[g2_npad + pos] = make_uint2(v.z, v.w);
+        return;
+    }
     const int W = stride / 4;
     const uint32_t *src = reinterpret_cast<const uint32_t *>(items + (size_t)i * stride);
     uint32_t *dst = reinterpret_cast<uint32_t *>(items_grouped + (size_t)pos * stride);
@@ -99,6 +105,7 @@ __global__ void g2_export_kernel(const uint32_t *__restrict__ info, const uint8_
     uint8_t v;
     if (k < 2) v = (uint8_t)(info[pos >> 4] >> (8 * k));
     else if (k < Kf) v = rows[(int64_t)(k - 2) * g2_npad + pos];
+    else if (stride == 16) v = items_grouped[((k >> 3) * g2_npad + pos) * 8 + (k & 7)];
     else v = items_grouped[pos * stride + k];
     out[(int64_t)k * N + id] = v;
 }
@@ -147,7 +154,7 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     fill(ix->perm, sizeof(uint32_t) * np, ICQ_PAD_ID);
     fill(ix->items_grouped, np * ix->item_stride, 0u);
     g2_scatter_kernel<<<nb, T, 0, s>>>(ix->fast, ix->Npad, ix->Kf, ix->N, ix->group_cursor, ix->items, ix->item_stride,
-                                       ix->perm, ix->items_grouped, ix->g2_rows, ix->g2_npad);
+                                       ix->perm, ix->items_grouped, ix->item_stride == 16, ix->g2_rows, ix->g2_npad);
     g2_info_kernel<<<G2_PAIRS / T, T, 0, s>>>(ix->group_start, ix->group_cursor, ix->g2_info);
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     ix->g2 = 1;

@@ -46,7 +46,8 @@ struct icq_index {
     // positions holds unrelated pairs -- every pair's run padded to whole 16 positions.  Stage 1 then
     // streams only the remaining Kf - 2 fast rows and forms the pair's table sum once per 16
     // positions.  Uses group_start [65537], perm [g2_npad] (ICQ_PAD_ID in the padding) and
-    // items_grouped [g2_npad][item_stride] as the Kf <= 2 grouping does.
+    // items_grouped [g2_npad][item_stride] as the Kf <= 2 grouping does; records of 16 bytes as [2][g2_npad][8], because stage 2
+    // reads the second half of few.
     int g2;                    // 1 when this grouping exists
     int64_t g2_npos;           // positions stage 1 walks: an upper bound of the padded total, whole block steps
     int64_t g2_npad;           // row stride of g2_rows = length of perm / items_grouped (g2_npos + read-ahead spare)
@@ -129,7 +130,7 @@ int64_t icq_mask_scan_end(const icq_index *ix);              // positions the hi
 // 2 * Q words of the workspace, which is at least that long.
 int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_ext, int Q, const float *thresholds,
                     int64_t cap, int topk, uint32_t *out_ids, float *out_dist, uint32_t *out_survivors,
-                    void *workspace, size_t workspace_bytes, icq_share share, void *stream);
+                    void *workspace, size_t workspace_bytes, icq_share share, const float *bound_dist, void *stream);
 // Stage 1 into hit bits.
 int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
                           size_t mask_stride, int64_t scan_end, bool *superset, hipStream_t s);
@@ -138,12 +139,15 @@ bool icq_scan_q16_usable(const icq_index *ix, int Q);
 int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
                               size_t mask_stride, int64_t scan_end, hipStream_t s);
 // Stage 2 from hit bits; keys [Q][cap] (+ slice lists in front, see icq_cand_keys); adds the survivors to cand_count.
-// thr != nullptr: the bits mark a superset of the survivors, and an item counts only if its crude distance
-// (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].
+// superset: the bits mark a superset of the survivors, and an item counts only if its crude distance
+// (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].  bound_dist (may be nullptr): the caller has no
+// use for items of query q beyond bound_dist[q][topk - 1], a finite distance.
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, unsigned long long *keys,
-                            uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr,
-                            uint32_t *out_ids, float *out_dist, hipStream_t s);
+                            uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset,
+                            const float *bound_dist, uint32_t *out_ids, float *out_dist, hipStream_t s);
+// A bound on the topk-th smallest distance from the items of the nearest runs, into out_dist[q][topk - 1] (icq_bound.hip).
+int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const float *thr, int topk, float *out_dist, hipStream_t s);
 
 // p[0..n) = 0, by a kernel (the call can sit inside a captured graph).
 void icq_zero_words(uint32_t *p, int n, hipStream_t s);

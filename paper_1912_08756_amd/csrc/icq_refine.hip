@@ -261,7 +261,7 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
 
 // ------------------------------------------------------------------ stage 2 from hit bits
 // icq_search with the item-by-item stage 1: stage 1 leaves one hit bit per scan position and query,
-// and this kernel turns them into distances and keys.  The positions are cut into chunks of 32768
+// and these kernels turn them into distances and keys.  The positions are cut into chunks of 32768
 // (4 KB of hit bits per query, 512 KB of 16-byte item records).  A block belongs to ONE query --
 // its tables stay in LDS for the block's whole life -- and walks a window of a few chunks, its
 // four wavefronts a chunk at a time each and each on its own (no barrier after the tables are
@@ -273,83 +273,63 @@ __global__ __launch_bounds__(RF_THREADS) void refine_dist_kernel(
 // cache at a time.  An item that survives for several queries of the batch -- or shares its cache
 // line with one that does -- is then fetched from memory once: with 1 % survivors and 128
 // queries that is ten uses per 128-byte line.  Per chunk and wavefront: the query's 256 words of hit
-// bits (one 128-bit load per lane, two chunks ahead), a prefix of their popcounts, the set bits
-// expanded into a position list in the wavefront's part of LDS, then per position the record
-// gather, the K table reads and the key, as in refine_dist_kernel.
-// (A wavefront may take half or a quarter of a chunk, see icq_launch_refine_masks; what follows says chunk for either.)
-// Every 65th chunk (or every 65th quarter of one, seed_parts = 4) is done in a first launch, unfiltered
-// (!FILTER); the select kernel's topk-th
-// distance of those keys then bounds what the others add in a second launch (FILTER: keys
-// above it are dropped; ties at it are kept, the final select decides).  The final lists are
-// unchanged -- at least topk keys at or below the bound are already there -- and the key lists
-// shrink to a few per cent.  Survivors are counted from the popcounts, added up per block.
+// bits (16 words per lane, a chunk ahead), the set bits expanded into a position list in the
+// wavefront's part of LDS, then per position the record gather, the table reads and the key, as in
+// refine_dist_kernel.
+// Where a bound of the topk-th distance is known (refine_bounded_kernel) only what reaches it gets a key, else
+// (refine_mask_kernel: small indexes) every survivor; ties at the bound are kept, the selection decides.
 constexpr int RM_THREADS = 256;
 constexpr int RM_WAVES = RM_THREADS / 64;
 constexpr uint32_t RM_CHUNK = 32768;                  // positions per chunk; a multiple of the scan kernel's block step
-constexpr int RM_FULL = RM_CHUNK / 32 / 64;           // 32-bit words of hit bits per lane and chunk (pieces of chunks: fewer)
+constexpr int RM_WORDS = RM_CHUNK / 32 / 64;          // 32-bit words of hit bits per lane and chunk
 constexpr int RM_PER = 4;                             // records a lane gathers together
 constexpr int RM_LIST = 512;                          // positions a wavefront expands per round
-constexpr int RM_QPB = 1;                             // queries per block (two: 1.39 against 1.25 ms at N = 1e8, 128 queries)
-constexpr int RM_SEED_EVERY = 65;                     // odd: the first launch's chunks are spread over all XCDs
-constexpr uint32_t RM_SEED_PARTS = 4;                 // of whole chunks the first launch may take quarters
 static_assert(RM_LIST % (64 * RM_PER) == 0, "a round of the list is whole steps of gathers");
 static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into the chunk");
 
-// QPB queries per block: their tables sit in LDS side by side and every chunk is worked through for one
-// query after the other, so the later ones find the chunk's records in the cache for certain.
+// PLANES (WORDS == 4): the records' halves at `items` and `tail`, 8 bytes per position each.
 // EXACT: the hit bits mark a superset of the survivors (the 16-bit pre-filter of stage 1); an item is a
 // survivor when the first Kf terms of its sum -- the crude distance of Eq. 2, the same fp32 additions
 // stage 1 makes item by item -- are below thr[q].  Only survivors are counted and get keys.
-// The filtered launch is held to the registers of five wavefronts per SIMD (the exact comparison's few
-// more would cost the fifth: 1.17 -> 1.29 ms for the stage at N = 1e8).
-template <int WORDS, bool FILTER, int QPB, bool EXACT, int RM_WORDS>
-__global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel(
-    const uint8_t *__restrict__ items, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
-    size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, uint32_t seed_every, uint32_t seed_parts, int window, int xs_shift, int Q,
-    const float *__restrict__ kth_dist, int topk, u64 *__restrict__ keys, uint32_t *__restrict__ key_count,
+template <int WORDS, bool PLANES, bool EXACT>
+__global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
+    const uint8_t *__restrict__ items, const uint8_t *__restrict__ tail, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
+    size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, int window, int xs_shift, int Q,
+    u64 *__restrict__ keys, uint32_t *__restrict__ key_count,
     int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
-    __shared__ __attribute__((aligned(16))) float T_all[QPB][4 * WORDS * ICQ_LUT_W];
+    __shared__ __attribute__((aligned(16))) float T[4 * WORDS * ICQ_LUT_W];
     __shared__ uint16_t cand_all[RM_WAVES][RM_LIST];  // positions inside the chunk (RM_CHUNK <= 65536)
-    __shared__ uint32_t sum_all[QPB], done_all[QPB];  // survivors of the block, wavefronts that have added theirs
+    __shared__ uint32_t sum_all, done_all;            // survivors of the block, wavefronts that have added theirs
     constexpr int RW = WORDS;
-    constexpr uint32_t PIECE = RM_WORDS * 2048;       // positions
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint16_t *cand = cand_all[wave];
-    // block -> (window, query group, XCD): chunks i = (win * window + j) * 8 + xcd, j = 0 .. window - 1, of this
-    // launch's; wavefront w takes j = w, w + 4, ..  (An index of few chunks is cut 2^xs_shift < 8 ways instead, so
+    // block -> (window, query, XCD): chunks i = (win * window + j) * 8 + xcd, j = 0 .. window - 1; wavefront
+    // w takes j = w, w + 4, ..  (An index of few chunks is cut 2^xs_shift < 8 ways instead, so
     // that a block still has a window's worth of chunks for the tables it loads.)
-    const uint32_t ngroups = ((uint32_t)Q + QPB - 1) / QPB;
     const uint32_t xcd = blockIdx.x & ((1u << xs_shift) - 1u), rest = blockIdx.x >> xs_shift;
-    const uint32_t q0 = (rest % ngroups) * QPB, win = rest / ngroups;
-    const uint32_t nq = (uint32_t)Q - q0 < (uint32_t)QPB ? (uint32_t)Q - q0 : (uint32_t)QPB;
+    const uint32_t q = rest % (uint32_t)Q, win = rest / (uint32_t)Q;
     auto chunk_of = [&](uint32_t j) -> uint32_t {
         const uint32_t i = ((win * (uint32_t)window + j) << xs_shift) + xcd;
-        if (j >= (uint32_t)window || i >= nsel) return 0xFFFFFFFFu;
-        if (!FILTER) return i * seed_every;
-        return seed_parts == 1u ? i + i / (RM_SEED_EVERY - 1u) + 1u : i;   // all but every 65th : all
+        return j >= (uint32_t)window || i >= nsel ? 0xFFFFFFFFu : i;
     };
     if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
-    // Word r of this lane covers the 32 positions from c * PIECE + (r * 64 + lane) * 32: neighbouring
+    // Word r of this lane covers the 32 positions from c * RM_CHUNK + (r * 64 + lane) * 32: neighbouring
     // words sit in neighbouring lanes, so a dense stretch of hits is shared out among many lanes.
-    // The wavefront's work is the sequence (chunk j, query qq), qq fastest; the next one's hit bits travel
-    // while the current one is worked on.
-    const uint32_t *mq = masks + (size_t)q0 * mask_words + lane;
-    uint32_t j = (uint32_t)wave, qq = 0;
+    // The next chunk's hit bits travel while the current one is worked on.
+    const uint32_t *mq = masks + (size_t)q * mask_words + lane;
+    uint32_t j = (uint32_t)wave;
     uint32_t c = chunk_of(j);
     uint32_t nxt[RM_WORDS];
     {
         const uint32_t c0 = c != 0xFFFFFFFFu ? c : 0u;
 #pragma unroll
-        for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mq + (size_t)c0 * (PIECE / 32) + r * 64);
+        for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mq + (size_t)c0 * (RM_CHUNK / 32) + r * 64);
     }
-    // the queries' tables -> LDS, one table per record byte, zero beyond K
-#pragma unroll
-    for (int g = 0; g < QPB; ++g) {
-        const uint32_t qg = q0 + ((uint32_t)g < nq ? (uint32_t)g : 0u);
-        const float4 *src = reinterpret_cast<const float4 *>(lut + (int64_t)qg * K * ICQ_LUT_W);
-        float4 *dst = reinterpret_cast<float4 *>(T_all[g]);
+    {   // the query's tables -> LDS, one table per record byte, zero beyond K
+        const float4 *src = reinterpret_cast<const float4 *>(lut + (int64_t)q * K * ICQ_LUT_W);
+        float4 *dst = reinterpret_cast<float4 *>(T);
         constexpr int N4 = 4 * WORDS * (ICQ_LUT_W / 4);
         float4 v[N4 / RM_THREADS];
 #pragma unroll
@@ -360,69 +340,36 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
 #pragma unroll
         for (int u = 0; u < N4 / RM_THREADS; ++u) dst[u * RM_THREADS + tid] = v[u];
     }
-    uint32_t bound_all[QPB];
-#pragma unroll
-    for (int g = 0; g < QPB; ++g) {
-        bound_all[g] = 0xFFFFFFFFu;
-        if (FILTER) {
-            const uint32_t qg = q0 + ((uint32_t)g < nq ? (uint32_t)g : 0u);
-            const uint32_t ob = icq_order_bits(kth_dist[(int64_t)qg * topk + topk - 1]);
-            if (ob < 0xFF800000u) bound_all[g] = ob;  // a finite topk-th distance; else the list is still open
-        }
-    }
-    if (tid < QPB) sum_all[tid] = done_all[tid] = 0;
+    const float tq = EXACT ? thr[q] : 0.0f;
+    u64 *kout = keys + (int64_t)q * cap;
+    if (tid == 0) sum_all = done_all = 0;
     __syncthreads();                                  // the only barrier: from here on every wavefront is on its own
-    uint32_t survivors[QPB];                          // of this wavefront's chunks (wavefront-uniform)
-    uint32_t lane_survivors[QPB];                     // EXACT: counted per lane, summed at the end
-#pragma unroll
-    for (int g = 0; g < QPB; ++g) survivors[g] = lane_survivors[g] = 0;
+    uint32_t survivors = 0;                           // of this wavefront's chunks (wavefront-uniform)
+    uint32_t lane_survivors = 0;                      // EXACT: counted per lane, summed at the end
     while (c != 0xFFFFFFFFu) {
         uint32_t w[RM_WORDS];
 #pragma unroll
         for (int r = 0; r < RM_WORDS; ++r) w[r] = nxt[r];
-        if (FILTER && RM_WORDS == RM_FULL && seed_parts > 1u) {       // the quarter that the first launch has done is out
-            const uint32_t at = c * RM_SEED_PARTS % RM_SEED_EVERY, done = at == 0u ? 0u : RM_SEED_EVERY - at;
-            if (done < RM_SEED_PARTS) {               // wavefront-uniform
-#pragma unroll
-                for (int r = 0; r < RM_WORDS; ++r) w[r] = (uint32_t)r / (RM_FULL / RM_SEED_PARTS) == done ? 0u : w[r];
-            }
-        }
-        // next piece of work: the next query of this chunk, else the wavefront's next chunk
-        uint32_t qn = qq + 1, jn = j, cn = c;
-        if (qn >= nq) {
-            qn = 0;
-            jn = j + RM_WAVES;
-            cn = chunk_of(jn);
-        }
+        j += RM_WAVES;
+        const uint32_t cn = chunk_of(j);
         if (cn != 0xFFFFFFFFu) {
-            const uint32_t *mn = mq + (size_t)qn * mask_words + (size_t)cn * (PIECE / 32);
 #pragma unroll
-            for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mn + r * 64);
+            for (int r = 0; r < RM_WORDS; ++r) nxt[r] = __builtin_nontemporal_load(mq + (size_t)cn * (RM_CHUNK / 32) + r * 64);
         }
-        const uint32_t q = q0 + qq;
-        const float tq = EXACT ? thr[q] : 0.0f;
-        const float *T = T_all[QPB == 1 ? 0 : qq];
-        uint32_t bound = bound_all[0];
-#pragma unroll
-        for (int g = 1; g < QPB; ++g) bound = qq == (uint32_t)g ? bound_all[g] : bound;
-        u64 *kout = keys + (int64_t)q * cap;
         uint32_t mine = 0;
 #pragma unroll
         for (int r = 0; r < RM_WORDS; ++r) mine += (uint32_t)__builtin_popcount(w[r]);
         const uint32_t incl = wave_scan_add(mine);
         const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         const uint32_t off = incl - mine;
-        if (!EXACT) {
-#pragma unroll
-            for (int g = 0; g < QPB; ++g) survivors[g] += qq == (uint32_t)g ? total : 0u;
-        }
-        // unfiltered: every survivor of the chunk gets a key, so their slots are reserved at once (the atomic's
+        // every survivor of the chunk gets a key, so their slots are reserved at once (the atomic's
         // answer travels while the positions are expanded)
         uint32_t chunk_slot = 0;
-        if (!FILTER && !EXACT && total != 0) {
-            if (lane == 0) chunk_slot = atomicAdd(&key_count[q], total);
+        if (!EXACT) {
+            survivors += total;
+            if (total != 0 && lane == 0) chunk_slot = atomicAdd(&key_count[q], total);
         }
-        const uint32_t cbase = c * PIECE, p0 = lane * 32u;
+        const uint32_t cbase = c * RM_CHUNK, p0 = lane * 32u;
         for (uint32_t lo = 0; lo < total; lo += RM_LIST) {      // wavefront-uniform; one round unless the chunk is dense
             wave_lds_order();                         // the last round's reads are done
             if (off + mine > lo && off < lo + RM_LIST) {
@@ -456,6 +403,12 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
                         const uint2 v = *reinterpret_cast<const uint2 *>(p);
                         rec[u][0] = v.x;
                         rec[u][1 % RW] = v.y;
+                    } else if (PLANES) {
+                        const uint2 v = reinterpret_cast<const uint2 *>(items)[id[u]], y = reinterpret_cast<const uint2 *>(tail)[id[u]];
+                        rec[u][0] = v.x;
+                        rec[u][1 % RW] = v.y;
+                        rec[u][2 % RW] = y.x;
+                        rec[u][3 % RW] = y.y;
                     } else {
                         const uint4 v = *reinterpret_cast<const uint4 *>(p);
                         rec[u][0] = v.x;
@@ -490,17 +443,15 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
                     bool keep = base + (uint32_t)u * 64u + lane < n;
                     if (EXACT) {
                         keep = keep && crude < tq;
-#pragma unroll
-                        for (int g = 0; g < QPB; ++g) lane_survivors[g] += (qq == (uint32_t)g && keep) ? 1u : 0u;
+                        lane_survivors += keep ? 1u : 0u;
                     }
-                    keep = keep && ob <= bound;
                     mk[u] = __builtin_amdgcn_ballot_w64(keep);
                     mycnt += (uint32_t)__builtin_popcountll(mk[u]);
                     key[u] = (u64)ob << 32;
                 }
                 if (mycnt == 0) continue;             // wavefront-uniform
                 uint32_t slot0 = 0;
-                if (FILTER || EXACT) {
+                if (EXACT) {
                     if (lane == 0) slot0 = atomicAdd(&key_count[q], mycnt);
                     slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot0);
                 } else {
@@ -517,25 +468,273 @@ __global__ __launch_bounds__(RM_THREADS, FILTER ? 5 : 1) void refine_mask_kernel
                 }
             }
         }
-        qq = qn;
-        j = jn;
         c = cn;
     }
-    if (EXACT) {
-#pragma unroll
-        for (int g = 0; g < QPB; ++g)
-            survivors[g] = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors[g]), 63);
-    }
+    if (EXACT) survivors = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors), 63);
     // one addition per block: thousands of wavefronts of one query at one counter would take 11 ns each.  The last of the four
     // to come here makes it.
-#pragma unroll
-    for (int g = 0; g < QPB; ++g) {
-        if (lane != 0) continue;
-        atomicAdd(&sum_all[g], survivors[g]);
+    if (lane == 0) {
+        atomicAdd(&sum_all, survivors);
         __threadfence_block();
-        if (atomicAdd(&done_all[g], 1u) != RM_WAVES - 1) continue;
-        const uint32_t sum = atomicAdd(&sum_all[g], 0u);
-        if ((uint32_t)g < nq && sum != 0) atomicAdd(&cand_count[q0 + g], sum);
+        if (atomicAdd(&done_all, 1u) == RM_WAVES - 1) {
+            const uint32_t sum = atomicAdd(&sum_all, 0u);
+            if (sum != 0) atomicAdd(&cand_count[q], sum);
+        }
+    }
+}
+
+// ---- the same with a bound on the result at hand
+// Where a finite upper bound of the topk-th distance is known before stage 2 (icq_bound.hip, or the list of the tiles
+// before), nearly every survivor can be dropped before its last table entries are read: with K > 8 the sum of the first
+// eight terms and the smallest the other tables can add is beyond the bound for all but a few per cent (10^8 items, K = 16,
+// codebooks shrinking by 0.8, 1 % survivors: 1.3 %).  So the first half of a 16-byte record is gathered for every survivor
+// -- over the pair ordering the halves lie in planes of their own, and a window of chunks is half as many bytes for the
+// XCD's cache -- and the second half only for what is left, collected 64 at a time.  K <= 8: the whole distance is known
+// at once, the same queue collects what reaches the bound.
+// A wavefront's positions go through a stack in LDS that outlives the chunk, so that the gathers always come 256 at a time.
+// A word's lowest hit bit goes there straight; what is left of words with several (one in seven at 1 %) is collected 64
+// words at a time first: with a loop over every word's bits the expansion was more than half of all vector instructions.
+// What bounds it: 10^8 items, 128 queries, 1 %: 4.0 GB fetched (1.6 of hit bits) in 0.77 ms, where the kernel that gathered
+// whole records took 0.92 + 0.09 ms for 5.9 GB; vector issue at half of its rate.  The fetched bytes grow with the window and
+// with everything that lets the queries' wavefronts drift apart (one block per query and XCD for the whole index: 1.5 ms),
+// and a wavefront lives through three chunks only, so that work at its end weighs: asking for the records of a batch before
+// the last one is worked off, words instead of positions in the stack, half chunks and more wavefronts were all slower
+// (0.85 to 1.0 ms).
+constexpr int RB_BATCH = 64 * RM_PER;                 // survivors gathered together
+constexpr int RB_LIST = RB_BATCH + 256;               // positions a wavefront holds
+constexpr int RB_MORE = 128;                          // words with hit bits left
+constexpr int RB_QUEUE = 128;                         // survivors to be finished
+
+// A survivor in the queue: position, bits of the sum so far, and the record's second half where it came with the first.
+template <bool WHOLE> struct RbRestT { uint32_t pos, sum; };
+template <> struct RbRestT<true> { uint32_t pos, sum, tail0, tail1; };
+
+// WORDS == 4: PLANES: first and second halves of the records at `items` and `tail`, 8 bytes per position; else (an index in
+// id order) records of 16 bytes, whose second half comes with the line of the first and waits in the queue.
+template <int WORDS, bool PLANES, bool EXACT>
+__global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
+    const uint8_t *__restrict__ items, const uint8_t *__restrict__ tail, int K, const float *__restrict__ lut,
+    const uint32_t *__restrict__ masks, size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, int window,
+    int xs_shift, int Q, const float *__restrict__ bound_dist, int topk, u64 *__restrict__ keys,
+    uint32_t *__restrict__ key_count, int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
+    constexpr int HW = WORDS < 2 ? WORDS : 2;         // words of a record's first half
+    constexpr int HT = 4 * HW;                        // its tables
+    constexpr bool WHOLE = WORDS == 4 && !PLANES;     // the whole record is fetched at once
+    constexpr int FW = WHOLE ? 4 : HW;                // words fetched
+    using RbRest = RbRestT<WHOLE>;
+    __shared__ __attribute__((aligned(16))) float T[HT * ICQ_LUT_W];
+    __shared__ uint32_t list_all[RM_WAVES][RB_LIST];
+    __shared__ uint2 more_all[RM_WAVES][RB_MORE];     // hit bits, first position of the word
+    __shared__ RbRest queue_all[RM_WAVES][RB_QUEUE];
+    __shared__ float tmin[8];                         // smallest entry of each table of the second half
+    __shared__ uint32_t sum_all, done_all;
+    const int tid = threadIdx.x;
+    const uint32_t lane = (uint32_t)tid & 63u;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t *list = list_all[wave];
+    uint2 *more = more_all[wave];
+    RbRest *queue = queue_all[wave];
+    // block -> (window, query, XCD) as in refine_mask_kernel
+    const uint32_t xcd = blockIdx.x & ((1u << xs_shift) - 1u), rest = blockIdx.x >> xs_shift;
+    const uint32_t q = rest % (uint32_t)Q, win = rest / (uint32_t)Q;
+    auto chunk_of = [&](uint32_t j) -> uint32_t {
+        const uint32_t i = ((win * (uint32_t)window + j) << xs_shift) + xcd;
+        return j >= (uint32_t)window || i >= nsel ? 0xFFFFFFFFu : i;
+    };
+    if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
+    const uint32_t *mq = masks + (size_t)q * mask_words + lane;
+    uint32_t j = (uint32_t)wave, c = chunk_of(j);
+    uint32_t w[RM_WORDS];
+#pragma unroll
+    for (int r = 0; r < RM_WORDS; ++r) w[r] = __builtin_nontemporal_load(mq + (c != 0xFFFFFFFFu ? c * (RM_CHUNK / 32) : 0u) + r * 64);
+    const float *Tq = lut + (int64_t)q * K * ICQ_LUT_W;
+    {
+        const float4 *src = reinterpret_cast<const float4 *>(Tq);
+        float4 *dst = reinterpret_cast<float4 *>(T);
+        constexpr int PER = HT / 4;                   // tables per wavefront
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int i = u * RM_THREADS + tid;
+            dst[i] = u * 4 + wave < K ? src[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+        if (WORDS == 4) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int k = 8 + u * 4 + wave;       // table k, whole
+                const float4 v = k < K ? src[k * (ICQ_LUT_W / 4) + (int)lane] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                const float m = wave_min_f32(fminf(fminf(v.x, v.y), fminf(v.z, v.w)));
+                if (lane == 0) tmin[u * 4 + wave] = m;
+            }
+        }
+    }
+    const float bound_f = bound_dist[(int64_t)q * topk + topk - 1];
+    uint32_t bound = icq_order_bits(bound_f);
+    const bool open = bound >= 0xFF800000u;           // infinite or not a number
+    if (open) bound = 0xFFFFFFFFu;
+    const float tq = EXACT ? thr[q] : 0.0f;
+    if (tid == 0) sum_all = done_all = 0;
+    __syncthreads();                                  // the only barrier: from here on every wavefront is on its own
+    // A sum of eight terms above `most` cannot come to the bound: the eight additions that follow give no less than the same
+    // ones of the tables' smallest entries would (rounding is monotone), which is (sum + those entries) (1 +- 8 * 2^-24); 1e-5
+    // covers that and the roundings here.  Open bounds and tables without a number drop nothing.
+    float most = INFINITY;
+    if (WORDS == 4 && !open) {
+        float s = 0.0f, a = fabsf(bound_f);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            s += tmin[k];
+            a += fabsf(tmin[k]);
+        }
+        most = (bound_f - s) + 1e-5f * a;
+    }
+    uint32_t n = 0, nm = 0, nq = 0;                   // positions, words with bits left, survivors in the queue (wavefront-uniform)
+    uint32_t lane_survivors = 0;
+    u64 *kout = keys + (int64_t)q * cap;
+    // the queue's last `cnt` (at most 64): the remaining terms, and a key for what reaches the bound
+    auto finish = [&](uint32_t cnt) __attribute__((always_inline)) {
+        wave_lds_order();
+        const bool in = lane < cnt;
+        const RbRest e = queue[nq - cnt + (in ? lane : 0u)];
+        nq -= cnt;
+        float d = __uint_as_float(e.sum);
+        if (WORDS == 4) {
+            uint2 r;
+            if constexpr (WHOLE) r = make_uint2(e.tail0, e.tail1);
+            else r = reinterpret_cast<const uint2 *>(tail)[e.pos];
+            float tv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t code = ((i < 4 ? r.x : r.y) >> (8 * (i & 3))) & 0xffu;
+                tv[i] = 8 + i < K ? Tq[(8 + i) * ICQ_LUT_W + code] : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) d += tv[i];
+        }
+        const uint32_t ob = icq_order_bits(d);
+        const bool keep = in && ob <= bound;
+        const uint64_t mk = __builtin_amdgcn_ballot_w64(keep);
+        if (mk == 0) return;                          // wavefront-uniform
+        uint32_t slot0 = 0;
+        if (lane == 0) slot0 = atomicAdd(&key_count[q], (uint32_t)__builtin_popcountll(mk));
+        slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot0);
+        if (keep) {
+            const uint64_t slot = (uint64_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, slot0));
+            if (slot < (uint64_t)cap) kout[slot] = ((u64)ob << 32) | (perm ? perm[e.pos] : e.pos);
+        }
+    };
+    // the list's last `cnt` (at most RB_BATCH)
+    auto batch = [&](uint32_t cnt) __attribute__((always_inline)) {
+        wave_lds_order();
+        uint32_t pos[RM_PER], rec[RM_PER][FW];
+#pragma unroll
+        for (int u = 0; u < RM_PER; ++u) {
+            const uint32_t i = (uint32_t)u * 64u + lane;
+            pos[u] = list[n - cnt + (i < cnt ? i : cnt - 1)];
+        }
+        n -= cnt;
+#pragma unroll
+        for (int u = 0; u < RM_PER; ++u) {
+            const uint32_t *p = reinterpret_cast<const uint32_t *>(items + (size_t)pos[u] * (FW * 4));
+            if (FW == 1) {
+                rec[u][0] = p[0];
+            } else if (FW == 2) {
+                const uint2 v = *reinterpret_cast<const uint2 *>(p);
+                rec[u][0] = v.x;
+                rec[u][1 % FW] = v.y;
+            } else {
+                const uint4 v = *reinterpret_cast<const uint4 *>(p);
+                rec[u][0] = v.x;
+                rec[u][1 % FW] = v.y;
+                rec[u][2 % FW] = v.z;
+                rec[u][3 % FW] = v.w;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RM_PER; ++u) {
+            // all table reads of the half record first, then the sum: k ascending like every other kernel, the first term
+            // standing for 0 + itself (no table holds -0)
+            float tv[HT];
+#pragma unroll
+            for (int x = 0; x < HT; ++x) tv[x] = T[x * ICQ_LUT_W + ((rec[u][x / 4] >> (8 * (x % 4))) & 0xffu)];
+            __builtin_amdgcn_sched_barrier(0);
+            float d = tv[0], crude = d;               // crude: the sum of the first Kf terms (Kf <= 4)
+#pragma unroll
+            for (int i = 1; i < HT; ++i) {
+                d += tv[i];
+                if (EXACT && i < 4) crude = i < Kf ? d : crude;
+            }
+            bool keep = (uint32_t)u * 64u + lane < cnt;
+            if (EXACT) keep = keep && crude < tq;
+            lane_survivors += keep ? 1u : 0u;
+            keep = keep && (WORDS == 4 ? !(d > most) : icq_order_bits(d) <= bound);
+            const uint64_t mk = __builtin_amdgcn_ballot_w64(keep);
+            if (mk == 0) continue;                    // wavefront-uniform
+            if (keep) {
+                RbRest e;
+                e.pos = pos[u];
+                e.sum = __float_as_uint(d);
+                if constexpr (WHOLE) {
+                    e.tail0 = rec[u][2];
+                    e.tail1 = rec[u][3];
+                }
+                queue[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, nq))] = e;
+            }
+            nq += (uint32_t)__builtin_popcountll(mk);
+            if (nq >= 64u) finish(64u);
+        }
+    };
+    // the lowest hit bit of every lane's word m (positions from `at`) -> list; returns the others
+    auto emit = [&](uint32_t m, uint32_t at) __attribute__((always_inline)) -> uint32_t {
+        const uint64_t mk = __builtin_amdgcn_ballot_w64(m != 0);
+        if (m != 0)
+            list[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, n))] = at + (uint32_t)__builtin_ctz(m);
+        n += (uint32_t)__builtin_popcountll(mk);
+        if (n > (uint32_t)(RB_LIST - 64)) batch(RB_BATCH);
+        return m & (m - 1);
+    };
+    // the last `cnt` words (at most 64) with bits left
+    auto drain = [&](uint32_t cnt) __attribute__((always_inline)) {
+        wave_lds_order();
+        uint2 e = more[nm - cnt + (lane < cnt ? lane : 0u)];
+        nm -= cnt;
+        if (lane >= cnt) e.x = 0;
+        while (__builtin_amdgcn_ballot_w64(e.x != 0) != 0) e.x = emit(e.x, e.y);
+    };
+    while (c != 0xFFFFFFFFu) {
+        uint32_t v[RM_WORDS];
+#pragma unroll
+        for (int r = 0; r < RM_WORDS; ++r) v[r] = w[r];
+        const uint32_t at = c * RM_CHUNK + lane * 32u;
+        j += RM_WAVES;
+        c = chunk_of(j);
+        if (c != 0xFFFFFFFFu) {
+#pragma unroll
+            for (int r = 0; r < RM_WORDS; ++r) w[r] = __builtin_nontemporal_load(mq + (size_t)c * (RM_CHUNK / 32) + r * 64);
+        }
+#pragma nounroll                                       // (the register of word r by index: unrolled it is 20000 instructions)
+        for (int r = 0; r < RM_WORDS; ++r) {
+            const uint32_t left = emit(v[r], at + (uint32_t)r * 2048u);
+            const uint64_t mk = __builtin_amdgcn_ballot_w64(left != 0);
+            if (mk == 0) continue;                    // wavefront-uniform
+            if (left != 0)
+                more[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, nm))] =
+                    make_uint2(left, at + (uint32_t)r * 2048u);
+            nm += (uint32_t)__builtin_popcountll(mk);
+            if (nm >= 64u) drain(64u);
+        }
+    }
+    if (nm != 0) drain(nm);
+    while (n != 0) batch(n < (uint32_t)RB_BATCH ? n : (uint32_t)RB_BATCH);
+    if (nq != 0) finish(nq);
+    const uint32_t survivors = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors), 63);
+    // one addition per block, as above
+    if (lane == 0) {
+        atomicAdd(&sum_all, survivors);
+        __threadfence_block();
+        if (atomicAdd(&done_all, 1u) == RM_WAVES - 1) {
+            const uint32_t sum = atomicAdd(&sum_all, 0u);
+            if (sum != 0) atomicAdd(&cand_count[q], sum);
+        }
     }
 }
 
@@ -642,103 +841,67 @@ int64_t icq_mask_scan_end(const icq_index *ix) {
 
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
                             int64_t scan_end, int64_t cap, int topk, int splits, u64 *keys, uint32_t *key_count,
-                            uint32_t *ticket, uint32_t *cand_count, const float *thr, uint32_t *out_ids, float *out_dist,
-                            hipStream_t s) {
+                            uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset, const float *bound_dist,
+                            uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
-    const bool g2 = icq_g2_usable(ix);
+    const bool g2 = icq_g2_usable(ix), planes = g2 && ix->item_stride == 16;
     const uint8_t *items = g2 ? ix->items_grouped : ix->items;
+    const uint8_t *tail = planes ? items + (size_t)ix->g2_npad * 8 : nullptr;
     const uint32_t *perm = g2 ? ix->perm : nullptr;
-    // few chunks: one unfiltered launch over all of them (a bound would save less than its second launch costs)
-    const uint32_t seed_every = scan_end / RM_CHUNK < 2 * RM_SEED_EVERY ? 1u : (uint32_t)RM_SEED_EVERY;
-    // A wavefront takes a chunk at a time, or half or a quarter of one.  What a call spends its time on depends on what survives:
-    // with little, on each piece's chain of steps and each block's tables, so that smaller pieces cost; with much, on the first
-    // launch, whose few wavefronts then hold long lists, and on records that leave the caches before the other queries'
-    // blocks come to them, so that smaller pieces and windows gain.  Whole chunks with a first launch of quarters and windows of
-    // four chunks lose to larger pieces at no share; smaller pieces stand where they do not lose at a low share either.  Whole
-    // calls, us, at 0.05 / 1 / 5 / 30 % (K = 16, Kf = 4; whole chunks in both launches, windows of 16, 12 from eight queries on | halves
-    // in both, windows of 8 | quarters, windows of 8 | this):
-    //   4.3e6 items, 1 query     44/102/317/2300 |  34/46/82/335   |  33/44/58/146     quarters
-    //   4.3e6, 3 queries        48/109/353/2339  |  45/56/107/330  |  46/62/88/183     halves
-    //   4.3e6, 8                57/106/302/1709  |  64/85/165/514  |  70/98/148/289    whole  53/74/156/509
-    //   9e6, 16                 100/162/375/1575 | 114/172/335/708 | 129/221/335/570   whole  97/152/342/734
-    //   2e7, 5                  80/158/395       |  84/127/207     |  85/123/167       halves
-    //   2e7, 64                 228/409/742/3756 | 254/413/645/2258| 266/439/607/1751  whole  222/399/665/3399
-    //   6e7, 8                  152/322/617/2274 | 133/248/373/1244| 152/243/356/859   halves
-    //   1e8, 1                  90/205/540/3472  |  90/166/260/753 |  87/184/252/473   halves
-    //   1e8, 64                 669/1220/2318    | 649/1088/1985   | 714/1178/2068     halves
-    // Codes not ordered by their first two (K = 8, Kf = 2): 9e6, 1 query 45/67/209/2055 | 37/41/67/248 | 42/45/63/142; 1.3e7, 4
-    // queries 63/91/233/1933 | 75/81/174/428 | 108/114/173 | whole 58/80/167/380.
-    const uint64_t whole = (uint64_t)(scan_end / RM_CHUNK), pairs = whole * (uint64_t)Q;
-    int words = RM_FULL;
-    if (seed_every != 1u) {
-        if (pairs <= 320) words = RM_FULL / 4;
-        else if (pairs <= 700 || (g2 && Q < 8 && whole >= 600) || (g2 && whole >= 1700 && pairs <= 200000)) words = RM_FULL / 2;
+    const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
+    const uint64_t pairs = (uint64_t)chunks * (uint64_t)Q;
+    // From 130 chunks on a bound is worth its launch of 8 to 12 us (20 to 40 for hundreds of queries).  Whole calls, us, one
+    // unfiltered launch (up to 130 chunks; beyond, behind one over every 65th chunk) / bounded: K = 16: 7.8e5 items, 37 queries
+    // 43 / 47; 1e6, 1000 queries 330 / 333; 4.3e6, 1 / 3 / 8 queries 44 / 39, 56 / 43, 76 / 52; 1e7, 16 queries, 30 % 765 / 146;
+    // 2e7, 64 queries 340 / 198; 1e8, 1 / 128 queries 161 / 104, 1797 / 1536; K = 12, Kf = 3, 1e7, 100 queries, 10 % 873 / 305;
+    // K = 8, Kf = 2, 1e7, 1 query 49 / 35, 1.3e7, 4 queries 83 / 47.
+    if (!bound_dist && chunks >= 130) {
+        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, out_dist, s);
+        if (rc != ICQ_OK) return rc;
+        bound_dist = out_dist;
     }
-    // (the largest calls have wavefronts enough for whole ones: 1e8 items, 128 queries 1802 us, with quarters 1823)
-    const uint32_t seed_parts = seed_every != 1u && words == RM_FULL && pairs <= 200000 ? RM_SEED_PARTS : 1u;
-    const int seed_words = words / (int)seed_parts;
-    const uint32_t chunks = (uint32_t)(scan_end / (2048 * words)), seed_chunks = (uint32_t)(scan_end / (2048 * seed_words));
-    const uint32_t nseed = (seed_chunks + seed_every - 1) / seed_every;
-    const uint32_t nmain = seed_every == 1u ? 0u : seed_parts == 1u ? chunks - nseed : chunks;
-    auto select = [&](bool more) -> int {
-        return icq_launch_select(keys, key_count, cap, Q, topk, splits, more, ticket, out_ids, out_dist, s);
-    };
-    // Pieces per block: few, so that the blocks in flight (two windows' worth when the queries fill the
-    // chip) keep to a few chunks per XCD.  With few queries one per wavefront.
-    // An unfiltered launch with little work for the chip (the first part of a large index: one chunk per
-    // wavefront is all the parallelism there is) is spread over as many blocks as possible; one that is the
-    // whole stage (a small index, many queries) takes full windows, and the chunks are cut fewer than 8
-    // ways when 8 windows' worth do not exist: 16 MB of records stay in the caches wherever the blocks run.
-    auto plan_for = [&](uint32_t nsel, bool filtered, int *xs_shift) -> int {
-        // whole chunks: 4, with more blocks than the chip holds for long 12 or 8 (at N = 1e8, 128 queries, pair ordering:
-        // 16 / 12 / 8 / 6 / 4: 1.105 / 1.090 / 1.109 / 1.18 / 1.31 ms; whole calls at 1 %, windows of 4 / 12: 2e7 items, 128 queries
-        // 512 / 529 us, 3e7, 200 queries (K = 8) 804 / 769)
-        int w = words != RM_FULL ? 8 : pairs <= 131072u ? 4 : g2 ? 12 : 8;
-        if ((uint64_t)nsel * (uint64_t)Q <= 16384u && (!filtered || Q < 8)) w = 4;
-        else if (!filtered) w = 16 * RM_FULL / seed_words;
-        // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
-        // keeps a chunk's records in ONE L2 is worth more than the longer windows: 1e4 queries, 1e6 items,
-        // 8-byte records: 0.80 ms with it, 0.83 without)
-        int shift = 3;
-        while (Q <= 2048 && shift > 0 && ((uint32_t)w << shift) > nsel) --shift;
-        *xs_shift = shift;
-        const int most = (int)((nsel + (1u << shift) - 1) >> shift);
-        return w < most ? w : (most > 0 ? most : 1);
-    };
+    // Chunks per block: few, so that the blocks in flight (two windows' worth when the queries fill the chip) keep to a few
+    // chunks per XCD, but enough to be worth the tables a block loads.  Bounded: three per wavefront while that leaves a block
+    // for every place on the chip (1e8 items, 128 queries, windows of 4 / 8 / 12 / 16 / 24: 1675 / 1545 / 1536 / 1541 / 1570 us; 1
+    // query 104 / 109 / 115 / 119; 1e7, 16 queries, 30 %: 146 / 192 / 239).  Unfiltered: one per wavefront while that is
+    // all the parallelism there is, else full windows, and the chunks cut fewer than 8 ways when 8 windows' worth do not
+    // exist: 16 MB of records stay in the caches wherever the blocks run.
+    // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
+    // keeps a chunk's records in ONE L2 is worth more than the longer windows: 1e4 queries, 1e6 items,
+    // 8-byte records: 0.80 ms with it, 0.83 without)
+    int window = pairs <= 16384u ? 4 : 16;
+    if (bound_dist) window = pairs < 2 * 4 * 1536u ? 4 : pairs < 3 * 4 * 1536u ? 8 : 12;
+    int xs_shift = 3;
+    while (Q <= 2048 && xs_shift > 0 && ((uint32_t)window << xs_shift) > chunks) --xs_shift;
+    const int most = (int)((chunks + (1u << xs_shift) - 1) >> xs_shift);
+    if (window > most) window = most > 0 ? most : 1;
+    const unsigned per_win = (unsigned)window << xs_shift;
+    const unsigned grid = ((chunks + per_win - 1) / per_win * (unsigned)Q) << xs_shift;
     const size_t mask_words = mask_stride / 2;
     const uint32_t *m32 = reinterpret_cast<const uint32_t *>(masks);
-#define ICQ_RM_LAUNCH(W, FILTER, NSEL)                                                                       \
-    do {                                                                                                     \
-        int xs_shift = 3;                                                                                    \
-        const int window = plan_for(NSEL, FILTER, &xs_shift);                                                \
-        const unsigned per_win = (unsigned)window << xs_shift;                                               \
-        const unsigned nwin = ((NSEL) + per_win - 1) / per_win;                                              \
-        const unsigned ngroups = ((unsigned)Q + RM_QPB - 1) / RM_QPB;                                        \
-        auto go = [&](auto kernel) {                                                                         \
-            kernel<<<(nwin * ngroups) << xs_shift, RM_THREADS, 0, s>>>(                                      \
-                items, ix->K, lut, m32, mask_words, perm, (NSEL), seed_every, seed_parts, window, xs_shift, Q, out_dist, topk,     \
-                keys, key_count, cap, cand_count, thr, ix->Kf);                                              \
-        };                                                                                                   \
-        const int piece = FILTER ? words : seed_words;                                                       \
-        if (piece == RM_FULL / 4) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 4>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 4>); } \
-        else if (piece == RM_FULL / 2) { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL / 2>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL / 2>); } \
-        else { if (thr) go(refine_mask_kernel<W, FILTER, RM_QPB, true, RM_FULL>); else go(refine_mask_kernel<W, FILTER, RM_QPB, false, RM_FULL>); }         \
+    auto bounded = [&](auto kernel) {
+        kernel<<<grid, RM_THREADS, 0, s>>>(items, tail, ix->K, lut, m32, mask_words, perm, chunks, window, xs_shift, Q, bound_dist,
+                                           topk, keys, key_count, cap, cand_count, thr, ix->Kf);
+    };
+    auto open = [&](auto kernel) {
+        kernel<<<grid, RM_THREADS, 0, s>>>(items, tail, ix->K, lut, m32, mask_words, perm, chunks, window, xs_shift, Q, keys,
+                                           key_count, cap, cand_count, thr, ix->Kf);
+    };
+#define ICQ_RM_LAUNCH(W, PLANES)                                             \
+    do {                                                                     \
+        if (bound_dist) {                                                    \
+            if (superset) bounded(refine_bounded_kernel<W, PLANES, true>);   \
+            else bounded(refine_bounded_kernel<W, PLANES, false>);           \
+        } else {                                                             \
+            if (superset) open(refine_mask_kernel<W, PLANES, true>);         \
+            else open(refine_mask_kernel<W, PLANES, false>);                 \
+        }                                                                    \
     } while (0)
-    switch (ix->item_stride) {
-        case 4: ICQ_RM_LAUNCH(1, false, nseed); break;
-        case 8: ICQ_RM_LAUNCH(2, false, nseed); break;
-        default: ICQ_RM_LAUNCH(4, false, nseed); break;
-    }
-    if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    if (nmain == 0) return select(false);
-    int rc = select(true);
-    if (rc != ICQ_OK) return rc;
-    switch (ix->item_stride) {
-        case 4: ICQ_RM_LAUNCH(1, true, nmain); break;
-        case 8: ICQ_RM_LAUNCH(2, true, nmain); break;
-        default: ICQ_RM_LAUNCH(4, true, nmain); break;
-    }
+    if (ix->item_stride == 4) ICQ_RM_LAUNCH(1, false);
+    else if (ix->item_stride == 8) ICQ_RM_LAUNCH(2, false);
+    else if (planes) ICQ_RM_LAUNCH(4, true);
+    else ICQ_RM_LAUNCH(4, false);
 #undef ICQ_RM_LAUNCH
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    return select(false);
+    return icq_launch_select(keys, key_count, cap, Q, topk, splits, false, ticket, out_ids, out_dist, s);
 }

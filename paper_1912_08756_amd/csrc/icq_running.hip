@@ -171,16 +171,19 @@ ICQ_EXPORT int icq_search_running(const icq_index *const *tiles, const uint32_t 
     running_init_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(out_ids, out_dist, n, thr, out_refined, tsurv,
                                                                      counters, Q);
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
+    int64_t seen = 0;
     for (int r = 0; r < R; ++r) {
         const icq_index *t = tiles[r];
         const int64_t c = cap < t->N ? cap : t->N;
-        // the list is empty before the first tile (every item's threshold is +inf) and its margin wide in the next ones
+        // the list is empty before the first tile (every item's threshold is +inf) and its margin wide in the next ones; from the tile on that finds it full,
+        // its furthest distance bounds what a tile can add
         rc = icq_search_impl(t, nullptr, lut, Q, thr, c, topk, tids, tdist, tsurv, ws + L.inner_off, L.inner_bytes,
-                             r == 0 ? ICQ_SHARE_ALL : ICQ_SHARE_MANY, stream);
+                             r == 0 ? ICQ_SHARE_ALL : ICQ_SHARE_MANY, seen >= topk ? out_dist : nullptr, stream);
         if (rc != ICQ_OK) return rc;
         running_merge_kernel<<<Q, RM_T, lds, s>>>(out_ids, out_dist, crude, tids, tdist, tsurv, counters, id_base[r], t->items,
                                                   t->item_stride, t->K, t->Kf, lut, sigma, topk, thr, out_refined);
         if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
+        seen += t->N;
     }
     return ICQ_OK;
 }

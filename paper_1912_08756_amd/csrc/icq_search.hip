@@ -72,11 +72,12 @@ ICQ_EXPORT int icq_workspace_bytes(const icq_index *ix, int Q, int64_t cap, int 
     return ICQ_OK;
 }
 
-// lut_ext: the queries' tables when the caller has built them already (queries is not read then).
+// lut_ext: the queries' tables when the caller has built them already (queries is not read then).  bound_dist (may be
+// nullptr): see icq_launch_refine_masks.
 int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_ext, int Q, const float *thresholds,
                     int64_t cap, int topk, uint32_t *out_ids, float *out_dist,
                     uint32_t *out_survivors, void *workspace, size_t workspace_bytes,
-                    icq_share share, void *stream) {
+                    icq_share share, const float *bound_dist, void *stream) {
     if (!ix || Q < 0 || Q > ICQ_MAX_Q || cap < 1 || topk < 1 || topk > ICQ_MAX_TOPK)
         return ICQ_ERR_ARG;
     if (Q == 0) return ICQ_OK;
@@ -130,7 +131,8 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
             if (rc != ICQ_OK) return rc;
             if (timed) ICQ_HIP_TRY(hipEventRecord(ev[2], s));
             rc = icq_launch_refine_masks(ix, lut, nq, masks, L.mask_stride, L.scan_end, cap, topk, L.splits, keys,
-                                         key_count, ticket, cnt, superset ? thresholds + q0 : nullptr,
+                                         key_count, ticket, cnt, thresholds + q0, superset,
+                                         bound_dist ? bound_dist + (int64_t)q0 * topk : nullptr,
                                          out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, s);
             if (rc != ICQ_OK) return rc;
             if (timed) ICQ_HIP_TRY(hipEventRecord(ev[3], s));
@@ -157,7 +159,7 @@ ICQ_EXPORT int icq_search(const icq_index *ix, const float *queries, int Q, cons
                           uint32_t *out_survivors, void *workspace, size_t workspace_bytes,
                           void *stream) {
     return icq_search_impl(ix, queries, nullptr, Q, thresholds, cap, topk, out_ids, out_dist, out_survivors, workspace,
-                           workspace_bytes, ICQ_SHARE_UNKNOWN, stream);
+                           workspace_bytes, ICQ_SHARE_UNKNOWN, nullptr, stream);
 }
 
 // ---- icq_search for callers that cannot allocate: the workspace is a fixed array in the
@@ -204,5 +206,5 @@ ICQ_EXPORT int icq_search_static(const icq_index *ix, const float *queries, int 
     const int rc = scratch_address(&ws);
     if (rc != ICQ_OK) return rc;
     return icq_search_impl(ix, queries, nullptr, Q, thresholds, cap, topk, out_ids, out_dist, out_survivors, ws,
-                       (size_t)ICQ_STATIC_SCRATCH_BYTES, ICQ_SHARE_UNKNOWN, stream);
+                       (size_t)ICQ_STATIC_SCRATCH_BYTES, ICQ_SHARE_UNKNOWN, nullptr, stream);
 }

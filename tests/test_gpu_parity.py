@@ -595,7 +595,7 @@ def test_argument_errors_on_a_live_index(gpu):
 # With Kf = 3 or 4 the index also keeps the items ordered by (code_0, code_1); stage 1 then forms
 # that pair's table sum once per 16 positions and streams only the other one or two fast rows.
 # Inside icq_search the survivors travel as one hit bit per scan position and query, and stage 2
-# walks them chunk by chunk (a first, unfiltered part of the chunks bounds what the rest may add).
+# walks them chunk by chunk (the items of the nearest runs bound what they may add).
 # Same additions in the same order as item by item: the two forms must agree bit for bit.
 @pytest.mark.parametrize("name,N,Q,over,frac,topk", [
     ("C4", 150_000, 37, {}, 0.01, 100),                      # Kf = 4, 16-byte records
@@ -643,8 +643,7 @@ def test_search_grouped_by_the_first_two_fast_codes(gpu, name, N, Q, over, frac,
 def test_search_over_many_chunks_of_hit_bits(gpu, mode, over, Q):
     """From 2^22 items on icq_search hands the survivors of the item-by-item stage 1 to stage 2 as
     hit bits.  Enough items for more than a hundred stage-2 chunks (32768 scan positions each), so
-    that both launches of the chunk walk run -- the unfiltered first part over several chunks, then
-    the rest bounded by its topk-th distance -- with a ragged last chunk; 4-, 8- and 16-byte records,
+    that the chunk walk is bounded by what the nearest runs hold, with a ragged last chunk; 4-, 8- and 16-byte records,
     one, two and four queries per pass of stage 1, and from six queries on over the pair ordering the
     16-bit pre-filter with eight queries per pass (ragged last pass), whose superset stage 2 cuts back
     by the exact comparison: thresholds that let everything, nothing, or only the items at the very
@@ -1028,7 +1027,7 @@ def test_running_search_at_full_size_sampled_against_oracle(gpu):
 
 @pytest.mark.parametrize("K,Kf,mode", [(4, 3, 0), (12, 4, 0), (4, 3, 1)])
 def test_search_from_hit_bits_in_pieces_of_chunks(gpu, K, Kf, mode):
-    """Stage 2 takes whole, half or quarter chunks of hit bits by the number of (chunk, query) pairs: 2100 queries at once, in
+    """Stage 2 takes windows of four to twelve chunks of hit bits by the number of (chunk, query) pairs: 2100 queries at once, in
     twos and in forties have the same lists, distances and counts, bit for bit (a query's work does not depend on the others)."""
     torch, b = gpu
     N, Q, d, topk = (1 << 22) + 4097, 2100, 16, 12
@@ -1065,9 +1064,8 @@ def test_search_from_hit_bits_in_pieces_of_chunks(gpu, K, Kf, mode):
 
 @pytest.mark.parametrize("K,Kf,mode,N", [(8, 3, 0, (1 << 22) + 70_001), (8, 2, 1, (1 << 22) + 65_537), (16, 4, 0, (1 << 22) + 1), (4, 3, 0, 20_000_003)])
 def test_search_from_hit_bits_in_pieces_over_the_shares(gpu, K, Kf, mode, N):
-    """Whole chunks after a first launch of quarters, halves in both, quarters in both: the same lists and counts, bit for bit,
-    whether nothing, a thousandth, a third or all of the items survive, and counts that are those of the crude distances
-    (a chunk's quarter that the first launch has done is not done again, and none is left out)."""
+    """Windows of four to twelve chunks of hit bits: the same lists and counts, bit for bit,
+    whether nothing, a thousandth, a third or all of the items survive, and counts that are those of the crude distances."""
     torch, b = gpu
     Q, d, topk = 24, 16, 100
     gen = torch.Generator(device="cuda")
@@ -1100,6 +1098,52 @@ def test_search_from_hit_bits_in_pieces_over_the_shares(gpu, K, Kf, mode, N):
     for step in (1, 5, 8):
         for x, y in zip(run(step), want):
             assert torch.equal(x, y), step
+
+
+@pytest.mark.parametrize("K,Kf,topk,codes", [
+    (16, 4, 100, "uniform"), (16, 3, 512, "clustered"), (12, 4, 1, "far"), (9, 3, 300, "far"), (8, 4, 100, "clustered"),
+    (4, 3, 47, "uniform"), (16, 2, 100, "uniform"), (8, 2, 512, "far"), (6, 1, 10, "clustered"), (16, 4, 100, "equal")])
+def test_search_bounded_before_stage_2_equals_the_staged_calls(gpu, K, Kf, topk, codes):
+    """Large indexes bound the result from the nearest runs before stage 2 drops what cannot reach it: the lists and counts of
+    the staged calls, bit for bit, where the nearest runs hold the neighbours, nothing at all ("far": no item has a codeword
+    near a query's first ones), thousands of items each ("clustered") or masses of equal distances ("equal"), and where fewer
+    than topk, a few thousandths, a third, all or none of the items survive.  Few queries take the fp32 stage 1, many the
+    16-bit pre-filter."""
+    torch, b = gpu
+    N, d, m = 4_300_001, 24, 3 if codes == "equal" else 256
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(100 * K + Kf)
+    cb = torch.randn((K, m, d), device="cuda", generator=gen) * torch.tensor([0.8 ** k for k in range(K)], device="cuda")[:, None, None]
+    c = torch.randint(0, m, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    if codes == "clustered":
+        centres = torch.randint(0, m, (Kf, 50), dtype=torch.uint8, device="cuda", generator=gen)
+        c[:Kf] = centres[:, torch.randint(0, 50, (N,), device="cuda", generator=gen)]
+    if codes == "far":
+        cb[:2, :128] *= 0.1                                       # the nearest codewords of a query near the origin
+        c[:2] |= 128
+    for Q in (2, 9) if Kf > 2 else (2, 4):
+        queries = (0.3 if codes == "far" else 1.5) * torch.randn((Q, d), device="cuda", generator=gen)
+        index = b.icq_index_create(cb.contiguous(), c, Kf)
+        lut = torch.empty((Q, K, 256), device="cuda")
+        b.icq_build_lut(index, queries, lut)
+        P = sum(lut[:, k].index_select(1, c[k, :50_000].long()) for k in range(Kf))
+        thr = torch.stack([P[q].kthvalue((1, 50, 500, 15_000)[q % 4]).values for q in range(Q)])
+        if Q > 4:
+            thr[4], thr[5], thr[6] = float("inf"), float("-inf"), float("nan")
+
+        def out():
+            return torch.empty((Q, topk), dtype=torch.int32, device="cuda"), torch.empty((Q, topk), device="cuda"), torch.empty((Q,), dtype=torch.int32, device="cuda")
+        ids, dist, count = out()
+        ws = torch.empty(b.icq_workspace_bytes(index, Q, N, topk), dtype=torch.uint8, device="cuda")
+        b.icq_search(index, queries, thr, N, topk, ids, dist, count, ws)
+        want_ids, want_dist, want_count = out()
+        cand = torch.empty((Q, N), dtype=torch.int32, device="cuda")
+        b.icq_scan_fast(index, lut, thr, cand, None, want_count, ws)
+        b.icq_refine(index, lut, cand, None, want_count, topk, want_ids, want_dist, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(count, want_count)
+        assert torch.equal(dist, want_dist) and torch.equal(ids, want_ids)
+        del index, ws, cand
 
 
 @pytest.mark.parametrize("K,d", [(1, 1), (4, 17), (8, 100), (8, 128), (8, 132), (8, 64), (16, 33), (3, 260)])
