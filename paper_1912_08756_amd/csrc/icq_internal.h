@@ -138,6 +138,9 @@ int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const fl
 bool icq_scan_q16_usable(const icq_index *ix, int Q);
 int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
                               size_t mask_stride, int64_t scan_end, hipStream_t s);
+// The same in 8 bits, sixteen queries at a time (icq_scan8.hip; icq_g2_usable).
+int icq_launch_scan_masks_q8(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
+                             size_t mask_stride, int64_t scan_end, hipStream_t s);
 // Stage 2 from hit bits; keys [Q][cap] (+ slice lists in front, see icq_cand_keys); adds the survivors to cand_count.
 // superset: the bits mark a superset of the survivors, and an item counts only if its crude distance
 // (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].  bound_dist (may be nullptr): the caller has no

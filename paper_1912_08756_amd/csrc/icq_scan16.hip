@@ -321,6 +321,10 @@ bool icq_scan_q16_usable(const icq_index *ix, int Q) { return ix->Kf <= 4 && Q >
 int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
                               size_t mask_stride, int64_t scan_end, hipStream_t s) {
     if (icq_g2_usable(ix)) {
+        // sixteen queries per pass in 8 bits where eight would need a second one (5e6 items, 9 queries 56 -> 55 us, 2e7, 9 / 16 / 24 /
+        // 64 queries 89 / 101 / 116 / 168 -> 83 / 95 / 112 / 153, 1e7, 200 queries 280 -> 240, 1e8, 128 queries 1527 -> 1400;
+        // Kf = 3, 6e7, 128 queries: 793 / 795); a pass takes 1.5 times as long as one of eight
+        if (Q > 8) return icq_launch_scan_masks_q8(ix, lut, Q, thr, masks, mask_stride, scan_end, s);
         if (ix->Kf == 3) return launch_q16<1, true>(ix, lut, Q, thr, masks, mask_stride, scan_end, s);
         return launch_q16<2, true>(ix, lut, Q, thr, masks, mask_stride, scan_end, s);
     }

@@ -1108,7 +1108,7 @@ def test_search_bounded_before_stage_2_equals_the_staged_calls(gpu, K, Kf, topk,
     the staged calls, bit for bit, where the nearest runs hold the neighbours, nothing at all ("far": no item has a codeword
     near a query's first ones), thousands of items each ("clustered") or masses of equal distances ("equal"), and where fewer
     than topk, a few thousandths, a third, all or none of the items survive.  Few queries take the fp32 stage 1, many the
-    16-bit pre-filter."""
+    8-bit pre-filter (nine: one of its second eight; 27: a last pass of eleven)."""
     torch, b = gpu
     N, d, m = 4_300_001, 24, 3 if codes == "equal" else 256
     gen = torch.Generator(device="cuda")
@@ -1121,8 +1121,9 @@ def test_search_bounded_before_stage_2_equals_the_staged_calls(gpu, K, Kf, topk,
     if codes == "far":
         cb[:2, :128] *= 0.1                                       # the nearest codewords of a query near the origin
         c[:2] |= 128
-    for Q in (2, 9) if Kf > 2 else (2, 4):
+    for Q in (2, 9, 27) if Kf > 2 else (2, 4):
         queries = (0.3 if codes == "far" else 1.5) * torch.randn((Q, d), device="cuda", generator=gen)
+        queries[::2] += sum(cb[k][c[k, :Q].long()] for k in range(K))[::2]        # every other one near an item
         index = b.icq_index_create(cb.contiguous(), c, Kf)
         lut = torch.empty((Q, K, 256), device="cuda")
         b.icq_build_lut(index, queries, lut)
