@@ -108,7 +108,7 @@ int icq_index_export_codes(const icq_index *index, int from_items, uint8_t *code
  * positions and streams only the remaining fast rows.  Values, survivors and
  * results are identical in every form (same additions in the same order).
  * ICQ_SCAN_AUTO picks a grouped form when it is available and cheaper (Kf = 3, 4:
- * from 64 * 65536 items on) and takes searches of few items and queries through one
+ * from 64 * 65536 items on, for searches of hundreds of queries from about 10^6) and takes searches of few items and queries through one
  * kernel for both stages, ICQ_SCAN_STREAMED always walks all Kf fast rows item
  * by item, ICQ_SCAN_GROUPED uses the grouped form whenever the index has it.
  */

@@ -195,7 +195,7 @@ ICQ_EXPORT int icq_index_export_codes(const icq_index *ix, int from_items, uint8
 ICQ_EXPORT int icq_index_scan_positions(const icq_index *ix, int Q, int64_t *out) {
     if (!ix || !out || Q < 0) return ICQ_ERR_ARG;
     if (icq_group_usable(ix, Q)) *out = ix->groups;
-    else if (icq_g2_usable(ix) && ix->Kf <= 4) *out = ix->g2_npos;
+    else if ((icq_masks_usable(ix, Q, 1) ? icq_g2_pays(ix, Q) : icq_g2_usable(ix)) && ix->Kf <= 4) *out = ix->g2_npos;
     else *out = ix->N;
     return ICQ_OK;
 }

@@ -67,6 +67,15 @@ static inline bool icq_g2_usable(const icq_index *ix) {
     if (!ix->g2 || ix->scan_mode == ICQ_SCAN_STREAMED) return false;
     return ix->scan_mode == ICQ_SCAN_GROUPED || ix->N >= 64ll * 65536;
 }
+// The same for a search that keeps hit bits and is bounded before stage 2: from fewer items on where many queries share
+// the walk, until the padding (1.7 times the positions at 10^6 items) outweighs two streamed rows fewer and stage 2's half
+// records.  Whole calls, us, in id order / by pairs: 7e5 items, 300 queries 101 / 103; 1e6, 64 / 120 / 200 / 1000 (960 dimensions)
+// queries 62 / 66, 70 / 74, 94 / 87, 330 / 266; 2e6, 32 / 64 / 200: 68 / 61, 92 / 72, 161 / 107; 4e6, 32 / 200: 111 / 68, 260 / 145;
+// Kf = 3, 4e6, 200 queries 235 / 137; Kf = 4, 4e6, 250 queries, 20 % surviving 1900 / 500.
+static inline bool icq_g2_pays(const icq_index *ix, int Q) {
+    if (icq_g2_usable(ix)) return true;
+    return ix->g2 && ix->scan_mode == ICQ_SCAN_AUTO && Q >= 32 && (double)ix->N * (double)ix->N * (double)ix->N * (double)Q >= 1.8e20;
+}
 int icq_encode_pack(icq_index *ix, hipStream_t s);             // enc_meta zero on entry
 int icq_group2_build(icq_index *ix, hipStream_t s);
 int icq_group2_export(const icq_index *ix, uint8_t *codes_out, hipStream_t s);
@@ -107,6 +116,7 @@ struct icq_ws_layout {
     int splits;                // parts a query's work in stage 2 is cut into
     // icq_search with the item-by-item stage 1: hit bits instead of candidate lists (ids_off holds them)
     bool masked;
+    bool pairs;                // those bits are over the pair ordering
     bool tickets;              // the selection may take a query's keys in parts
     size_t mask_stride;        // 16-bit words of hit bits per query
     int64_t scan_end;          // scan positions the hit bits cover (whole chunks)
@@ -117,14 +127,15 @@ static inline size_t icq_align_up(size_t x, size_t a) { return (x + a - 1) / a *
 // Layout for `Q` queries processed together.  with_lut / with_cands select the
 // parts a call needs (icq_scan_fast and icq_refine get their tables and lists
 // from the caller).
+// small: without the pair ordering where icq_g2_usable does not ask for it.
 icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool with_lut,
-                         bool with_cands);
+                         bool with_cands, bool small = false);
 int icq_stage2_splits(const icq_index *ix, int Q, int64_t cap, int topk);
 bool icq_selects(const icq_index *ix, int topk);             // stage 2 selects from keys (else the generic kernel)
 // icq_search with the item-by-item stage 1 hands the survivors to stage 2 as one hit bit per scan
 // position and query instead of lists.
 bool icq_masks_usable(const icq_index *ix, int Q, int topk);
-int64_t icq_mask_scan_end(const icq_index *ix);              // positions the hit bits cover: whole stage-2 chunks
+int64_t icq_mask_scan_end(const icq_index *ix, bool pairs);  // positions the hit bits cover: whole stage-2 chunks
 // icq_search's body; lut_ext (device, [Q][K][256]) replaces the table build when not null.  The table build
 // zeroes the call's counters; with lut_ext the caller has done so: out_survivors (not null then) and the first
 // 2 * Q words of the workspace, which is at least that long.
@@ -133,12 +144,12 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
                     void *workspace, size_t workspace_bytes, icq_share share, const float *bound_dist, void *stream);
 // Stage 1 into hit bits.
 int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
-                          size_t mask_stride, int64_t scan_end, bool *superset, hipStream_t s);
+                          size_t mask_stride, int64_t scan_end, bool pairs, bool *superset, hipStream_t s);
 // The 16-bit pre-filter over the pair ordering (icq_scan16.hip): hit bits of a superset of the survivors.
 bool icq_scan_q16_usable(const icq_index *ix, int Q);
 int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
-                              size_t mask_stride, int64_t scan_end, hipStream_t s);
-// The same in 8 bits, sixteen queries at a time (icq_scan8.hip; icq_g2_usable).
+                              size_t mask_stride, int64_t scan_end, bool pairs, hipStream_t s);
+// The same in 8 bits, sixteen queries at a time (icq_scan8.hip; over the pair ordering).
 int icq_launch_scan_masks_q8(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
                              size_t mask_stride, int64_t scan_end, hipStream_t s);
 // Stage 2 from hit bits; keys [Q][cap] (+ slice lists in front, see icq_cand_keys); adds the survivors to cand_count.
@@ -146,7 +157,7 @@ int icq_launch_scan_masks_q8(const icq_index *ix, const float *lut, int Q, const
 // (the first Kf terms of the sum, the additions of Eq. 2) is below thr[q].  bound_dist (may be nullptr): the caller has no
 // use for items of query q beyond bound_dist[q][topk - 1], a finite distance.
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
-                            int64_t scan_end, int64_t cap, int topk, int splits, unsigned long long *keys,
+                            int64_t scan_end, bool pairs, int64_t cap, int topk, int splits, unsigned long long *keys,
                             uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset,
                             const float *bound_dist, uint32_t *out_ids, float *out_dist, hipStream_t s);
 // A bound on the topk-th smallest distance from the items of the nearest runs, into out_dist[q][topk - 1] (icq_bound.hip).

@@ -287,14 +287,13 @@ constexpr int RM_LIST = 512;                          // positions a wavefront e
 static_assert(RM_LIST % (64 * RM_PER) == 0, "a round of the list is whole steps of gathers");
 static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into the chunk");
 
-// PLANES (WORDS == 4): the records' halves at `items` and `tail`, 8 bytes per position each.
 // EXACT: the hit bits mark a superset of the survivors (the 16-bit pre-filter of stage 1); an item is a
 // survivor when the first Kf terms of its sum -- the crude distance of Eq. 2, the same fp32 additions
 // stage 1 makes item by item -- are below thr[q].  Only survivors are counted and get keys.
-template <int WORDS, bool PLANES, bool EXACT>
+template <int WORDS, bool EXACT>
 __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
-    const uint8_t *__restrict__ items, const uint8_t *__restrict__ tail, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
-    size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, int window, int xs_shift, int Q,
+    const uint8_t *__restrict__ items, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
+    size_t mask_words, uint32_t nsel, int window, int xs_shift, int Q,
     u64 *__restrict__ keys, uint32_t *__restrict__ key_count,
     int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
     __shared__ __attribute__((aligned(16))) float T[4 * WORDS * ICQ_LUT_W];
@@ -403,12 +402,6 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
                         const uint2 v = *reinterpret_cast<const uint2 *>(p);
                         rec[u][0] = v.x;
                         rec[u][1 % RW] = v.y;
-                    } else if (PLANES) {
-                        const uint2 v = reinterpret_cast<const uint2 *>(items)[id[u]], y = reinterpret_cast<const uint2 *>(tail)[id[u]];
-                        rec[u][0] = v.x;
-                        rec[u][1 % RW] = v.y;
-                        rec[u][2 % RW] = y.x;
-                        rec[u][3 % RW] = y.y;
                     } else {
                         const uint4 v = *reinterpret_cast<const uint4 *>(p);
                         rec[u][0] = v.x;
@@ -462,7 +455,7 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
                     if ((mk[u] >> lane) & 1ull) {
                         const uint64_t slot = (uint64_t)__builtin_amdgcn_mbcnt_hi(
                             (uint32_t)(mk[u] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk[u], slot0));
-                        if (slot < (uint64_t)cap) kout[slot] = key[u] | (perm ? perm[id[u]] : id[u]);
+                        if (slot < (uint64_t)cap) kout[slot] = key[u] | id[u];
                     }
                     slot0 += (uint32_t)__builtin_popcountll(mk[u]);
                 }
@@ -834,45 +827,52 @@ bool icq_masks_usable(const icq_index *ix, int Q, int topk) {
            ix->N + 16ll * 65536 < (1ll << 31);
 }
 
-int64_t icq_mask_scan_end(const icq_index *ix) {
-    const int64_t npos = icq_g2_usable(ix) ? ix->g2_npos : ix->N;
+int64_t icq_mask_scan_end(const icq_index *ix, bool pairs) {
+    const int64_t npos = pairs ? ix->g2_npos : ix->N;
     return (npos + RM_CHUNK - 1) / RM_CHUNK * RM_CHUNK;
 }
 
 int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const uint16_t *masks, size_t mask_stride,
-                            int64_t scan_end, int64_t cap, int topk, int splits, u64 *keys, uint32_t *key_count,
+                            int64_t scan_end, bool pairs, int64_t cap, int topk, int splits, u64 *keys, uint32_t *key_count,
                             uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset, const float *bound_dist,
                             uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
-    const bool g2 = icq_g2_usable(ix), planes = g2 && ix->item_stride == 16;
-    const uint8_t *items = g2 ? ix->items_grouped : ix->items;
+    const bool planes = pairs && ix->item_stride == 16;
+    const uint8_t *items = pairs ? ix->items_grouped : ix->items;
     const uint8_t *tail = planes ? items + (size_t)ix->g2_npad * 8 : nullptr;
-    const uint32_t *perm = g2 ? ix->perm : nullptr;
+    const uint32_t *perm = pairs ? ix->perm : nullptr;
     const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
-    const uint64_t pairs = (uint64_t)chunks * (uint64_t)Q;
-    // From 130 chunks on a bound is worth its launch of 8 to 12 us (20 to 40 for hundreds of queries).  Whole calls, us, one
+    const uint64_t visits = (uint64_t)chunks * (uint64_t)Q;
+    // From 130 chunks on, and over the pair ordering, a bound is worth its launch of 8 to 12 us (20 to 40 for hundreds of queries).  Whole calls, us, one
     // unfiltered launch (up to 130 chunks; beyond, behind one over every 65th chunk) / bounded: K = 16: 7.8e5 items, 37 queries
-    // 43 / 47; 1e6, 1000 queries 330 / 333; 4.3e6, 1 / 3 / 8 queries 44 / 39, 56 / 43, 76 / 52; 1e7, 16 queries, 30 % 765 / 146;
+    // 43 / 47; 1e6, 1000 queries (id order) 330 / 333; 4.3e6, 1 / 3 / 8 queries 44 / 39, 56 / 43, 76 / 52; 1e7, 16 queries, 30 % 765 / 146;
     // 2e7, 64 queries 340 / 198; 1e8, 1 / 128 queries 161 / 104, 1797 / 1536; K = 12, Kf = 3, 1e7, 100 queries, 10 % 873 / 305;
     // K = 8, Kf = 2, 1e7, 1 query 49 / 35, 1.3e7, 4 queries 83 / 47.
-    if (!bound_dist && chunks >= 130) {
+    if (!bound_dist && (pairs || chunks >= 130)) {
         const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, out_dist, s);
         if (rc != ICQ_OK) return rc;
         bound_dist = out_dist;
     }
     // Chunks per block: few, so that the blocks in flight (two windows' worth when the queries fill the chip) keep to a few
-    // chunks per XCD, but enough to be worth the tables a block loads.  Bounded: three per wavefront while that leaves a block
-    // for every place on the chip (1e8 items, 128 queries, windows of 4 / 8 / 12 / 16 / 24: 1675 / 1545 / 1536 / 1541 / 1570 us; 1
-    // query 104 / 109 / 115 / 119; 1e7, 16 queries, 30 %: 146 / 192 / 239).  Unfiltered: one per wavefront while that is
+    // chunks per XCD, but enough to be worth the tables a block loads.  Bounded: up to three per wavefront while that leaves a
+    // block for every place on the chip (1e8 items, 128 queries, windows of 4 / 8 / 12 / 16 / 24: 1675 / 1545 / 1536 / 1541 / 1570 us;
+    // 1 query 104 / 109 / 115 / 119; 2e6, 80 queries 81 / 73 / 77; 3e7, 20 queries - / 144 / 149; 1e7, 60 queries 119 / 117 / 118).  Unfiltered: one per wavefront while that is
     // all the parallelism there is, else full windows, and the chunks cut fewer than 8 ways when 8 windows' worth do not
     // exist: 16 MB of records stay in the caches wherever the blocks run.
     // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
     // keeps a chunk's records in ONE L2 is worth more than the longer windows: 1e4 queries, 1e6 items,
     // 8-byte records: 0.80 ms with it, 0.83 without)
-    int window = pairs <= 16384u ? 4 : 16;
-    if (bound_dist) window = pairs < 2 * 4 * 1536u ? 4 : pairs < 3 * 4 * 1536u ? 8 : 12;
-    int xs_shift = 3;
-    while (Q <= 2048 && xs_shift > 0 && ((uint32_t)window << xs_shift) > chunks) --xs_shift;
+    int window = visits <= 16384u ? 4 : 16, xs_shift = 3;
+    if (bound_dist) {
+        window = visits < 5000u ? 4 : visits < 40000u ? 8 : 12;
+        // Few windows: four ways where the last of eight would leave a sixth of the wavefronts without a chunk (2e6 items, 200
+        // queries, windows of 8 cut 8 / 4 / 1 ways 117 / 105 / 116 us; 1e6, 1000 queries, of 12, 4 / 1 ways 265 / 278)
+        const uint32_t places = (chunks + ((uint32_t)window << 3) - 1) / ((uint32_t)window << 3) * ((uint32_t)window << 3);
+        if (places * 5u > chunks * 6u) xs_shift = 2;
+        while (xs_shift > 0 && ((uint32_t)window << (xs_shift - 1)) >= chunks) --xs_shift;
+    } else {
+        while (Q <= 2048 && xs_shift > 0 && ((uint32_t)window << xs_shift) > chunks) --xs_shift;
+    }
     const int most = (int)((chunks + (1u << xs_shift) - 1) >> xs_shift);
     if (window > most) window = most > 0 ? most : 1;
     const unsigned per_win = (unsigned)window << xs_shift;
@@ -884,8 +884,7 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                                            topk, keys, key_count, cap, cand_count, thr, ix->Kf);
     };
     auto open = [&](auto kernel) {
-        kernel<<<grid, RM_THREADS, 0, s>>>(items, tail, ix->K, lut, m32, mask_words, perm, chunks, window, xs_shift, Q, keys,
-                                           key_count, cap, cand_count, thr, ix->Kf);
+        kernel<<<grid, RM_THREADS, 0, s>>>(items, ix->K, lut, m32, mask_words, chunks, window, xs_shift, Q, keys, key_count, cap, cand_count, thr, ix->Kf);
     };
 #define ICQ_RM_LAUNCH(W, PLANES)                                             \
     do {                                                                     \
@@ -893,8 +892,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
             if (superset) bounded(refine_bounded_kernel<W, PLANES, true>);   \
             else bounded(refine_bounded_kernel<W, PLANES, false>);           \
         } else {                                                             \
-            if (superset) open(refine_mask_kernel<W, PLANES, true>);         \
-            else open(refine_mask_kernel<W, PLANES, false>);                 \
+            if (superset) open(refine_mask_kernel<W, true>);                 \
+            else open(refine_mask_kernel<W, false>);                         \
         }                                                                    \
     } while (0)
     if (ix->item_stride == 4) ICQ_RM_LAUNCH(1, false);

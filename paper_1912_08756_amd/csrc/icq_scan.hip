@@ -692,12 +692,12 @@ int icq_launch_scan(const icq_index *ix, const float *lut, int Q, const float *t
 // *superset: the bits written mark a superset of the survivors (the 16-bit pre-filter); stage 2 then
 // applies the exact comparison itself.
 int icq_launch_scan_masks(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
-                          size_t mask_stride, int64_t scan_end, bool *superset, hipStream_t s) {
+                          size_t mask_stride, int64_t scan_end, bool pairs, bool *superset, hipStream_t s) {
     *superset = false;
     if (Q == 0) return ICQ_OK;
     if (icq_scan_q16_usable(ix, Q)) {
         *superset = true;
-        return icq_launch_scan_masks_q16(ix, lut, Q, thr, masks, mask_stride, scan_end, s);
+        return icq_launch_scan_masks_q16(ix, lut, Q, thr, masks, mask_stride, scan_end, pairs, s);
     }
     return launch_stream_any(ix, lut, Q, thr, nullptr, nullptr, 0, masks, mask_stride, scan_end, s);
 }

@@ -319,8 +319,8 @@ bool icq_scan_q16_usable(const icq_index *ix, int Q) { return ix->Kf <= 4 && Q >
 
 // Hit bits of a superset of the survivors; the caller's stage 2 applies the exact comparison.
 int icq_launch_scan_masks_q16(const icq_index *ix, const float *lut, int Q, const float *thr, uint16_t *masks,
-                              size_t mask_stride, int64_t scan_end, hipStream_t s) {
-    if (icq_g2_usable(ix)) {
+                              size_t mask_stride, int64_t scan_end, bool pairs, hipStream_t s) {
+    if (pairs) {
         // sixteen queries per pass in 8 bits where eight would need a second one (5e6 items, 9 queries 56 -> 55 us, 2e7, 9 / 16 / 24 /
         // 64 queries 89 / 101 / 116 / 168 -> 83 / 95 / 112 / 153, 1e7, 200 queries 280 -> 240, 1e8, 128 queries 1527 -> 1400;
         // Kf = 3, 6e7, 128 queries: 793 / 795); a pass takes 1.5 times as long as one of eight

@@ -7,7 +7,7 @@
 #include <mutex>
 
 icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool with_lut,
-                         bool with_cands) {
+                         bool with_cands, bool small) {
     icq_ws_layout L = {};
     // icq_search with the grouped stage 1 keeping the lists on chip: no candidate lists in the
     // workspace, only (few queries, several blocks per query) the parts' lists for the merge
@@ -27,7 +27,8 @@ icq_ws_layout icq_layout(const icq_index *ix, int Q, int64_t cap, int topk, bool
     if (with_lut) off = icq_align_up(off + sizeof(float) * (size_t)Q * ix->K * ICQ_LUT_W, ICQ_ALIGN);
     L.ids_off = off;
     if (L.masked) {
-        L.scan_end = icq_mask_scan_end(ix);
+        L.pairs = small ? icq_g2_usable(ix) : icq_g2_pays(ix, Q);
+        L.scan_end = icq_mask_scan_end(ix, L.pairs);
         L.mask_stride = (size_t)(L.scan_end / 16);
         // rows for whole groups of eight queries: the pre-filter kernel stores all eight slots of its last group
         off = icq_align_up(off + sizeof(uint16_t) * (size_t)((Q + 7) / 8 * 8) * L.mask_stride, ICQ_ALIGN);
@@ -88,11 +89,16 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
 
     // Largest sub-batch (all of Q, else a multiple of 64 queries) that fits the workspace.
     int Qb = Q < SEARCH_MAX_BATCH ? Q : SEARCH_MAX_BATCH;
-    while (icq_layout(ix, Qb, cap, topk, own_lut, true).total > workspace_bytes) {
+    bool small = false;        // the smaller of the forms that a call may take, before it is cut
+    while (icq_layout(ix, Qb, cap, topk, own_lut, true, small).total > workspace_bytes) {
+        if (!small) {
+            small = true;
+            continue;
+        }
         if (Qb <= 64) return ICQ_ERR_WORKSPACE;
         Qb = ((Qb / 2) + 63) / 64 * 64;
     }
-    if (Q % Qb != 0 && icq_layout(ix, Q % Qb, cap, topk, own_lut, true).total > workspace_bytes)
+    if (Q % Qb != 0 && icq_layout(ix, Q % Qb, cap, topk, own_lut, true, small).total > workspace_bytes)
         return ICQ_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char *ws = static_cast<char *>(workspace);
@@ -106,7 +112,7 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
     for (int q0 = 0; q0 < Q; q0 += Qb) {
         const bool timed = tm && q0 == 0;
         const int nq = (Q - q0) < Qb ? (Q - q0) : Qb;
-        const icq_ws_layout L = icq_layout(ix, nq, cap, topk, own_lut, true);
+        const icq_ws_layout L = icq_layout(ix, nq, cap, topk, own_lut, true, small);
         const float *lut = own_lut ? reinterpret_cast<float *>(ws + L.lut_off)
                                    : lut_ext + (int64_t)q0 * ix->K * ICQ_LUT_W;
         uint32_t *ids = reinterpret_cast<uint32_t *>(ws + L.ids_off);
@@ -127,10 +133,11 @@ int icq_search_impl(const icq_index *ix, const float *queries, const float *lut_
             // item-by-item stage 1 into hit bits, stage 2 chunk by chunk from them
             uint16_t *masks = reinterpret_cast<uint16_t *>(ws + L.ids_off);
             bool superset = false;
-            rc = icq_launch_scan_masks(ix, lut, nq, thresholds + q0, masks, L.mask_stride, L.scan_end, &superset, s);
+            rc = icq_launch_scan_masks(ix, lut, nq, thresholds + q0, masks, L.mask_stride, L.scan_end, L.pairs, &superset, s);
             if (rc != ICQ_OK) return rc;
             if (timed) ICQ_HIP_TRY(hipEventRecord(ev[2], s));
-            rc = icq_launch_refine_masks(ix, lut, nq, masks, L.mask_stride, L.scan_end, cap, topk, L.splits, keys,
+            rc = icq_launch_refine_masks(ix, lut, nq, masks, L.mask_stride, L.scan_end, L.pairs, cap, topk, L.splits,
+                                         keys,
                                          key_count, ticket, cnt, thresholds + q0, superset,
                                          bound_dist ? bound_dist + (int64_t)q0 * topk : nullptr,
                                          out_ids + (int64_t)q0 * topk, out_dist + (int64_t)q0 * topk, s);
@@ -201,7 +208,7 @@ ICQ_EXPORT int icq_search_static(const icq_index *ix, const float *queries, int 
     if (hipGetDevice(&dev) != hipSuccess) return ICQ_ERR_HIP;
     if (dev != ix->device) return ICQ_ERR_ARG;          // the array used is the current device's
     // the whole call must fit at once: no silent split into sub-batches here
-    if (icq_layout(ix, Q, cap, topk, true, true).total > (size_t)ICQ_STATIC_SCRATCH_BYTES) return ICQ_ERR_SCRATCH;
+    if (icq_layout(ix, Q, cap, topk, true, true, true).total > (size_t)ICQ_STATIC_SCRATCH_BYTES) return ICQ_ERR_SCRATCH;
     void *ws = nullptr;
     const int rc = scratch_address(&ws);
     if (rc != ICQ_OK) return rc;

@@ -1147,6 +1147,47 @@ def test_search_bounded_before_stage_2_equals_the_staged_calls(gpu, K, Kf, topk,
         del index, ws, cand
 
 
+@pytest.mark.parametrize("K,Kf,N,Q,topk", [(16, 4, 1_000_003, 190, 100), (12, 3, 2_000_001, 40, 300), (8, 4, 600_011, 900, 10)])
+def test_search_of_many_queries_over_the_pair_ordering_equals_id_order(gpu, K, Kf, N, Q, topk):
+    """Many queries over an index of half a million to four million items walk the pair ordering, the stage-2 bound first: the
+    lists and counts of the walk in id order, bit for bit, for thresholds that let all, nothing, a hundredth or a tenth
+    through; and in a workspace that holds the bits of id order only (or whole calls of fewer queries) the same again."""
+    torch, b = gpu
+    d = 20
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    cb = torch.randn((K, 200, d), device="cuda", generator=gen) * torch.tensor([0.8 ** k for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, 200, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    index = b.icq_index_create(cb.contiguous(), codes, Kf)
+    queries = 1.5 * torch.randn((Q, d), device="cuda", generator=gen)
+    queries[::2] += sum(cb[k][codes[k, :Q].long()] for k in range(K))[::2]
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = sum(lut[:, k].index_select(1, codes[k, :20_000].long()) for k in range(Kf))
+    thr = P.kthvalue(200, dim=1).values.contiguous()
+    thr[0::7] = P.kthvalue(2000, dim=1).values[0::7]
+    thr[1], thr[2], thr[3] = float("inf"), float("-inf"), float("nan")
+    cap = N
+
+    def run(bytes_, mode):
+        b.icq_index_set_scan_mode(index, mode)
+        ids = torch.empty((Q, topk), dtype=torch.int32, device="cuda")
+        dist = torch.empty((Q, topk), device="cuda")
+        count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+        b.icq_search(index, queries, thr, cap, topk, ids, dist, count, torch.empty(bytes_, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        return ids, dist, count
+    full = b.icq_workspace_bytes(index, Q, cap, topk)
+    want = run(full, 1)
+    assert int(want[2][1]) == N and int(want[2][2]) == 0
+    b.icq_index_set_scan_mode(index, 0)
+    assert b.icq_index_scan_positions(index, Q) > N
+    bits = Q * (b.icq_index_scan_positions(index, Q) - N) // 8
+    for bytes_ in (full, full - bits // 2) + ((full // 2,) if Q > 128 else ()):        # (64 queries are not cut further)
+        for x, y in zip(run(bytes_, 0), want):
+            assert torch.equal(x, y), bytes_
+
+
 @pytest.mark.parametrize("K,d", [(1, 1), (4, 17), (8, 100), (8, 128), (8, 132), (8, 64), (16, 33), (3, 260)])
 def test_tables_of_few_queries_equal_those_of_many(gpu, K, d):
     """Few queries' tables come from wavefronts of their own, many queries' from blocks that stage in LDS: the same sums in the
