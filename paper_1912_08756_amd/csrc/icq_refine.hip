@@ -484,7 +484,7 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 // -- over the pair ordering the halves lie in planes of their own, and a window of chunks is half as many bytes for the
 // XCD's cache -- and the second half only for what is left, collected 64 at a time.  K <= 8: the whole distance is known
 // at once, the same queue collects what reaches the bound.
-// A wavefront's positions go through a stack in LDS that outlives the chunk, so that the gathers always come 256 at a time.
+// A wavefront's positions go through a stack in LDS that outlives the chunk, so that the gathers always come 256 or 512 at a time.
 // A word's lowest hit bit goes there straight; what is left of words with several (one in seven at 1 %) is collected 64
 // words at a time first: with a loop over every word's bits the expansion was more than half of all vector instructions.
 // What bounds it: 10^8 items, 128 queries, 1 %: 4.0 GB fetched (1.6 of hit bits) in 0.77 ms, where the kernel that gathered
@@ -492,9 +492,8 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 // with everything that lets the queries' wavefronts drift apart (one block per query and XCD for the whole index: 1.5 ms),
 // and a wavefront lives through three chunks only, so that work at its end weighs: asking for the records of a batch before
 // the last one is worked off, words instead of positions in the stack, half chunks and more wavefronts were all slower
-// (0.85 to 1.0 ms).
-constexpr int RB_BATCH = 64 * RM_PER;                 // survivors gathered together
-constexpr int RB_LIST = RB_BATCH + 256;               // positions a wavefront holds
+// (0.85 to 1.0 ms).  512 gathers at a time, for indexes of many chunks, 0.74 ms (2e7 items, 64 queries, whole calls 187 / 183 us,
+// 1e8, 20 queries 388 / 371; 1e7, 200 queries 247 / 254; 1e6, 1000 queries 266 / 280; 1e8, 1 query 119 / 122; 640 and more at a time are slower).
 constexpr int RB_MORE = 128;                          // words with hit bits left
 constexpr int RB_QUEUE = 128;                         // survivors to be finished
 
@@ -504,7 +503,7 @@ template <> struct RbRestT<true> { uint32_t pos, sum, tail0, tail1; };
 
 // WORDS == 4: PLANES: first and second halves of the records at `items` and `tail`, 8 bytes per position; else (an index in
 // id order) records of 16 bytes, whose second half comes with the line of the first and waits in the queue.
-template <int WORDS, bool PLANES, bool EXACT>
+template <int WORDS, bool PLANES, bool EXACT, int PER>
 __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
     const uint8_t *__restrict__ items, const uint8_t *__restrict__ tail, int K, const float *__restrict__ lut,
     const uint32_t *__restrict__ masks, size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, int window,
@@ -515,8 +514,10 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
     constexpr bool WHOLE = WORDS == 4 && !PLANES;     // the whole record is fetched at once
     constexpr int FW = WHOLE ? 4 : HW;                // words fetched
     using RbRest = RbRestT<WHOLE>;
+    constexpr uint32_t BATCH = 64 * PER;              // survivors gathered together
+    constexpr uint32_t LIST = BATCH + 64;             // positions a wavefront holds
     __shared__ __attribute__((aligned(16))) float T[HT * ICQ_LUT_W];
-    __shared__ uint32_t list_all[RM_WAVES][RB_LIST];
+    __shared__ uint32_t list_all[RM_WAVES][LIST];
     __shared__ uint2 more_all[RM_WAVES][RB_MORE];     // hit bits, first position of the word
     __shared__ RbRest queue_all[RM_WAVES][RB_QUEUE];
     __shared__ float tmin[8];                         // smallest entry of each table of the second half
@@ -544,9 +545,8 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
     {
         const float4 *src = reinterpret_cast<const float4 *>(Tq);
         float4 *dst = reinterpret_cast<float4 *>(T);
-        constexpr int PER = HT / 4;                   // tables per wavefront
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
+        for (int u = 0; u < HT / 4; ++u) {            // tables per wavefront
             const int i = u * RM_THREADS + tid;
             dst[i] = u * 4 + wave < K ? src[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
@@ -615,18 +615,18 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
             if (slot < (uint64_t)cap) kout[slot] = ((u64)ob << 32) | (perm ? perm[e.pos] : e.pos);
         }
     };
-    // the list's last `cnt` (at most RB_BATCH)
+    // the list's last `cnt` (at most BATCH)
     auto batch = [&](uint32_t cnt) __attribute__((always_inline)) {
         wave_lds_order();
-        uint32_t pos[RM_PER], rec[RM_PER][FW];
+        uint32_t pos[PER], rec[PER][FW];
 #pragma unroll
-        for (int u = 0; u < RM_PER; ++u) {
+        for (int u = 0; u < PER; ++u) {
             const uint32_t i = (uint32_t)u * 64u + lane;
             pos[u] = list[n - cnt + (i < cnt ? i : cnt - 1)];
         }
         n -= cnt;
 #pragma unroll
-        for (int u = 0; u < RM_PER; ++u) {
+        for (int u = 0; u < PER; ++u) {
             const uint32_t *p = reinterpret_cast<const uint32_t *>(items + (size_t)pos[u] * (FW * 4));
             if (FW == 1) {
                 rec[u][0] = p[0];
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
             }
         }
 #pragma unroll
-        for (int u = 0; u < RM_PER; ++u) {
+        for (int u = 0; u < PER; ++u) {
             // all table reads of the half record first, then the sum: k ascending like every other kernel, the first term
             // standing for 0 + itself (no table holds -0)
             float tv[HT];
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         if (m != 0)
             list[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, n))] = at + (uint32_t)__builtin_ctz(m);
         n += (uint32_t)__builtin_popcountll(mk);
-        if (n > (uint32_t)(RB_LIST - 64)) batch(RB_BATCH);
+        if (n > LIST - 64) batch(BATCH);
         return m & (m - 1);
     };
     // the last `cnt` words (at most 64) with bits left
@@ -717,7 +717,7 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         }
     }
     if (nm != 0) drain(nm);
-    while (n != 0) batch(n < (uint32_t)RB_BATCH ? n : (uint32_t)RB_BATCH);
+    while (n != 0) batch(n < BATCH ? n : BATCH);
     if (nq != 0) finish(nq);
     const uint32_t survivors = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors), 63);
     // one addition per block, as above
@@ -886,11 +886,15 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     auto open = [&](auto kernel) {
         kernel<<<grid, RM_THREADS, 0, s>>>(items, ix->K, lut, m32, mask_words, chunks, window, xs_shift, Q, keys, key_count, cap, cand_count, thr, ix->Kf);
     };
+    // (a wavefront's gathers at a time: see the kernel)
 #define ICQ_RM_LAUNCH(W, PLANES)                                             \
     do {                                                                     \
-        if (bound_dist) {                                                    \
-            if (superset) bounded(refine_bounded_kernel<W, PLANES, true>);   \
-            else bounded(refine_bounded_kernel<W, PLANES, false>);           \
+        if (bound_dist && PLANES && chunks >= 600 && visits >= 30000u) {      \
+            if (superset) bounded(refine_bounded_kernel<W, PLANES, true, PLANES ? 8 : RM_PER>);      \
+            else bounded(refine_bounded_kernel<W, PLANES, false, PLANES ? 8 : RM_PER>);              \
+        } else if (bound_dist) {                                             \
+            if (superset) bounded(refine_bounded_kernel<W, PLANES, true, RM_PER>);                   \
+            else bounded(refine_bounded_kernel<W, PLANES, false, RM_PER>);                           \
         } else {                                                             \
             if (superset) open(refine_mask_kernel<W, true>);                 \
             else open(refine_mask_kernel<W, false>);                         \
