@@ -2,7 +2,7 @@
 // nearest-neighbour list).  Any topk items that pass the crude comparison bound the topk-th smallest distance from above,
 // and the nearer they are the better: the index keeps its items in runs of equal first two fast sub-codes (Kf <= 2: the
 // tuples; Kf = 3, 4: the pairs), and the runs whose two table entries add up to least hold most of a query's neighbours.
-// 10^8 items, K = 16, topk = 100: 2 of the 65536 runs, 3000 items, give a bound that a few hundred items reach, in 12 us; an
+// 10^8 items, K = 16, topk = 100: one or two of the 65536 runs, 2000 items, give a bound that a few hundred items reach, in 12 us; an
 // unfiltered walk over every 65th part of the index took 97 us for one that 6500 reach.
 //
 // One block per query.  The pairs looked at are the four smallest entries of the first table with all of the second; a
@@ -19,23 +19,26 @@
 
 namespace {
 
+// (256 / 512 / 1024 threads and 1024 / 2048 items: 1e8 items, one query, 105 / 101 / 103 us, with 2048 items 102 at 512; 1e6, 1000
+// queries 275 / 261 / 268, 266; 1e7, two queries, Kf = 2: 39 / 35 / 37, 37)
+constexpr int NB_THREADS = 512;
 constexpr int NB_PER = 4;              // items a thread fetches together
 constexpr int NB_PAIRS = 4 * ICQ_LUT_W;
 constexpr uint32_t NB_SPREAD = 16384;  // items of the second look
 
 // FORM: 0 the pairs of Kf = 3, 4 (icq_group2.hip), else the tuples of Kf = FORM.
-template <int WORDS, int FORM, int THREADS>
-__global__ __launch_bounds__(THREADS) void near_bound_kernel(
+template <int WORDS, int FORM>
+__global__ __launch_bounds__(NB_THREADS) void near_bound_kernel(
     const uint8_t *__restrict__ items, size_t plane, const uint8_t *__restrict__ by_id, uint32_t N,
     const float *__restrict__ lut, int K, int Kf, const float *__restrict__ thr, const uint32_t *__restrict__ run_begin, const uint32_t *__restrict__ run_end, uint32_t target, uint32_t most, int topk,
     float *__restrict__ out_dist) {
-    constexpr int WAVES = THREADS / 64, PAIRS = NB_PAIRS / THREADS;
+    constexpr int WAVES = NB_THREADS / 64, PAIRS = NB_PAIRS / NB_THREADS;
     __shared__ __attribute__((aligned(16))) float T[4 * WORDS * ICQ_LUT_W];
     __shared__ uint32_t run_pos[NB_PAIRS], run_off[NB_PAIRS + 1];        // the runs taken: first position - offset, offset
     __shared__ uint32_t wsum[WAVES][2];
     __shared__ uint32_t s_found;
     __shared__ float tmin[4];
-    __shared__ IcqKthSharedT<THREADS> kth;
+    __shared__ IcqKthSharedT<NB_THREADS> kth;
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
         const float4 *src = reinterpret_cast<const float4 *>(lut + (int64_t)q * K * ICQ_LUT_W);
         constexpr int N4 = 4 * WORDS * (ICQ_LUT_W / 4);
 #pragma unroll
-        for (int i = 0; i < N4; i += THREADS) {
+        for (int i = 0; i < N4; i += NB_THREADS) {
             const int e = i + tid;
             if (e < N4) reinterpret_cast<float4 *>(T)[e] = e / (ICQ_LUT_W / 4) < K ? src[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
         }
 #pragma unroll
         for (int u = 0; u < PAIRS; ++u) {
-            const uint32_t i = (uint32_t)u * THREADS + (uint32_t)tid, c = i & (ICQ_LUT_W - 1), r = i / ICQ_LUT_W;   // r: wavefront-uniform
+            const uint32_t i = (uint32_t)u * NB_THREADS + (uint32_t)tid, c = i & (ICQ_LUT_W - 1), r = i / ICQ_LUT_W;   // r: wavefront-uniform
             const uint32_t c0 = FORM == 1 ? c : r == 0 ? row[0] : r == 1 ? row[1] : r == 2 ? row[2] : row[3];
             const uint32_t slot = FORM == 0 ? icq_g2_slot_of_pair(c0 | (c << 8)) : FORM == 1 ? c0 : c0 * 256u + c;
             first[u] = run_begin[slot];
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
     uint32_t off, at, total, runs;                       // (its barriers also put tmin in place)
     scan(sum(valid), (uint32_t)__builtin_popcount(valid), off, at, total, runs);
     if (total > target) {                                                    // block-uniform
-        const uint32_t cut = block_kth_impl<PAIRS, true, THREADS>(kth, v, n, valid, target, false, tid, lane, wave);
+        const uint32_t cut = block_kth_impl<PAIRS, true, NB_THREADS>(kth, v, n, valid, target, false, tid, lane, wave);
 #pragma unroll
         for (int u = 0; u < PAIRS; ++u)
             if (v[u] > cut) valid &= ~(1u << u);
@@ -135,11 +138,11 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
         __syncthreads();
         if (tid == 0) s_found = 0;
         uint32_t least[2] = {0xFFFFFFFFu, 0xFFFFFFFFu}, any = 0;
-        for (uint32_t base = 0; base < total; base += THREADS * NB_PER) {
+        for (uint32_t base = 0; base < total; base += NB_THREADS * NB_PER) {
             uint32_t rec[NB_PER][WORDS];
 #pragma unroll
             for (int u = 0; u < NB_PER; ++u) {
-                uint32_t i = base + (uint32_t)u * THREADS + (uint32_t)tid;
+                uint32_t i = base + (uint32_t)u * NB_THREADS + (uint32_t)tid;
                 i = i < total ? i : total - 1;
                 const uint8_t *from = items;
                 uint32_t pos;
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
                     d += T[i * ICQ_LUT_W + ((rec[u][i / 4] >> (8 * (i % 4))) & 0xffu)];
                     if (i < 4) crude = i < Kf ? d : crude;
                 }
-                if (base + (uint32_t)u * THREADS + (uint32_t)tid < total && crude < t) {
+                if (base + (uint32_t)u * NB_THREADS + (uint32_t)tid < total && crude < t) {
                     const uint32_t ob = icq_order_bits(d);
                     least[u % 2] = ob < least[u % 2] ? ob : least[u % 2];
                     any |= 1u << (u % 2);
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
         if (lane == 0) atomicAdd(&s_found, have);
         __syncthreads();
         if (s_found < (uint32_t)topk) continue;                              // block-uniform
-        bound = icq_unorder_bits(block_kth<2, THREADS>(kth, least, any, (uint32_t)topk, false, tid, lane, wave));
+        bound = icq_unorder_bits(block_kth<2, NB_THREADS>(kth, least, any, (uint32_t)topk, false, tid, lane, wave));
         break;
     }
     if (tid == 0) out_dist[(int64_t)q * topk + topk - 1] = bound;
@@ -207,23 +210,17 @@ __global__ __launch_bounds__(THREADS) void near_bound_kernel(
 
 // out_dist[q][topk - 1] = an upper bound of query q's topk-th smallest distance among the survivors, +inf for none.
 int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const float *thr, int topk, float *out_dist, hipStream_t s) {
-    const uint32_t target = 8u * (uint32_t)topk > 2048u ? 8u * (uint32_t)topk : 2048u;
+    const uint32_t target = 8u * (uint32_t)topk > 1024u ? 8u * (uint32_t)topk : 1024u;
     const int words = ix->item_stride / 4;
-#define ICQ_NB_GO(W, FORM, T)                                                                                                    \
-    near_bound_kernel<W, FORM, T><<<(unsigned)Q, T, 0, s>>>(ix->items_grouped, (size_t)ix->g2_npad, ix->items, (uint32_t)ix->N,    \
-                                                            lut, ix->K, ix->Kf, thr, ix->group_start,                              \
-                                                            ix->group_cursor, target, 2 * target, topk, out_dist)
+    auto go = [&](auto kernel) {
+        kernel<<<(unsigned)Q, NB_THREADS, 0, s>>>(ix->items_grouped, (size_t)ix->g2_npad, ix->items, (uint32_t)ix->N, lut, ix->K, ix->Kf,
+                                                  thr, ix->group_start, ix->group_cursor, target, 2 * target, topk, out_dist);
+    };
 #define ICQ_NB(FORM)                                                   \
     do {                                                               \
-        if (Q <= 256) {                                                \
-            if (words == 1) ICQ_NB_GO(1, FORM, 1024);                  \
-            else if (words == 2) ICQ_NB_GO(2, FORM, 1024);             \
-            else ICQ_NB_GO(4, FORM, 1024);                             \
-        } else {                                                       \
-            if (words == 1) ICQ_NB_GO(1, FORM, 512);                   \
-            else if (words == 2) ICQ_NB_GO(2, FORM, 512);              \
-            else ICQ_NB_GO(4, FORM, 512);                              \
-        }                                                              \
+        if (words == 1) go(near_bound_kernel<1, FORM>);                \
+        else if (words == 2) go(near_bound_kernel<2, FORM>);           \
+        else go(near_bound_kernel<4, FORM>);                           \
     } while (0)
     if (ix->Kf > 2) ICQ_NB(0);
     else if (ix->Kf == 1) ICQ_NB(1);
