@@ -856,7 +856,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // Chunks per block: few, so that the blocks in flight (two windows' worth when the queries fill the chip) keep to a few
     // chunks per XCD, but enough to be worth the tables a block loads.  Bounded: up to three per wavefront while that leaves a
     // block for every place on the chip (1e8 items, 128 queries, windows of 4 / 8 / 12 / 16 / 24: 1675 / 1545 / 1536 / 1541 / 1570 us;
-    // 1 query 104 / 109 / 115 / 119; 2e6, 80 queries 81 / 73 / 77; 3e7, 20 queries - / 144 / 149; 1e7, 60 queries 119 / 117 / 118).  Unfiltered: one per wavefront while that is
+    // 1 query 104 / 109 / 115 / 119; 2e6, 80 queries 81 / 73 / 77; 3e7, 20 queries - / 144 / 149; 1e7, 60 queries 119 / 117 / 118; 1e8 in
+    // id order, 128 queries 2641 / 2589 / 2790).  Unfiltered: one per wavefront while that is
     // all the parallelism there is, else full windows, and the chunks cut fewer than 8 ways when 8 windows' worth do not
     // exist: 16 MB of records stay in the caches wherever the blocks run.
     // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
@@ -864,7 +865,7 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // 8-byte records: 0.80 ms with it, 0.83 without)
     int window = visits <= 16384u ? 4 : 16, xs_shift = 3;
     if (bound_dist) {
-        window = visits < 5000u ? 4 : visits < 40000u ? 8 : 12;
+        window = visits < 5000u ? 4 : visits < 40000u || !pairs ? 8 : 12;
         // Few windows: four ways where the last of eight would leave a sixth of the wavefronts without a chunk (2e6 items, 200
         // queries, windows of 8 cut 8 / 4 / 1 ways 117 / 105 / 116 us; 1e6, 1000 queries, of 12, 4 / 1 ways 265 / 278)
         const uint32_t places = (chunks + ((uint32_t)window << 3) - 1) / ((uint32_t)window << 3) * ((uint32_t)window << 3);
