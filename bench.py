@@ -685,13 +685,13 @@ def index_words(K):
 def stage1_form(Kf, K, N, Qb, topk):
     """Which stage-1 form the library picks in automatic mode (icq_index_set_scan_mode) for a call
     of Qb queries: 'tuples' (Kf <= 2: one evaluation per fast-code tuple, distances and lists in the
-    same kernel), 'pairs' (Kf = 3, 4 from 64 * 65536 items on: items ordered by their first two fast
-    sub-codes, the other rows streamed) or 'items' (all Kf rows streamed); and whether stage 1
+    same kernel), 'pairs' (Kf = 3, 4 from 64 * 65536 items on, with many queries from about 10^6: items ordered
+    by their first two fast sub-codes, the other rows streamed) or 'items' (all Kf rows streamed); and whether stage 1
     hands stage 2 hit bits (from 2^22 items on) or candidate lists."""
     if Kf <= 2 and Qb > 4 and N >= 256 ** Kf // 2:
         return "tuples", False
     bits = Kf <= 4 and K <= 16 and topk <= 512 and (N >= 1 << 22 or (N >= 1 << 19 and Qb >= 32))
-    if Kf in (3, 4) and N >= 64 * 65536:
+    if Kf in (3, 4) and (N >= 64 * 65536 or (bits and Qb >= 32 and float(N) ** 3 * Qb >= 1.8e20)):
         return "pairs", bits
     return "items", bits
 
@@ -704,6 +704,8 @@ def stage1_kernel_name(Kf, K, N, Qb, topk, mode_streamed=False):
         return "group_keys_kernel<%d,%d,%s>" % (Kf, index_words(K), "true" if topk <= 256 and K <= 16 else "false")
     if Kf > 4:
         return "scan_items_kernel"
+    if bits and form == "pairs" and Qb > 8:
+        return "scan_pairs_q8_kernel<%d>" % (Kf - 2)
     if bits and Qb >= 6:
         return "scan_pairs_q16_kernel<%d,%s>" % ((Kf - 2, "true") if form == "pairs" else (Kf, "false"))
     B = 4 if Qb >= 3 else Qb
@@ -711,14 +713,23 @@ def stage1_kernel_name(Kf, K, N, Qb, topk, mode_streamed=False):
                                                        "true" if form == "pairs" else "false", "true" if bits else "false")
 
 
-def stage1_model(Kf, npos, Qb, pairs, q16=False):
+def prefilter_bits(kernel):
+    """8 or 16 for the integer pre-filters of stage 1, 0 for the fp32 kernels."""
+    return 8 if kernel.startswith("scan_pairs_q8") else 16 if kernel.startswith("scan_pairs_q16") else 0
+
+
+def stage1_model(Kf, npos, Qb, pairs, prefilter=0):
     """Work of ONE launch of the item-by-item stage-1 kernel over npos scan positions for Qb
     queries.  fp32 form, four queries per pass -- per (query, position): one table read per
     streamed row, the additions of Eq. 2 left of the threshold, one comparison, one instruction
     that collects the hit bit; per position and pass: one byte extraction and one address per
     streamed row (shared by the pass's four queries).  pairs: the first two entries' sum comes once
     per 16 positions (not counted) and is one more addition per (query, position).
-    q16 (the 16-bit pre-filter, eight queries per pass): a 32-bit instruction serves two queries,
+    prefilter 8 (sixteen queries per pass): a 32-bit instruction serves four queries; per position and pass one
+    address per streamed row, per FOUR queries one three-operand addition and (but for the first of eight
+    positions) a shift and a bit-field insert; per 16 positions and pass about 80 more (the pair's part of
+    the sum in 16 bits, masks, the swap between neighbouring lanes, stores).
+    prefilter 16 (eight queries per pass): a 32-bit instruction serves two queries,
     so per position and pass there are one address per streamed row, and per PAIR of queries the
     additions (two of them fold into one three-operand instruction) and, per TWO positions, one
     byte permute, one shift and one bit-field insert that collect the four miss bits; per 16
@@ -726,7 +737,15 @@ def stage1_model(Kf, npos, Qb, pairs, q16=False):
     queries sit a step out, masks, stores).
     alu_ops counts lanes of wavefront instructions either way."""
     R = Kf - 2 if pairs else Kf
-    if q16:
+    if prefilter == 8:
+        passes = (Qb + 15) // 16
+        return {"positions": npos, "queries": Qb, "passes": passes, "streamed_rows": R,
+                "alu_ops": npos * passes * R + npos // 16 * passes * (4 * (16 + 2 * 14) + 80),
+                "lds_addresses": npos * passes * R,
+                "table_entries": npos * Qb * R,
+                "code_bytes": npos * passes * R + npos * passes // 4,
+                "hit_bit_bytes": npos * Qb // 8}
+    if prefilter == 16:
         passes = (Qb + 7) // 8
         addr = R if R <= 2 else 2 * R          # one byte permute per address with 16 table copies, extract + shift-add with 8
         # per query pair and TWO positions: the additions of both (two per instruction), permute, shift, insert
@@ -907,16 +926,16 @@ def main():
     else:
         # Item-by-item stage 1: bound by the vector ALUs (every (query, position) pair costs a few
         # plain vector instructions whatever the memory system does; SQ counters in profiles/).
-        q16 = kern1.startswith("scan_pairs_q16")
-        m = stage1_model(Kf, npos, int(round(qmean)), form == "pairs", q16)
+        pre = prefilter_bits(kern1)
+        m = stage1_model(Kf, npos, int(round(qmean)), form == "pairs", pre)
         t = stage[1] * 1e-3
         ach = m["alu_ops"] / t / 1e12
-        tr = pmc_traffic("scan_pairs_q16_kernel" if q16 else kern1.split("<")[0] + ("_pairs" if form == "pairs" else "_items"), wl)
+        tr = pmc_traffic(kern1.split("<")[0] if pre else kern1.split("<")[0] + ("_pairs" if form == "pairs" else "_items"), wl)
         roofline = {"bound": "alu", "kernel": kern1, "achieved": round(ach, 3), "peak": round(ALU_PEAK_TOPS, 2),
                     "unit": "Tops/s", "frac": round(ach / ALU_PEAK_TOPS, 4), "ms": round(stage[1], 4),
                     "work_model": m,
                     # Eq. 2 as written: Kf - 1 additions and one comparison per (query, item).  The kernel needs fewer
-                    # instructions than that (two queries per 32-bit instruction, the first two terms once per run of
+                    # instructions than that (four queries per 32-bit instruction, the first two terms once per run of
                     # items), so this rate can exceed the vector peak; it does not depend on how the kernel is written.
                     "eq2": {"ops_per_launch": int(N) * int(round(qmean)) * Kf,
                             "Tops_per_s": round(N * qmean * Kf / t / 1e12, 2),
@@ -931,8 +950,8 @@ def main():
                     "note": "one launch per icq_search call; duration = the stage-1 event pair inside the one-stream calls "
                             "(counter fill .. after the scan kernel).  achieved = lanes of the vector instructions of the "
                             "work model (alu_ops; see stage1_model in bench.py: additions, comparison, hit-bit "
-                            "collection, table addresses -- a 32-bit instruction serves two queries' 16-bit sums in the "
-                            "16-bit pre-filter) per second; peak = 256 CU x 4 SIMD x 16 lanes x 2.4 GHz.  lds / hbm: the same launch against the other two resources "
+                            "collection, table addresses -- a 32-bit instruction serves four queries' 8-bit sums, or two "
+                            "16-bit ones, in the pre-filters) per second; peak = 256 CU x 4 SIMD x 16 lanes x 2.4 GHz.  lds / hbm: the same launch against the other two resources "
                             "(LDS: lane addresses against the 7.72e12 per second measured for 16-byte reads; HBM: code "
                             "rows per pass plus the hit bits written -- all passes but the first are served by the caches, "
                             "see traffic).  The vector peak is the rate of three-operand and compare instructions; "
@@ -950,8 +969,9 @@ def main():
                    "survivors_mean": round(float(surv_np.mean()), 1),
                    "stage1": {"tuples": "one evaluation per fast-code tuple, distances and lists in the same kernel",
                               "pairs": "items ordered by their first two fast sub-codes, remaining fast rows streamed"
-                                       + (" through a conservative 16-bit pre-filter, eight queries per pass; stage 2 "
-                                          "applies the exact comparison" if kern1.startswith("scan_pairs_q16") else ""),
+                                       + (" through a conservative %d-bit pre-filter, %d queries per pass; stage 2 "
+                                          "applies the exact comparison" % (prefilter_bits(kern1), 128 // prefilter_bits(kern1))
+                                          if prefilter_bits(kern1) else ""),
                               "items": "all fast rows streamed item by item"}[form],
                    "stage1_to_stage2": "hit bits" if bits else ("on chip" if form == "tuples" else "candidate lists")},
         "ms_per_step_one_stream": round(ms_one_stream, 4),
@@ -968,10 +988,10 @@ def main():
         rec = index_words(K) * 4
         alg2 = n_surv_batch * rec + (npos * qmean / 8 if bits else 4 * n_surv_batch) + 4.0 * qmean * K * 256 + 8.0 * qmean * topk
         ach2 = alg2 / (stage[2] * 1e-3) / 1e9
-        k2 = "refine_mask_kernel<%d,true>" % index_words(K) if bits else "refine_dist_kernel<%d>" % index_words(K)
+        k2 = ("refine_%s_kernel<%d>" % ("bounded" if form == "pairs" or N >= 130 * 32768 else "mask", index_words(K))) if bits else "refine_dist_kernel<%d>" % index_words(K)
         tr2 = pmc_traffic(k2.split("<")[0], wl)
         result["roofline_stage2"] = {
-            "bound": "hbm", "kernel": k2 + " (+ its unfiltered first part and two selections)" if bits else k2 + " + select_kernel",
+            "bound": "hbm", "kernel": k2 + " (+ the bound before it and the selection)" if bits else k2 + " + select_kernel",
             "achieved": round(ach2, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach2 / HBM_PEAK_GBS, 4),
             "algorithmic_bytes": alg2, "traffic": tr2["bytes"] if tr2 else None, "traffic_source": tr2["source"] if tr2 else None,
             "ms": round(stage[2], 4), "survivors_per_call": n_surv_batch,
@@ -999,7 +1019,7 @@ def main():
         b.icq_index_set_scan_mode(index, b.ICQ_SCAN_AUTO)
         if Kf <= 4:
             kern_s = stage1_kernel_name(Kf, K, N, batch, topk, True)
-            m = stage1_model(Kf, N, int(round(qmean)), False, kern_s.startswith("scan_pairs_q16"))
+            m = stage1_model(Kf, N, int(round(qmean)), False, prefilter_bits(kern_s))
             t = stage_s[1] * 1e-3
             ach = m["alu_ops"] / t / 1e12
             result["roofline_streamed"] = {

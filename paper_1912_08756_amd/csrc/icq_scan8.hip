@@ -16,8 +16,8 @@
 // 1 % survivors the bits mark 8 % more items than survive (16-bit: 0.8 %), which costs stage 2 less than a tenth of what
 // stage 1 gains.  A query near the items has entries far below the others in every table (its own codewords); in the first
 // two tables they only saturate p.
-// What bounds it (10^8 items, 128 queries, 16-bit / 8-bit: 780 / 600 us): vector issue and the LDS at three quarters of their
-// rates each beside 1.6 GB of hit bits written (without the stores: 468 us; stores of two bytes, of four after a swap between
+// What bounds it (10^8 items, 128 queries, 16-bit / 8-bit: 780 / 600 us): vector issue at three quarters of its rate
+// (331 instructions per 1024 positions and pass) beside 1.6 GB of hit bits written (without the stores: 468 us; stores of two bytes, of four after a swap between
 // neighbouring lanes, ordinary or non-temporal ones, rows of other lengths: the same time).
 #include "icq_internal.h"
 #include "icq_sort.h"
