@@ -208,8 +208,10 @@ int icq_refine(const icq_index *index, const float *lut, int Q, const uint32_t *
  * the grouped stage 1 of Kf <= 2 with records of at most 16 bytes and
  * topk <= 256, where the candidates never leave the chip; and, from 2^22 items
  * on with K <= 16 and topk <= 512, the item-by-item stage 1, which hands stage 2
- * one hit bit per item and query and keeps only the keys that can still reach
- * the result.)  Calls with more than 32768 queries are worked off in slices.
+ * one hit bit per item and query and keeps only the keys within a bound on the
+ * result: from samples of the survivors it sees to it that about cap / 4 of them
+ * are, cap >= 128 * topk and cap >= survivors / 64 provided -- as far as samples
+ * tell, so where survivors come in few dense runs leave it more room.)  Calls with more than 32768 queries are worked off in slices.
  */
 int icq_search(const icq_index *index, const float *queries, int Q, const float *thresholds,
                int64_t cap, int topk, uint32_t *out_ids, float *out_dist, uint32_t *out_survivors,

@@ -160,8 +160,11 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                             int64_t scan_end, bool pairs, int64_t cap, int topk, int splits, unsigned long long *keys,
                             uint32_t *key_count, uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset,
                             const float *bound_dist, uint32_t *out_ids, float *out_dist, hipStream_t s);
-// A bound on the topk-th smallest distance from the items of the nearest runs, into out_dist[q][topk - 1] (icq_bound.hip).
-int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const float *thr, int topk, float *out_dist, hipStream_t s);
+// A bound on the topk-th smallest distance into out_dist[q][topk - 1], +inf for none (icq_bound.hip): given[q][topk - 1] (given may
+// be nullptr) or what the nearest runs say, tightened where more than about `cap` of the survivors that `masks` marks reach it.
+int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const float *thr, int topk, const uint16_t *masks,
+                          size_t mask_stride, int64_t scan_end, bool pairs, int64_t cap, const float *given, float *out_dist,
+                          hipStream_t s);
 
 // p[0..n) = 0, by a kernel (the call can sit inside a captured graph).
 void icq_zero_words(uint32_t *p, int n, hipStream_t s);

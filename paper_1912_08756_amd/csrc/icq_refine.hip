@@ -848,8 +848,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // 43 / 47; 1e6, 1000 queries (id order) 330 / 333; 4.3e6, 1 / 3 / 8 queries 44 / 39, 56 / 43, 76 / 52; 1e7, 16 queries, 30 % 765 / 146;
     // 2e7, 64 queries 340 / 198; 1e8, 1 / 128 queries 161 / 104, 1797 / 1536; K = 12, Kf = 3, 1e7, 100 queries, 10 % 873 / 305;
     // K = 8, Kf = 2, 1e7, 1 query 49 / 35, 1.3e7, 4 queries 83 / 47.
-    if (!bound_dist && (pairs || chunks >= 130)) {
-        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, out_dist, s);
+    if (pairs || chunks >= 130) {
+        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, masks, mask_stride, scan_end, pairs, cap, bound_dist, out_dist, s);
         if (rc != ICQ_OK) return rc;
         bound_dist = out_dist;
     }

@@ -1147,6 +1147,51 @@ def test_search_bounded_before_stage_2_equals_the_staged_calls(gpu, K, Kf, topk,
         del index, ws, cand
 
 
+@pytest.mark.parametrize("K,Kf,topk,codes,mode,share,cap", [
+    (16, 4, 100, "late", 0, 0.01, 8192), (16, 4, 512, "far", 0, 0.05, 40960), (16, 4, 100, "far", 1, 0.01, 8192), (12, 3, 100, "far", 0, 0.1, 12288),
+    (16, 3, 10, "late", 0, 0.005, 2048), (8, 4, 100, "late", 1, 0.01, 8192), (8, 2, 100, "far", 0, 0.01, 8192), (4, 2, 50, "far", 0, 0.02, 8192),
+    (6, 1, 100, "flat", 0, 0.3, 40960), (16, 2, 100, "flat", 0, 0.01, 8192)])
+def test_search_from_hit_bits_is_complete_where_cap_is_below_the_survivors(gpu, K, Kf, topk, codes, mode, share, cap):
+    """The bound before stage 2 keeps what is written within `cap` keys a query also where the nearest runs say nothing of the neighbours:
+    first codebooks that tell little ("late": the first two a third of the next two; "flat": all of one size) and runs that are
+    empty or do not survive ("far").  `cap` holds fewer keys than there are survivors, and than reach the bound of the nearest runs (late, far), but more than
+    128 topk, or a 64th of the survivors where that is more: the lists are those of the staged calls with room for all, bit for bit."""
+    torch, b = gpu
+    N, d, m, Q = 4_300_001, 24, 256, 12 if Kf > 2 else 3
+    scale = [1.0] * K if codes == "flat" else [0.8 ** k for k in range(K)] if codes == "far" else [0.3, 0.3] + [1.0] * 2 + [0.5] * (K - 4)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1000 * K + 10 * Kf + mode)
+    cb = torch.randn((K, m, d), device="cuda", generator=gen) * torch.tensor(scale, device="cuda")[:, None, None]
+    c = torch.randint(0, m, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    if codes == "far":                                            # no item has a codeword near a query's first ones
+        cb[:min(2, Kf), :128] *= 0.1
+        c[:min(2, Kf)] |= 128
+    index = b.icq_index_create(cb.contiguous(), c, Kf)
+    b.icq_index_set_scan_mode(index, mode)
+    queries = 0.3 * torch.randn((Q, d), device="cuda", generator=gen)
+    if codes != "far":
+        queries += sum(cb[k][c[k, :Q].long()] for k in range(K))
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = sum(lut[:, k].index_select(1, c[k, :100_000].long()) for k in range(Kf))
+    thr = P.kthvalue(int(share * 100_000), dim=1).values.contiguous()
+
+    def out():
+        return torch.empty((Q, topk), dtype=torch.int32, device="cuda"), torch.empty((Q, topk), device="cuda"), torch.empty((Q,), dtype=torch.int32, device="cuda")
+    ids, dist, count = out()
+    ws = torch.empty(b.icq_workspace_bytes(index, Q, cap, topk), dtype=torch.uint8, device="cuda")
+    b.icq_search(index, queries, thr, cap, topk, ids, dist, count, ws)
+    want_ids, want_dist, want_count = out()
+    cand = torch.empty((Q, N), dtype=torch.int32, device="cuda")
+    ws = torch.empty(b.icq_workspace_bytes(index, Q, N, topk), dtype=torch.uint8, device="cuda")
+    b.icq_scan_fast(index, lut, thr, cand, None, want_count, ws)
+    b.icq_refine(index, lut, cand, None, want_count, topk, want_ids, want_dist, ws)
+    torch.cuda.synchronize()
+    assert int(count.min()) > cap
+    assert torch.equal(count, want_count)
+    assert torch.equal(dist, want_dist) and torch.equal(ids, want_ids)
+
+
 @pytest.mark.parametrize("K,Kf,N,Q,topk", [(16, 4, 1_000_003, 190, 100), (12, 3, 2_000_001, 40, 300), (8, 4, 600_011, 900, 10)])
 def test_search_of_many_queries_over_the_pair_ordering_equals_id_order(gpu, K, Kf, N, Q, topk):
     """Many queries over an index of half a million to four million items walk the pair ordering, the stage-2 bound first: the
