@@ -12,9 +12,12 @@
 // 128 + 2 * 63 and 128 + 127 fit a byte.  So four queries' sums share a 32-bit word and ONE plain addition adds them with no
 // carry between them, a 16-byte LDS read brings sixteen queries' entries, and bit 7 of a byte is clear exactly when the item
 // passes; it is collected by a shift and a bit-field insert.  The unit is what lets the largest entry of the streamed tables
-// reach CAP, or a hundredth of the threshold's distance from the tables' minimum if that is finer: at 10^8 items, Kf = 4,
-// 1 % survivors the bits mark 8 % more items than survive (16-bit: 0.8 %), which costs stage 2 less than a tenth of what
-// stage 1 gains.  A query near the items has entries far below the others in every table (its own codewords); in the first
+// reach CAP, or if that is finer a hundredth of the threshold's distance from the tables' minimum (an eightieth with two streamed tables:
+// an entry that stops at CAP is then four fifths of that distance.  With a hundredth it is 0.63, and where the streamed
+// codebooks are the larger ones, the first two 0.3 of them, 1.2 to 2.7 times as many items pass as survive, with an eightieth 1.12 to
+// 1.21, at shares of 10 to 0.1 %; 1e8 items, 128 queries, whole calls 4910 / 4330 us.  Codebooks that shrink or are of one size: within 0.02).
+// At 10^8 items, Kf = 4, 1 % survivors, codebooks shrinking by 0.8 the bits mark 8 % more items than survive (16-bit: 0.8 %),
+// which costs stage 2 less than a tenth of what stage 1 gains.  A query near the items has entries far below the others in every table (its own codewords); in the first
 // two tables they only saturate p.
 // What bounds it (10^8 items, 128 queries, 16-bit / 8-bit: 780 / 600 us): vector issue at three quarters of its rate
 // (331 instructions per 1024 positions and pass) beside 1.6 GB of hit bits written (without the stores: 468 us; stores of two bytes, of four after a swap between
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(Q8_THREADS) void scan_pairs_q8_kernel(
             sub = 0xFFFFu;
         } else if (t > L) {
             const float gap = t - L;
-            float s = fminf(range / (float)CAP, gap / 100.0f);
+            float s = fminf(range / (float)CAP, gap * (KF == 2 ? 1.0f / 80.0f : 1.0f / 100.0f));
             s = fmaxf(fmaxf(s, gap / 255.0f), fmaxf(fabsf(t) * 1.52587890625e-5f, 1e-30f));
             if (s < INFINITY) {
                 inv = 1.0f / s;
