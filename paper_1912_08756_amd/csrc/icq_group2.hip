@@ -6,13 +6,23 @@
 //
 // Layout (built once by a counting sort): the 65536 pairs in the scattered order of
 // icq_g2_pair_of_slot, every pair's run padded to whole 16 positions; per position the item id (perm),
-// the item's record (items_grouped; 16-byte records as two planes, the halves of all positions behind each other) and its remaining fast sub-codes as rows of their own (g2_rows);
+// the item's record (items_grouped; 16-byte records as two planes, the halves of all positions behind each other, g2_halves, and
+// whole besides where many queries read both, g2_split) and its remaining fast sub-codes as rows of their own (g2_rows);
 // per 16 positions the pair and the number of real items (g2_info).
 #include "icq_internal.h"
 
 namespace {
 
 constexpr int G2_PAIRS = 65536;
+
+// Where the codebooks of a record's second half are small beside the first half's, stage 2 drops nearly every survivor after
+// the first half; else most queries gather whole records, the index keeps those too, and a search has a launch for those queries and one
+// for the others (see refine_bounded_kernel).  A launch that finds nothing to do is 5 us, 12 at 10^8 items and 128 queries, and one that
+// is left a few of the queries costs their chain, so the line is drawn by the index: by the share of the largest norms, for
+// sixteen codebooks shrinking by 0.8 / 0.86 / 0.9 / of one size 0.14 / 0.23 / 0.30 / 0.5.  Whole calls, us, first halves only / both:
+// by 0.86: 1e8 items, 128 queries 2370 / 2240, 2e7, 64 queries 336 / 305, 1e6, 1000 queries 335 / 255, 1e8, one 129 / 129; by 0.83 (0.18)
+// both launches gain nothing; K = 12 by 0.9 (0.206): 1e7, 100 queries 631 / 643, 4.3e6, three 55 / 45; fast 1, slow 0.3 (0.21): 412 / 417, 49 / 58.
+constexpr float G2_TAIL = 0.215f;
 
 __device__ __forceinline__ uint32_t slot_of_item(const uint8_t *__restrict__ fast, int64_t Npad, int64_t i) {
     return icq_g2_slot_of_pair((uint32_t)fast[i] | ((uint32_t)fast[Npad + i] << 8));
@@ -53,21 +63,22 @@ __global__ __launch_bounds__(1024) void g2_offsets_kernel(uint32_t *__restrict__
 
 __global__ void g2_scatter_kernel(const uint8_t *__restrict__ fast, int64_t Npad, int Kf, int64_t N,
                                   uint32_t *__restrict__ cursor, const uint8_t *__restrict__ items, int stride,
-                                  uint32_t *__restrict__ perm, uint8_t *__restrict__ items_grouped, bool planes,
-                                  uint8_t *__restrict__ rows, int64_t g2_npad) {
+                                  uint32_t *__restrict__ perm, uint8_t *__restrict__ items_grouped,
+                                  uint2 *__restrict__ halves, uint8_t *__restrict__ rows, int64_t g2_npad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
     const uint32_t pos = atomicAdd(&cursor[slot_of_item(fast, Npad, i)], 1u);
     perm[pos] = (uint32_t)i;
     for (int r = 0; r < Kf - 2; ++r) rows[(int64_t)r * g2_npad + pos] = fast[(int64_t)(r + 2) * Npad + i];
-    if (planes) {                            // 16-byte records: first and second halves apart
-        const uint4 v = *reinterpret_cast<const uint4 *>(items + (size_t)i * 16);
-        reinterpret_cast<uint2 *>(items_grouped)[pos] = make_uint2(v.x, v.y);
-        reinterpret_cast<uint2 *>(items_grouped)[g2_npad + pos] = make_uint2(v.z, v.w);
-        return;
-    }
     const int W = stride / 4;
     const uint32_t *src = reinterpret_cast<const uint32_t *>(items + (size_t)i * stride);
+    if (halves) {                            // stride == 16
+        const uint4 v = *reinterpret_cast<const uint4 *>(src);
+        halves[pos] = make_uint2(v.x, v.y);
+        halves[g2_npad + pos] = make_uint2(v.z, v.w);
+        if (items_grouped) reinterpret_cast<uint4 *>(items_grouped)[pos] = v;
+        return;
+    }
     uint32_t *dst = reinterpret_cast<uint32_t *>(items_grouped + (size_t)pos * stride);
     for (int w = 0; w < W; ++w) dst[w] = src[w];
 }
@@ -92,11 +103,11 @@ __global__ void g2_fill_kernel(uint32_t *__restrict__ p, size_t n, uint32_t v) {
     if (i < n) p[i] = v;
 }
 
-// codes_out[k][perm[pos]] from the grouped layout alone: rows 0, 1 from the pair of the position's
+// (halves: the records' two planes where there are no whole ones) codes_out[k][perm[pos]] from the grouped layout alone: rows 0, 1 from the pair of the position's
 // group of 16, rows 2 .. Kf-1 from the streamed rows, the rest from the grouped item records.
 __global__ void g2_export_kernel(const uint32_t *__restrict__ info, const uint8_t *__restrict__ rows, int64_t g2_npad,
-                                 const uint8_t *__restrict__ items_grouped, const uint32_t *__restrict__ perm,
-                                 int64_t npos, int64_t N, int Kf, int stride, uint8_t *__restrict__ out) {
+                                 const uint8_t *__restrict__ items_grouped, const uint8_t *__restrict__ halves,
+                                 const uint32_t *__restrict__ perm, int64_t npos, int64_t N, int Kf, int stride, uint8_t *__restrict__ out) {
     const int k = blockIdx.y;
     const int64_t pos = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (pos >= npos) return;
@@ -105,7 +116,7 @@ __global__ void g2_export_kernel(const uint32_t *__restrict__ info, const uint8_
     uint8_t v;
     if (k < 2) v = (uint8_t)(info[pos >> 4] >> (8 * k));
     else if (k < Kf) v = rows[(int64_t)(k - 2) * g2_npad + pos];
-    else if (stride == 16) v = items_grouped[((k >> 3) * g2_npad + pos) * 8 + (k & 7)];
+    else if (!items_grouped) v = halves[((k >> 3) * g2_npad + pos) * 8 + (k & 7)];
     else v = items_grouped[pos * stride + k];
     out[(int64_t)k * N + id] = v;
 }
@@ -127,11 +138,23 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     g2_count_kernel<<<nb, T, 0, s>>>(ix->fast, ix->Npad, ix->N, ix->group_cursor);
     g2_offsets_kernel<<<1, 1024, 0, s>>>(ix->group_cursor, ix->group_start);
     uint32_t total = 0;
+    const bool halves = ix->item_stride == 16;                 // 9 to 16 codebooks
+    float4 meta[16];
+    ix->g2_split = false;
     if (icq_check_launch() != ICQ_OK ||
         hipMemcpyAsync(&total, ix->group_start + G2_PAIRS, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        (halves && hipMemcpyAsync(meta, ix->enc_meta, sizeof(float4) * (size_t)ix->K, hipMemcpyDeviceToHost, s) != hipSuccess) ||
         hipStreamSynchronize(s) != hipSuccess) {
         (void)hipGetLastError();
         return ICQ_ERR_HIP;
+    }
+    if (halves) {
+        float all = 0.0f, tail = 0.0f;
+        for (int k = 0; k < ix->K; ++k) {
+            all += meta[k].y;
+            if (k >= 8) tail += meta[k].y;
+        }
+        ix->g2_split = !(tail < G2_TAIL * all);
     }
     // whole block steps of the scan kernel, plus a spare step: its read-ahead never checks bounds
     ix->g2_npos = ((int64_t)total + 16383) / 16384 * 16384;
@@ -140,7 +163,8 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     ok = hipMalloc(&ix->g2_rows, (size_t)(ix->Kf - 2) * np) == hipSuccess &&
          hipMalloc(&ix->g2_info, sizeof(uint32_t) * (np / 16)) == hipSuccess &&
          hipMalloc(&ix->perm, sizeof(uint32_t) * np) == hipSuccess &&
-         hipMalloc(&ix->items_grouped, np * ix->item_stride) == hipSuccess;
+         (halves && !ix->g2_split ? true : hipMalloc(&ix->items_grouped, np * ix->item_stride) == hipSuccess) &&
+         (!halves || hipMalloc(&ix->g2_halves, np * 2 * sizeof(uint2)) == hipSuccess);
     if (!ok) {
         (void)hipGetLastError();
         return ICQ_ERR_HIP;
@@ -152,9 +176,10 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     fill(ix->g2_rows, (size_t)(ix->Kf - 2) * np, 0u);
     fill(ix->g2_info, sizeof(uint32_t) * (np / 16), 0u);
     fill(ix->perm, sizeof(uint32_t) * np, ICQ_PAD_ID);
-    fill(ix->items_grouped, np * ix->item_stride, 0u);
+    if (ix->items_grouped) fill(ix->items_grouped, np * ix->item_stride, 0u);
+    if (halves) fill(ix->g2_halves, np * 2 * sizeof(uint2), 0u);
     g2_scatter_kernel<<<nb, T, 0, s>>>(ix->fast, ix->Npad, ix->Kf, ix->N, ix->group_cursor, ix->items, ix->item_stride,
-                                       ix->perm, ix->items_grouped, ix->item_stride == 16, ix->g2_rows, ix->g2_npad);
+                                       ix->perm, ix->items_grouped, ix->g2_halves, ix->g2_rows, ix->g2_npad);
     g2_info_kernel<<<G2_PAIRS / T, T, 0, s>>>(ix->group_start, ix->group_cursor, ix->g2_info);
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     ix->g2 = 1;
@@ -164,7 +189,8 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
 int icq_group2_export(const icq_index *ix, uint8_t *codes_out, hipStream_t s) {
     const int T = 256;
     dim3 g((unsigned)((ix->g2_npos + T - 1) / T), (unsigned)ix->K);
-    g2_export_kernel<<<g, T, 0, s>>>(ix->g2_info, ix->g2_rows, ix->g2_npad, ix->items_grouped, ix->perm, ix->g2_npos,
+    g2_export_kernel<<<g, T, 0, s>>>(ix->g2_info, ix->g2_rows, ix->g2_npad, ix->items_grouped,
+                                     reinterpret_cast<const uint8_t *>(ix->g2_halves), ix->perm, ix->g2_npos,
                                      ix->N, ix->Kf, ix->item_stride, codes_out);
     return icq_check_launch();
 }

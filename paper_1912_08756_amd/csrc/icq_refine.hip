@@ -478,12 +478,17 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 
 // ---- the same with a bound on the result at hand
 // Where a finite upper bound of the topk-th distance is known before stage 2 (icq_bound.hip, or the list of the tiles
-// before), nearly every survivor can be dropped before its last table entries are read: with K > 8 the sum of the first
-// eight terms and the smallest the other tables can add is beyond the bound for all but a few per cent (10^8 items, K = 16,
-// codebooks shrinking by 0.8, 1 % survivors: 1.3 %).  So the first half of a 16-byte record is gathered for every survivor
-// -- over the pair ordering the halves lie in planes of their own, and a window of chunks is half as many bytes for the
-// XCD's cache -- and the second half only for what is left, collected 64 at a time.  K <= 8: the whole distance is known
-// at once, the same queue collects what reaches the bound.
+// before), a survivor can be dropped as soon as its sum and the smallest that the tables left can add are beyond it.  With K > 8 and
+// codebooks that shrink, the first eight terms do that for nearly all (10^8 items, K = 16, 1 % survivors, shrinking by 0.8: all
+// but 1.3 %).  So the first half of a 16-byte record is gathered for every survivor -- over the pair ordering the halves lie
+// in planes of their own, and a window of chunks is half as many bytes for the XCD's cache -- and the second half only for
+// what is left, collected 64 at a time.  Where the second half's codebooks are as large as the others that is
+// next to everything (by 0.9: 93 %, of one size: all), and a half record more, its tables read from memory, costs twice what the whole
+// record would: those queries (icq_bound.hip says which, by a sample of their survivors) gather whole records, with all tables in
+// the LDS.  1e8 items, 128 queries, codebooks shrinking by 0.9 / of one size / fast 1, slow 0.3 each, us: halves only 3310 / 5000 / 3660,
+// with whole records 1850 / 1900 / 1800; 2e7, 64 queries 552 / 1121 / 559 -> 242 / 293 / 248; 1e6, 1000 queries 346 / 372 / 352 -> 231 / 253 / 238.
+// Records of 16 bytes in id order come in one line, and whole (2e7, 64 queries, shrinking by 0.8 / of one size, with the second half waiting in the
+// queue 331 / 1182, whole 322 / 373; 1e7, four, Kf = 2 50.5 / 105, 49.7 / 56).  K <= 8: the whole distance is known at once.
 // A wavefront's positions go through a stack in LDS that outlives the chunk, so that the gathers always come 256 or 512 at a time.
 // A word's lowest hit bit goes there straight; what is left of words with several (one in seven at 1 %) is collected 64
 // words at a time first: with a loop over every word's bits the expansion was more than half of all vector instructions.
@@ -497,26 +502,23 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 constexpr int RB_MORE = 128;                          // words with hit bits left
 constexpr int RB_QUEUE = 128;                         // survivors to be finished
 
-// A survivor in the queue: position, bits of the sum so far, and the record's second half where it came with the first.
-template <bool WHOLE> struct RbRestT { uint32_t pos, sum; };
-template <> struct RbRestT<true> { uint32_t pos, sum, tail0, tail1; };
+struct RbRest { uint32_t pos, sum; };                 // a survivor in the queue: position, bits of the sum so far
 
-// WORDS == 4: PLANES: first and second halves of the records at `items` and `tail`, 8 bytes per position; else (an index in
-// id order) records of 16 bytes, whose second half comes with the line of the first and waits in the queue.
-template <int WORDS, bool PLANES, bool EXACT, int PER>
+// WHOLE: records are gathered whole; else (16 bytes over the pair ordering) the halves lie in planes of their own, `items`
+// and `tail`.  whole_of (may be nullptr: all queries): two launches share the queries, WHOLE takes those with whole_of[q][topk - 1] != 0
+// (one kernel with both loops holds the tables and registers of the larger one for all: 51 -> 57 us at 2e6 items, 200 queries).
+template <int WORDS, bool WHOLE, bool EXACT, int PER>
 __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
     const uint8_t *__restrict__ items, const uint8_t *__restrict__ tail, int K, const float *__restrict__ lut,
     const uint32_t *__restrict__ masks, size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, int window,
-    int xs_shift, int Q, const float *__restrict__ bound_dist, int topk, u64 *__restrict__ keys,
+    int xs_shift, int Q, const float *__restrict__ bound_dist, const uint32_t *__restrict__ whole_of, int topk, u64 *__restrict__ keys,
     uint32_t *__restrict__ key_count, int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
-    constexpr int HW = WORDS < 2 ? WORDS : 2;         // words of a record's first half
-    constexpr int HT = 4 * HW;                        // its tables
-    constexpr bool WHOLE = WORDS == 4 && !PLANES;     // the whole record is fetched at once
-    constexpr int FW = WHOLE ? 4 : HW;                // words fetched
-    using RbRest = RbRestT<WHOLE>;
+    constexpr bool HALF = WORDS == 4 && !WHOLE;       // a second half is left
+    constexpr int FW = HALF ? 2 : WORDS;              // words of a record that are fetched
+    constexpr int FT = 4 * FW;                        // their tables
     constexpr uint32_t BATCH = 64 * PER;              // survivors gathered together
     constexpr uint32_t LIST = BATCH + 64;             // positions a wavefront holds
-    __shared__ __attribute__((aligned(16))) float T[HT * ICQ_LUT_W];
+    __shared__ __attribute__((aligned(16))) float T[FT * ICQ_LUT_W];
     __shared__ uint32_t list_all[RM_WAVES][LIST];
     __shared__ uint2 more_all[RM_WAVES][RB_MORE];     // hit bits, first position of the word
     __shared__ RbRest queue_all[RM_WAVES][RB_QUEUE];
@@ -536,6 +538,7 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         return j >= (uint32_t)window || i >= nsel ? 0xFFFFFFFFu : i;
     };
     if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
+    if (whole_of && (whole_of[(int64_t)q * topk + topk - 1] != 0u) != WHOLE) return;
     const uint32_t *mq = masks + (size_t)q * mask_words + lane;
     uint32_t j = (uint32_t)wave, c = chunk_of(j);
     uint32_t w[RM_WORDS];
@@ -546,11 +549,11 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         const float4 *src = reinterpret_cast<const float4 *>(Tq);
         float4 *dst = reinterpret_cast<float4 *>(T);
 #pragma unroll
-        for (int u = 0; u < HT / 4; ++u) {            // tables per wavefront
+        for (int u = 0; u < FT / 4; ++u) {            // tables per wavefront
             const int i = u * RM_THREADS + tid;
             dst[i] = u * 4 + wave < K ? src[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
-        if (WORDS == 4) {
+        if (HALF) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const int k = 8 + u * 4 + wave;       // table k, whole
@@ -571,7 +574,7 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
     // ones of the tables' smallest entries would (rounding is monotone), which is (sum + those entries) (1 +- 8 * 2^-24); 1e-5
     // covers that and the roundings here.  Open bounds and tables without a number drop nothing.
     float most = INFINITY;
-    if (WORDS == 4 && !open) {
+    if (HALF && !open) {
         float s = 0.0f, a = fabsf(bound_f);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
@@ -580,9 +583,9 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         }
         most = (bound_f - s) + 1e-5f * a;
     }
-    uint32_t n = 0, nm = 0, nq = 0;                   // positions, words with bits left, survivors in the queue (wavefront-uniform)
     uint32_t lane_survivors = 0;
     u64 *kout = keys + (int64_t)q * cap;
+    uint32_t n = 0, nm = 0, nq = 0;                   // positions, words with bits left, survivors in the queue (wavefront-uniform)
     // the queue's last `cnt` (at most 64): the remaining terms, and a key for what reaches the bound
     auto finish = [&](uint32_t cnt) __attribute__((always_inline)) {
         wave_lds_order();
@@ -590,10 +593,8 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         const RbRest e = queue[nq - cnt + (in ? lane : 0u)];
         nq -= cnt;
         float d = __uint_as_float(e.sum);
-        if (WORDS == 4) {
-            uint2 r;
-            if constexpr (WHOLE) r = make_uint2(e.tail0, e.tail1);
-            else r = reinterpret_cast<const uint2 *>(tail)[e.pos];
+        if (HALF) {
+            const uint2 r = reinterpret_cast<const uint2 *>(tail)[e.pos];
             float tv[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -627,51 +628,42 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         n -= cnt;
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            const uint32_t *p = reinterpret_cast<const uint32_t *>(items + (size_t)pos[u] * (FW * 4));
             if (FW == 1) {
-                rec[u][0] = p[0];
+                rec[u][0] = reinterpret_cast<const uint32_t *>(items)[pos[u]];
             } else if (FW == 2) {
-                const uint2 v = *reinterpret_cast<const uint2 *>(p);
-                rec[u][0] = v.x;
-                rec[u][1 % FW] = v.y;
+                const uint2 x = reinterpret_cast<const uint2 *>(items)[pos[u]];
+                rec[u][0] = x.x;
+                rec[u][1 % FW] = x.y;
             } else {
-                const uint4 v = *reinterpret_cast<const uint4 *>(p);
-                rec[u][0] = v.x;
-                rec[u][1 % FW] = v.y;
-                rec[u][2 % FW] = v.z;
-                rec[u][3 % FW] = v.w;
+                const uint4 x = reinterpret_cast<const uint4 *>(items)[pos[u]];
+                rec[u][0] = x.x;
+                rec[u][1 % FW] = x.y;
+                rec[u][2 % FW] = x.z;
+                rec[u][3 % FW] = x.w;
             }
         }
 #pragma unroll
         for (int u = 0; u < PER; ++u) {
-            // all table reads of the half record first, then the sum: k ascending like every other kernel, the first term
+            // all table reads of the (half) record first, then the sum: k ascending like every other kernel, the first term
             // standing for 0 + itself (no table holds -0)
-            float tv[HT];
+            float tv[FT];
 #pragma unroll
-            for (int x = 0; x < HT; ++x) tv[x] = T[x * ICQ_LUT_W + ((rec[u][x / 4] >> (8 * (x % 4))) & 0xffu)];
+            for (int x = 0; x < FT; ++x) tv[x] = T[x * ICQ_LUT_W + ((rec[u][x / 4] >> (8 * (x % 4))) & 0xffu)];
             __builtin_amdgcn_sched_barrier(0);
             float d = tv[0], crude = d;               // crude: the sum of the first Kf terms (Kf <= 4)
 #pragma unroll
-            for (int i = 1; i < HT; ++i) {
+            for (int i = 1; i < FT; ++i) {
                 d += tv[i];
                 if (EXACT && i < 4) crude = i < Kf ? d : crude;
             }
             bool keep = (uint32_t)u * 64u + lane < cnt;
             if (EXACT) keep = keep && crude < tq;
             lane_survivors += keep ? 1u : 0u;
-            keep = keep && (WORDS == 4 ? !(d > most) : icq_order_bits(d) <= bound);
+            keep = keep && (HALF ? !(d > most) : icq_order_bits(d) <= bound);
             const uint64_t mk = __builtin_amdgcn_ballot_w64(keep);
             if (mk == 0) continue;                    // wavefront-uniform
-            if (keep) {
-                RbRest e;
-                e.pos = pos[u];
-                e.sum = __float_as_uint(d);
-                if constexpr (WHOLE) {
-                    e.tail0 = rec[u][2];
-                    e.tail1 = rec[u][3];
-                }
-                queue[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, nq))] = e;
-            }
+            if (keep)
+                queue[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, nq))] = {pos[u], __float_as_uint(d)};
             nq += (uint32_t)__builtin_popcountll(mk);
             if (nq >= 64u) finish(64u);
         }
@@ -682,7 +674,7 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         if (m != 0)
             list[__builtin_amdgcn_mbcnt_hi((uint32_t)(mk >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mk, n))] = at + (uint32_t)__builtin_ctz(m);
         n += (uint32_t)__builtin_popcountll(mk);
-        if (n > LIST - 64) batch(BATCH);
+        if (n > BATCH) batch(BATCH);
         return m & (m - 1);
     };
     // the last `cnt` words (at most 64) with bits left
@@ -837,9 +829,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                             uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset, const float *bound_dist,
                             uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
-    const bool planes = pairs && ix->item_stride == 16;
+    const bool halves = pairs && ix->item_stride == 16;
     const uint8_t *items = pairs ? ix->items_grouped : ix->items;
-    const uint8_t *tail = planes ? items + (size_t)ix->g2_npad * 8 : nullptr;
     const uint32_t *perm = pairs ? ix->perm : nullptr;
     const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
     const uint64_t visits = (uint64_t)chunks * (uint64_t)Q;
@@ -849,7 +840,8 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // 2e7, 64 queries 340 / 198; 1e8, 1 / 128 queries 161 / 104, 1797 / 1536; K = 12, Kf = 3, 1e7, 100 queries, 10 % 873 / 305;
     // K = 8, Kf = 2, 1e7, 1 query 49 / 35, 1.3e7, 4 queries 83 / 47.
     if (pairs || chunks >= 130) {
-        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, masks, mask_stride, scan_end, pairs, cap, bound_dist, out_dist, s);
+        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, masks, mask_stride, scan_end, pairs, cap, bound_dist,
+                                             halves && ix->g2_split ? out_ids : nullptr, out_dist, s);
         if (rc != ICQ_OK) return rc;
         bound_dist = out_dist;
     }
@@ -863,49 +855,68 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // (with thousands of queries a window's blocks no longer run at the same time, and the 8-way cut that
     // keeps a chunk's records in ONE L2 is worth more than the longer windows: 1e4 queries, 1e6 items,
     // 8-byte records: 0.80 ms with it, 0.83 without)
-    int window = visits <= 16384u ? 4 : 16, xs_shift = 3;
-    if (bound_dist) {
-        window = visits < 5000u ? 4 : visits < 40000u || !pairs ? 8 : 12;
-        // Few windows: four ways where the last of eight would leave a sixth of the wavefronts without a chunk (2e6 items, 200
-        // queries, windows of 8 cut 8 / 4 / 1 ways 117 / 105 / 116 us; 1e6, 1000 queries, of 12, 4 / 1 ways 265 / 278)
-        const uint32_t places = (chunks + ((uint32_t)window << 3) - 1) / ((uint32_t)window << 3) * ((uint32_t)window << 3);
-        if (places * 5u > chunks * 6u) xs_shift = 2;
-        while (xs_shift > 0 && ((uint32_t)window << (xs_shift - 1)) >= chunks) --xs_shift;
-    } else {
-        while (Q <= 2048 && xs_shift > 0 && ((uint32_t)window << xs_shift) > chunks) --xs_shift;
-    }
-    const int most = (int)((chunks + (1u << xs_shift) - 1) >> xs_shift);
-    if (window > most) window = most > 0 ? most : 1;
-    const unsigned per_win = (unsigned)window << xs_shift;
-    const unsigned grid = ((chunks + per_win - 1) / per_win * (unsigned)Q) << xs_shift;
+    struct plan { int window, xs_shift; unsigned grid; };
+    auto plan_for = [&](int window) -> plan {
+        int xs_shift = 3;
+        if (bound_dist) {
+            // Few windows: four ways where the last of eight would leave a sixth of the wavefronts without a chunk (2e6 items, 200
+            // queries, windows of 8 cut 8 / 4 / 1 ways 117 / 105 / 116 us; 1e6, 1000 queries, of 12, 4 / 1 ways 265 / 278)
+            const uint32_t places = (chunks + ((uint32_t)window << 3) - 1) / ((uint32_t)window << 3) * ((uint32_t)window << 3);
+            if (places * 5u > chunks * 6u) xs_shift = 2;
+            while (xs_shift > 0 && ((uint32_t)window << (xs_shift - 1)) >= chunks) --xs_shift;
+        } else {
+            while (Q <= 2048 && xs_shift > 0 && ((uint32_t)window << xs_shift) > chunks) --xs_shift;
+        }
+        const int most = (int)((chunks + (1u << xs_shift) - 1) >> xs_shift);
+        if (window > most) window = most > 0 ? most : 1;
+        const unsigned per_win = (unsigned)window << xs_shift;
+        return {window, xs_shift, ((chunks + per_win - 1) / per_win * (unsigned)Q) << xs_shift};
+    };
     const size_t mask_words = mask_stride / 2;
     const uint32_t *m32 = reinterpret_cast<const uint32_t *>(masks);
-    auto bounded = [&](auto kernel) {
-        kernel<<<grid, RM_THREADS, 0, s>>>(items, tail, ix->K, lut, m32, mask_words, perm, chunks, window, xs_shift, Q, bound_dist,
-                                           topk, keys, key_count, cap, cand_count, thr, ix->Kf);
-    };
-    auto open = [&](auto kernel) {
-        kernel<<<grid, RM_THREADS, 0, s>>>(items, ix->K, lut, m32, mask_words, chunks, window, xs_shift, Q, keys, key_count, cap, cand_count, thr, ix->Kf);
-    };
-    // (a wavefront's gathers at a time: see the kernel)
-#define ICQ_RM_LAUNCH(W, PLANES)                                             \
-    do {                                                                     \
-        if (bound_dist && PLANES && chunks >= 600 && visits >= 30000u) {      \
-            if (superset) bounded(refine_bounded_kernel<W, PLANES, true, PLANES ? 8 : RM_PER>);      \
-            else bounded(refine_bounded_kernel<W, PLANES, false, PLANES ? 8 : RM_PER>);              \
-        } else if (bound_dist) {                                             \
-            if (superset) bounded(refine_bounded_kernel<W, PLANES, true, RM_PER>);                   \
-            else bounded(refine_bounded_kernel<W, PLANES, false, RM_PER>);                           \
-        } else {                                                             \
-            if (superset) open(refine_mask_kernel<W, true>);                 \
-            else open(refine_mask_kernel<W, false>);                         \
-        }                                                                    \
+    if (bound_dist) {
+        const uint8_t *tail = halves ? reinterpret_cast<const uint8_t *>(ix->g2_halves + ix->g2_npad) : nullptr;
+        auto go = [&](auto kernel, const uint8_t *from, int window) {
+            const plan p = plan_for(window);
+            kernel<<<p.grid, RM_THREADS, 0, s>>>(from, tail, ix->K, lut, m32, mask_words, perm, chunks, p.window, p.xs_shift, Q,
+                                                 bound_dist, halves && ix->g2_split ? out_ids : nullptr, topk, keys, key_count, cap,
+                                                 cand_count, thr, ix->Kf);
+        };
+        const int window = visits < 5000u ? 4 : visits < 40000u || !pairs ? 8 : 12;
+#define ICQ_RB(W, WHOLE, PER, FROM, WIN)                                                          \
+    do {                                                                                         \
+        if (superset) go(refine_bounded_kernel<W, WHOLE, true, PER>, FROM, WIN);                 \
+        else go(refine_bounded_kernel<W, WHOLE, false, PER>, FROM, WIN);                         \
     } while (0)
-    if (ix->item_stride == 4) ICQ_RM_LAUNCH(1, false);
-    else if (ix->item_stride == 8) ICQ_RM_LAUNCH(2, false);
-    else if (planes) ICQ_RM_LAUNCH(4, true);
-    else ICQ_RM_LAUNCH(4, false);
-#undef ICQ_RM_LAUNCH
+        if (ix->item_stride == 4) ICQ_RB(1, true, RM_PER, items, window);
+        else if (ix->item_stride == 8) ICQ_RB(2, true, RM_PER, items, window);
+        else if (!halves) ICQ_RB(4, true, RM_PER, items, window);
+        else {
+            const uint8_t *first = reinterpret_cast<const uint8_t *>(ix->g2_halves);
+            // (a wavefront's gathers at a time: see the kernel)
+            if (chunks >= 600 && visits >= 30000u) ICQ_RB(4, false, 8, first, window);
+            else ICQ_RB(4, false, RM_PER, first, window);
+            // (whole records leave the caches sooner, so the windows are shorter: codebooks shrinking by 0.9, 1e8 items, 128 queries, windows of
+            // 8 / 12 / 16: 1827 / 1962 / 1996 us; of one size, 1e7, 16 queries, 30 %, 4 / 8: 303 / 329; 2e7, 64 queries 293 / 298)
+            if (ix->g2_split) ICQ_RB(4, true, RM_PER, items, visits < 40000u ? 4 : 8);
+        }
+#undef ICQ_RB
+    } else {
+        auto go = [&](auto kernel) {
+            const plan p = plan_for(visits <= 16384u ? 4 : 16);
+            kernel<<<p.grid, RM_THREADS, 0, s>>>(items, ix->K, lut, m32, mask_words, chunks, p.window, p.xs_shift, Q, keys, key_count, cap,
+                                                 cand_count, thr, ix->Kf);
+        };
+#define ICQ_RM(W)                                                        \
+    do {                                                                 \
+        if (superset) go(refine_mask_kernel<W, true>);                   \
+        else go(refine_mask_kernel<W, false>);                           \
+    } while (0)
+        if (ix->item_stride == 4) ICQ_RM(1);
+        else if (ix->item_stride == 8) ICQ_RM(2);
+        else ICQ_RM(4);
+#undef ICQ_RM
+    }
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     return icq_launch_select(keys, key_count, cap, Q, topk, splits, false, ticket, out_ids, out_dist, s);
 }

@@ -1192,6 +1192,43 @@ def test_search_from_hit_bits_is_complete_where_cap_is_below_the_survivors(gpu, 
     assert torch.equal(dist, want_dist) and torch.equal(ids, want_ids)
 
 
+@pytest.mark.parametrize("K,Kf,N,Q,ratio,share", [
+    (16, 4, 4_300_001, 5, 1.0, 0.01), (16, 4, 4_300_001, 40, 0.87, 0.02), (12, 3, 4_300_001, 40, 0.95, 0.1), (9, 4, 4_300_001, 12, 4.0, 0.003),
+    (16, 3, 1_100_003, 160, 0.87, 0.3), (13, 4, 1_100_003, 140, 1.0, 0.01), (16, 4, 20_000_003, 60, 0.87, 0.004), (16, 4, 4_300_001, 40, 0.8, 0.01)])
+def test_search_of_whole_and_half_records_equals_id_order(gpu, K, Kf, N, Q, ratio, share):
+    """Over the pair ordering with 9 to 16 codebooks stage 2 reads first halves, whole records, or (codebooks that shrink a little) the
+    one for some queries and the other for the rest: the lists and counts of the walk in id order, bit for bit.  Every third query far from
+    all items (nothing near bounds its result), every seventh threshold infinite or below everything."""
+    torch, b = gpu
+    d, topk, cap = 24, 100, N
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K * Q)
+    cb = torch.randn((K, 256, d), device="cuda", generator=gen) * torch.tensor([ratio ** (k if ratio < 2 else k >= 8) for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, 256, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    index = b.icq_index_create(cb.contiguous(), codes, Kf)
+    queries = sum(cb[k][codes[k, :Q].long()] for k in range(K)) + 0.2 * torch.randn((Q, d), device="cuda", generator=gen)
+    queries[::3] *= 3.0
+    lut = torch.empty((Q, K, 256), device="cuda")
+    b.icq_build_lut(index, queries, lut)
+    P = sum(lut[:, k].index_select(1, codes[k, :20_000].long()) for k in range(Kf))
+    thr = P.kthvalue(int(share * 20_000), dim=1).values.contiguous()
+    thr[1::14], thr[6::14] = float("-inf"), float("inf") if N < 2_000_000 else thr[6::14] * 1.05
+    got = []
+    for mode in (0, 1):
+        b.icq_index_set_scan_mode(index, mode)
+        ids = torch.empty((Q, topk), dtype=torch.int32, device="cuda")
+        dist = torch.empty((Q, topk), device="cuda")
+        count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+        ws = torch.empty(b.icq_workspace_bytes(index, Q, cap, topk), dtype=torch.uint8, device="cuda")
+        b.icq_search(index, queries, thr, cap, topk, ids, dist, count, ws)
+        torch.cuda.synchronize()
+        got.append((ids, dist, count))
+    b.icq_index_set_scan_mode(index, 0)
+    assert b.icq_index_scan_positions(index, Q) > N
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.parametrize("K,Kf,N,Q,topk", [(16, 4, 1_000_003, 190, 100), (12, 3, 2_000_001, 40, 300), (8, 4, 600_011, 900, 10)])
 def test_search_of_many_queries_over_the_pair_ordering_equals_id_order(gpu, K, Kf, N, Q, topk):
     """Many queries over an index of half a million to four million items walk the pair ordering, the stage-2 bound first: the
