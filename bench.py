@@ -691,7 +691,7 @@ def stage1_form(Kf, K, N, Qb, topk):
     if Kf <= 2 and Qb > 4 and N >= 256 ** Kf // 2:
         return "tuples", False
     bits = Kf <= 4 and K <= 16 and topk <= 512 and (N >= 1 << 22 or (N >= 1 << 19 and Qb >= 32))
-    if Kf in (3, 4) and (N >= 64 * 65536 or (bits and Qb >= 32 and float(N) ** 3 * Qb >= 1.8e20)):
+    if Kf in (3, 4) and (N >= 64 * 65536 or (bits and Qb >= 32 and N >= 755_000 and float(N) ** 3 * Qb >= 1.8e20)):   # (65536 pairs)
         return "pairs", bits
     return "items", bits
 

@@ -70,13 +70,17 @@ static inline bool icq_g2_usable(const icq_index *ix) {
     return ix->scan_mode == ICQ_SCAN_GROUPED || ix->N >= 64ll * 65536;
 }
 // The same for a search that keeps hit bits and is bounded before stage 2: from fewer items on where many queries share
-// the walk, until the padding (1.7 times the positions at 10^6 items) outweighs two streamed rows fewer and stage 2's half
-// records.  Whole calls, us, in id order / by pairs: 7e5 items, 300 queries 101 / 103; 1e6, 64 / 120 / 200 / 1000 (960 dimensions)
-// queries 62 / 66, 70 / 74, 94 / 87, 330 / 266; 2e6, 32 / 64 / 200: 68 / 61, 92 / 72, 161 / 107; 4e6, 32 / 200: 111 / 68, 260 / 145;
-// Kf = 3, 4e6, 200 queries 235 / 137; Kf = 4, 4e6, 250 queries, 20 % surviving 1900 / 500.
+// the walk, while the padding (half as many positions again at 7.5e5 items and 65536 pairs) does not outweigh two streamed rows fewer and
+// what stage 2 gains.  Whole calls, K = 16, Kf = 4, codebooks shrinking by 0.8 / of one size, us, in id order - by pairs: 1 % surviving:
+// 5.3e5 items (padded 1.99 times), 500 / 1000 / 2000 queries 117 - 126 / 131, 166 - 196 / 227, 290 - 317 / 357; 7e5 (1.57), 500 / 1000 / 2000:
+// 132 - 128 / 142, 197 - 203 / 232, 356 - 347 / 395; 1e6 (1.43), 128 / 250 / 500 / 1000: 76 - 79 / 80, 104 - 99 / 102, 167 - 141 / 157,
+// 265 - 224 / 256; 2e6, 32 / 64 / 500: 71 - 64 / 69, 95 - 77 / 85, 267 - 193 / 230; 4.1e6, 32: 115 - 71 / 91.  0.3 %: 1e6, 250 / 500:
+// 85 - 93 / 95, 137 - 130 / 144; 2e6, 64 / 128: 71 - 73 / 78, 95 - 84 / 91.  5 %: 1e6, 250: 190 - 126 / 142.  4096 pairs (64 codewords, 1.03 to 1.06):
+// 5.3e5, 250 / 1000: 79 - 78, 165 - 152; 1e6, 64: 63 - 58.
 static inline bool icq_g2_pays(const icq_index *ix, int Q) {
     if (icq_g2_usable(ix)) return true;
-    return ix->g2 && ix->scan_mode == ICQ_SCAN_AUTO && Q >= 32 && (double)ix->N * (double)ix->N * (double)ix->N * (double)Q >= 1.8e20;
+    return ix->g2 && ix->scan_mode == ICQ_SCAN_AUTO && Q >= 32 && 2 * ix->g2_npos <= 3 * ix->N &&
+           (double)ix->N * (double)ix->N * (double)ix->N * (double)Q >= 1.8e20;
 }
 int icq_encode_pack(icq_index *ix, hipStream_t s);             // enc_meta zero on entry
 int icq_group2_build(icq_index *ix, hipStream_t s);

@@ -1229,6 +1229,20 @@ def test_search_of_whole_and_half_records_equals_id_order(gpu, K, Kf, N, Q, rati
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("m,N,Q,pairs", [(256, 600_000, 2000, False), (256, 740_000, 2000, False), (256, 1_000_000, 200, True), (64, 600_000, 1000, True), (256, 1_000_000, 31, False)])
+def test_the_pair_ordering_is_taken_where_its_padding_is_small(gpu, m, N, Q, pairs):
+    """Searches of many queries over half a million to four million items walk the pair ordering unless its runs' padding to 16 makes
+    it more than half as long again as the items (7.5e5 items in 65536 runs)."""
+    torch, b = gpu
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m + N)
+    cb = torch.randn((8, m, 8), device="cuda", generator=gen)
+    index = b.icq_index_create(cb, torch.randint(0, m, (8, N), dtype=torch.uint8, device="cuda", generator=gen), 4)
+    assert (b.icq_index_scan_positions(index, Q) > N) == pairs
+    b.icq_index_set_scan_mode(index, b.ICQ_SCAN_GROUPED)
+    assert b.icq_index_scan_positions(index, Q) > N
+
+
 @pytest.mark.parametrize("K,Kf,N,Q,topk", [(16, 4, 1_000_003, 190, 100), (12, 3, 2_000_001, 40, 300), (8, 4, 600_011, 900, 10)])
 def test_search_of_many_queries_over_the_pair_ordering_equals_id_order(gpu, K, Kf, N, Q, topk):
     """Many queries over an index of half a million to four million items walk the pair ordering, the stage-2 bound first: the
