@@ -988,7 +988,7 @@ def main():
         rec = index_words(K) * 4
         alg2 = n_surv_batch * rec + (npos * qmean / 8 if bits else 4 * n_surv_batch) + 4.0 * qmean * K * 256 + 8.0 * qmean * topk
         ach2 = alg2 / (stage[2] * 1e-3) / 1e9
-        k2 = ("refine_%s_kernel<%d>" % ("bounded" if form == "pairs" or N >= 130 * 32768 else "mask", index_words(K))) if bits else "refine_dist_kernel<%d>" % index_words(K)
+        k2 = ("refine_%s_kernel<%d>" % ("bounded" if form == "pairs" or N >= 128 * 32768 else "mask", index_words(K))) if bits else "refine_dist_kernel<%d>" % index_words(K)
         tr2 = pmc_traffic(k2.split("<")[0], wl)
         result["roofline_stage2"] = {
             "bound": "hbm", "kernel": k2 + " (+ the bound before it and the selection)" if bits else k2 + " + select_kernel",

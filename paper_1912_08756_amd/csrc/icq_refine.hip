@@ -287,10 +287,10 @@ constexpr int RM_LIST = 512;                          // positions a wavefront e
 static_assert(RM_LIST % (64 * RM_PER) == 0, "a round of the list is whole steps of gathers");
 static_assert(RM_CHUNK <= 65536, "the position lists hold 16-bit offsets into the chunk");
 
-// EXACT: the hit bits mark a superset of the survivors (the 16-bit pre-filter of stage 1); an item is a
-// survivor when the first Kf terms of its sum -- the crude distance of Eq. 2, the same fp32 additions
+// The hit bits mark a superset of the survivors (the 16-bit pre-filter of stage 1: indexes this small keep hit bits for calls of many queries
+// only); an item is a survivor when the first Kf terms of its sum -- the crude distance of Eq. 2, the same fp32 additions
 // stage 1 makes item by item -- are below thr[q].  Only survivors are counted and get keys.
-template <int WORDS, bool EXACT>
+template <int WORDS>
 __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
     const uint8_t *__restrict__ items, int K, const float *__restrict__ lut, const uint32_t *__restrict__ masks,
     size_t mask_words, uint32_t nsel, int window, int xs_shift, int Q,
@@ -339,12 +339,11 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 #pragma unroll
         for (int u = 0; u < N4 / RM_THREADS; ++u) dst[u * RM_THREADS + tid] = v[u];
     }
-    const float tq = EXACT ? thr[q] : 0.0f;
+    const float tq = thr[q];
     u64 *kout = keys + (int64_t)q * cap;
     if (tid == 0) sum_all = done_all = 0;
     __syncthreads();                                  // the only barrier: from here on every wavefront is on its own
-    uint32_t survivors = 0;                           // of this wavefront's chunks (wavefront-uniform)
-    uint32_t lane_survivors = 0;                      // EXACT: counted per lane, summed at the end
+    uint32_t lane_survivors = 0;                      // counted per lane, summed at the end
     while (c != 0xFFFFFFFFu) {
         uint32_t w[RM_WORDS];
 #pragma unroll
@@ -361,13 +360,6 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
         const uint32_t incl = wave_scan_add(mine);
         const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         const uint32_t off = incl - mine;
-        // every survivor of the chunk gets a key, so their slots are reserved at once (the atomic's
-        // answer travels while the positions are expanded)
-        uint32_t chunk_slot = 0;
-        if (!EXACT) {
-            survivors += total;
-            if (total != 0 && lane == 0) chunk_slot = atomicAdd(&key_count[q], total);
-        }
         const uint32_t cbase = c * RM_CHUNK, p0 = lane * 32u;
         for (uint32_t lo = 0; lo < total; lo += RM_LIST) {      // wavefront-uniform; one round unless the chunk is dense
             wave_lds_order();                         // the last round's reads are done
@@ -430,26 +422,19 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 #pragma unroll
                     for (int i = 1; i < 4 * WORDS; ++i) {
                         d += tv[i];
-                        if (EXACT && i < 4) crude = i < Kf ? d : crude;
+                        if (i < 4) crude = i < Kf ? d : crude;
                     }
                     const uint32_t ob = icq_order_bits(d);
-                    bool keep = base + (uint32_t)u * 64u + lane < n;
-                    if (EXACT) {
-                        keep = keep && crude < tq;
-                        lane_survivors += keep ? 1u : 0u;
-                    }
+                    const bool keep = base + (uint32_t)u * 64u + lane < n && crude < tq;
+                    lane_survivors += keep ? 1u : 0u;
                     mk[u] = __builtin_amdgcn_ballot_w64(keep);
                     mycnt += (uint32_t)__builtin_popcountll(mk[u]);
                     key[u] = (u64)ob << 32;
                 }
                 if (mycnt == 0) continue;             // wavefront-uniform
                 uint32_t slot0 = 0;
-                if (EXACT) {
-                    if (lane == 0) slot0 = atomicAdd(&key_count[q], mycnt);
-                    slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot0);
-                } else {
-                    slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)chunk_slot) + lo + base;
-                }
+                if (lane == 0) slot0 = atomicAdd(&key_count[q], mycnt);
+                slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot0);
 #pragma unroll
                 for (int u = 0; u < RM_PER; ++u) {
                     if ((mk[u] >> lane) & 1ull) {
@@ -463,7 +448,7 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
         }
         c = cn;
     }
-    if (EXACT) survivors = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors), 63);
+    const uint32_t survivors = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_add(lane_survivors), 63);
     // one addition per block: thousands of wavefronts of one query at one counter would take 11 ns each.  The last of the four
     // to come here makes it.
     if (lane == 0) {
@@ -808,12 +793,10 @@ ICQ_EXPORT int icq_refine(const icq_index *ix, const float *lut, int Q, const ui
                              out_ids, out_dist, (hipStream_t)stream);
 }
 
-// From about four million items on: below that the item records stay in the caches whatever the
-// order of the gathers, and candidate lists with the flat distance kernel are quicker (N = 1e6,
-// K = 16, 1000 queries: 0.15 against 0.24 ms for stage 2).
+// From 2^22 items on; with the pre-filters (eight or sixteen queries per pass of stage 1) and enough queries to fill the
+// chunk walk already from 2^19 (1000 queries, K = 16: lists are ahead up to 3e5 items, hit bits from 6e5).  Below that the item
+// records stay in the caches whatever the order of the gathers, and candidate lists with the flat distance kernel are quicker.
 bool icq_masks_usable(const icq_index *ix, int Q, int topk) {
-    // from 2^22 items on; with the 16-bit pre-filter (eight queries per pass of stage 1) and enough queries to
-    // fill the chunk walk already from 2^19 (1000 queries, K = 16: lists are ahead up to 3e5 items, hit bits from 6e5)
     const bool large = ix->N >= (1ll << 22) || (ix->N >= (1ll << 19) && Q >= 32 && icq_scan_q16_usable(ix, Q));
     return ix->Kf <= 4 && !icq_group_usable(ix, Q) && icq_selects(ix, topk) && large &&
            ix->N + 16ll * 65536 < (1ll << 31);
@@ -834,12 +817,12 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     const uint32_t *perm = pairs ? ix->perm : nullptr;
     const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
     const uint64_t visits = (uint64_t)chunks * (uint64_t)Q;
-    // From 130 chunks on, and over the pair ordering, a bound is worth its launch of 8 to 12 us (20 to 40 for hundreds of queries).  Whole calls, us, one
+    // From 128 chunks on (2^22 items), and over the pair ordering, a bound is worth its launch of 8 to 12 us (20 to 40 for hundreds of queries).  Whole calls, us, one
     // unfiltered launch (up to 130 chunks; beyond, behind one over every 65th chunk) / bounded: K = 16: 7.8e5 items, 37 queries
     // 43 / 47; 1e6, 1000 queries (id order) 330 / 333; 4.3e6, 1 / 3 / 8 queries 44 / 39, 56 / 43, 76 / 52; 1e7, 16 queries, 30 % 765 / 146;
     // 2e7, 64 queries 340 / 198; 1e8, 1 / 128 queries 161 / 104, 1797 / 1536; K = 12, Kf = 3, 1e7, 100 queries, 10 % 873 / 305;
     // K = 8, Kf = 2, 1e7, 1 query 49 / 35, 1.3e7, 4 queries 83 / 47.
-    if (pairs || chunks >= 130) {
+    if (pairs || chunks >= 128) {
         const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, masks, mask_stride, scan_end, pairs, cap, bound_dist,
                                              halves && ix->g2_split ? out_ids : nullptr, out_dist, s);
         if (rc != ICQ_OK) return rc;
@@ -907,15 +890,9 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
             kernel<<<p.grid, RM_THREADS, 0, s>>>(items, ix->K, lut, m32, mask_words, chunks, p.window, p.xs_shift, Q, keys, key_count, cap,
                                                  cand_count, thr, ix->Kf);
         };
-#define ICQ_RM(W)                                                        \
-    do {                                                                 \
-        if (superset) go(refine_mask_kernel<W, true>);                   \
-        else go(refine_mask_kernel<W, false>);                           \
-    } while (0)
-        if (ix->item_stride == 4) ICQ_RM(1);
-        else if (ix->item_stride == 8) ICQ_RM(2);
-        else ICQ_RM(4);
-#undef ICQ_RM
+        if (ix->item_stride == 4) go(refine_mask_kernel<1>);
+        else if (ix->item_stride == 8) go(refine_mask_kernel<2>);
+        else go(refine_mask_kernel<4>);
     }
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
     return icq_launch_select(keys, key_count, cap, Q, topk, splits, false, ticket, out_ids, out_dist, s);

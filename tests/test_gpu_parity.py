@@ -1229,6 +1229,45 @@ def test_search_of_whole_and_half_records_equals_id_order(gpu, K, Kf, N, Q, rati
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("N", [1 << 22, (1 << 22) + 1, 129 * 32768])
+@pytest.mark.parametrize("K,Kf,mode", [(8, 2, 0), (16, 4, 1), (4, 3, 1)])
+def test_search_from_hit_bits_in_id_order_from_four_million_items_on(gpu, N, K, Kf, mode):
+    """From 2^22 items on (128 chunks) every search from hit bits is bounded before stage 2, in id order too; below, only calls of 32
+    queries or more keep hit bits, behind the pre-filter, and are not.  Lists and counts are those of the staged calls, bit for bit."""
+    torch, b = gpu
+    d, topk = 12, 30
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N + K)
+    cb = torch.randn((K, 256, d), device="cuda", generator=gen) * torch.tensor([0.8 ** k for k in range(K)], device="cuda")[:, None, None]
+    codes = torch.randint(0, 256, (K, N), dtype=torch.uint8, device="cuda", generator=gen)
+    for n, Qs in ((N, (1, 4) if Kf == 2 else (1, 5, 6)), (N // 4, (32,) if Kf > 2 else ())):
+        part = codes[:, :n].contiguous()
+        index = b.icq_index_create(cb.contiguous(), part, Kf)
+        b.icq_index_set_scan_mode(index, mode)
+        for Q in Qs:
+            queries = sum(cb[k][part[k, :Q].long()] for k in range(K)) + 0.1 * torch.randn((Q, d), device="cuda", generator=gen)
+            lut = torch.empty((Q, K, 256), device="cuda")
+            b.icq_build_lut(index, queries, lut)
+            P = sum(lut[:, k].index_select(1, part[k, :20_000].long()) for k in range(Kf))
+            thr = P.kthvalue(200, dim=1).values.contiguous()
+            got = []
+            for staged in (False, True):
+                ids = torch.empty((Q, topk), dtype=torch.int32, device="cuda")
+                dist = torch.empty((Q, topk), device="cuda")
+                count = torch.empty((Q,), dtype=torch.int32, device="cuda")
+                ws = torch.empty(b.icq_workspace_bytes(index, Q, n, topk), dtype=torch.uint8, device="cuda")
+                if staged:
+                    cand = torch.empty((Q, n), dtype=torch.int32, device="cuda")
+                    b.icq_scan_fast(index, lut, thr, cand, None, count, ws)
+                    b.icq_refine(index, lut, cand, None, count, topk, ids, dist, ws)
+                else:
+                    b.icq_search(index, queries, thr, n, topk, ids, dist, count, ws)
+                torch.cuda.synchronize()
+                got.append((ids, dist, count))
+            for x, y in zip(*got):
+                assert torch.equal(x, y), (n, Q)
+
+
 @pytest.mark.parametrize("m,N,Q,pairs", [(256, 600_000, 2000, False), (256, 740_000, 2000, False), (256, 1_000_000, 200, True), (64, 600_000, 1000, True), (256, 1_000_000, 31, False)])
 def test_the_pair_ordering_is_taken_where_its_padding_is_small(gpu, m, N, Q, pairs):
     """Searches of many queries over half a million to four million items walk the pair ordering unless its runs' padding to 16 makes
