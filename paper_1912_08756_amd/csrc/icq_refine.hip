@@ -866,22 +866,22 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                                                  cand_count, thr, ix->Kf);
         };
         const int window = visits < 5000u ? 4 : visits < 40000u || !pairs ? 8 : 12;
-#define ICQ_RB(W, WHOLE, PER, FROM, WIN)                                                          \
+#define ICQ_RB(W, WHOLE, FROM, WIN)                                                               \
     do {                                                                                         \
-        if (superset) go(refine_bounded_kernel<W, WHOLE, true, PER>, FROM, WIN);                 \
-        else go(refine_bounded_kernel<W, WHOLE, false, PER>, FROM, WIN);                         \
+        if (superset) go(refine_bounded_kernel<W, WHOLE, true, RM_PER>, FROM, WIN);              \
+        else go(refine_bounded_kernel<W, WHOLE, false, RM_PER>, FROM, WIN);                      \
     } while (0)
-        if (ix->item_stride == 4) ICQ_RB(1, true, RM_PER, items, window);
-        else if (ix->item_stride == 8) ICQ_RB(2, true, RM_PER, items, window);
-        else if (!halves) ICQ_RB(4, true, RM_PER, items, window);
+        if (ix->item_stride == 4) ICQ_RB(1, true, items, window);
+        else if (ix->item_stride == 8) ICQ_RB(2, true, items, window);
+        else if (!halves) ICQ_RB(4, true, items, window);
         else {
             const uint8_t *first = reinterpret_cast<const uint8_t *>(ix->g2_halves);
-            // (a wavefront's gathers at a time: see the kernel)
-            if (chunks >= 600 && visits >= 30000u) ICQ_RB(4, false, 8, first, window);
-            else ICQ_RB(4, false, RM_PER, first, window);
+            // (a wavefront's gathers at a time: see the kernel; fewer than six queries have no superset, and so many chunks only beyond 1.6e8 items)
+            if (superset && chunks >= 600 && visits >= 30000u) go(refine_bounded_kernel<4, false, true, 8>, first, window);
+            else ICQ_RB(4, false, first, window);
             // (whole records leave the caches sooner, so the windows are shorter: codebooks shrinking by 0.9, 1e8 items, 128 queries, windows of
             // 8 / 12 / 16: 1827 / 1962 / 1996 us; of one size, 1e7, 16 queries, 30 %, 4 / 8: 303 / 329; 2e7, 64 queries 293 / 298)
-            if (ix->g2_split) ICQ_RB(4, true, RM_PER, items, visits < 40000u ? 4 : 8);
+            if (ix->g2_split) ICQ_RB(4, true, items, visits < 40000u ? 4 : 8);
         }
 #undef ICQ_RB
     } else {
