@@ -206,12 +206,11 @@ int icq_launch_small(const icq_index *ix, const float *lut, int Q, const float *
 bool icq_group_usable(const icq_index *ix, int Q);
 int icq_group_fused_parts(const icq_index *ix, int Q);
 // The topk smallest keys of every query (icq_select.hip; topk <= 512).  count != nullptr: count[q] <= cap keys at
-// keys + q * cap, selected in up to `splits` parts (ticket [Q] zero, left zero; not read if splits == 1) and used up;
+// keys + q * cap, selected in up to `splits` parts (ticket [Q] zero; not read if splits == 1) and used up;
 // count == nullptr: cap keys at keys + q * cap, KEY_PAD where there is none, splits = 1.
 int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk);
-// compact: the result's keys also replace the query's keys (and count[q] their number).
-int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
-                      uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s);
+int icq_launch_select(unsigned long long *keys, const uint32_t *count, int64_t cap, int Q, int topk, int splits, uint32_t *ticket,
+                      uint32_t *out_ids, float *out_dist, hipStream_t s);
 // The same from `parts` ascending lists of topk distinct keys per query, KEY_PAD where one is short.
 int icq_launch_join(const unsigned long long *lists, int Q, int parts, int topk, uint32_t *out_ids, float *out_dist, hipStream_t s);
 int icq_launch_group_scan(const icq_index *ix, const float *lut, int Q, const float *thr,

@@ -755,7 +755,7 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
             }
             if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
         }
-        return icq_launch_select(keys, const_cast<uint32_t *>(cand_count), cap, Q, topk, splits, false, ticket, out_ids,
+        return icq_launch_select(keys, cand_count, cap, Q, topk, splits, ticket, out_ids,
                                  out_dist, s);
     }
     const int bufn = bufn_for(topk);
@@ -767,7 +767,7 @@ int icq_launch_refine(const icq_index *ix, const float *lut, int Q, const uint32
     if (splits == 1) return ICQ_OK;
     // join the slices' lists, KEY_PAD where one is short (splits * topk <= 4096)
     if (topk <= 512)
-        return icq_launch_select(keys, nullptr, (int64_t)splits * topk, Q, topk, 1, false, nullptr, out_ids, out_dist, s);
+        return icq_launch_select(keys, nullptr, (int64_t)splits * topk, Q, topk, 1, nullptr, out_ids, out_dist, s);
     int len = 2;
     while (len < splits * topk) len <<= 1;
     merge_kernel<<<Q, RF_THREADS, sizeof(u64) * len, s>>>(keys, splits, topk, len, out_ids, out_dist);
@@ -895,5 +895,5 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         else go(refine_mask_kernel<4>);
     }
     if (icq_check_launch() != ICQ_OK) return ICQ_ERR_HIP;
-    return icq_launch_select(keys, key_count, cap, Q, topk, splits, false, ticket, out_ids, out_dist, s);
+    return icq_launch_select(keys, key_count, cap, Q, topk, splits, ticket, out_ids, out_dist, s);
 }

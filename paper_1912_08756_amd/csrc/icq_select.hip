@@ -265,11 +265,10 @@ __device__ int block_select(SelShared<T> &sh, u64 *list, const u64 *in, u64 n, u
 
 // Grid: Q * splits blocks.  count != nullptr: count[q] keys (at most cap) at keys_in + q * cap, worked off
 // by one of the query's blocks, or if they are more than `alone` by one per SEL_PART keys; count == nullptr: cap keys,
-// splits == 1.  compact: the result's keys also replace the query's keys, and their number count[q] (more keys
-// are going to be appended; what is left out here cannot reach the result).
+// splits == 1.
 template <int T, int PER, int MIN>
-__global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count, int64_t cap, int topk, int splits,
-                                                   uint32_t alone, int compact, uint32_t *ticket,
+__global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, const uint32_t *count, int64_t cap, int topk, int splits,
+                                                   uint32_t alone, uint32_t *ticket,
                                                    uint32_t *__restrict__ out_ids, float *__restrict__ out_dist) {
     __shared__ SelShared<T> sh;
     __shared__ __attribute__((aligned(16))) u64 list[SEL_LIST];
@@ -301,7 +300,6 @@ __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count
         }
         __syncthreads();
         if (sh.last == 0) return;                          // block-uniform
-        if (tid == 0) ticket[q] = 0;                       // for the call's next selection
         kept = block_select<T, PER, MIN, true>(sh, list, mine, (u64)used * topk, per, topk);
     }
     for (int i = tid; i < topk; i += T) {
@@ -309,9 +307,7 @@ __global__ __launch_bounds__(T) void select_kernel(u64 *keys_in, uint32_t *count
         const u64 k = list[have ? i : 0];
         out_ids[(int64_t)q * topk + i] = have ? (uint32_t)k : ICQ_PAD_ID;
         out_dist[(int64_t)q * topk + i] = have ? icq_unorder_bits((uint32_t)(k >> 32)) : INFINITY;
-        if (compact && have) mine[i] = k;                      // kept <= count[q]: inside the query's keys
     }
-    if (compact && tid == 0) count[q] = (uint32_t)kept;
 }
 
 // One block per query: `parts` ascending lists of topk keys, KEY_PAD behind the last, no key twice, SEL_LIST keys at most.
@@ -358,10 +354,10 @@ __global__ __launch_bounds__(JOIN_THREADS) void join_kernel(const u64 *__restric
 }
 
 template <int T, int PER, int MIN>
-int launch_select(u64 *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, uint32_t alone, bool compact,
-                  uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
-    select_kernel<T, PER, MIN><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, alone, compact ? 1 : 0,
-                                                                       ticket, out_ids, out_dist);
+int launch_select(u64 *keys, const uint32_t *count, int64_t cap, int Q, int topk, int splits, uint32_t alone, uint32_t *ticket,
+                  uint32_t *out_ids, float *out_dist, hipStream_t s) {
+    select_kernel<T, PER, MIN><<<(unsigned)Q * (unsigned)splits, T, 0, s>>>(keys, count, cap, topk, splits, alone, ticket, out_ids,
+                                                                       out_dist);
     return icq_check_launch();
 }
 
@@ -388,8 +384,8 @@ int icq_select_splits(const icq_index *ix, int Q, int64_t cap, int topk) {
     return s < 1 ? 1 : (int)s;
 }
 
-int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, int Q, int topk, int splits, bool compact,
-                      uint32_t *ticket, uint32_t *out_ids, float *out_dist, hipStream_t s) {
+int icq_launch_select(unsigned long long *keys, const uint32_t *count, int64_t cap, int Q, int topk, int splits, uint32_t *ticket,
+                      uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
     // 1024 threads while every query's block finds a CU to itself or to share with one other; else 512 threads, of which
     // a CU runs four blocks (1000 queries of 10^4 keys: 34 us against 45), with two minima each where one each would
@@ -398,7 +394,7 @@ int icq_launch_select(unsigned long long *keys, uint32_t *count, int64_t cap, in
     // of 1000, topk = 400: 67 / 44 us).  Eight keys per thread in registers: sixteen gain nothing on lists that fit and
     // hold twice the registers on those that do not.
     const uint32_t alone = select_alone(Q, topk);
-#define ICQ_SEL(T, PER, MIN) launch_select<T, PER, MIN>(keys, count, cap, Q, topk, splits, alone, compact, ticket, out_ids, out_dist, s)
+#define ICQ_SEL(T, PER, MIN) launch_select<T, PER, MIN>(keys, count, cap, Q, topk, splits, alone, ticket, out_ids, out_dist, s)
     if (count && (int64_t)Q * splits <= 512) return ICQ_SEL(1024, 8, 1);
     if (Q > 512 && cap <= SEL_LIST) return ICQ_SEL(256, 4, 2);
     if (topk > 256) return ICQ_SEL(512, 8, 2);
@@ -415,6 +411,6 @@ int icq_launch_join(const unsigned long long *lists, int Q, int parts, int topk,
         join_kernel<<<(unsigned)Q, JOIN_THREADS, 0, s>>>(lists, parts, topk, out_ids, out_dist);
         return icq_check_launch();
     }
-    return icq_launch_select(const_cast<unsigned long long *>(lists), nullptr, (int64_t)parts * topk, Q, topk, 1, false,
-                             nullptr, out_ids, out_dist, s);
+    return icq_launch_select(const_cast<unsigned long long *>(lists), nullptr, (int64_t)parts * topk, Q, topk, 1, nullptr,
+                             out_ids, out_dist, s);
 }
