@@ -118,12 +118,15 @@ int icq_index_export_codes(const icq_index *index, int from_items, uint8_t *code
 int icq_index_set_scan_mode(icq_index *index, int mode);
 
 /*
- * Number of positions stage 1 walks per pass over the index in its current scan
- * mode (host call; a measurement aid for work and traffic models): N for the
- * item-by-item scan; the 65536 runs' padded total, rounded up to whole block
- * steps, when the items grouped by their first two fast sub-codes are walked
+ * Number of positions stage 1 of icq_search walks per pass over the index in its
+ * current scan mode (host call; a measurement aid for work and traffic models): N
+ * for the item-by-item scan; the 65536 runs' padded total, rounded up to whole
+ * block steps, when the items grouped by their first two fast sub-codes are walked
  * (Kf = 3, 4); 256^Kf (one evaluation per tuple) for the grouped form of
- * Kf <= 2 with more than 4 queries.  *out is a host pointer.
+ * Kf <= 2 with more than 4 queries.  That is for a search of Q queries with
+ * topk <= 512 in a workspace of icq_workspace_bytes: below 64 * 65536 items and
+ * with Kf = 3, 4 a search in a smaller workspace or with a longer result, and
+ * icq_scan_fast, walk N positions (in ICQ_SCAN_AUTO).  *out is a host pointer.
  */
 int icq_index_scan_positions(const icq_index *index, int Q, int64_t *out /*host*/);
 

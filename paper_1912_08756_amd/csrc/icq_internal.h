@@ -38,14 +38,15 @@ struct icq_index {
     int groups;                // 256^Kf, or 0 when the index is not grouped
     int scan_mode;             // ICQ_SCAN_AUTO / ICQ_SCAN_STREAMED / ICQ_SCAN_GROUPED
     uint32_t *group_start;     // [groups + 1] first grouped position of each tuple
-    uint32_t *group_cursor;    // [groups] scratch of the build
+    uint32_t *group_cursor;    // [groups] end of each tuple's items (the build's cursors); read by every bounded search (icq_bound.hip)
     uint32_t *perm;            // [N] grouped position -> item id
     uint8_t *items_grouped;    // [N][item_stride] the item records in grouped order
     // Grouping by the first two fast sub-codes (Kf = 3, 4 and N large enough, icq_group2.hip): the
     // items ordered by that pair -- the pairs themselves in a scattered order, so that any stretch of
     // positions holds unrelated pairs -- every pair's run padded to whole 16 positions.  Stage 1 then
     // streams only the remaining Kf - 2 fast rows and forms the pair's table sum once per 16
-    // positions.  Uses group_start [65537], group_cursor [65536], perm [g2_npad] (ICQ_PAD_ID in the padding) and
+    // positions.  Uses group_start [65537], group_cursor [65536] (end of each pair's
+    // items, before its padding), perm [g2_npad] (ICQ_PAD_ID in the padding) and
     // items_grouped [g2_npad][item_stride] as the Kf <= 2 grouping does; records of 16 bytes lie in g2_halves, and in items_grouped
     // too only with g2_split.
     int g2;                    // 1 when this grouping exists
