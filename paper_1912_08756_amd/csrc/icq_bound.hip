@@ -26,8 +26,6 @@
 // survivors each, without the looks / with them: first two codebooks a third of the next 1080000 / 22000, codebooks of one size
 // 119000 / 115000 (a few queries escape the glance), nearest runs empty 805000 / 111000; 2e7, 64 queries: 217000 / 20500, 27000 / 22500,
 // 151000 / 99000.  The bound takes 12 us then as before, 50 with the closer look.
-// Over the pair ordering of 16-byte records the glance also says which queries' survivors mostly need their records' second halves
-// (see refine_bounded_kernel).
 // What bounds it is latency: four trips to memory in a chain and a dozen barriers (1e8 items, 128 queries: 12 us, of which 2 are the
 // glance's).
 #include "icq_internal.h"
@@ -45,7 +43,6 @@ constexpr int NB_PAIRS = 4 * ICQ_LUT_W;
 constexpr uint32_t NB_KEYS = 16384;    // keys a query may leave for the selection before a better bound is worth its look
 constexpr int NB_SLOTS = 320;          // the closer look: positions a wavefront collects (four blocks a CU with it, three with 512)
 constexpr uint32_t NB_SAMPLE = 2 * NB_THREADS;   // survivors of the sample at most
-constexpr uint32_t NB_WHOLE = 2;       // whole records where more than half of the survivors need them
 constexpr int NB_AHEAD = 4;            // the closer look: stretches whose hit bits are asked for together
 
 // FORM: 0 the pairs of Kf = 3, 4 (icq_group2.hip), else the tuples of Kf = FORM.  masks: hit bits over the pair ordering
@@ -56,17 +53,16 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
     const uint8_t *__restrict__ items, const uint2 *__restrict__ halves, size_t plane, const uint8_t *__restrict__ by_id, const float *__restrict__ lut, int K,
     int Kf, const float *__restrict__ thr, const uint32_t *__restrict__ run_begin, const uint32_t *__restrict__ run_end,
     uint32_t target, uint32_t most, int topk, const uint32_t *__restrict__ masks, size_t mask_words, uint32_t place, bool pairs,
-    uint32_t limit, bool room, const float *given, uint32_t *whole, float *out_dist) {
+    uint32_t limit, bool room, const float *given, float *out_dist) {
     constexpr int WAVES = NB_THREADS / 64, PAIRS = NB_PAIRS / NB_THREADS, TABLES = 4 * WORDS;
-    constexpr bool HALVES = FORM == 0 && WORDS == 4;     // stage 2 may read first halves only
     __shared__ __attribute__((aligned(16))) float T[TABLES * ICQ_LUT_W];
     __shared__ uint32_t run_pos[NB_PAIRS], run_off[NB_PAIRS + 1];        // the runs taken: first position - offset, offset
     __shared__ uint32_t slots[WAVES][NB_SLOTS];
     static_assert(WAVES * NB_SLOTS >= 5 * NB_THREADS, "the sample's hit bits lie there before");
     uint32_t *held = &slots[0][0];                       // [NB_THREADS] hits before the thread's in its wavefront, [4][NB_THREADS] words
     __shared__ uint32_t wsum[WAVES][2], hsum[WAVES];
-    __shared__ uint32_t s_found[2], s_seen[4];
-    __shared__ float tmin[4], tmin_rest[8];              // smallest entries of the fast tables, of those of a record's second half
+    __shared__ uint32_t s_found[2], s_seen[2];
+    __shared__ float tmin[4];
     __shared__ IcqKthSharedT<NB_THREADS> kth;
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u;
@@ -95,7 +91,7 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
             if (e < N4) reinterpret_cast<float4 *>(T)[e] = e / (ICQ_LUT_W / 4) < K ? src[e] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
     }
-    if (tid < 4) s_found[tid & 1] = s_seen[tid] = 0;
+    if (tid < 2) s_found[tid] = s_seen[tid] = 0;
     // a record by its position in the runs (grouped) or its id
     auto record = [&](bool grouped, uint32_t pos, uint32_t (&rec)[WORDS]) __attribute__((always_inline)) {
         const uint8_t *base = grouped ? items : by_id;
@@ -116,15 +112,14 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
             rec[0] = reinterpret_cast<const uint32_t *>(base)[pos];
         }
     };
-    // its distance, the crude one (Kf <= 4 terms) and that of its first half
-    auto measure = [&](const uint32_t (&rec)[WORDS], float &crude, float &half) __attribute__((always_inline)) -> float {
+    // its distance, and the crude one (Kf <= 4 terms)
+    auto measure = [&](const uint32_t (&rec)[WORDS], float &crude) __attribute__((always_inline)) -> float {
         float d = T[rec[0] & 0xffu];
         crude = d;
 #pragma unroll
         for (int i = 1; i < TABLES; ++i) {
             d += T[i * ICQ_LUT_W + ((rec[i / 4] >> (8 * (i % 4))) & 0xffu)];
             if (i < 4) crude = i < Kf ? d : crude;
-            if (i == TABLES / 2 - 1) half = d;
         }
         return d;
     };
@@ -144,12 +139,6 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
         const float4 x = reinterpret_cast<const float4 *>(T)[wave * (ICQ_LUT_W / 4) + (int)lane];
         const float m = wave_min_f32(fminf(fminf(x.x, x.y), fminf(x.z, x.w)));
         if (lane == 0) tmin[wave] = m;
-    }
-    if (HALVES) {
-        static_assert(WAVES == 8, "a table for each");
-        const float4 x = reinterpret_cast<const float4 *>(T)[(TABLES / 2 + wave) * (ICQ_LUT_W / 4) + (int)lane];
-        const float m = wave_min_f32(fminf(fminf(x.x, x.y), fminf(x.z, x.w)));
-        if (lane == 0) tmin_rest[wave] = m;
     }
     // sums of two numbers over the block: before this thread, and all
     auto scan = [&](uint32_t a, uint32_t b, uint32_t &ex_a, uint32_t &ex_b, uint32_t &tot_a, uint32_t &tot_b) {
@@ -254,8 +243,8 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
                 }
 #pragma unroll
                 for (int u = 0; u < NB_PER; ++u) {
-                    float crude, half;
-                    const float d = measure(rec[u], crude, half);
+                    float crude;
+                    const float d = measure(rec[u], crude);
                     if (base + (uint32_t)u * NB_THREADS + (uint32_t)tid < total && crude < t) {
                         const uint32_t ob = icq_order_bits(d);
                         least[u % 2] = ob < least[u % 2] ? ob : least[u % 2];
@@ -268,27 +257,15 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
     }
     auto reaches = [&](float d) -> bool { return !(bound < INFINITY) || icq_order_bits(d) <= icq_order_bits(bound); };
     // the glance: a position looked at stands for `share`; two more hits for what it leaves open
-    float half[2] = {0.0f, 0.0f};
-    // hits of the glance that stage 2 cannot drop before their second half is read (see refine_bounded_kernel)
-    auto add_passing = [&](uint32_t *sum) __attribute__((always_inline)) {
-        float s = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) s += tmin_rest[k];
-        uint32_t p = 0;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) p += half[u] > bound - s ? 0u : stands[u];
-        p = wave_scan_add(p);
-        if (lane == 63) atomicAdd(sum, p);
-    };
     if (glances) {                                                           // wavefront-uniform
         uint32_t r = 0, c = 0;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             float crude;
-            const float d = measure(glance[u], crude, half[u]);
-            if (!(crude < t)) stands[u] = 0;
+            const float d = measure(glance[u], crude);
+            if (!(crude < t) || stands[u] == 0) continue;
             c += stands[u];
-            r += stands[u] != 0 && reaches(d) ? stands[u] | 1u << 20 : 0u;   // (64 hits of 1024 at most, and their number above)
+            r += reaches(d) ? stands[u] | 1u << 20 : 0u;                     // (64 hits of 1024 at most, and their number above)
         }
         r = wave_scan_add(r);
         c = wave_scan_add(c);
@@ -296,12 +273,10 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
             atomicAdd(&s_seen[0], r);
             atomicAdd(&s_seen[1], c);
         }
-        if (HALVES && whole) add_passing(&s_seen[2]);
     }
     __syncthreads();
     uint32_t reach = s_seen[0] & 0xFFFFFu, seen = s_seen[1];
-    const uint32_t ones = s_seen[0] >> 20, glanced = seen;
-    uint32_t passing = s_seen[2];
+    const uint32_t ones = s_seen[0] >> 20;
     float each = (float)share;                                               // survivors that one of those seen stands for
     // (a hit that stands for 64 may mislead: where it is only a matter of time four must agree; where the caller's room is short
     // there is always a second look)
@@ -367,8 +342,8 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                float crude, half;
-                const float d = measure(rec[u], crude, half);
+                float crude;
+                const float d = measure(rec[u], crude);
                 if ((uint32_t)u * NB_THREADS + (uint32_t)tid >= count || !(crude < t)) continue;
                 c += 1u;
                 r += reaches(d) ? 1u : 0u;
@@ -382,7 +357,7 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
     if (closer) {
         // survivors wanted, stretches of 64 words per wavefront that hold them: 1/32 of the index, 16 for a small one
         // (half the limit where a key is finished 64 at a time in a chain: stage 2 with first halves only)
-        float want = (HALVES && !whole ? 2.0f : 1.0f) * (float)topk * (float)seen * each / (float)limit;
+        float want = (halves && pairs ? 2.0f : 1.0f) * (float)topk * (float)seen * each / (float)limit;
         want = fminf(fmaxf(want, 8.0f * (float)topk), 128.0f * (float)topk);
         const uint32_t space = place / 8u > 16u ? place / 8u : 16u;          // of 4 * place, 32 at least
         const float need = seen != 0 ? want * 4.0f * (float)place / ((float)seen * each) : (float)space;
@@ -400,8 +375,8 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
             have -= cnt;
 #pragma unroll
             for (int u = 0; u < NB_PER; ++u) {
-                float crude, half;
-                const float x = measure(rec[u], crude, half);
+                float crude;
+                const float x = measure(rec[u], crude);
                 if ((uint32_t)u * 64u + lane < cnt && crude < t) {
                     const uint32_t ob = icq_order_bits(x);
                     least[u % 2] = ob < least[u % 2] ? ob : least[u % 2];
@@ -449,16 +424,8 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
         while (have != 0) work(have < 64u * NB_PER ? have : 64u * NB_PER);
         const float kth_seen = kth_of(least, any, s_found[1]);
         if (kth_seen < bound) bound = kth_seen;
-        if (HALVES && whole) {
-            if (glances) add_passing(&s_seen[3]);                            // wavefront-uniform
-            __syncthreads();
-            passing = s_seen[3];
-        }
     }
-    if (tid == 0) {
-        out_dist[(int64_t)q * topk + topk - 1] = bound;
-        if (HALVES && whole) whole[(int64_t)q * topk + topk - 1] = passing * NB_WHOLE > glanced ? 1u : 0u;
-    }
+    if (tid == 0) out_dist[(int64_t)q * topk + topk - 1] = bound;
 }
 
 }  // namespace
@@ -467,8 +434,8 @@ __global__ __launch_bounds__(NB_THREADS, 8) void near_bound_kernel(
 // superset does), +inf for none; such that about `cap` survivors reach it at most, where the survivors' sample can
 // see to that.
 int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const float *thr, int topk, const uint16_t *masks,
-                          size_t mask_stride, int64_t scan_end, bool pairs, int64_t cap, const float *given, uint32_t *whole,
-                          float *out_dist, hipStream_t s) {
+                          size_t mask_stride, int64_t scan_end, bool pairs, int64_t cap, const float *given, float *out_dist,
+                          hipStream_t s) {
     const uint32_t target = 8u * (uint32_t)topk > 1024u ? 8u * (uint32_t)topk : 1024u;
     // a key is a line of ids read and one of keys written: fewer of them pay where there are hundreds of queries
     const int64_t pays = (2 << 20) / (int64_t)Q, keys = pays > NB_KEYS ? NB_KEYS : pays > 2048 ? pays : 2048;
@@ -477,10 +444,10 @@ int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const fl
     const uint32_t place = (uint32_t)(scan_end / 128 / NB_THREADS);          // scan_end: 2^19 at least
     const int words = ix->item_stride / 4;
     auto go = [&](auto kernel) {
-        kernel<<<(unsigned)Q, NB_THREADS, 0, s>>>(ix->items_grouped, ix->g2_split ? nullptr : ix->g2_halves, (size_t)ix->g2_npad, ix->items, lut, ix->K, ix->Kf, thr,
+        kernel<<<(unsigned)Q, NB_THREADS, 0, s>>>(ix->items_grouped, ix->g2_halves, (size_t)ix->g2_npad, ix->items, lut, ix->K, ix->Kf, thr,
                                                   ix->group_start, ix->group_cursor, target, 2 * target, topk,
                                                   reinterpret_cast<const uint32_t *>(masks), mask_stride / 2, place, pairs, limit,
-                                                  room, given, whole, out_dist);
+                                                  room, given, out_dist);
     };
 #define ICQ_NB(FORM)                                                   \
     do {                                                               \

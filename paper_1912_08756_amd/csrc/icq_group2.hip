@@ -6,8 +6,8 @@
 //
 // Layout (built once by a counting sort): the 65536 pairs in the scattered order of
 // icq_g2_pair_of_slot, every pair's run padded to whole 16 positions; per position the item id (perm),
-// the item's record (items_grouped; 16-byte records as two planes, the halves of all positions behind each other, g2_halves, and
-// whole besides where many queries read both, g2_split) and its remaining fast sub-codes as rows of their own (g2_rows);
+// the item's record (items_grouped; or, 16 bytes and codebooks that shrink, as two planes, the halves of all positions behind each
+// other: g2_halves) and its remaining fast sub-codes as rows of their own (g2_rows);
 // per 16 positions the pair and the number of real items (g2_info).
 #include "icq_internal.h"
 
@@ -16,13 +16,20 @@ namespace {
 constexpr int G2_PAIRS = 65536;
 
 // Where the codebooks of a record's second half are small beside the first half's, stage 2 drops nearly every survivor after
-// the first half; else most queries gather whole records, the index keeps those too, and a search has a launch for those queries and one
-// for the others (see refine_bounded_kernel).  A launch that finds nothing to do is 5 us, 12 at 10^8 items and 128 queries, and one that
-// is left a few of the queries costs their chain, so the line is drawn by the index: by the share of the largest norms, for
-// sixteen codebooks shrinking by 0.8 / 0.86 / 0.9 / of one size 0.14 / 0.23 / 0.30 / 0.5.  Whole calls, us, first halves only / both:
-// by 0.86: 1e8 items, 128 queries 2370 / 2240, 2e7, 64 queries 336 / 305, 1e6, 1000 queries 335 / 255, 1e8, one 129 / 129; by 0.83 (0.18)
-// both launches gain nothing; K = 12 by 0.9 (0.206): 1e7, 100 queries 631 / 643, 4.3e6, three 55 / 45; fast 1, slow 0.3 (0.21): 412 / 417, 49 / 58.
-constexpr float G2_TAIL = 0.215f;
+// the first half, and the halves lie apart; else whole records are gathered (see refine_bounded_kernel).  The codebooks decide, by the share of
+// the largest norms from the ninth on: sixteen shrinking by 0.8 / 0.82 / 0.84 / 0.86 / 0.9, of one size: 0.14 / 0.17 / 0.20 / 0.23 / 0.30, 0.5; twelve by
+// 0.86 / 0.9, of one size 0.16 / 0.21, 0.33.  Whole calls, us, halves / whole records:
+//   K = 16, by                           0.7         0.8         0.82        0.84        0.86        0.9        of one size
+//   1e8 items, 128 queries, 1 %       1265/1502   1405/1588   1505/1565   1748/1614   2256/1640   3324/1737   4946/1891
+//   1e8, one                            92/93      106/93      111/95      117/96      123/95      169/106     269/156
+//   2e7, 64                            166/201     187/210     217/213     268/218     322/221     569/244    1114/294
+//   1e7, 16, 30 % surviving            188/213     200/217     224/217     266/218     360/219     656/223    4402/300
+//   1e6, 1000                          193/211     223/211     255/213     294/215     320/220     357/228     395/254
+//   4e6, 250, 20 %                     477/764     506/790     537/788     661/788     946/787    2003/805    2863/875
+//   K = 12, Kf = 3: 1e7, 100, 10 %     300/379     306/382     315/386     331/388     364/393     595/398    3017/460
+// Queries that nothing is near to need the second halves whatever the codebooks (every other query far from all items, codebooks shrinking by
+// 0.8: 2495/1882, 251/169, 478/305, 631/264, 295/253, 803/760, 470/455); an index cannot know them.
+constexpr float G2_TAIL = 0.18f;
 
 __device__ __forceinline__ uint32_t slot_of_item(const uint8_t *__restrict__ fast, int64_t Npad, int64_t i) {
     return icq_g2_slot_of_pair((uint32_t)fast[i] | ((uint32_t)fast[Npad + i] << 8));
@@ -72,11 +79,10 @@ __global__ void g2_scatter_kernel(const uint8_t *__restrict__ fast, int64_t Npad
     for (int r = 0; r < Kf - 2; ++r) rows[(int64_t)r * g2_npad + pos] = fast[(int64_t)(r + 2) * Npad + i];
     const int W = stride / 4;
     const uint32_t *src = reinterpret_cast<const uint32_t *>(items + (size_t)i * stride);
-    if (halves) {                            // stride == 16
+    if (halves) {                            // 16 bytes
         const uint4 v = *reinterpret_cast<const uint4 *>(src);
         halves[pos] = make_uint2(v.x, v.y);
         halves[g2_npad + pos] = make_uint2(v.z, v.w);
-        if (items_grouped) reinterpret_cast<uint4 *>(items_grouped)[pos] = v;
         return;
     }
     uint32_t *dst = reinterpret_cast<uint32_t *>(items_grouped + (size_t)pos * stride);
@@ -103,7 +109,7 @@ __global__ void g2_fill_kernel(uint32_t *__restrict__ p, size_t n, uint32_t v) {
     if (i < n) p[i] = v;
 }
 
-// (halves: the records' two planes where there are no whole ones) codes_out[k][perm[pos]] from the grouped layout alone: rows 0, 1 from the pair of the position's
+// codes_out[k][perm[pos]] from the grouped layout alone: rows 0, 1 from the pair of the position's
 // group of 16, rows 2 .. Kf-1 from the streamed rows, the rest from the grouped item records.
 __global__ void g2_export_kernel(const uint32_t *__restrict__ info, const uint8_t *__restrict__ rows, int64_t g2_npad,
                                  const uint8_t *__restrict__ items_grouped, const uint8_t *__restrict__ halves,
@@ -116,7 +122,7 @@ __global__ void g2_export_kernel(const uint32_t *__restrict__ info, const uint8_
     uint8_t v;
     if (k < 2) v = (uint8_t)(info[pos >> 4] >> (8 * k));
     else if (k < Kf) v = rows[(int64_t)(k - 2) * g2_npad + pos];
-    else if (!items_grouped) v = halves[((k >> 3) * g2_npad + pos) * 8 + (k & 7)];
+    else if (halves) v = halves[((k >> 3) * g2_npad + pos) * 8 + (k & 7)];
     else v = items_grouped[pos * stride + k];
     out[(int64_t)k * N + id] = v;
 }
@@ -138,9 +144,8 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     g2_count_kernel<<<nb, T, 0, s>>>(ix->fast, ix->Npad, ix->N, ix->group_cursor);
     g2_offsets_kernel<<<1, 1024, 0, s>>>(ix->group_cursor, ix->group_start);
     uint32_t total = 0;
-    const bool halves = ix->item_stride == 16;                 // 9 to 16 codebooks
+    bool halves = ix->item_stride == 16;                       // 9 to 16 codebooks
     float4 meta[16];
-    ix->g2_split = false;
     if (icq_check_launch() != ICQ_OK ||
         hipMemcpyAsync(&total, ix->group_start + G2_PAIRS, sizeof(uint32_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
         (halves && hipMemcpyAsync(meta, ix->enc_meta, sizeof(float4) * (size_t)ix->K, hipMemcpyDeviceToHost, s) != hipSuccess) ||
@@ -154,7 +159,7 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
             all += meta[k].y;
             if (k >= 8) tail += meta[k].y;
         }
-        ix->g2_split = !(tail < G2_TAIL * all);
+        halves = tail < G2_TAIL * all;
     }
     // whole block steps of the scan kernel, plus a spare step: its read-ahead never checks bounds
     ix->g2_npos = ((int64_t)total + 16383) / 16384 * 16384;
@@ -163,8 +168,7 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     ok = hipMalloc(&ix->g2_rows, (size_t)(ix->Kf - 2) * np) == hipSuccess &&
          hipMalloc(&ix->g2_info, sizeof(uint32_t) * (np / 16)) == hipSuccess &&
          hipMalloc(&ix->perm, sizeof(uint32_t) * np) == hipSuccess &&
-         (halves && !ix->g2_split ? true : hipMalloc(&ix->items_grouped, np * ix->item_stride) == hipSuccess) &&
-         (!halves || hipMalloc(&ix->g2_halves, np * 2 * sizeof(uint2)) == hipSuccess);
+         (halves ? hipMalloc(&ix->g2_halves, np * 2 * sizeof(uint2)) : hipMalloc(&ix->items_grouped, np * ix->item_stride)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         return ICQ_ERR_HIP;
@@ -176,8 +180,7 @@ int icq_group2_build(icq_index *ix, hipStream_t s) {
     fill(ix->g2_rows, (size_t)(ix->Kf - 2) * np, 0u);
     fill(ix->g2_info, sizeof(uint32_t) * (np / 16), 0u);
     fill(ix->perm, sizeof(uint32_t) * np, ICQ_PAD_ID);
-    if (ix->items_grouped) fill(ix->items_grouped, np * ix->item_stride, 0u);
-    if (halves) fill(ix->g2_halves, np * 2 * sizeof(uint2), 0u);
+    fill(halves ? (void *)ix->g2_halves : ix->items_grouped, np * ix->item_stride, 0u);
     g2_scatter_kernel<<<nb, T, 0, s>>>(ix->fast, ix->Npad, ix->Kf, ix->N, ix->group_cursor, ix->items, ix->item_stride,
                                        ix->perm, ix->items_grouped, ix->g2_halves, ix->g2_rows, ix->g2_npad);
     g2_info_kernel<<<G2_PAIRS / T, T, 0, s>>>(ix->group_start, ix->group_cursor, ix->g2_info);

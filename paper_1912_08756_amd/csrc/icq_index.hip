@@ -125,7 +125,7 @@ ICQ_EXPORT int icq_index_create(icq_index **out, const float *codebooks, const u
     ix->cb = nullptr; ix->cnorm = nullptr; ix->fast = nullptr; ix->items = nullptr;
     ix->groups = 0; ix->scan_mode = ICQ_SCAN_AUTO; ix->timer = nullptr;
     ix->group_start = nullptr; ix->group_cursor = nullptr; ix->perm = nullptr; ix->items_grouped = nullptr;
-    ix->g2 = 0; ix->g2_npos = 0; ix->g2_npad = 0; ix->g2_split = false; ix->g2_halves = nullptr; ix->g2_rows = nullptr; ix->g2_info = nullptr;
+    ix->g2 = 0; ix->g2_npos = 0; ix->g2_npad = 0; ix->g2_halves = nullptr; ix->g2_rows = nullptr; ix->g2_info = nullptr;
     hipDeviceProp_t prop;
     if (hipGetDevice(&ix->device) != hipSuccess ||
         hipGetDeviceProperties(&prop, ix->device) != hipSuccess) {

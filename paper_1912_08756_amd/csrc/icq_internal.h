@@ -47,13 +47,11 @@ struct icq_index {
     // streams only the remaining Kf - 2 fast rows and forms the pair's table sum once per 16
     // positions.  Uses group_start [65537], group_cursor [65536] (end of each pair's
     // items, before its padding), perm [g2_npad] (ICQ_PAD_ID in the padding) and
-    // items_grouped [g2_npad][item_stride] as the Kf <= 2 grouping does; records of 16 bytes lie in g2_halves, and in items_grouped
-    // too only with g2_split.
+    // items_grouped [g2_npad][item_stride] as the Kf <= 2 grouping does, or g2_halves in its place.
     int g2;                    // 1 when this grouping exists
     int64_t g2_npos;           // positions stage 1 walks: an upper bound of the padded total, whole block steps
     int64_t g2_npad;           // row stride of g2_rows = length of perm / items_grouped (g2_npos + read-ahead spare)
-    bool g2_split;             // records of 16 bytes: many queries need most survivors' second halves (icq_group2.hip)
-    uint2 *g2_halves;          // [2][g2_npad] first and second halves of records of 16 bytes: stage 2 reads the second half of few
+    uint2 *g2_halves;          // [2][g2_npad] first and second halves of records of 16 bytes where stage 2 reads the second half of few, else nullptr
     uint8_t *g2_rows;          // [Kf - 2][g2_npad] the remaining fast sub-codes in grouped order
     uint32_t *g2_info;         // [g2_npad / 16] c0 | c1 << 8 | valid positions << 16 of each 16 positions
     icq_stage_timer *timer;    // nullptr unless stage timing is on
@@ -169,10 +167,9 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                             const float *bound_dist, uint32_t *out_ids, float *out_dist, hipStream_t s);
 // A bound on the topk-th smallest distance into out_dist[q][topk - 1], +inf for none (icq_bound.hip): given[q][topk - 1] (given may
 // be nullptr) or what the nearest runs say, tightened where more than about `cap` of the survivors that `masks` marks reach it.
-// whole (may be nullptr; records of 16 bytes over the pair ordering): whole[q][topk - 1] = 1 where most survivors need their second half, else 0.
 int icq_launch_near_bound(const icq_index *ix, const float *lut, int Q, const float *thr, int topk, const uint16_t *masks,
-                          size_t mask_stride, int64_t scan_end, bool pairs, int64_t cap, const float *given, uint32_t *whole,
-                          float *out_dist, hipStream_t s);
+                          size_t mask_stride, int64_t scan_end, bool pairs, int64_t cap, const float *given, float *out_dist,
+                          hipStream_t s);
 
 // p[0..n) = 0, by a kernel (the call can sit inside a captured graph).
 void icq_zero_words(uint32_t *p, int n, hipStream_t s);

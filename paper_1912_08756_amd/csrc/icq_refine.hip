@@ -469,9 +469,7 @@ __global__ __launch_bounds__(RM_THREADS) void refine_mask_kernel(
 // in planes of their own, and a window of chunks is half as many bytes for the XCD's cache -- and the second half only for
 // what is left, collected 64 at a time.  Where the second half's codebooks are as large as the others that is
 // next to everything (by 0.9: 93 %, of one size: all), and a half record more, its tables read from memory, costs twice what the whole
-// record would: those queries (icq_bound.hip says which, by a sample of their survivors) gather whole records, with all tables in
-// the LDS.  1e8 items, 128 queries, codebooks shrinking by 0.9 / of one size / fast 1, slow 0.3 each, us: halves only 3310 / 5000 / 3660,
-// with whole records 1850 / 1900 / 1800; 2e7, 64 queries 552 / 1121 / 559 -> 242 / 293 / 248; 1e6, 1000 queries 346 / 372 / 352 -> 231 / 253 / 238.
+// record would: such an index keeps its records whole (icq_group2.hip has the line and both sides), and all tables are in the LDS.
 // Records of 16 bytes in id order come in one line, and whole (2e7, 64 queries, shrinking by 0.8 / of one size, with the second half waiting in the
 // queue 331 / 1182, whole 322 / 373; 1e7, four, Kf = 2 50.5 / 105, 49.7 / 56).  K <= 8: the whole distance is known at once.
 // A wavefront's positions go through a stack in LDS that outlives the chunk, so that the gathers always come 256 or 512 at a time.
@@ -490,13 +488,12 @@ constexpr int RB_QUEUE = 128;                         // survivors to be finishe
 struct RbRest { uint32_t pos, sum; };                 // a survivor in the queue: position, bits of the sum so far
 
 // WHOLE: records are gathered whole; else (16 bytes over the pair ordering) the halves lie in planes of their own, `items`
-// and `tail`.  whole_of (may be nullptr: all queries): two launches share the queries, WHOLE takes those with whole_of[q][topk - 1] != 0
-// (one kernel with both loops holds the tables and registers of the larger one for all: 51 -> 57 us at 2e6 items, 200 queries).
+// and `tail`.
 template <int WORDS, bool WHOLE, bool EXACT, int PER>
 __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
     const uint8_t *__restrict__ items, const uint8_t *__restrict__ tail, int K, const float *__restrict__ lut,
     const uint32_t *__restrict__ masks, size_t mask_words, const uint32_t *__restrict__ perm, uint32_t nsel, int window,
-    int xs_shift, int Q, const float *__restrict__ bound_dist, const uint32_t *__restrict__ whole_of, int topk, u64 *__restrict__ keys,
+    int xs_shift, int Q, const float *__restrict__ bound_dist, int topk, u64 *__restrict__ keys,
     uint32_t *__restrict__ key_count, int64_t cap, uint32_t *__restrict__ cand_count, const float *__restrict__ thr, int Kf) {
     constexpr bool HALF = WORDS == 4 && !WHOLE;       // a second half is left
     constexpr int FW = HALF ? 2 : WORDS;              // words of a record that are fetched
@@ -523,7 +520,6 @@ __global__ __launch_bounds__(RM_THREADS, 5) void refine_bounded_kernel(
         return j >= (uint32_t)window || i >= nsel ? 0xFFFFFFFFu : i;
     };
     if (chunk_of(0) == 0xFFFFFFFFu) return;           // block-uniform: nothing for this block
-    if (whole_of && (whole_of[(int64_t)q * topk + topk - 1] != 0u) != WHOLE) return;
     const uint32_t *mq = masks + (size_t)q * mask_words + lane;
     uint32_t j = (uint32_t)wave, c = chunk_of(j);
     uint32_t w[RM_WORDS];
@@ -812,7 +808,7 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
                             uint32_t *ticket, uint32_t *cand_count, const float *thr, bool superset, const float *bound_dist,
                             uint32_t *out_ids, float *out_dist, hipStream_t s) {
     if (Q == 0) return ICQ_OK;
-    const bool halves = pairs && ix->item_stride == 16;
+    const bool halves = pairs && ix->g2_halves;
     const uint8_t *items = pairs ? ix->items_grouped : ix->items;
     const uint32_t *perm = pairs ? ix->perm : nullptr;
     const uint32_t chunks = (uint32_t)(scan_end / RM_CHUNK);
@@ -823,8 +819,7 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     // 2e7, 64 queries 340 / 198; 1e8, 1 / 128 queries 161 / 104, 1797 / 1536; K = 12, Kf = 3, 1e7, 100 queries, 10 % 873 / 305;
     // K = 8, Kf = 2, 1e7, 1 query 49 / 35, 1.3e7, 4 queries 83 / 47.
     if (pairs || chunks >= 128) {
-        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, masks, mask_stride, scan_end, pairs, cap, bound_dist,
-                                             halves && ix->g2_split ? out_ids : nullptr, out_dist, s);
+        const int rc = icq_launch_near_bound(ix, lut, Q, thr, topk, masks, mask_stride, scan_end, pairs, cap, bound_dist, out_dist, s);
         if (rc != ICQ_OK) return rc;
         bound_dist = out_dist;
     }
@@ -862,8 +857,7 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
         auto go = [&](auto kernel, const uint8_t *from, int window) {
             const plan p = plan_for(window);
             kernel<<<p.grid, RM_THREADS, 0, s>>>(from, tail, ix->K, lut, m32, mask_words, perm, chunks, p.window, p.xs_shift, Q,
-                                                 bound_dist, halves && ix->g2_split ? out_ids : nullptr, topk, keys, key_count, cap,
-                                                 cand_count, thr, ix->Kf);
+                                                 bound_dist, topk, keys, key_count, cap, cand_count, thr, ix->Kf);
         };
         const int window = visits < 5000u ? 4 : visits < 40000u || !pairs ? 8 : 12;
 #define ICQ_RB(W, WHOLE, FROM, WIN)                                                               \
@@ -873,15 +867,15 @@ int icq_launch_refine_masks(const icq_index *ix, const float *lut, int Q, const 
     } while (0)
         if (ix->item_stride == 4) ICQ_RB(1, true, items, window);
         else if (ix->item_stride == 8) ICQ_RB(2, true, items, window);
-        else if (!halves) ICQ_RB(4, true, items, window);
-        else {
+        else if (!halves) {
+            // (whole records leave the caches sooner, so the windows are shorter: codebooks shrinking by 0.9, 1e8 items, 128 queries, windows of
+            // 8 / 12 / 16: 1827 / 1962 / 1996 us; of one size, 1e7, 16 queries, 30 %, 4 / 8: 303 / 329; 2e7, 64 queries 293 / 298)
+            ICQ_RB(4, true, items, !pairs ? window : visits < 40000u ? 4 : 8);
+        } else {
             const uint8_t *first = reinterpret_cast<const uint8_t *>(ix->g2_halves);
             // (a wavefront's gathers at a time: see the kernel; fewer than six queries have no superset, and so many chunks only beyond 1.6e8 items)
             if (superset && chunks >= 600 && visits >= 30000u) go(refine_bounded_kernel<4, false, true, 8>, first, window);
             else ICQ_RB(4, false, first, window);
-            // (whole records leave the caches sooner, so the windows are shorter: codebooks shrinking by 0.9, 1e8 items, 128 queries, windows of
-            // 8 / 12 / 16: 1827 / 1962 / 1996 us; of one size, 1e7, 16 queries, 30 %, 4 / 8: 303 / 329; 2e7, 64 queries 293 / 298)
-            if (ix->g2_split) ICQ_RB(4, true, items, visits < 40000u ? 4 : 8);
         }
 #undef ICQ_RB
     } else {

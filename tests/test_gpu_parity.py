@@ -1194,11 +1194,12 @@ def test_search_from_hit_bits_is_complete_where_cap_is_below_the_survivors(gpu, 
 
 @pytest.mark.parametrize("K,Kf,N,Q,ratio,share", [
     (16, 4, 4_300_001, 5, 1.0, 0.01), (16, 4, 4_300_001, 40, 0.87, 0.02), (12, 3, 4_300_001, 40, 0.95, 0.1), (9, 4, 4_300_001, 12, 4.0, 0.003),
-    (16, 3, 1_100_003, 160, 0.87, 0.3), (13, 4, 1_100_003, 140, 1.0, 0.01), (16, 4, 20_000_003, 60, 0.87, 0.004), (16, 4, 4_300_001, 40, 0.8, 0.01)])
+    (16, 3, 1_100_003, 160, 0.8, 0.3), (13, 4, 1_100_003, 140, 1.0, 0.01), (16, 4, 20_000_003, 60, 0.8, 0.004), (16, 4, 20_000_003, 60, 0.9, 0.004),
+    (16, 4, 4_300_001, 40, 0.8, 0.01), (10, 3, 4_300_001, 4, 0.8, 0.01)])
 def test_search_of_whole_and_half_records_equals_id_order(gpu, K, Kf, N, Q, ratio, share):
-    """Over the pair ordering with 9 to 16 codebooks stage 2 reads first halves, whole records, or (codebooks that shrink a little) the
-    one for some queries and the other for the rest: the lists and counts of the walk in id order, bit for bit.  Every third query far from
-    all items (nothing near bounds its result), every seventh threshold infinite or below everything."""
+    """Over the pair ordering with 9 to 16 codebooks stage 2 reads first halves where the codebooks shrink, whole records where they do
+    not: the lists and counts of the walk in id order, bit for bit.  Every third query far from all items (nothing near bounds its
+    result), every seventh threshold infinite or below everything."""
     torch, b = gpu
     d, topk, cap = 24, 100, N
     gen = torch.Generator(device="cuda")
