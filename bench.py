@@ -983,9 +983,10 @@ def main():
         "roofline": roofline,
     }
     if form != "tuples":
-        # stage 2: record gathers; what the method must move per call is one 16-byte record per
-        # survivor, the hit bits once more, the tables and the result rows
-        rec = index_words(K) * 4
+        # stage 2: record gathers; what the method must move per call is one record per survivor (over the pair
+        # ordering the first eight bytes of a 16-byte one: these codebooks shrink, the rest is read for a few per
+        # cent), the hit bits once more, the tables and the result rows
+        rec = 8 if form == "pairs" and index_words(K) == 4 else index_words(K) * 4
         alg2 = n_surv_batch * rec + (npos * qmean / 8 if bits else 4 * n_surv_batch) + 4.0 * qmean * K * 256 + 8.0 * qmean * topk
         ach2 = alg2 / (stage[2] * 1e-3) / 1e9
         k2 = ("refine_%s_kernel<%d>" % ("bounded" if form == "pairs" or N >= 128 * 32768 else "mask", index_words(K))) if bits else "refine_dist_kernel<%d>" % index_words(K)
@@ -996,7 +997,7 @@ def main():
             "algorithmic_bytes": alg2, "traffic": tr2["bytes"] if tr2 else None, "traffic_source": tr2["source"] if tr2 else None,
             "ms": round(stage[2], 4), "survivors_per_call": n_surv_batch,
             "note": "all stage-2 kernels of a call (event pair after stage 1 .. results written); algorithmic bytes = "
-                    "survivors x record + hit bits (or ids) + tables + result rows.  A random 16-byte gather moves a "
+                    "survivors x record (8 bytes of 16 over the pair ordering) + hit bits (or ids) + tables + result rows.  A random gather moves a "
                     "whole cache line, so the traffic is a multiple of the algorithmic bytes unless the line is "
                     "reused from the cache by the batch's other queries"}
         # `roofline` is the stage that takes longer between the library's events; the other keeps its own key

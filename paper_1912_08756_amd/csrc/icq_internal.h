@@ -71,11 +71,11 @@ static inline bool icq_g2_usable(const icq_index *ix) {
 // The same for a search that keeps hit bits and is bounded before stage 2: from fewer items on where many queries share
 // the walk, while the padding (half as many positions again at 7.5e5 items and 65536 pairs) does not outweigh two streamed rows fewer and
 // what stage 2 gains.  Whole calls, K = 16, Kf = 4, codebooks shrinking by 0.8 / of one size, us, in id order - by pairs: 1 % surviving:
-// 5.3e5 items (padded 1.99 times), 500 / 1000 / 2000 queries 117 - 126 / 131, 166 - 196 / 227, 290 - 317 / 357; 7e5 (1.57), 500 / 1000 / 2000:
-// 132 - 128 / 142, 197 - 203 / 232, 356 - 347 / 395; 1e6 (1.43), 128 / 250 / 500 / 1000: 76 - 79 / 80, 104 - 99 / 102, 167 - 141 / 157,
-// 265 - 224 / 256; 2e6, 32 / 64 / 500: 71 - 64 / 69, 95 - 77 / 85, 267 - 193 / 230; 4.1e6, 32: 115 - 71 / 91.  0.3 %: 1e6, 250 / 500:
-// 85 - 93 / 95, 137 - 130 / 144; 2e6, 64 / 128: 71 - 73 / 78, 95 - 84 / 91.  5 %: 1e6, 250: 190 - 126 / 142.  4096 pairs (64 codewords, 1.03 to 1.06):
-// 5.3e5, 250 / 1000: 79 - 78, 165 - 152; 1e6, 64: 63 - 58.
+// 5.3e5 items (padded 1.99 times), 500 / 1000 / 2000 queries 115 - 125 / 127, 164 - 194 / 219, 288 - 315 / 349; 7e5 (1.57), 500 / 1000 / 2000:
+// 134 - 129 / 140, 200 - 208 / 225, 359 - 345 / 390; 9e5 (1.46), 500: 154 - 134 / 147; 1e6 (1.43), 128 / 250 / 500 / 1000: 73 - 77 / 77, 101 - 98 / 98,
+// 162 - 137 / 150, 265 - 227 / 257; 2e6, 32 / 64 / 500: 69 - 64 / 68, 93 - 77 / 83, 269 - 193 / 226; 4.1e6, 32: 115 - 70 / 89.  0.3 %: 1e6, 250 / 500:
+// 83 - 93 / 94, 133 - 128 / 136; 2e6, 64 / 128: 70 - 71 / 76, 93 - 83 / 89.  5 %: 1e6, 250: 188 - 121 / 141.  4096 pairs (64 codewords, 1.03 to 1.06):
+// 5.3e5, 250 / 1000: 75 - 77 / 76, 162 - 150 / 181; 1e6, 64: 63 - 57 / 58.
 static inline bool icq_g2_pays(const icq_index *ix, int Q) {
     if (icq_g2_usable(ix)) return true;
     return ix->g2 && ix->scan_mode == ICQ_SCAN_AUTO && Q >= 32 && 2 * ix->g2_npos <= 3 * ix->N &&

@@ -15,7 +15,7 @@
 // reach CAP, or if that is finer a hundredth of the threshold's distance from the tables' minimum (an eightieth with two streamed tables:
 // an entry that stops at CAP is then four fifths of that distance.  With a hundredth it is 0.63, and where the streamed
 // codebooks are the larger ones, the first two 0.3 of them, 1.2 to 2.7 times as many items pass as survive, with an eightieth 1.12 to
-// 1.21, at shares of 10 to 0.1 %; 1e8 items, 128 queries, whole calls 4910 / 4330 us.  Codebooks that shrink or are of one size: within 0.02).
+// 1.21, at shares of 10 to 0.1 %; 1e8 items, 128 queries, whole calls 2345 / 1919 us, 2e7, 64 379 / 299.  Codebooks that shrink or are of one size: within 0.02).
 // At 10^8 items, Kf = 4, 1 % survivors, codebooks shrinking by 0.8 the bits mark 8 % more items than survive (16-bit: 0.8 %),
 // which costs stage 2 less than a tenth of what stage 1 gains.  A query near the items has entries far below the others in every table (its own codewords); in the first
 // two tables they only saturate p.
